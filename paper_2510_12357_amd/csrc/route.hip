@@ -134,33 +134,75 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gate_route_kernel(const S* _
   select_token(P, t, lane, raw);
 }
 
-// conf[t] = 1 / sum_v exp(z_tv - max_v z_tv): one workgroup per token, two sweeps over the row.
-constexpr int kConfThreads = 256;
-__global__ __launch_bounds__(kConfThreads) void confidence_kernel(const float* __restrict__ z, int V,
-                                                                   float* __restrict__ conf) {
-  __shared__ float s_part[kConfThreads / 64];
+// conf[t] = 1 / sum_v exp(z_tv - max_v z_tv): one workgroup per token, one sweep over the row.
+// Bound: a single CU's share of the work, since a row stays in one workgroup (the call has no
+// workspace through which several could meet): the 16-byte loads of a row, kConfUnroll of them in
+// flight per thread, and one v_exp_f32 per logit.  Every thread keeps a running maximum m and
+// s = sum exp(z - m) over the values seen, rescaled when a batch of loads raises m, so the row is
+// read once.  exp(z - m) is exp2((z - m) log2 e): its error is below the two-sweep version's, whose
+// chains of additions were four times as long.
+// T = 64, V = 131072: 207 us with one 4-byte load in flight per thread and two sweeps, 9.5 us so
+// (rel. error 4.1e-7 -> 5.9e-8).
+constexpr int kConfUnroll = 8;
+
+struct ExpSum { float m, s; };                          // s = sum exp(z - m)
+
+__device__ __forceinline__ float conf_exp(float d) { return __builtin_amdgcn_exp2f(d * 1.44269504088896341f); }
+// nothing but -inf seen yet: every term is exp(-inf) = 0
+__device__ __forceinline__ float conf_base(float m) { return m == -INFINITY ? 0.f : m; }
+__device__ __forceinline__ float conf_rescale(ExpSum a, float m) { return a.m == m ? a.s : a.s * conf_exp(a.m - m); }
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void confidence_kernel(const float* __restrict__ z, int V,
+                                                              float* __restrict__ conf) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ float s_m[kWaves], s_s[kWaves];
   const float* row = z + (size_t)blockIdx.x * V;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float m = -INFINITY;
-  for (int v = tid; v < V; v += kConfThreads) m = fmaxf(m, row[v]);
-  m = wave_max(m);
-  if (lane == 0) s_part[wave] = m;
-  __syncthreads();
-  m = s_part[0];
+  ExpSum a = {-INFINITY, 0.f};
+  // rows of an odd V start anywhere: single values up to the first 16-byte boundary, and behind the last
+  const int head = min(V, (int)((16u - ((unsigned)(uintptr_t)row & 15u)) & 15u) >> 2);
+  const int n4 = (V - head) >> 2, tail = head + 4 * n4;
+  const float4* body = reinterpret_cast<const float4*>(row + head);
+  for (int i0 = tid; i0 < n4; i0 += THREADS * kConfUnroll) {
+    float4 v[kConfUnroll];
 #pragma unroll
-  for (int i = 1; i < kConfThreads / 64; ++i) m = fmaxf(m, s_part[i]);
-  __syncthreads();
-  float s = 0.f;
-  for (int v = tid; v < V; v += kConfThreads) s += expf(row[v] - m);
-  s = wave_sum(s);
-  if (lane == 0) s_part[wave] = s;
-  __syncthreads();
-  if (tid == 0) {
-    float tot = 0.f;
+    for (int u = 0; u < kConfUnroll; ++u) {
+      const int i = i0 + u * THREADS;
+      v[u] = i < n4 ? body[i] : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+    float m = a.m;
 #pragma unroll
-    for (int i = 0; i < kConfThreads / 64; ++i) tot += s_part[i];
-    conf[blockIdx.x] = 1.f / tot;
+    for (int u = 0; u < kConfUnroll; ++u) m = fmaxf(fmaxf(fmaxf(m, v[u].x), fmaxf(v[u].y, v[u].z)), v[u].w);
+    a.s = conf_rescale(a, m);
+    a.m = m;
+    const float mb = conf_base(m);
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < kConfUnroll; ++u) {
+      part[0] += conf_exp(v[u].x - mb); part[1] += conf_exp(v[u].y - mb);
+      part[2] += conf_exp(v[u].z - mb); part[3] += conf_exp(v[u].w - mb);
+    }
+    a.s += (part[0] + part[1]) + (part[2] + part[3]);
   }
+  const int extra = tid < head ? tid : tail + tid - head;   // at most 3 + 3 single values
+  if (extra < V && tid < head + (V - tail)) {
+    const float x = row[extra], m = fmaxf(a.m, x);
+    a.s = conf_rescale(a, m);
+    a.m = m;
+    a.s += conf_exp(x - conf_base(m));
+  }
+  // the workgroup's maximum, then every thread's sum brought to it
+  const float wm = wave_max(a.m);
+  const float ws = wave_sum(conf_rescale(a, wm));
+  if (lane == 0) { s_m[wave] = wm; s_s[wave] = ws; }
+  __syncthreads();
+  if (wave != 0) return;
+  const ExpSum w = {lane < kWaves ? s_m[lane] : -INFINITY, lane < kWaves ? s_s[lane] : 0.f};
+  const float m = wave_max(w.m);
+  const float tot = wave_sum(conf_rescale(w, m));
+  if (lane != 0) return;
+  conf[blockIdx.x] = m == -INFINITY ? NAN : 1.f / tot;   // a row of -inf has no distribution
 }
 
 RouteParams make_params(const moe_config& c, const float* conf, int32_t* idx, float* w, uint8_t* important,
@@ -212,7 +254,10 @@ int launch_gate_gemv(const moe_config& c, const void* x, const void* Wg, const f
 
 int launch_confidence(const float* z, int T, int V, float* conf, hipStream_t s) {
   if (T == 0) return MOE_OK;
-  hipLaunchKernelGGL(confidence_kernel, dim3((unsigned)T), dim3(kConfThreads), 0, s, z, V, conf);
+  // a row of at most 8192 values is one batch of loads of 256 threads; a larger workgroup would only add waves
+  // without a load to the reduction (T = 64, both about 7.4 us, the rate of launches)
+  if (V <= 8192) hipLaunchKernelGGL(confidence_kernel<256>, dim3((unsigned)T), dim3(256), 0, s, z, V, conf);
+  else hipLaunchKernelGGL(confidence_kernel<1024>, dim3((unsigned)T), dim3(1024), 0, s, z, V, conf);
   return hip_fail(hipGetLastError(), "confidence_kernel launch");
 }
 
