@@ -143,6 +143,19 @@ SlabPlan slab_plan(const moe_config& c) {
 }
 
 namespace {
+// bf16 steps whose weight rows meet this many token rows on average run on 256 x 256 tiles
+// (ffn_wide.hip), smaller ones on 128 x 256 (ffn_tiled.hip), whose two extra waves per SIMD hide the
+// loads of short tiles better.  gate+up + down, us, 128 x 256 against 256 x 256: 8 experts of 14336, 131
+// rows 644 / 672, 192 rows 700 / 711, 384 rows 1083 / 956; 64 of 1024, 192 rows 250 / 254, 384 rows
+// 370 / 358; 60 of 1408 + 5632 shared, 109 rows 285 / 316, 224 rows 390 / 382, 448 rows 660 / 549.
+constexpr long long kWideMinRows = 208;
+bool wide_tiles(const moe_config& c) {
+  long long sh = 0;
+  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
+  // rows x weight rows, with the mean of the two expert counts per token
+  const long long work = (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh;
+  return c.dtype == MOE_BF16 && work >= kWideMinRows * ((long long)c.E * c.I + sh);
+}
 struct FfnLayout {
   size_t h_routed, h_shared[MOE_MAX_SHARED], total;
 };
@@ -334,13 +347,17 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   // below that the weights are streamed once through the skinny kernel.
   const bool tiled = cfg->dtype != MOE_FP32 && cfg->T >= kTiledMinT;
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
+  const bool wide = tiled && wide_tiles(*cfg);
+  auto launch = [&](StreamMode mode) {
+    return wide ? launch_wide(mode, a, s) : (tiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s));
+  };
   {
     ProfScope ps(kProfFfnGateUp, s);
-    rc = tiled ? launch_tiled(kGateUp, wfmt, a, s) : launch_stream(kGateUp, cfg->dtype, a, s);
+    rc = launch(kGateUp);
     if (rc) return rc;
   }
   ProfScope ps(kProfFfnDown, s);
-  return tiled ? launch_tiled(kDown, wfmt, a, s) : launch_stream(kDown, cfg->dtype, a, s);
+  return launch(kDown);
 }
 
 extern "C" int moe_combine(const moe_config* cfg, const float* y, const float* topk_w,

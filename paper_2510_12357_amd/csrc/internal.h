@@ -95,6 +95,9 @@ int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, h
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
 
+// the same with bf16 weights on 256 x 256 tiles, for large groups (ffn_wide.hip)
+int launch_wide(StreamMode mode, const StreamArgs& a, hipStream_t s);
+
 // ---- a whole decode step in one launch (decode_step.hip) -------------------------------------
 constexpr int kDecodeMaxTokens = 64;
 struct DecodeLaunch {

@@ -7,6 +7,7 @@ import torch
 
 import oracle
 from paper_2510_12357_amd import binding as mm
+from paper_2510_12357_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,49 @@ def test_confidence_row_edges(V):
     ref = oracle.token_confidence(z[:2].numpy())
     assert np.all(np.abs(got[:2] / ref - 1.0) <= 4e-6)
     assert got[2] == 1.0 and abs(got[3] * V - 1.0) <= 4e-6 and np.isnan(got[4])
+
+
+def _assigned_layer(counts, H, I, shared, seed):
+    """A bf16 layer in which expert e gets counts[e] tokens (one expert per token), through given logits."""
+    E, T = len(counts), sum(counts)
+    cfg = wl.LayerConfig("edge", T=T, H=H, E=E, I=I, k_big=1, k_little=1, shared_I=shared)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    x = rnd(T, H).bfloat16()
+    experts = (rnd(E, 3 * H * I) * 0.05).bfloat16()
+    sh = [(rnd(3 * H * i) * 0.05).bfloat16() for i in shared]
+    of = torch.repeat_interleave(torch.arange(E), torch.tensor(counts))[torch.randperm(T, generator=torch.Generator().manual_seed(seed))]
+    b = mm.StepBuffers(cfg)
+    b.logits.fill_(0.0)
+    b.logits[torch.arange(T), of.cuda()] = 4.0
+    table = torch.tensor([w.data_ptr() for w in experts], dtype=torch.int64, device="cuda")
+    return cfg, x, experts, sh, table, b
+
+
+def _ffn32(w, H, I, x):
+    w = w.float()
+    a = x.float() @ w[:H * I].view(I, H).t()
+    h = (a * torch.sigmoid(a) * (x.float() @ w[H * I:2 * H * I].view(I, H).t())).bfloat16().float()
+    return h @ w[2 * H * I:].view(H, I).t()
+
+
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 200, 264, ()),      # every tile shape, ragged K and N
+    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),    # one chunk of K, padded to the ring's length
+    ([400, 512, 31, 450], 576, 128, (1512, 8)),                     # shared experts cut along K; whole tiles
+    ([1300], 128, 40, ()),                                          # one group, fewer panels than XCDs
+])
+def test_wide_tiles(counts, H, I, shared):
+    """256 x 256 tiles against fp32 products of the same bf16 operands: the activations h round to
+    bf16 on both sides, where fp32 sums in another order may fall to the neighbouring value (2^-8 of one of
+    I terms), so rows agree far inside the bf16 bar of 2e-2 of the tensor's RMS."""
+    cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=len(counts) * 7 + H)
+    b.y.fill_(7.0)
+    mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
+    off, st = b.expert_offsets.tolist(), b.sorted_token.long()
+    assert [off[e + 1] - off[e] for e in range(cfg.E)] == list(counts)
+    ref = torch.cat([_ffn32(experts[e], H, I, x[st[off[e]:off[e + 1]]]) for e in range(cfg.E)])
+    assert ((b.y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+    if shared:
+        ref = sum(_ffn32(w, H, i, x) for w, i in zip(sh, shared))
+        assert ((b.shared_out.sum(0) - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
