@@ -12,7 +12,7 @@
 //
 // A workgroup has two kinds of waves:
 //   * waves 0..3, loaders: issue the global->LDS loads of the weight chunks and nothing else.  A
-//     work item is 32 weight rows (16 gate + 16 up rows, or 32 down rows) x all of K for up to 32
+//     work item is 32 weight rows (16 gate + 16 up rows, or 32 down rows) x all of K for up to 32 (64)
 //     token rows, cut into chunks of 256 k (bf16; the narrower formats take 64 rows, see below);
 //     one chunk = 32 rows x 512 B = one 16 KB stage = 4 load instructions per loader.  The chunks of all items of the workgroup form one stream, so the
 //     ring never drains at an item boundary.  A loader issues exactly 4 loads per iteration (a
@@ -32,7 +32,7 @@
 //     the three iterations that the computers lag behind.
 //   * Inside a stage, the 16-byte column c of row r sits at column c ^ (r & 15): the
 //     ds_read_b128 of a fragment (16 rows x the same logical column) is bank-conflict free.
-//   * Groups with more than 32 token rows become several items that read the same weights; the
+//   * Groups with more token rows become several items that read the same weights; the
 //     item order places them 8 items apart, i.e. on workgroups of the same XCD at the same time,
 //     so that the repeats hit in that XCD's L2.
 //   * 8-bit weights (WB = 1): a stage is 64 rows x 256 bytes (256 k per chunk; see Fmt).  A 16-byte column
@@ -66,7 +66,6 @@ constexpr int kStageBytes = 16384;           // one stage of the ring = one chun
 constexpr int kStages = 4;
 constexpr int kWorkers = 4;                  // loader waves = computer waves
 constexpr int kThreadsL = 2 * kWorkers * 64;
-constexpr int kTok = 32;                     // token rows per item, at most (two tiles of 16)
 constexpr int kKParts = 2;                   // worker waves that split the k-steps of one token tile
 
 // Weight formats (template parameter WB): 2 = bf16, 1 = 8-bit codes, 0 = MXFP4 (half a byte), and
@@ -88,6 +87,12 @@ template <int WB> struct Fmt {
   static constexpr int kOutRows = kRows;                          // output rows per down item; gate/up: half
   static __device__ __forceinline__ unsigned row_bytes(int k) { return WB ? (unsigned)k * WB : (unsigned)k / 2u; }
 };
+
+// Token rows per item of a group with m rows; TT: token tiles (of 16 rows) that a computer can hold.
+// Every item streams its weights again (through L2), so steps with large groups take two tiles per
+// computer and items of up to 64 rows (see launch_stream_lds).
+template <int TT>
+__device__ __forceinline__ int item_rows(int m) { return TT == 2 && m > 32 ? 64 : 32; }
 
 // vmcnt(n): bits [3:0] and [15:14]; expcnt and lgkmcnt left at their maxima (no wait)
 #define MM_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0f70 | ((n) & 15) | (((n) >> 4) << 14))
@@ -112,7 +117,7 @@ struct Item {
   int nch;          // chunks
   int K, N, m;
   int r0, n0;       // first token row / first weight row of the item
-  int ntn;          // token tiles in use (1..2)
+  int ntn;          // token tiles in use (1..4)
   int gather, row0;
   unsigned ldwb;    // bytes between rows of W
   unsigned ldbb;    // bytes between rows of B
@@ -127,14 +132,15 @@ struct Item {
   // computers: this lane's token row.  decode_item leaves the row number here (for a routed
   // gate/up item it comes from sorted_token, i.e. from memory) and resolve_row turns it into a byte
   // offset when the item becomes the current one, chunks later: no wave waits for that load.
-  unsigned boff;        // byte offset of the row (kOob: none)
+  unsigned boff[2];     // byte offset of the row of each token tile (kOob: none)
 };
 
 __device__ __forceinline__ void resolve_row(Item& it, int T) {
-  it.boff = it.boff == kOob ? kOob : (unsigned)clampi((int)it.boff, 0, T - 1) * it.ldbb;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) it.boff[u] = it.boff[u] == kOob ? kOob : (unsigned)clampi((int)it.boff[u], 0, T - 1) * it.ldbb;
 }
 
-template <int MODE, int WB>
+template <int MODE, int WB, int TT>
 __device__ __forceinline__ Item decode_item(const StreamArgs& a, int j, int total, int n_groups,
                                             const int* s_prefix, const GroupSrc* s_src, int wave, int lane) {
   Item it;
@@ -157,7 +163,8 @@ __device__ __forceinline__ Item decode_item(const StreamArgs& a, int j, int tota
   const int local = item - uni(s_prefix[g]);
   constexpr int per = MODE == kGateUp ? Fmt<WB>::kRows / 2 : Fmt<WB>::kRows;
   const int rows = (G.N + per - 1) / per;
-  const int tgs = max(1, (G.m + kTok - 1) / kTok);
+  const int tok = item_rows<TT>(G.m);
+  const int tgs = max(1, (G.m + tok - 1) / tok);
   int tg = 0, row_item = local;     // one token block (the usual case at decode): nothing to divide
   if (tgs > 1) {
     const int block = local / (8 * tgs);
@@ -166,12 +173,12 @@ __device__ __forceinline__ Item decode_item(const StreamArgs& a, int j, int tota
     tg = rem / nb;
     row_item = block * 8 + (rem - tg * nb);
   }
-  it.r0 = tg * kTok;
+  it.r0 = tg * tok;
   it.n0 = row_item * per;
   it.K = it.valid ? G.K : 0;
   it.N = G.N; it.m = it.valid ? G.m : 0;
   it.nch = (it.K + KC - 1) / KC;
-  it.ntn = clampi((it.m - it.r0 + 15) >> 4, 1, kTok / 16);
+  it.ntn = clampi((it.m - it.r0 + 15) >> 4, 1, tok >> 4);
   it.gather = G.gather; it.row0 = G.row0;
   it.ldwb = Fmt<WB>::row_bytes(G.ldw);
   it.ldbb = (unsigned)G.ldw * 2u;
@@ -195,21 +202,22 @@ __device__ __forceinline__ Item decode_item(const StreamArgs& a, int j, int tota
     }
     it.a_row[i] = (it.valid && n < G.N) ? off : kOob;
   }
-  {
-    const int r = it.r0 + (wave & 1) * 16 + (lane & 15);
-    const bool val = it.valid && r < it.m;
-    it.boff = val ? (it.gather ? (unsigned)a.sorted_token[it.row0 + r] : (unsigned)r) : kOob;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int r = it.r0 + ((wave & 1) + 2 * u) * 16 + (lane & 15);
+    const bool val = it.valid && r < it.m && u < TT;
+    it.boff[u] = val ? (it.gather ? (unsigned)a.sorted_token[it.row0 + r] : (unsigned)r) : kOob;
   }
   return it;
 }
 
 
-template <int WB>
+template <int WB, int TT>
 struct Smem {
   char ring[kStages * kStageBytes];
-  // K-split partial sums (the item counts during set-up).  Two row tiles: every computer writes its
-  // sums; four row tiles: only the computers of the second k part do, the others add their own
-  float red[Fmt<WB>::kTiles > 2 ? 2 : kWorkers][Fmt<WB>::kTiles][4][64];
+  // K-split partial sums (the item counts during set-up).  Two row tiles and one token tile: every
+  // computer writes its sums; otherwise only the computers of the second k part do, the others add their own
+  float red[Fmt<WB>::kTiles > 2 || TT > 1 ? 2 * TT : kWorkers][Fmt<WB>::kTiles][4][64];
   GroupSrc src[kMaxGroups];
   int prefix[kMaxGroups + 1];
   // MXFP4: the scale bytes of the chunk being consumed, double-buffered by iteration parity:
@@ -219,15 +227,15 @@ struct Smem {
 };
 
 
-template <int MODE, int WB>
+template <int MODE, int WB, int TT>
 __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4))) void stream_lds_kernel(const StreamArgs a) {
   typedef Fmt<WB> F;
   constexpr int KC = F::kPerChunk;           // k per chunk
   constexpr int kHalves = F::kSteps;         // MFMA k-steps fed by one 16-byte column: 1 (bf16), 2 (8-bit), 4 (MXFP4)
   constexpr int kTiles = F::kTiles, kReads = F::kReads, kRowBytes = F::kRowBytes;
-  constexpr bool kOwnSums = kTiles > 2;      // the computers of k part 0 add their own sums to those of part 1
+  constexpr bool kOwnSums = kTiles > 2 || TT > 1;   // the computers of k part 0 add their own sums to those of part 1
   // One LDS object, ring first (1 KB aligned: every load instruction fills one aligned KB).
-  __shared__ __attribute__((aligned(1024))) Smem<WB> sm;
+  __shared__ __attribute__((aligned(1024))) Smem<WB, TT> sm;
   char* const s_ring = sm.ring;
   auto& s_red = sm.red;
   GroupSrc* const s_src = sm.src;
@@ -244,7 +252,7 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
     const Group G = make_group<uint16_t, MODE, WB>(a, g, src);
     constexpr int per = MODE == kGateUp ? F::kRows / 2 : F::kRows;
     const int rows = (G.N + per - 1) / per;
-    const int tgs = (G.m + kTok - 1) / kTok;
+    const int tgs = (G.m + item_rows<TT>(G.m) - 1) / item_rows<TT>(G.m);
     s_src[g] = src;
     s_cnt[g] = rows * tgs;
   }
@@ -270,7 +278,7 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
 
   if (wave < kWorkers) {
     // =================================== loader ===================================
-    Item it = decode_item<MODE, WB>(a, 0, total, n_groups, s_prefix, s_src, wave, lane);
+    Item it = decode_item<MODE, WB, TT>(a, 0, total, n_groups, s_prefix, s_src, wave, lane);
     Item nx = it;
     int j = 0, k = 0, drain = 0, s = 0;
     unsigned a_col[4], addr[4];     // logical 16-byte column per load instruction; running offsets
@@ -304,7 +312,7 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
         ++k;
 #pragma unroll
         for (int i = 0; i < 4; ++i) addr[i] += kRowBytes;
-        if (k == 1) nx = decode_item<MODE, WB>(a, j + 1, total, n_groups, s_prefix, s_src, wave, lane);   // under the loads
+        if (k == 1) nx = decode_item<MODE, WB, TT>(a, j + 1, total, n_groups, s_prefix, s_src, wave, lane);   // under the loads
         if (k == it.nch) {
           it = nx; ++j; k = 0;
           rs = make_rsrc(it.w0, it.wbytes);
@@ -328,9 +336,9 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
 
   // =================================== computer ===================================
   const int c = wave - kWorkers, tw = c & 1, kp = c >> 1;
-  Item cur = decode_item<MODE, WB>(a, 0, total, n_groups, s_prefix, s_src, c, lane);
+  Item cur = decode_item<MODE, WB, TT>(a, 0, total, n_groups, s_prefix, s_src, c, lane);
   resolve_row(cur, a.T);
-  Item nx = decode_item<MODE, WB>(a, 1, total, n_groups, s_prefix, s_src, c, lane);
+  Item nx = decode_item<MODE, WB, TT>(a, 1, total, n_groups, s_prefix, s_src, c, lane);
   int j = 0, k = 0;                 // item ordinal and chunk being consumed
   int pending = 0;                  // the previous item's partial sums wait for their epilogue
   int need_nx = 0;                  // nx is stale (cur just moved on)
@@ -364,11 +372,13 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
   for (int t = 0; t < kReads; ++t)
     rd_off[t] = ring_base + (unsigned)c16 * kRowBytes + (unsigned)((((kp + t * kKParts) * 4 + q) ^ c16) * 16);
   // token rows of one chunk: for read t, the kHalves x 8 k behind column (kp + 2t) * 4 + q
-  i32x4 bbuf[kReads][kHalves];
+  i32x4 bbuf[TT][kReads][kHalves];
 #pragma unroll
-  for (int t = 0; t < kReads; ++t)
+  for (int u = 0; u < TT; ++u)
 #pragma unroll
-    for (int h = 0; h < kHalves; ++h) bbuf[t][h] = i32x4{0, 0, 0, 0};
+    for (int t = 0; t < kReads; ++t)
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) bbuf[u][t][h] = i32x4{0, 0, 0, 0};
   // MXFP4: computer 3 moves the scale bytes.  Lane l fetches the 16 blocks of item row l of the
   // chunk with one 16-byte load, one chunk ahead, and writes them to LDS in front of the "landed"
   // barrier of the iteration that consumes the chunk.
@@ -407,19 +417,24 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
     *reinterpret_cast<i32x4*>(buf + lane * 16) = i32x4{(int)out[0], (int)out[1], (int)out[2], (int)out[3]};
   };
 
-  f32x4 acc[kTiles];                // the sums of an item stay here until its epilogue, one barrier after its last chunk
+  f32x4 acc[TT][kTiles];           // the sums of an item stay here until its epilogue, one barrier after its last chunk
+  auto clear_sums = [&]() {
 #pragma unroll
-  for (int rt = 0; rt < kTiles; ++rt) acc[rt] = f32x4{0, 0, 0, 0};
+    for (int u = 0; u < TT; ++u)
+#pragma unroll
+      for (int rt = 0; rt < kTiles; ++rt) acc[u][rt] = f32x4{0, 0, 0, 0};
+  };
+  clear_sums();
 
   // Scale (8-bit weights), activate and store this lane's kTiles x 4 sums of the item that ended.
-  auto store_outputs = [&](float (&val)[kTiles][4]) {
+  auto store_outputs = [&](float (&val)[kTiles][4], int tile) {
     if (WB == 1) {
 #pragma unroll
       for (int rt = 0; rt < kTiles; ++rt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) val[rt][v] *= sc[rt][v];
     }
-    const int r = f_r0 + tw * 16 + c16;
+    const int r = f_r0 + tile * 16 + c16;
     if (r < f_m) {
       if (MODE == kGateUp) {
 #pragma unroll
@@ -448,22 +463,27 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
     }
   };
   auto epilogue = [&]() {
-    // computers 0 and 1 finish token tiles 0 and 1: add the two k parts (part 0 first), activate, store
-    if (kp == 0 && tw < f_ntn) {
-      float val[kTiles][4];
+    // the computers of k part 0 finish their token tiles: add the two k parts (part 0 first), activate, store
+    if (kp != 0) return;
 #pragma unroll
-      for (int rt = 0; rt < kTiles; ++rt)
+    for (int u = 0; u < TT; ++u) {
+      if (tw + 2 * u < f_ntn) {
+        float val[kTiles][4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          if constexpr (kOwnSums) val[rt][v] = acc[rt][v] + s_red[tw][rt][v][lane];
-          else val[rt][v] = s_red[tw][rt][v][lane] + s_red[tw + 2][rt][v][lane];
-        }
-      store_outputs(val);
+        for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            if constexpr (kOwnSums) val[rt][v] = acc[u][rt][v] + s_red[tw + 2 * u][rt][v][lane];
+            else val[rt][v] = s_red[tw][rt][v][lane] + s_red[tw + 2][rt][v][lane];
+          }
+        store_outputs(val, tw + 2 * u);
+      }
     }
   };
 
   // Fragments of the chunk in stage `stage`, MFMAs against the token rows in bbuf.
   auto consume = [&](int stage, const unsigned char* mx_sc) {
+    const bool two = TT == 2 && tw + 2 < cur.ntn;          // this wave's second token tile holds rows
     const unsigned st = (unsigned)(stage * kStageBytes);
     bf16x8 f[kTiles][kReads];                               // row tile, 16-byte column
     constexpr int kT = 16 * kRowBytes;                      // bytes between row tiles
@@ -501,18 +521,24 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
 #pragma unroll
     for (int t = 0; t < kReads; ++t) {
       if constexpr (WB == 2) {
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, bbuf[t][0]);
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, bbuf[0][t][0]);
 #pragma unroll
         for (int rt = 0; rt < kTiles; ++rt)
-          acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[rt][t], bv, acc[rt], 0, 0, 0);
+          acc[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[rt][t], bv, acc[0][rt], 0, 0, 0);
+        if (two) {
+          const bf16x8 bw = __builtin_bit_cast(bf16x8, bbuf[TT - 1][t][0]);
+#pragma unroll
+          for (int rt = 0; rt < kTiles; ++rt)
+            acc[TT - 1][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[rt][t], bw, acc[TT - 1][rt], 0, 0, 0);
+        }
       } else if constexpr (WB == 1) {
 #pragma unroll
         for (int h = 0; h < kHalves; ++h) {
-          const bf16x8 bv = __builtin_bit_cast(bf16x8, bbuf[t][h]);
+          const bf16x8 bv = __builtin_bit_cast(bf16x8, bbuf[0][t][h]);
 #pragma unroll
           for (int rt = 0; rt < kTiles; ++rt) {
             const i32x4 w = __builtin_bit_cast(i32x4, f[rt][t]);
-            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_e4m3(w[2 * h], w[2 * h + 1]), bv, acc[rt], 0, 0, 0);
+            acc[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_e4m3(w[2 * h], w[2 * h + 1]), bv, acc[0][rt], 0, 0, 0);
           }
         }
       } else {
@@ -521,11 +547,11 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
         for (int rt = 0; rt < kTiles; ++rt) sv[rt] = e8m0_to_f32((mx_s[rt] >> (8 * t)) & 0xffu);
 #pragma unroll
         for (int h = 0; h < kHalves; ++h) {
-          const bf16x8 bv = __builtin_bit_cast(bf16x8, bbuf[t][h]);
+          const bf16x8 bv = __builtin_bit_cast(bf16x8, bbuf[0][t][h]);
 #pragma unroll
           for (int rt = 0; rt < kTiles; ++rt) {
             const i32x4 w = __builtin_bit_cast(i32x4, f[rt][t]);
-            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_mx4(w[h], sv[rt]), bv, acc[rt], 0, 0, 0);
+            acc[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_mx4(w[h], sv[rt]), bv, acc[0][rt], 0, 0, 0);
           }
         }
       }
@@ -539,14 +565,18 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
     MM_WAIT_VMCNT(0);
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(cur.b, cur.bbytes);
 #pragma unroll
-    for (int t = 0; t < kReads; ++t)
+    for (int u = 0; u < TT; ++u) {
+      if (u > 0 && tw + 2 * u >= cur.ntn) continue;
 #pragma unroll
-      for (int h = 0; h < kHalves; ++h) {
-        // the k behind 16-byte column (kp + 2t) * 4 + q of the weight rows (k-step h of that column)
-        const int kk = k * KC + ((kp + t * kKParts) * 4 + q) * F::kPerColumn + h * 8;
-        const bool ok = cur.valid && kk < cur.K && cur.boff != kOob;
-        bbuf[t][h] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)(ok ? cur.boff + (unsigned)kk * 2u : kOob), 0, 0);
-      }
+      for (int t = 0; t < kReads; ++t)
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+          // the k behind 16-byte column (kp + 2t) * 4 + q of the weight rows (k-step h of that column)
+          const int kk = k * KC + ((kp + t * kKParts) * 4 + q) * F::kPerColumn + h * 8;
+          const bool ok = cur.valid && kk < cur.K && cur.boff[u] != kOob;
+          bbuf[u][t][h] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)(ok ? cur.boff[u] + (unsigned)kk * 2u : kOob), 0, 0);
+        }
+    }
   };
 
   // One iteration.
@@ -561,9 +591,11 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
       if (++k == cur.nch) {         // item done: hand the partial sums over, move on
         if (!kOwnSums || kp == 1) {
 #pragma unroll
-          for (int rt = 0; rt < kTiles; ++rt)
+          for (int u = 0; u < TT; ++u)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s_red[kOwnSums ? tw : c][rt][v][lane] = acc[rt][v];
+            for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) s_red[kOwnSums ? tw + 2 * u : c][rt][v][lane] = acc[u][rt][v];
         }
         f_r0 = cur.r0; f_n0 = cur.n0; f_m = cur.m; f_N = cur.N; f_ntn = cur.ntn; f_out = cur.out;
         pending = 1;
@@ -583,13 +615,12 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
     if (pending) {
       pending = 0;
       epilogue();
-#pragma unroll
-      for (int rt = 0; rt < kTiles; ++rt) acc[rt] = f32x4{0, 0, 0, 0};    // the next chunk is consumed in the next iteration
+      clear_sums();                                         // the next chunk is consumed in the next iteration
     }
     if (need_nx) {
       need_nx = 0;
       load_scales(cur);
-      nx = decode_item<MODE, WB>(a, j + 1, total, n_groups, s_prefix, s_src, c, lane);
+      nx = decode_item<MODE, WB, TT>(a, j + 1, total, n_groups, s_prefix, s_src, c, lane);
     }
     return cur.valid || s < 2;
   };
@@ -597,37 +628,46 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
   for (int s = 0; step(s); ++s) {}
 }
 
-template <int MODE, int WB>
+template <int MODE, int WB, int TT>
 int launch_lds_typed(const StreamArgs& a, hipStream_t s) {
-  const long items = item_upper_bound((StreamMode)MODE, a, kTok);
+  const long items = item_upper_bound((StreamMode)MODE, a, 32);
   if (items <= 0) return MOE_OK;
   // persistent workgroups: exactly as many as are resident at once
   static std::atomic<int> cached{0};                      // the same on every device this library runs on (gfx950)
   int per_cu = cached.load(std::memory_order_relaxed);
   if (per_cu == 0) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stream_lds_kernel<MODE, WB>, kThreadsL, 0) != hipSuccess || n < 1) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stream_lds_kernel<MODE, WB, TT>, kThreadsL, 0) != hipSuccess || n < 1) n = 1;
     per_cu = n;
     cached.store(n, std::memory_order_relaxed);
   }
   long grid = (long)device_cu_count() * per_cu;
   if (grid > items) grid = items;
-  hipLaunchKernelGGL((stream_lds_kernel<MODE, WB>), dim3((unsigned)grid), dim3(kThreadsL), 0, s, a);
+  hipLaunchKernelGGL((stream_lds_kernel<MODE, WB, TT>), dim3((unsigned)grid), dim3(kThreadsL), 0, s, a);
   return hip_fail(hipGetLastError(), "stream_lds_kernel launch");
 }
 
 }  // namespace
 
+// Token tiles per computer.  bf16 has the registers for two (110 of a computer's 128); the narrower
+// formats, at 114 and 125 with one, have not.  Up to 64 tokens one tile is as fast or faster: the token
+// rows of 33 .. 64 rows, whose loads queue behind the weight stream, are then fetched by two
+// workgroups (60 experts, 64 tokens, gate+up 124 us, with two tiles 131; down at 8 tokens 26.5 / 28.4).
+// Above: 8 experts of 14336, 200 tokens, gate+up 518 us with one tile, 394 with two, down 265 / 202; 64
+// experts of 1024, 200 tokens 98 / 92; 60 experts, 250 tokens 177 / 172 and 102 / 98.
+constexpr int kOneTileMaxT = 64;
+
 int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (weight_format == 2) {
-    if (mode == kGateUp) return launch_lds_typed<kGateUp, 2>(a, s);
-    if (mode == kDown) return launch_lds_typed<kDown, 2>(a, s);
+    const bool two = a.T > kOneTileMaxT;
+    if (mode == kGateUp) return two ? launch_lds_typed<kGateUp, 2, 2>(a, s) : launch_lds_typed<kGateUp, 2, 1>(a, s);
+    if (mode == kDown) return two ? launch_lds_typed<kDown, 2, 2>(a, s) : launch_lds_typed<kDown, 2, 1>(a, s);
   } else if (weight_format == 1) {
-    if (mode == kGateUp) return launch_lds_typed<kGateUp, 1>(a, s);
-    if (mode == kDown) return launch_lds_typed<kDown, 1>(a, s);
+    if (mode == kGateUp) return launch_lds_typed<kGateUp, 1, 1>(a, s);
+    if (mode == kDown) return launch_lds_typed<kDown, 1, 1>(a, s);
   } else if (weight_format == 0) {
-    if (mode == kGateUp) return launch_lds_typed<kGateUp, 0>(a, s);
-    if (mode == kDown) return launch_lds_typed<kDown, 0>(a, s);
+    if (mode == kGateUp) return launch_lds_typed<kGateUp, 0, 1>(a, s);
+    if (mode == kDown) return launch_lds_typed<kDown, 0, 1>(a, s);
   }
   return fail(MOE_E_BADARG, "bad stream mode / weight format");
 }

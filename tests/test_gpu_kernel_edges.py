@@ -56,16 +56,7 @@ def _ffn32(w, H, I, x):
     return h @ w[2 * H * I:].view(H, I).t()
 
 
-@pytest.mark.parametrize("counts,H,I,shared", [
-    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 200, 264, ()),      # every tile shape, ragged K and N
-    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),    # one chunk of K, padded to the ring's length
-    ([400, 512, 31, 450], 576, 128, (1512, 8)),                     # shared experts cut along K; whole tiles
-    ([1300], 128, 40, ()),                                          # one group, fewer panels than XCDs
-])
-def test_wide_tiles(counts, H, I, shared):
-    """256 x 256 tiles against fp32 products of the same bf16 operands: the activations h round to
-    bf16 on both sides, where fp32 sums in another order may fall to the neighbouring value (2^-8 of one of
-    I terms), so rows agree far inside the bf16 bar of 2e-2 of the tensor's RMS."""
+def _check_assigned(counts, H, I, shared):
     cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=len(counts) * 7 + H)
     b.y.fill_(7.0)
     mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
@@ -76,3 +67,27 @@ def test_wide_tiles(counts, H, I, shared):
     if shared:
         ref = sum(_ffn32(w, H, i, x) for w, i in zip(sh, shared))
         assert ((b.shared_out.sum(0) - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+
+
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 200, 264, ()),      # every tile shape, ragged K and N
+    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),    # one chunk of K, padded to the ring's length
+    ([400, 512, 31, 450], 576, 128, (1512, 8)),                     # shared experts cut along K; whole tiles
+    ([1300], 128, 40, ()),                                          # one group, fewer panels than XCDs
+])
+def test_wide_tiles(counts, H, I, shared):
+    """256 x 256 tiles against fp32 products of the same bf16 operands: the activations h round to
+    bf16 on both sides, where fp32 sums in another order may fall to the neighbouring value (2^-8 of one of
+    I terms), so rows agree far inside the bf16 bar of 2e-2 of the tensor's RMS."""
+    _check_assigned(counts, H, I, shared)
+
+
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 32, 33, 64, 65, 50], 200, 264, ()),                    # items of 64 token rows, their remainders
+    ([16, 17, 48, 49], 1032, 72, (520,)),                          # several chunks of K; a shared expert of 130 rows
+    ([65], 64, 40, ()),
+])
+def test_streamed_items_of_64_rows(counts, H, I, shared):
+    """Steps of 65 .. 255 tokens: groups of more than 32 rows in items of 64.  Bar as for the wide tiles."""
+    assert 64 < sum(counts) < 256
+    _check_assigned(counts, H, I, shared)
