@@ -348,6 +348,7 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   const bool tiled = cfg->dtype != MOE_FP32 && cfg->T >= kTiledMinT;
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
   const bool wide = tiled && wide_tiles(*cfg);
+  a.by_rows = tiled && tiles_by_rows(*cfg);
   auto launch = [&](StreamMode mode) {
     return wide ? launch_wide(mode, a, s) : (tiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s));
   };

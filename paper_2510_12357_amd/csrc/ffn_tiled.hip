@@ -145,8 +145,9 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   constexpr int kPerChunk = kInsA + kInsB;                         // loads of one wave per chunk
   constexpr int kOutCols = (MODE == kGateUp) ? BNR / 2 : BNR;     // output columns per tile
 
-  __shared__ int s_cnt[kMaxGroups];
+  __shared__ int s_cnt[kMaxGroups];                                // rows per group, then tiles per list entry
   __shared__ int s_prefix[kMaxGroups + 1];
+  __shared__ short s_group[kMaxGroups];                            // list entry -> group
   extern __shared__ __attribute__((aligned(1024))) char s_tiles[];   // kStages x (A rows | B rows)
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -157,10 +158,45 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   constexpr int kAhead = kStages - 1;                              // chunks in flight ahead of the one consumed
   const int n_groups = a.n_routed + (MODE == kDown ? a.n_slabs : a.n_shared);
 
-  // ---- tile list: tiles per group, exclusive prefix ----
-  for (int g = tid; g < n_groups; g += kThreads) {
-    const Group G = make_group<S, MODE, WB>(a, g, load_group_src<MODE>(a, g));
-    s_cnt[g] = ((G.N + kOutCols - 1) / kOutCols) * ((G.m + BM - 1) / BM);
+  // ---- tile list (workgroup b runs on XCD b % 8).  In either order the token tiles of a weight panel
+  // (the weight rows of one tile) are adjacent, so that the panel is fetched from HBM once and re-read
+  // from one XCD's L2:
+  //   * one list of all tiles, cut into 8 contiguous ranges, one per XCD: an XCD holds few groups, and at
+  //     any time some XCDs are at groups bound by the matrix cores and others at groups bound by
+  //     their weights;
+  //   * a.by_rows: a list per XCD, panel n of group g on XCD (n + g) % 8, groups with most rows first: every
+  //     XCD has the same work, which counts where a workgroup has only two or three tiles (see
+  //     launch_tiled for the rule).
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslots = gridDim.x >> 3;
+  const bool by_rows = a.by_rows != 0;
+  constexpr int kPerThread = (kMaxGroups + kThreads - 1) / kThreads;
+  int my_tiles[kPerThread], my_rank[kPerThread];
+  if (by_rows) {
+    for (int g = tid; g < n_groups; g += kThreads) s_cnt[g] = load_group_src<MODE>(a, g).m;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int k = 0; k < kPerThread; ++k) {
+    const int g = tid + k * kThreads;
+    if (g < n_groups) {
+      const int N = MODE == kDown ? a.H : (g < a.n_shared ? a.shared_I[g] : a.I), nt = (N + kOutCols - 1) / kOutCols;
+      if (by_rows) {
+        const int m = s_cnt[g], first = (xcd - g) & 7;
+        int rank = 0;
+        for (int o = 0; o < n_groups; ++o) rank += s_cnt[o] > m || (s_cnt[o] == m && o < g);
+        my_rank[k] = rank;
+        my_tiles[k] = (nt > first ? (nt - first + 7) >> 3 : 0) * ((m + BM - 1) / BM);
+      } else {
+        my_rank[k] = g;
+        my_tiles[k] = nt * ((load_group_src<MODE>(a, g).m + BM - 1) / BM);
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPerThread; ++k) {
+    const int g = tid + k * kThreads;
+    if (g < n_groups) { s_cnt[my_rank[k]] = my_tiles[k]; s_group[my_rank[k]] = (short)g; }
   }
   __syncthreads();
   if (wave == 0) {
@@ -181,9 +217,8 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   __syncthreads();
   const int total = s_prefix[n_groups];
 
-  // ---- XCD-aware walk: workgroup b runs on XCD b % 8; each XCD owns a contiguous range ----
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslots = gridDim.x >> 3;
-  const int lo_t = (int)((long)total * xcd / 8), hi_t = (int)((long)total * (xcd + 1) / 8);
+  const int lo_t = by_rows ? 0 : (int)((long)total * xcd / 8), hi_t = by_rows ? total : (int)((long)total * (xcd + 1) / 8);
+  const int mine = hi_t - lo_t > slot ? (hi_t - lo_t - slot - 1) / nslots + 1 : 0;   // tiles of this workgroup
 
   // ---- per-lane constants of the loads: instruction p of this wave fills tile rows
   // kRowsPerIns * (lw * kIns + p) + lane / kCols at physical column lane % kCols ----
@@ -203,18 +238,22 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   constexpr int kJw = 32 * kRowBW;                                 // next 32 weight rows
   constexpr int kUp = (MODE == kGateUp) ? (BNR / 2) * kRowBW : (TN / 2) * kJw;   // j >= TN/2: the up rows / the next blocks
 
-  for (int tile = lo_t + slot; tile < hi_t; tile += nslots) {
+  for (int i_tile = 0; i_tile < mine; ++i_tile) {
+    // in the order by rows half of the workgroups start from the back, so that tiles bound by the matrix
+    // cores and tiles bound by their weights run at the same time
+    const int tile = lo_t + slot + nslots * (by_rows && 2 * slot >= nslots ? mine - 1 - i_tile : i_tile);
     int lo = 0, hi = n_groups;
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
       if (s_prefix[mid] <= tile) lo = mid; else hi = mid;
     }
-    const Group G = make_group<S, MODE, WB>(a, lo, load_group_src<MODE>(a, lo));
+    const int g = s_group[lo];
+    const Group G = make_group<S, MODE, WB>(a, g, load_group_src<MODE>(a, g));
     const int local = tile - s_prefix[lo];
     const int mt = (G.m + BM - 1) / BM;
-    const int n_tile = local / mt;                         // token tiles of one weight panel adjacent
-    const int m0 = (local - n_tile * mt) * BM;
-    const int n0 = n_tile * kOutCols;
+    const int panel = local / mt;
+    const int m0 = (local - panel * mt) * BM;
+    const int n0 = (by_rows ? ((xcd - g) & 7) + 8 * panel : panel) * kOutCols;
     const int K = G.K;
 
     const int nk = (K + BK - 1) / BK;
@@ -520,6 +559,23 @@ int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
 typedef Shape<MOE_TILED_SHAPE> DefaultShape;
 
 }  // namespace
+
+// The order by rows pays for narrow weights in steps of few rows and few tiles per workgroup (a.by_rows).
+// gate+up + down, us, contiguous / by rows: 8-bit, 64 experts of 1024, 777 tokens 201 / 181, 2048 tokens
+// 285 / 270; 60 of 1408 + 5632 shared, 400 tokens 251 / 206, 1000 tokens 275 / 277; 64 of 1408 + 2 shared,
+// 600 tokens 256 / 233, 900 tokens 257 / 263; MXFP4, 60 experts, 600 tokens 225 / 200, 64 of 1024, 777
+// tokens 165 / 163, 2048 tokens 235 / 238.  With bf16 weights, twice the bytes per tile, mixing the two
+// kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more panels
+// than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
+bool tiles_by_rows(const moe_config& c) {
+  if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
+  long long sh = 0;
+  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
+  const long long weight_rows = (long long)c.E * c.I + sh;
+  const long long work = (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh;
+  const long long limit = c.dtype == MOE_BF16_W8 && c.n_shared == 0 ? 208 : 88;
+  return work < limit * weight_rows && weight_rows < 3ll * (DefaultShape::BNR / 2) * device_cu_count();
+}
 
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (weight_format == 2) {

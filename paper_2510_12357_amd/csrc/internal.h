@@ -75,6 +75,7 @@ struct StreamArgs {
   const int32_t* offsets;             // device [E+1]
   const int32_t* sorted_token;        // device [T*k_big]
   int max_pairs;                      // T * k_big
+  int by_rows;                        // tiled kernel: order of its tiles
   const void* x;                      // [T,H]
   void* h_routed;                     // [T*k_big, I]   SwiGLU activations (storage dtype)
   void* h_shared[MOE_MAX_SHARED];     // [T, I_s]
@@ -94,6 +95,7 @@ int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, h
 // ---- large-m grouped GEMM on LDS-tiled MFMA (prefill regime; bf16 activations) ---------------
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
+bool tiles_by_rows(const moe_config& c);   // value of StreamArgs::by_rows for a step
 
 // the same with bf16 weights on 256 x 256 tiles, for large groups (ffn_wide.hip)
 int launch_wide(StreamMode mode, const StreamArgs& a, hipStream_t s);

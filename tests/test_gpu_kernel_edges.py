@@ -91,3 +91,34 @@ def test_streamed_items_of_64_rows(counts, H, I, shared):
     """Steps of 65 .. 255 tokens: groups of more than 32 rows in items of 64.  Bar as for the wide tiles."""
     assert 64 < sum(counts) < 256
     _check_assigned(counts, H, I, shared)
+
+
+@pytest.mark.parametrize("counts,H,I", [
+    ([0, 5, 128, 129, 1, 40, 64, 33], 256, 384),                   # tiles listed by rows: few rows per expert
+    ([300, 0, 290, 400], 128, 256),                                # contiguous ranges: many rows per expert
+    ([1] * 200 + [100], 128, 128),                                 # more groups than a wave has lanes
+])
+def test_tiled_mxfp4_orders(counts, H, I):
+    """Prefill with MXFP4 experts in both tile orders, against fp32 products with the dequantised
+    weights (the kernel widens code x scale exactly); bar as for the wide tiles."""
+    E, T = len(counts), sum(counts)
+    assert T >= 256
+    g = torch.Generator(device="cuda").manual_seed(T)
+    n = 3 * H * I
+    codes = torch.randint(0, 256, (E, n // 2), generator=g, device="cuda").to(torch.uint8)
+    scales = torch.randint(117, 122, (E, n // 32), generator=g, device="cuda").to(torch.uint8)
+    grid = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6], device="cuda")
+    grid = torch.cat([grid, -grid])
+    dense = torch.stack([grid[(codes & 15).long()], grid[(codes >> 4).long()]], dim=2).view(E, n // 32, 32)
+    dense = (dense * torch.exp2(scales.float() - 127.0)[..., None]).view(E, n)
+    cfg, x, _, _, _, b = _assigned_layer(counts, H, I, (), seed=T)
+    cfg = cfg.with_(dtype="bf16mx4")
+    blob = torch.cat([codes, scales], dim=1)
+    table = torch.tensor([w.data_ptr() for w in blob], dtype=torch.int64, device="cuda")
+    logits = b.logits
+    b = mm.StepBuffers(cfg)
+    b.logits.copy_(logits)
+    mm.layer_step(b, x, None, None, None, table, [], logits_given=True)
+    off, st = b.expert_offsets.tolist(), b.sorted_token.long()
+    ref = torch.cat([_ffn32(dense[e], H, I, x[st[off[e]:off[e + 1]]]) for e in range(E)])
+    assert ((b.y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
