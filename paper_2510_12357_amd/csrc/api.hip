@@ -223,9 +223,13 @@ extern "C" int moe_route(const moe_config* cfg, const void* x, const void* Wg, c
   hipStream_t s = static_cast<hipStream_t>(stream);
   // decode sizes: plain-FMA GEMV spread over many waves; larger T: MFMA router GEMM
   constexpr int kGemvMaxT = 256;
-  // decode batches: logits and selection of a token in one workgroup, one launch
+  // decode batches: logits and selection of a token in one workgroup, one launch.  Every workgroup reads the
+  // whole gate matrix, so above 64 tokens only while that is small (60 x 2048, 200 tokens: two
+  // launches 10.3 us, one 8.5; the four-token blocks of the GEMV read a large matrix a quarter as often)
   constexpr int kOneLaunchMaxT = 64;
-  if (!logits_given && cfg->T <= kOneLaunchMaxT) {
+  constexpr long long kOneLaunchGate = 1 << 18;
+  const bool one_launch = cfg->T <= kOneLaunchMaxT || (cfg->T <= kGemvMaxT && (long long)cfg->E * cfg->H <= kOneLaunchGate);
+  if (!logits_given && one_launch) {
     ProfScope ps(kProfRouteTopk, s);
     return launch_gate_route(*cfg, x, Wg, gate_bias, conf, logits, topk_idx, topk_w, important, k_t, s);
   }

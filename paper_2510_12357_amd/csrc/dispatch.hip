@@ -3,12 +3,14 @@
 // (token, rank) pairs grouped per expert; the order is fixed to (expert asc, token asc), i.e. a
 // stable counting sort of the pair list by expert id.
 //
-// The order is produced without order-dependent operations: expert e's segment comes from scanning
-// the tokens in ascending order and compacting the matches with ballot/popcount prefix sums, so the
-// result is unique and reproducible (the large-T count pass adds up per-chunk histograms with LDS
-// integer atomics: a sum, which does not depend on their order).  The experts of one token must be
-// distinct, as the selection stage produces them.  Two shapes:
-//   * T <= kSmallT: one workgroup, one wave per expert (round-robin), one launch.
+// The order is produced without order-dependent operations: every pair sets its token's bit in its
+// expert's token mask in LDS (atomic OR, which does not depend on the order), and a pair's position is its
+// expert's offset plus the number of bits below its token's, so the result is unique and reproducible,
+// and all pairs are placed at once (the masks took the place of a loop over the experts that scanned
+// the tokens for each: 200 tokens 12.4 -> 4.8 us, 64 tokens 5.5 -> 4.6; the scatter kernel at 2048 tokens, 8 of 64
+// experts, 11.3 -> 7.2).  The experts of one token must be distinct,
+// as the selection stage produces them.  Two shapes:
+//   * T <= kSmallT: one workgroup, one launch.
 //   * larger T: one workgroup per chunk of 128 tokens; a count kernel, then a scatter kernel
 //     that rebuilds the prefixes of the counts itself.
 #include "internal.h"
@@ -24,49 +26,49 @@ __device__ __forceinline__ unsigned long long lanemask_lt(int lane) {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// rank at which token t names expert e in the LDS copy of the selection (-1 = not named);
-// entries beyond k_t were stored as -1, so no k_t lookup is needed here
-__device__ __forceinline__ int match_rank_lds(const int* s_idx, int t, int T, int K, int e) {
-  if (t >= T) return -1;
-  int found = -1;
-  for (int j = K - 1; j >= 0; --j)
-    if (s_idx[t * K + j] == e) found = j;
-  return found;
+// expert of pair i of the chunk that starts at token t0, -1 if it is none
+__device__ __forceinline__ int pair_expert(const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t,
+                                           int j_lo, int t, int j, size_t at, int E, int K) {
+  int kt = k_t[t];
+  kt = kt < 0 ? 0 : (kt > K ? K : kt);
+  const int e = idx[at];
+  return j >= j_lo && j < kt && (unsigned)e < (unsigned)E ? e : -1;
 }
 
 __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t, int j_lo, int T, int E, int K,
     int32_t* __restrict__ offsets, int32_t* __restrict__ sorted_token,
     int32_t* __restrict__ sorted_rank, int32_t* __restrict__ inv_pos) {
-  __shared__ int s_idx[kSmallT * MOE_MAX_TOPK];
-  __shared__ int s_count[MOE_MAX_EXPERTS];
+  constexpr int kWords = kSmallT / 64, kPerThread = kSmallT * MOE_MAX_TOPK / kSmallThreads;
+  __shared__ unsigned long long s_mask[MOE_MAX_EXPERTS][kWords];
   __shared__ int s_off[MOE_MAX_EXPERTS + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kWaves = kSmallThreads / 64;
-
-  // stage the selection once: every later pass reads LDS only
-  for (int i = tid; i < T * K; i += kSmallThreads) {
-    const int t = i / K, j = i - t * K;
-    int kt = k_t[t];
-    kt = kt < 0 ? 0 : (kt > K ? K : kt);
-    const int e = idx[i];
-    const bool pair = j >= j_lo && j < kt && (unsigned)e < (unsigned)E;
-    s_idx[i] = pair ? e : -1;
-    if (!pair) inv_pos[i] = -1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = T * K;
+  int pe[kPerThread];                                  // this thread's pairs tid, tid + kSmallThreads, ..
+#pragma unroll
+  for (int c = 0; c < kPerThread; ++c) {
+    const int i = tid + c * kSmallThreads, t = i / K;
+    pe[c] = i < n ? pair_expert(idx, k_t, j_lo, t, i - t * K, i, E, K) : -1;
   }
+  for (int i = tid; i < E * kWords; i += kSmallThreads) (&s_mask[0][0])[i] = 0;
   __syncthreads();
-  for (int e = wave; e < E; e += kWaves) {
-    int cnt = 0;
-    for (int t0 = 0; t0 < T; t0 += 64)
-      cnt += __popcll(__ballot(match_rank_lds(s_idx, t0 + lane, T, K, e) >= 0));
-    if (lane == 0) s_count[e] = cnt;
+#pragma unroll
+  for (int c = 0; c < kPerThread; ++c) {
+    const int t = (tid + c * kSmallThreads) / K;
+    if (pe[c] >= 0) atomicOr(&s_mask[pe[c]][t >> 6], 1ull << (t & 63));
   }
   __syncthreads();
   if (wave == 0) {                                     // exclusive prefix over <= 256 experts
     constexpr int C = MOE_MAX_EXPERTS / 64;
     int loc[C], sum = 0;
 #pragma unroll
-    for (int c = 0; c < C; ++c) { const int e = lane * C + c; loc[c] = e < E ? s_count[e] : 0; sum += loc[c]; }
+    for (int c = 0; c < C; ++c) {
+      const int e = lane * C + c;
+      loc[c] = 0;
+      if (e < E)
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) loc[c] += __popcll(s_mask[e][w]);
+      sum += loc[c];
+    }
     int incl = sum;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(incl, d); if (lane >= d) incl += v; }
@@ -76,61 +78,45 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     if (lane == 63) s_off[E] = incl;
   }
   __syncthreads();
-  for (int e = wave; e < E; e += kWaves) {
-    int pos = s_off[e];
-    for (int t0 = 0; t0 < T; t0 += 64) {
-      const int t = t0 + lane;
-      const int j = match_rank_lds(s_idx, t, T, K, e);
-      const unsigned long long b = __ballot(j >= 0);
-      if (j >= 0) {
-        const int p = pos + __popcll(b & lanemask_lt(lane));
-        sorted_token[p] = t;
-        sorted_rank[p] = j;
-        inv_pos[(size_t)t * K + j] = p;
-      }
-      pos += __popcll(b);
+#pragma unroll
+  for (int c = 0; c < kPerThread; ++c) {
+    const int i = tid + c * kSmallThreads;
+    if (i >= n) break;
+    int p = -1;
+    if (pe[c] >= 0) {
+      const int t = i / K;
+      p = s_off[pe[c]] + __popcll(s_mask[pe[c]][t >> 6] & lanemask_lt(t & 63));
+#pragma unroll
+      for (int w = 0; w < kWords - 1; ++w) if (w < t >> 6) p += __popcll(s_mask[pe[c]][w]);
+      sorted_token[p] = t;
+      sorted_rank[p] = i - t * K;
     }
+    inv_pos[i] = p;
   }
   for (int e = tid; e <= E; e += kSmallThreads) offsets[e] = s_off[e];
-  const int P = s_off[E];
-  for (int i = P + tid; i < T * K; i += kSmallThreads) { sorted_token[i] = -1; sorted_rank[i] = -1; }
+  for (int i = s_off[E] + tid; i < n; i += kSmallThreads) { sorted_token[i] = -1; sorted_rank[i] = -1; }
 }
 
 // ---- large T: one workgroup per chunk of kChunk tokens ------------------------------------------
 // Pass 1 counts, per chunk, the pairs of every expert (LDS integer atomics: a sum, so the result
 // does not depend on their order).  Pass 2 turns the counts into each chunk's first position
-// inside every expert segment, then places the chunk's pairs expert by expert with ballot
-// prefixes, which keeps tokens ascending inside a segment.
+// inside every expert segment, then places the chunk's pairs by their bits in the experts' token masks,
+// which keeps tokens ascending inside a segment.
 constexpr int kChunk = 128;
+static_assert(kChunk == 128, "two mask words per chunk");
 constexpr int kCountSlab = 32 * MOE_MAX_EXPERTS;        // ints of the count table held in LDS at a time
-
-__device__ __forceinline__ void stage_chunk(const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t,
-                                            int j_lo, int t0, int T, int E, int K, int* s_idx,
-                                            int32_t* __restrict__ inv_pos) {
-  const int n = min(kChunk, T - t0) * K;
-  for (int i = threadIdx.x; i < n; i += kBigThreads) {
-    const int tl = i / K, j = i - tl * K;
-    int kt = k_t[t0 + tl];
-    kt = kt < 0 ? 0 : (kt > K ? K : kt);
-    const int e = idx[(size_t)t0 * K + i];
-    const bool pair = j >= j_lo && j < kt && (unsigned)e < (unsigned)E;
-    s_idx[i] = pair ? e : -1;
-    if (inv_pos && !pair) inv_pos[(size_t)t0 * K + i] = -1;
-  }
-}
 
 __global__ __launch_bounds__(kBigThreads) void dispatch_count_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t, int j_lo, int T, int E, int K,
     int32_t* __restrict__ counts /* [chunks][E] */) {
-  __shared__ int s_idx[kChunk * MOE_MAX_TOPK];
   __shared__ int s_hist[MOE_MAX_EXPERTS];
-  const int t0 = blockIdx.x * kChunk;
+  const int t0 = blockIdx.x * kChunk, n = min(kChunk, T - t0) * K;
   for (int e = threadIdx.x; e < E; e += kBigThreads) s_hist[e] = 0;
-  stage_chunk(idx, k_t, j_lo, t0, T, E, K, s_idx, nullptr);
   __syncthreads();
-  const int n = min(kChunk, T - t0) * K;
-  for (int i = threadIdx.x; i < n; i += kBigThreads)
-    if (s_idx[i] >= 0) atomicAdd(&s_hist[s_idx[i]], 1);
+  for (int i = threadIdx.x; i < n; i += kBigThreads) {
+    const int tl = i / K, e = pair_expert(idx, k_t, j_lo, t0 + tl, i - tl * K, (size_t)t0 * K + i, E, K);
+    if (e >= 0) atomicAdd(&s_hist[e], 1);
+  }
   __syncthreads();
   for (int e = threadIdx.x; e < E; e += kBigThreads) counts[(size_t)blockIdx.x * E + e] = s_hist[e];
 }
@@ -140,12 +126,25 @@ __global__ __launch_bounds__(kBigThreads) void dispatch_scatter_kernel(
     const int32_t* __restrict__ counts, int n_chunks, int32_t* __restrict__ offsets,
     int32_t* __restrict__ sorted_token, int32_t* __restrict__ sorted_rank,
     int32_t* __restrict__ inv_pos) {
-  __shared__ int s_idx[kChunk * MOE_MAX_TOPK];
+  constexpr int kWords = kChunk / 64, kPerThread = kChunk * MOE_MAX_TOPK / kBigThreads;
+  __shared__ unsigned long long s_mask[MOE_MAX_EXPERTS][kWords];
   __shared__ int s_base[MOE_MAX_EXPERTS];       // first position of this chunk inside expert e's segment
   __shared__ int s_wsum[kBigThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int chunk = blockIdx.x, t0 = chunk * kChunk;
-  stage_chunk(idx, k_t, j_lo, t0, T, E, K, s_idx, inv_pos);
+  const int chunk = blockIdx.x, t0 = chunk * kChunk, np = min(kChunk, T - t0) * K;
+  int pe[kPerThread];                                  // this thread's pairs of the chunk
+#pragma unroll
+  for (int c = 0; c < kPerThread; ++c) {
+    const int i = tid + c * kBigThreads, tl = i / K;
+    pe[c] = i < np ? pair_expert(idx, k_t, j_lo, t0 + tl, i - tl * K, (size_t)t0 * K + i, E, K) : -1;
+  }
+  for (int i = tid; i < E * kWords; i += kBigThreads) (&s_mask[0][0])[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kPerThread; ++c) {
+    const int tl = (tid + c * kBigThreads) / K;
+    if (pe[c] >= 0) atomicOr(&s_mask[pe[c]][tl >> 6], 1ull << (tl & 63));
+  }
   // per expert (one thread each, E <= 256 = kBigThreads): pairs in earlier chunks, pairs in all
   // chunks.  The count table goes through LDS in slabs with coalesced, independent loads (a
   // per-thread loop over global memory would pay one memory latency per chunk).
@@ -180,35 +179,19 @@ __global__ __launch_bounds__(kBigThreads) void dispatch_scatter_kernel(
   }
   if (chunk == 0 && tid == 0) offsets[E] = P;
   __syncthreads();
-  const int nt = min(kChunk, T - t0);
-  // each lane keeps the selections of its two tokens (one per 64-token half of the chunk) in
-  // registers, so the loop over experts is compares, a ballot and the stores
-  static_assert(kChunk == 128, "two 64-token halves per chunk");
-  int sel[2][MOE_MAX_TOPK];
 #pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-    for (int j = 0; j < MOE_MAX_TOPK; ++j) {
-      const int tl = hb * 64 + lane;
-      sel[hb][j] = (tl < nt && j < K) ? s_idx[tl * K + j] : -1;
+  for (int c = 0; c < kPerThread; ++c) {
+    const int i = tid + c * kBigThreads;
+    if (i >= np) break;
+    int p = -1;
+    if (pe[c] >= 0) {
+      const int tl = i / K;
+      p = s_base[pe[c]] + __popcll(s_mask[pe[c]][tl >> 6] & lanemask_lt(tl & 63));
+      if (tl >= 64) p += __popcll(s_mask[pe[c]][0]);
+      sorted_token[p] = t0 + tl;
+      sorted_rank[p] = i - tl * K;
     }
-  for (int e = wave; e < E; e += kBigThreads / 64) {
-    int pos = s_base[e];
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      int j = -1;
-#pragma unroll
-      for (int jj = MOE_MAX_TOPK - 1; jj >= 0; --jj) if (sel[hb][jj] == e) j = jj;
-      const unsigned long long b = __ballot(j >= 0);
-      if (j >= 0) {
-        const int tl = hb * 64 + lane;
-        const int p = pos + __popcll(b & lanemask_lt(lane));
-        sorted_token[p] = t0 + tl;
-        sorted_rank[p] = j;
-        inv_pos[(size_t)(t0 + tl) * K + j] = p;
-      }
-      pos += __popcll(b);
-    }
+    inv_pos[(size_t)t0 * K + i] = p;
   }
   // positions beyond P are not pairs
   const int n = T * K;

@@ -122,3 +122,30 @@ def test_tiled_mxfp4_orders(counts, H, I):
     off, st = b.expert_offsets.tolist(), b.sorted_token.long()
     ref = torch.cat([_ffn32(dense[e], H, I, x[st[off[e]:off[e + 1]]]) for e in range(E)])
     assert ((b.y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+
+
+@pytest.mark.parametrize("T,E,K", [(1, 1, 1), (63, 5, 3), (64, 60, 4), (65, 256, 16), (255, 7, 7), (256, 256, 16),
+                                   (257, 64, 8), (300, 256, 16), (1024, 9, 2)])
+@pytest.mark.parametrize("j_lo", [0, 1])
+def test_dispatch_masks(T, E, K, j_lo):
+    """Edges of the token masks (64 tokens a word), of the two shapes and of the thread-to-pair
+    mapping, against a sort of the pairs; k_t from 0 to K."""
+    rng = np.random.default_rng(T * 1000 + E)
+    cfg = wl.LayerConfig("edge", T=T, H=64, E=E, I=64, k_big=K, k_little=1)
+    idx = np.stack([rng.permutation(E)[:K] for _ in range(T)]).astype(np.int32)
+    k_t = rng.integers(0, K + 1, T).astype(np.int32)
+    idx[np.arange(K)[None, :] >= k_t[:, None]] = -1
+    b = mm.StepBuffers(cfg)
+    b.topk_idx.copy_(torch.from_numpy(idx))
+    b.k_t.copy_(torch.from_numpy(k_t))
+    mm.moe_dispatch_from(b.c, b.topk_idx, b.k_t, j_lo, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos,
+                         b.dws, b.dws_bytes)
+    pairs = sorted((idx[t, j], t, j) for t in range(T) for j in range(j_lo, k_t[t]))
+    off = np.searchsorted([p[0] for p in pairs], np.arange(E + 1)).astype(np.int32)
+    tok, rank = np.full(T * K, -1, np.int32), np.full(T * K, -1, np.int32)
+    inv = np.full((T, K), -1, np.int32)
+    for p, (_, t, j) in enumerate(pairs):
+        tok[p], rank[p], inv[t, j] = t, j, p
+    assert np.array_equal(b.expert_offsets.cpu().numpy(), off)
+    assert np.array_equal(b.sorted_token.cpu().numpy(), tok) and np.array_equal(b.sorted_rank.cpu().numpy(), rank)
+    assert np.array_equal(b.inv_pos.cpu().numpy(), inv)
