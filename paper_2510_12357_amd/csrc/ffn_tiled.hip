@@ -291,6 +291,11 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         bcol[p] = (ld_pcw ^ WF::key(br)) * WF::kPerCol;
         boff[p] = (n < G.N ? (unsigned)n * WF::bytes((unsigned)G.ldw) + extra : kOob) + WF::bytes((unsigned)bcol[p]);
       }
+      // The bf16 weights of a panel with one token tile are read once and need no place in the caches, which
+      // then hold the token rows longer.  gate+up, us, 64 experts of 1024: 300 tokens 93 -> 82, 777 tokens
+      // 136 -> 128, 2048 tokens 151 -> 146; 8 of 14336, 700 tokens 377 -> 357.  Narrow weights lose by it,
+      // their chunks being half a cache line and less (MXFP4, 60 experts, 600 tokens 123 -> 147).
+      const bool once = WB == 2 && mt == 1;
       // chunk `kt` into stage `st`, then step the offsets to the next chunk
       auto issue = [&](int st, int kt) {
         char* const sa = s_tiles + st * kStageBytes + (lw * kInsA) * 1024;
@@ -305,7 +310,8 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
 #pragma unroll
         for (int p = 0; p < kInsB; ++p) {
           const unsigned off = full ? boff[p] : ((kt * BK + bcol[p] < K) ? boff[p] : kOob);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off, 0, 0, 0);
+          if (once) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off, 0, 0, kStreamOnce);
+          else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off, 0, 0, 0);
           boff[p] += kRowBW;
         }
       };

@@ -83,6 +83,17 @@ def test_wide_tiles(counts, H, I, shared):
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 40, 127, 128, 129, 1], 200, 264, ()),                  # one token tile per panel, and two
+    ([90, 64, 128, 31], 72, 136, (264,)),                          # a shared expert of three token tiles
+])
+def test_tiled_bf16_weights_read_once(counts, H, I, shared):
+    """Prefill with few rows per expert: panels of one token tile load their weights past the caches, the
+    others through them.  Bar as for the wide tiles."""
+    assert sum(counts) >= 256
+    _check_assigned(counts, H, I, shared)
+
+
+@pytest.mark.parametrize("counts,H,I,shared", [
     ([0, 1, 32, 33, 64, 65, 50], 200, 264, ()),                    # items of 64 token rows, their remainders
     ([16, 17, 48, 49], 1032, 72, (520,)),                          # several chunks of K; a shared expert of 130 rows
     ([65], 64, 40, ()),
