@@ -145,16 +145,19 @@ SlabPlan slab_plan(const moe_config& c) {
 namespace {
 // bf16 steps whose weight rows meet this many token rows on average run on 256 x 256 tiles
 // (ffn_wide.hip), smaller ones on 128 x 256 (ffn_tiled.hip), whose two extra waves per SIMD hide the
-// loads of short tiles better.  gate+up + down, us, 128 x 256 against 256 x 256: 8 experts of 14336, 131
-// rows 644 / 672, 192 rows 700 / 711, 384 rows 1083 / 956; 64 of 1024, 192 rows 250 / 254, 384 rows
-// 370 / 358; 60 of 1408 + 5632 shared, 109 rows 285 / 316, 224 rows 390 / 382, 448 rows 660 / 549.
-constexpr long long kWideMinRows = 208;
+// loads of short tiles better.  Many experts are hit unevenly, so that half of them still have short
+// tiles at a mean where few experts have none; the full groups of shared experts come in between.
+// gate+up + down, us, 128 x 256 / 256 x 256: 8 experts of 14336, 192 rows 700 / 711, 215 rows 708 / 698,
+// 384 rows 1081 / 952; 64 of 1024, 281 rows 284 / 296, 384 rows 361 / 352; 64 of 1408 + 2 shared, 217
+// rows 355 / 360, 246 rows 398 / 389, 403 rows 540 / 504; 60 of 1408 + 5632 shared, 229 rows 369 / 383,
+// 273 rows 425 / 415, 448 rows 649 / 539.
+long long wide_min_rows(const moe_config& c) { return c.E <= kFewExperts ? 208 : (c.n_shared > 0 ? 240 : 352); }
 bool wide_tiles(const moe_config& c) {
   long long sh = 0;
   for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
   // rows x weight rows, with the mean of the two expert counts per token
   const long long work = (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh;
-  return c.dtype == MOE_BF16 && work >= kWideMinRows * ((long long)c.E * c.I + sh);
+  return c.dtype == MOE_BF16 && work >= wide_min_rows(c) * ((long long)c.E * c.I + sh);
 }
 struct FfnLayout {
   size_t h_routed, h_shared[MOE_MAX_SHARED], total;
@@ -352,7 +355,7 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   const bool tiled = cfg->dtype != MOE_FP32 && cfg->T >= kTiledMinT;
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
   const bool wide = tiled && wide_tiles(*cfg);
-  a.by_rows = tiled && tiles_by_rows(*cfg);
+  a.by_rows = wide ? wide_by_rows(*cfg) : tiled && tiles_by_rows(*cfg);
   auto launch = [&](StreamMode mode) {
     return wide ? launch_wide(mode, a, s) : (tiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s));
   };

@@ -26,9 +26,9 @@
 //     1152 us, remainder next to the whole tiles 1057, even heights 1045; ffn_tiled.hip 1137 .. 1177.)
 //
 // Measured, ffn_tiled.hip -> this kernel, us (gate+up / down): 8 experts of 14336, 4096 tokens 1137 / 636
-// -> 1080 / 602, 2048 tokens 668 / 415 -> 638 / 318; 60 experts of 1408 + 5632 shared, 4096 tokens
-// 394 / 266 -> 346 / 203; 64 of 1408 + 2 shared, 4096 tokens 326 / 221 -> 329 / 193.  The MFMAs alone (no
-// loads, no fragment reads) take 747 of the 1080 us.
+// -> 1077 / 597, 2048 tokens 668 / 415 -> 641 / 320; 60 experts of 1408 + 5632 shared, 4096 tokens
+// 394 / 266 -> 350 / 204; 64 of 1408 + 2 shared, 4096 tokens 326 / 221 -> 304 / 192.  The MFMAs alone (no
+// loads, no fragment reads) take 747 of the 1077 us.
 #include <atomic>
 #include <type_traits>
 
@@ -214,11 +214,14 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   const int n_sh = MODE == kDown ? a.n_slabs : a.n_shared;
   const int n_groups = a.n_routed + n_sh;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslots = gridDim.x >> 3;
+  const bool by_rows = uniform(a.by_rows) != 0;
+  const int workers = by_rows ? nslots : 8 * nslots;        // workgroups that share a tile list
 
-  // Panel n (kOut output columns) of group g belongs to XCD (n + g) % 8.  Tile height: 256 rows use
+  // Two orders of the tiles.  By rows: panel n (kOut output columns) of group g belongs to XCD (n + g) % 8 and
+  // each XCD has a list of its own; otherwise one list by groups, cut into 8 contiguous ranges.  Tile height: 256 rows use
   // LDS best, but a few large tiles can leave the last round half empty (8 experts of 614 rows,
   // down: 48 tiles of 205 rows on 32 CUs take 632 us, 64 of 160 rows 570); the height with the
-  // smallest estimate of this XCD's time is taken.
+  // smallest estimate of the list's time is taken.
   int gm[kGrpC], gp[kGrpC];
   int R = 256;
   {
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
           const int N = MODE == kDown ? a.H : (g < n_sh ? a.shared_I[g] : a.I);
           const int nt = (N + kOut - 1) / kOut, first = (xcd - g) & 7;
           gm[c] = s.m;
-          gp[c] = nt > first ? (nt - first + 7) >> 3 : 0;
+          gp[c] = !by_rows ? nt : (nt > first ? (nt - first + 7) >> 3 : 0);
         }
       }
     }
@@ -256,11 +259,11 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
         }
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) n_top += __shfl_xor(n_top, d);
-      const int est = uniform(max(sum / nslots, (n_top + nslots - 1) / nslots * top));
+      const int est = uniform(max(sum / workers, (n_top + workers - 1) / workers * top));
       if (est < best) { best = est; R = r; }
     }
   }
-  // Tile list of this XCD: inclusive prefix over the groups c * 64 + lane, groups with many rows first;
+  // Tile list: inclusive prefix over the groups c * 64 + lane, by rows the groups with many rows first;
   // the token tiles of a panel are adjacent, so that they run side by side.
   int pref[kBuckets][kGrpC], tot[kBuckets];
 #pragma unroll
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
 #pragma unroll
   for (int c = 0; c < kGrpC; ++c) {
     const int v = (gm[c] + R - 1) / R * gp[c], m = gm[c];
-    const int bk = m > 256 ? 0 : (m > 192 ? 1 : (m > 128 ? 2 : 6 - ((m - 1) >> 5)));
+    const int bk = m > 256 || !by_rows ? 0 : (m > 192 ? 1 : (m > 128 ? 2 : 6 - ((m - 1) >> 5)));
 #pragma unroll
     for (int k = 0; k < kBuckets; ++k) {
       pref[k][c] = 0x7fffffff;
@@ -284,7 +287,10 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   int total = 0;
 #pragma unroll
   for (int k = 0; k < kBuckets; ++k) total += tot[k];
-  const int mine = total > slot ? (total - slot - 1) / nslots + 1 : 0;      // tiles of this workgroup
+  // first tile and number of tiles of this XCD, then the tiles of this workgroup
+  const int first_tile = by_rows ? 0 : (int)((long)total * xcd / 8);
+  const int xcd_tiles = by_rows ? total : (int)((long)total * (xcd + 1) / 8) - first_tile;
+  const int mine = xcd_tiles > slot ? (xcd_tiles - slot - 1) / nslots + 1 : 0;
 
   // ---- this workgroup's i-th tile.  Half of the workgroups take theirs from the back, so that tiles bound
   // by their weights and tiles bound by the matrix cores run at the same time (64 experts of
@@ -293,8 +299,8 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
     Tile T = {};
     T.valid = i < mine;
     if (!T.valid) return T;
-    if (2 * slot >= nslots) i = mine - 1 - i;
-    int v = i * nslots + slot;
+    if (by_rows && 2 * slot >= nslots) i = mine - 1 - i;
+    int v = first_tile + i * nslots + slot;
     int bk = -1, g = 0, ex = 0;
 #pragma unroll
     for (int k = 0; k < kBuckets; ++k) {
@@ -334,7 +340,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
     T.m = T.m0 + rows;
     T.tall = rows > 128;
     T.nb = rows > 192 ? 4 : (rows > 128 ? 3 : (rows + 31) >> 5);
-    T.n0 = (((xcd - g) & 7) + 8 * panel) * kOut;
+    T.n0 = (by_rows ? ((xcd - g) & 7) + 8 * panel : panel) * kOut;
     T.N = G.N; T.K = G.K; T.row0 = G.row0; T.gather = G.gather;
     T.ldb = (unsigned)G.ldw * 2u;
     T.w0 = G.w0; T.b = G.b; T.out = G.out; T.wbytes = G.wbytes; T.bbytes = G.bbytes;
@@ -568,6 +574,21 @@ int launch_wide_mode(const StreamArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+// Contiguous ranges keep a group's token rows in one L2 and its weights in one range of memory; the order by rows
+// (a.by_rows) gives every XCD the same mix of tile heights.  With few experts a range lies in one or two groups and its
+// tiles are alike; with many, heights differ by the skew of the selection, and by the shared experts'
+// full groups until the experts have about as many rows as a tile.  gate+up + down, us, mean of six random
+// layers, contiguous / by rows (rows per expert): 8 experts of 14336, 1150 tokens 698 / 722, 2048 tokens
+// 952 / 957, 4096 tokens 1697 / 1715; 64 of 1024, 3000 tokens 300 / 296, 4096 tokens 356 / 352; 64 of
+// 1408 + 2 shared, 2500 (176) 398 / 389, 3000 (211) 400 / 433, 4096 (288) 504 / 516; 60 of 1408 + 5632
+// shared, 2500 (125) 474 / 415, 4096 (205) 559 / 539.  Ranges of equal estimated time instead of equal tile
+// counts: the last 531, but 2500 434 and the 64 experts 388.
+constexpr long long kContiguousMinRows = 208;
+bool wide_by_rows(const moe_config& c) {
+  if (c.E <= kFewExperts) return false;
+  return c.n_shared == 0 || (long long)c.T * (c.k_big + c.k_little) < 2 * kContiguousMinRows * c.E;
+}
 
 int launch_wide(StreamMode mode, const StreamArgs& a, hipStream_t s) {
   return mode == kGateUp ? launch_wide_mode<kGateUp>(a, s) : launch_wide_mode<kDown>(a, s);

@@ -74,6 +74,9 @@ def _check_assigned(counts, H, I, shared):
     ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),    # one chunk of K, padded to the ring's length
     ([400, 512, 31, 450], 576, 128, (1512, 8)),                     # shared experts cut along K; whole tiles
     ([1300], 128, 40, ()),                                          # one group, fewer panels than XCDs
+    ([0, 1, 40, 128, 129, 193, 257, 300] + [3] * 10, 200, 264, (1512,)),  # few rows beside a shared expert: by rows
+    ([400] * 15 + [900, 1, 0], 64, 296, ()),                        # many experts: by rows
+    ([300], 64, 40, (72, 2048)),                                    # by groups, fewer tiles than workgroups
 ])
 def test_wide_tiles(counts, H, I, shared):
     """256 x 256 tiles against fp32 products of the same bf16 operands: the activations h round to
