@@ -23,7 +23,8 @@
 //     c ^ ((r >> 1) & 7), which spreads the 16 rows that a b128 fragment read touches in one
 //     pass over all banks.
 //   * tiles are enumerated on the device from expert_offsets (the host never sees the counts);
-//     persistent workgroups; the tile list is cut into 8 contiguous ranges, one per XCD, and
+//     persistent workgroups; the tile list is cut into 8 contiguous ranges, one per XCD, or dealt to
+//     the XCDs by panels (two orders, below); either way
 //     the token tiles that share a weight panel are adjacent in the list, so a panel is fetched
 //     from HBM once and re-read from that XCD's L2.
 //   * 8-bit weights (WB = 1: E4M3 codes with one fp32 scale per weight row): the weight rows of a

@@ -7,7 +7,7 @@
 // selection decisions are comparisons on the fp32 logits, so they are exact and reproducible.
 //
 // Kernels:
-//   gate_route_kernel router logits and selection of one token per workgroup (decode batches)
+//   gate_route_kernel router logits and selection of one token per workgroup (small steps)
 //   gate_gemv_kernel  router logits alone (up to 256 tokens): plain fp32 FMAs, one wave per
 //                     small block of logits, so that even one token spreads over E waves
 //   route_kernel      softmax / importance / top-k on given logits
@@ -104,7 +104,7 @@ void launch_gemv(const moe_config& c, const void* x, const void* Wg, const float
                      c.T, c.H, c.E, logits);
 }
 
-// Router logits and selection of one token in one workgroup (decode batches): the waves split the
+// Router logits and selection of one token in one workgroup (small steps): the waves split the
 // experts, every wave sums its experts' dot products exactly as gate_gemv_kernel does (per lane
 // the 8-element chunks lane, lane + 64, ... in ascending order, then the same shuffle reduction),
 // so the logits are bit-identical to that kernel's; they go to global memory and to LDS, and wave
@@ -224,7 +224,7 @@ int launch_route(const moe_config& c, const float* conf, const float* logits, in
   return hip_fail(hipGetLastError(), "route_kernel launch");
 }
 
-// Router logits + selection in one launch; for steps of at most kFusedRouteMaxT tokens.
+// Router logits + selection in one launch; for small steps (rule in moe_route).
 int launch_gate_route(const moe_config& c, const void* x, const void* Wg, const float* bias, const float* conf,
                       float* logits, int32_t* idx, float* w, uint8_t* important, int32_t* k_t, hipStream_t s) {
   if (c.T == 0) return MOE_OK;
