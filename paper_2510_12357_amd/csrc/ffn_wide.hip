@@ -34,9 +34,12 @@
 
 #include "internal.h"
 #include "groups.h"
+#include "wide_layout.h"
 
 namespace mm {
 namespace {
+
+using namespace wide;
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -45,10 +48,7 @@ typedef uint16_t S;
 constexpr int kThreadsW = 256;
 constexpr int kBuckets = 7;             // groups by their token rows, most first
 constexpr int kGrpC = (kMaxGroups + 63) / 64;
-constexpr int kRowB = 128;              // bytes of a tile row in LDS (64 k)
-constexpr int kSlotB = 256 * kRowB;     // a token or a weight slot
 constexpr int kOutCols(int mode) { return mode == kGateUp ? 128 : 256; }
-constexpr int SA = 2, SB = 3;           // token slots, then weight slots: all of the CU's LDS
 constexpr int kA = 8, kB = 8;           // loads of a wave per token / weight chunk
 constexpr int kLoads = (kA + kB) / 4;   // ... per k-step
 constexpr int kLdsBytes = (SA + SB) * kSlotB;
@@ -66,6 +66,7 @@ struct Loads { i32x4 rs[4]; unsigned vo[4]; int so[4]; int md[4]; };
 #define MF(i, j) "v_mfma_f32_32x32x16_bf16 %[c" #i #j "], %[a" #i "], %[b" #j "], %[c" #i #j "]\n\t"
 #define RA(i) "ds_read_b128 %[na" #i "], %[pa] offset:%[oa" #i "]\n\t"
 #define RB(j) "ds_read_b128 %[nb" #j "], %[pb] offset:%[ob" #j "]\n\t"
+#define RQ(j) "ds_read_b128 %[nb" #j "], %[q" #j "] offset:%[ob" #j "]\n\t"
 #define LD(l) "s_mov_b32 m0, %[md" #l "]\n\ts_nop 0\n\tbuffer_load_dwordx4 %[vo" #l "], %[rs" #l "], %[so" #l "] offen lds\n\t"
 #define BAR "s_waitcnt vmcnt(%[vm])\n\ts_barrier\n\t"
 // the compiler does not see what the block holds: wait states between its vector instructions and the
@@ -82,13 +83,17 @@ struct Loads { i32x4 rs[4]; unsigned vo[4]; int so[4]; int md[4]; };
   [vo0] "v"(L.vo[0]), [vo1] "v"(L.vo[1]), [vo2] "v"(L.vo[2]), [vo3] "v"(L.vo[3]), \
   [so0] "s"(L.so[0]), [so1] "s"(L.so[1]), [so2] "s"(L.so[2]), [so3] "s"(L.so[3]), \
   [md0] "s"(L.md[0]), [md1] "s"(L.md[1]), [md2] "s"(L.md[2]), [md3] "s"(L.md[3])
-#define OFFS [oa0] "n"(0), [oa1] "n"(4096), [oa2] "n"(8192), [oa3] "n"(12288)
-#define OFFB [ob0] "n"(0), [ob1] "n"(4096), [ob2] "n"(UP), [ob3] "n"(UP + 4096)
+#define OFFS [oa0] "n"(0), [oa1] "n"(kBlock * kRowB), [oa2] "n"(2 * kBlock * kRowB), [oa3] "n"(3 * kBlock * kRowB)
+#define OB(j) [ob##j] "n"(b_frag_row(GU, j) * kRowB)
+#define OFFB OB(0), OB(1), OB(2), OB(3)
+// addresses of the weight fragments of the next tile's first k-step: pq for those that a narrow tile has no use for
+#define QB(j) [q##j] "v"(j == 0 || j == second_frag(GU) ? pb : pq)
+#define NEXT QB(0), QB(1), QB(2), QB(3), [vm] "n"(VM)
 #define NALL NA(0), NA(1), NA(2), NA(3), NB_(0), NB_(1), NB_(2), NB_(3)
 #define IN4 IA(0), IA(1), IA(2), IA(3), IB(0), IB(1), IB(2), IB(3)
 #define REST [pa] "v"(pa), [pb] "v"(pb), LOADS4, OFFS, OFFB
-// the reads behind the barrier fetch all eight fragments, whatever shape the next tile has
-#define RDALL RB(0) RB(1) RB(2) RB(3) RA(0) RA(1) RA(2) RA(3)
+// the reads behind the barrier fetch all eight fragments, whatever shape the next tile has (b_row_of)
+#define RDALL RQ(0) RQ(1) RQ(2) RQ(3) RA(0) RA(1) RA(2) RA(3)
 
 #define C2J(i, J) C1(i, 0), C1(i, J)
 #define NARROW_STEPS(J)                                                                                                  \
@@ -100,7 +105,7 @@ struct Loads { i32x4 rs[4]; unsigned vo[4]; int so[4]; int md[4]; };
     else                                                                                                                 \
       asm volatile(START MF(0,0) MF(0,J) BAR MF(1,0) RDALL MF(1,J) LD(0) MF(2,0) LD(1) MF(2,J) LD(2) MF(3,0) LD(3) MF(3,J) END \
                    : C2J(0, J), C2J(1, J), C2J(2, J), C2J(3, J), NALL                                                     \
-                   : IA(0), IA(1), IA(2), IA(3), IB(0), IB(J), REST, [vm] "n"(VM) : "memory");                            \
+                   : IA(0), IA(1), IA(2), IA(3), IB(0), IB(J), REST, NEXT : "memory");                            \
   } else if constexpr (NB == 3) {                                                                                        \
     if constexpr (!BARRIER)                                                                                              \
       asm volatile(START MF(0,0) RB(0) RB(J) MF(0,J) RA(0) LD(0) MF(1,0) RA(1) RA(2) MF(1,J) LD(1) MF(2,0) LD(2) LD(3) MF(2,J) END \
@@ -109,7 +114,7 @@ struct Loads { i32x4 rs[4]; unsigned vo[4]; int so[4]; int md[4]; };
     else                                                                                                                 \
       asm volatile(START MF(0,0) MF(0,J) BAR MF(1,0) RDALL MF(1,J) LD(0) LD(1) MF(2,0) LD(2) LD(3) MF(2,J) END           \
                    : C2J(0, J), C2J(1, J), C2J(2, J), NALL                                                                \
-                   : IA(0), IA(1), IA(2), IB(0), IB(J), REST, [vm] "n"(VM) : "memory");                                   \
+                   : IA(0), IA(1), IA(2), IB(0), IB(J), REST, NEXT : "memory");                                   \
   } else if constexpr (NB == 2) {                                                                                        \
     if constexpr (!BARRIER)                                                                                              \
       asm volatile(START MF(0,0) RB(0) RB(J) MF(0,J) RA(0) RA(1) LD(0) MF(1,0) LD(1) LD(2) MF(1,J) LD(3) END             \
@@ -118,7 +123,7 @@ struct Loads { i32x4 rs[4]; unsigned vo[4]; int so[4]; int md[4]; };
     else                                                                                                                 \
       asm volatile(START MF(0,0) MF(0,J) BAR MF(1,0) RDALL MF(1,J) LD(0) LD(1) LD(2) LD(3) END                           \
                    : C2J(0, J), C2J(1, J), NALL                                                                           \
-                   : IA(0), IA(1), IB(0), IB(J), REST, [vm] "n"(VM) : "memory");                                          \
+                   : IA(0), IA(1), IB(0), IB(J), REST, NEXT : "memory");                                          \
   } else {                                                                                                               \
     if constexpr (!BARRIER)                                                                                              \
       asm volatile(START MF(0,0) RB(0) RB(J) RA(0) MF(0,J) LD(0) LD(1) LD(2) LD(3) END                                   \
@@ -127,24 +132,24 @@ struct Loads { i32x4 rs[4]; unsigned vo[4]; int so[4]; int md[4]; };
     else                                                                                                                 \
       asm volatile(START MF(0,0) MF(0,J) BAR RDALL LD(0) LD(1) LD(2) LD(3) END                                           \
                    : C2J(0, J), NALL                                                                                      \
-                   : IA(0), IB(0), IB(J), REST, [vm] "n"(VM) : "memory");                                                 \
+                   : IA(0), IB(0), IB(J), REST, NEXT : "memory");                                                 \
   }
 
-// UP: byte distance between the first and the second half of a wave's weight rows in a slot.  Tiles of
-// more than 128 tokens: waves in a 2 x 2 grid, NB x 4 matrix tiles each.  Narrower ones: the waves
-// split the weight rows four ways, NB x 2 tiles each (weight fragments 0 and J).
-template <bool TALL, int NB, int UP, int J, bool BARRIER>
+// GU: gate/up.  Tiles of more than 128 tokens: waves in a 2 x 2 grid, NB x 4 matrix tiles each.  Narrower
+// ones: the waves split the weight rows four ways, NB x 2 tiles each (weight fragments 0 and
+// second_frag).  pq: as pb, from the row b_row_of of the other two fragments on.
+template <bool TALL, int NB, bool GU, bool BARRIER>
 __device__ __forceinline__ void kstep(f32x16 (&c)[4][4], const bf16x8 (&fa)[4], const bf16x8 (&fb)[4], bf16x8 (&na)[4],
-                                      bf16x8 (&nb)[4], unsigned pa, unsigned pb, const Loads& L) {
+                                      bf16x8 (&nb)[4], unsigned pa, unsigned pb, unsigned pq, const Loads& L) {
   if constexpr (TALL && NB == 4) {
     if constexpr (!BARRIER)
       asm volatile(START MF(0,0) RB(0) MF(0,1) RB(1) MF(0,2) RB(2) LD(0) MF(0,3) RB(3) MF(1,0) RA(0) MF(1,1) RA(1) LD(1) MF(1,2) RA(2) MF(1,3) RA(3)
                    MF(2,0) LD(2) MF(2,1) MF(2,2) MF(2,3) MF(3,0) LD(3) MF(3,1) MF(3,2) MF(3,3) END
                    : C4(0), C4(1), C4(2), C4(3), NALL : IN4, REST : "memory");
     else
-      asm volatile(START MF(0,0) MF(0,1) MF(0,2) MF(0,3) BAR MF(1,0) RB(0) RB(1) MF(1,1) RB(2) RB(3) MF(1,2) RA(0) RA(1) MF(1,3) RA(2) RA(3)
+      asm volatile(START MF(0,0) MF(0,1) MF(0,2) MF(0,3) BAR MF(1,0) RQ(0) RQ(1) MF(1,1) RQ(2) RQ(3) MF(1,2) RA(0) RA(1) MF(1,3) RA(2) RA(3)
                    MF(2,0) LD(0) MF(2,1) MF(2,2) LD(1) MF(2,3) MF(3,0) LD(2) MF(3,1) MF(3,2) LD(3) MF(3,3) END
-                   : C4(0), C4(1), C4(2), C4(3), NALL : IN4, REST, [vm] "n"(VM) : "memory");
+                   : C4(0), C4(1), C4(2), C4(3), NALL : IN4, REST, NEXT : "memory");
   } else if constexpr (TALL && NB == 3) {
     if constexpr (!BARRIER)
       asm volatile(START MF(0,0) RB(0) MF(0,1) RB(1) MF(0,2) RB(2) LD(0) MF(0,3) RB(3) MF(1,0) RA(0) MF(1,1) RA(1) LD(1) MF(1,2) RA(2) MF(1,3)
@@ -152,10 +157,10 @@ __device__ __forceinline__ void kstep(f32x16 (&c)[4][4], const bf16x8 (&fa)[4], 
                    : C4(0), C4(1), C4(2), NA(0), NA(1), NA(2), NB_(0), NB_(1), NB_(2), NB_(3)
                    : IA(0), IA(1), IA(2), IB(0), IB(1), IB(2), IB(3), REST : "memory");
     else
-      asm volatile(START MF(0,0) MF(0,1) MF(0,2) MF(0,3) BAR MF(1,0) RB(0) RB(1) MF(1,1) RB(2) RB(3) MF(1,2) RA(0) RA(1) MF(1,3) RA(2) RA(3)
+      asm volatile(START MF(0,0) MF(0,1) MF(0,2) MF(0,3) BAR MF(1,0) RQ(0) RQ(1) MF(1,1) RQ(2) RQ(3) MF(1,2) RA(0) RA(1) MF(1,3) RA(2) RA(3)
                    MF(2,0) LD(0) MF(2,1) LD(1) MF(2,2) LD(2) MF(2,3) LD(3) END
-                   : C4(0), C4(1), C4(2), NALL : IA(0), IA(1), IA(2), IB(0), IB(1), IB(2), IB(3), REST, [vm] "n"(VM) : "memory");
-  } else if constexpr (J == 2) {
+                   : C4(0), C4(1), C4(2), NALL : IA(0), IA(1), IA(2), IB(0), IB(1), IB(2), IB(3), REST, NEXT : "memory");
+  } else if constexpr (second_frag(GU) == 2) {
     NARROW_STEPS(2)
   } else {
     NARROW_STEPS(1)
@@ -164,9 +169,9 @@ __device__ __forceinline__ void kstep(f32x16 (&c)[4][4], const bf16x8 (&fa)[4], 
 #undef NARROW_STEPS
 
 // first fragments: nothing to multiply yet
-template <int UP>
-__device__ __forceinline__ void first_frags(bf16x8 (&na)[4], bf16x8 (&nb)[4], unsigned pa, unsigned pb) {
-  asm volatile(BAR RDALL END : NALL : [pa] "v"(pa), [pb] "v"(pb), OFFS, OFFB, [vm] "n"(VM) : "memory");
+template <bool GU>
+__device__ __forceinline__ void first_frags(bf16x8 (&na)[4], bf16x8 (&nb)[4], unsigned pa, unsigned pb, unsigned pq) {
+  asm volatile(BAR RDALL END : NALL : [pa] "v"(pa), OFFS, OFFB, NEXT : "memory");
 }
 __device__ __forceinline__ void load_one(i32x4 rs, unsigned vo, int so, int md) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" :: "v"(vo), "s"(rs), "s"(so), "s"(md) : "memory");
@@ -363,8 +368,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   if (!cur.valid) return;
   const int h = lane >> 5;
   const unsigned fkey = (unsigned)((lane & 31) >> 1) & 7u;
-  constexpr int UP = MODE == kGateUp ? 128 * kRowB : 64 * kRowB;
-  constexpr int J = MODE == kGateUp ? 2 : 1;                 // second weight fragment of a narrow tile's wave
+  constexpr bool GU = MODE == kGateUp;
 
   Tile nx = tile_at(ord++);
   int ids_nx = row_ids(nx);
@@ -457,17 +461,15 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   unsigned col[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) col[k] = lds0 + (unsigned)((lane & 31) * kRowB) + ((unsigned)(2 * k + h) ^ fkey) * 16u;
-  // a wave's first token row and first weight row in a slot
-  auto a_row = [&](const Tile& T) { return T.tall ? (wave >> 1) * T.nb * 32 * kRowB : 0; };
-  auto b_row = [&](const Tile& T) {
-    const int half = MODE == kGateUp ? 32 * kRowB : 64 * kRowB;      // rows of a narrow tile's wave in (the gate half of) a slot
-    return SA * kSlotB + (T.tall ? (wave & 1) * 2 * half : wave * half);
-  };
+  // bytes from a slot's start to a wave's first token row and first weight rows
+  auto a_at = [&](const Tile& T) { return uniform(a_row(T.tall, T.nb, wave) * kRowB); };
+  auto b_at = [&](const Tile& T) { return uniform(SA * kSlotB + b_row(GU, T.tall, wave) * kRowB); };
+  auto q_at = [&](const Tile& T) { return uniform(SA * kSlotB + b_row_of(GU, T.tall, wave, 3) * kRowB); };
   bf16x8 fa[2][4], fb[2][4];
   f32x16 acc[4][4];
   int cA = 0, cB = 0;                                      // slots of the chunk being multiplied
-  int arow = uniform(a_row(cur)), brow = uniform(b_row(cur));
-  first_frags<UP>(fa[0], fb[0], col[0] + arow, col[0] + brow);
+  int arow = a_at(cur), brow = b_at(cur), qrow = q_at(cur);
+  first_frags<GU>(fa[0], fb[0], col[0] + arow, col[0] + brow, col[0] + qrow);
   // loads 0 .. kLoads-1 of period 0
 #pragma unroll
   for (int l = 0; l < kLoads; ++l) load_one(rsA, aoff[l], ka, ldsA + slA * kSlotB + l * 1024);
@@ -475,7 +477,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   auto run_tile = [&](auto tall_tag, auto nb_tag) {
     constexpr bool TALL = decltype(tall_tag)::value;
     constexpr int NB = decltype(nb_tag)::value, TN = TALL ? 4 : 2;
-    constexpr int JS = TALL ? 1 : J;                       // weight fragments 0, JS, ..
+    constexpr int JS = TALL ? 1 : second_frag(GU);                       // weight fragments 0, JS, ..
     const int wm = TALL ? wave >> 1 : 0, wn = TALL ? wave & 1 : wave;
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -489,22 +491,22 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
       Loads L;
 #pragma unroll
       for (int d = 0; d < kLoads; ++d) put(L, d, kLoads + d);
-      kstep<TALL, NB, UP, J, false>(acc, fa[0], fb[0], fa[1], fb[1], col[1] + oA, col[1] + oB, L);
+      kstep<TALL, NB, GU, false>(acc, fa[0], fb[0], fa[1], fb[1], col[1] + oA, col[1] + oB, 0u, L);
 #pragma unroll
       for (int d = 0; d < kLoads; ++d) put(L, d, 2 * kLoads + d);
-      kstep<TALL, NB, UP, J, false>(acc, fa[1], fb[1], fa[0], fb[0], col[2] + oA, col[2] + oB, L);
+      kstep<TALL, NB, GU, false>(acc, fa[1], fb[1], fa[0], fb[0], col[2] + oA, col[2] + oB, 0u, L);
       step_a();
 #pragma unroll
       for (int d = 0; d < kLoads; ++d) put(L, d, 3 * kLoads + d);
-      kstep<TALL, NB, UP, J, false>(acc, fa[0], fb[0], fa[1], fb[1], col[3] + oA, col[3] + oB, L);
+      kstep<TALL, NB, GU, false>(acc, fa[0], fb[0], fa[1], fb[1], col[3] + oA, col[3] + oB, 0u, L);
       step_b();
       cA = cA + 1 == SA ? 0 : cA + 1;
       cB = cB + 1 == SB ? 0 : cB + 1;
-      if (kt + 1 == nk) { arow = uniform(a_row(nx)); brow = uniform(b_row(nx)); }   // the next chunk is the next tile's first
+      if (kt + 1 == nk) { arow = a_at(nx); brow = b_at(nx); qrow = q_at(nx); }   // the next chunk is the next tile's first
 #pragma unroll
       for (int d = 0; d < kLoads; ++d) put(L, d, d);
-      kstep<TALL, NB, UP, J, true>(acc, fa[1], fb[1], fa[0], fb[0], col[0] + (unsigned)(cA * kSlotB + arow),
-                                   col[0] + (unsigned)(cB * kSlotB + brow), L);
+      kstep<TALL, NB, GU, true>(acc, fa[1], fb[1], fa[0], fb[0], col[0] + (unsigned)(cA * kSlotB + arow),
+                                col[0] + (unsigned)(cB * kSlotB + brow), col[0] + (unsigned)(cB * kSlotB + qrow), L);
     }
     asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");      // matrix results are readable
     // ---- epilogue: accumulator v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.  The buffer
