@@ -360,9 +360,6 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
     if (T.valid && T.gather) id = val ? clampi(a.sorted_token[T.row0 + r], 0, a.T - 1) : -1;
     return id;
   };
-  // chunks of a tile: at least SB, so that the load cursors never run past the next tile
-  auto chunks = [&](const Tile& T) { const int n = (T.K + 63) >> 6; return n < SB ? SB : n; };
-
   int ord = 0;
   Tile cur = tile_at(ord++);
   if (!cur.valid) return;
@@ -394,9 +391,9 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
     }
   };
   auto open_a = [&](const Tile& T, int ids) {
-    rsA = rsrc4(T.valid ? T.b : a.x, T.valid ? T.bbytes : 0u);
+    rsA = rsrc4(T.valid ? T.b : a.x, buffer_bytes(T.valid ? T.bbytes : 0u));
     const unsigned closed = T.valid ? 0u : kOob;           // no such tile: nothing is read
-    ka = 0; Ka = uniform(T.K); na_left = T.valid ? chunks(T) : 0x7fffffff;
+    ka = 0; Ka = uniform(T.K); na_left = T.valid ? tile_chunks(T.K) : 0x7fffffff;
 #pragma unroll
     for (int p = 0; p < kA; ++p) {
       const int id = __shfl(ids, 8 * p + sub);
@@ -406,9 +403,9 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
     if (Ka < 64) tail_a();
   };
   auto open_b = [&](const Tile& T) {
-    rsB = rsrc4(T.valid ? T.w0 : a.x, T.valid ? T.wbytes : 0u);
+    rsB = rsrc4(T.valid ? T.w0 : a.x, buffer_bytes(T.valid ? T.wbytes : 0u));
     const unsigned closed = T.valid ? 0u : kOob;
-    kb = 0; Kb = uniform(T.K); nb_left = T.valid ? chunks(T) : 0x7fffffff;
+    kb = 0; Kb = uniform(T.K); nb_left = T.valid ? tile_chunks(T.K) : 0x7fffffff;
 #pragma unroll
     for (int p = 0; p < kB; ++p) {
       int n;
@@ -485,7 +482,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j * JS][v] = 0.f;
-    const int nk = uniform(chunks(cur));
+    const int nk = uniform(tile_chunks(cur.K));
     for (int kt = 0; kt < nk; ++kt) {
       const unsigned oA = (unsigned)(cA * kSlotB + arow), oB = (unsigned)(cB * kSlotB + brow);
       Loads L;

@@ -31,5 +31,14 @@ constexpr int b_row_of(bool gate_up, bool tall, int wave, int j) {
   return tall || j == 0 || j == second_frag(gate_up) ? b_row(gate_up, tall, wave) : 0;
 }
 
+// Chunks of a tile that the load cursors step through: at least SB, so that they never run past the next tile.
+constexpr int tile_chunks(int K) { return (K + 63) >> 6 < SB ? SB : (K + 63) >> 6; }
+// Size that a buffer descriptor states.  A cursor's scalar offset goes on behind the row where K is shorter
+// than SB chunks, and by up to SB chunks where there is no next tile.  All lanes are at kOob by then, but the
+// hardware takes the scalar offset from the stated size before it compares, and that difference must not
+// go below zero.  Lanes with data lie inside the tensor by themselves (rows and columns are checked), so
+// stating more than a short tensor has lets nothing through.
+constexpr unsigned buffer_bytes(unsigned bytes) { return bytes < (unsigned)(SB * kRowB) ? (unsigned)(SB * kRowB) : bytes; }
+
 }  // namespace wide
 }  // namespace mm

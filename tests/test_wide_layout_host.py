@@ -12,16 +12,20 @@ CSRC = os.path.join(ROOT, "paper_2510_12357_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def reads(tmp_path_factory):
+def output(tmp_path_factory):
     cxx = shutil.which(os.environ.get("CXX", "g++"))
     if cxx is None:
         pytest.skip("no host C++ compiler")
     out = str(tmp_path_factory.mktemp("wide") / "wide_layout_check")
     subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC,
                     os.path.join(ROOT, "tests", "host", "wide_layout_check.cpp"), "-o", out], check=True)
-    lines = subprocess.run([out], capture_output=True, text=True, check=True).stdout.splitlines()
-    slot_rows, lds = map(int, lines[0].split())
-    rows = [line.split() for line in lines[1:]]
+    return subprocess.run([out], capture_output=True, text=True, check=True).stdout.splitlines()
+
+
+@pytest.fixture(scope="module")
+def reads(output):
+    slot_rows, lds = map(int, output[0].split())
+    rows = [line.split() for line in output[1:] if not line.startswith("k")]
     return slot_rows, lds, [(int(m), int(t), int(nb), int(w), op, int(f), int(r), int(at)) for m, t, nb, w, op, f, r, at in rows]
 
 
@@ -48,3 +52,15 @@ def test_used_fragments_cover_the_tile_once(reads):
                 if mode:      # gate and up rows of the same outputs in one wave
                     for w in range(4):
                         assert {j + 128 for j in b[w] if j < 128} == {j for j in b[w] if j >= 128}
+
+
+def test_load_offsets_stay_below_the_stated_size(output):
+    """Chunk i of a tile is loaded at scalar offset 128 i, also where a short K has no such chunk; behind the
+    last tile (K = 0) up to three more.  The size that the descriptor states covers the offset, and
+    is not larger than the tensor unless that is shorter than the ring."""
+    cursors = [list(map(int, line.split()[1:])) for line in output if line.startswith("k")]
+    assert [c[0] for c in cursors] == list(range(0, 329, 8))
+    for K, chunks, size in cursors:
+        assert chunks == max(3, (K + 63) // 64)
+        assert 128 * (chunks - 1) <= size, K
+        assert size == max(2 * K, 3 * 128), K
