@@ -187,6 +187,9 @@ int moe_dispatch(const moe_config* cfg, const int32_t* topk_idx, const int32_t* 
  * shared_out device [S, T, H] fp32, S = moe_shared_out_slabs(cfg) >= n_shared (NULL allowed when
  *            nothing shared is run)
  * run_routed / run_shared  select which of the two parts this call computes
+ *            A call with run_routed and without run_shared is taken for a part of a step (a fallback
+ *            pass, a wave of experts) and its kernels are chosen for few rows per expert.  For a whole
+ *            step of a layer without shared experts pass run_shared = 1 too: nothing more is run.
  * ws         device scratch holding the SwiGLU activations
  * The number of pairs per expert is read on the device; the host never waits for it.
  */

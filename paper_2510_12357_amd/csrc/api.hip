@@ -75,9 +75,6 @@ int device_cu_count() {
   return cached_cu;
 }
 
-// Steps of this many tokens and more run the LDS-tiled kernels (bf16 activations).
-constexpr int kTiledMinT = 256;
-
 int validate_config(const moe_config* c) {
   if (!c) return fail(MOE_E_BADARG, "config is NULL");
   if (c->dtype != MOE_BF16 && c->dtype != MOE_FP32 && c->dtype != MOE_BF16_W8 && c->dtype != MOE_BF16_MXFP4)
@@ -143,22 +140,6 @@ SlabPlan slab_plan(const moe_config& c) {
 }
 
 namespace {
-// bf16 steps whose weight rows meet this many token rows on average run on 256 x 256 tiles
-// (ffn_wide.hip), smaller ones on 128 x 256 (ffn_tiled.hip), whose two extra waves per SIMD hide the
-// loads of short tiles better.  Many experts are hit unevenly, so that half of them still have short
-// tiles at a mean where few experts have none; the full groups of shared experts come in between.
-// gate+up + down, us, 128 x 256 / 256 x 256: 8 experts of 14336, 192 rows 700 / 711, 215 rows 708 / 698,
-// 384 rows 1081 / 952; 64 of 1024, 281 rows 284 / 296, 384 rows 361 / 352; 64 of 1408 + 2 shared, 217
-// rows 355 / 360, 246 rows 398 / 389, 403 rows 540 / 504; 60 of 1408 + 5632 shared, 229 rows 369 / 383,
-// 273 rows 425 / 415, 448 rows 649 / 539.
-long long wide_min_rows(const moe_config& c) { return c.E <= kFewExperts ? 208 : (c.n_shared > 0 ? 240 : 352); }
-bool wide_tiles(const moe_config& c) {
-  long long sh = 0;
-  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
-  // rows x weight rows, with the mean of the two expert counts per token
-  const long long work = (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh;
-  return c.dtype == MOE_BF16 && work >= wide_min_rows(c) * ((long long)c.E * c.I + sh);
-}
 struct FfnLayout {
   size_t h_routed, h_shared[MOE_MAX_SHARED], total;
 };
@@ -350,14 +331,12 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   a.n_slabs = shared ? plan.n_slabs : 0;
   for (int i = 0; i < a.n_slabs; ++i) { a.slab_shared[i] = plan.slab_shared[i]; a.slab_chunk[i] = plan.slab_chunk[i]; }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // Regime: with many tokens per step the experts see enough rows for LDS-tiled MFMA GEMMs;
-  // below that the weights are streamed once through the skinny kernel.
-  const bool tiled = cfg->dtype != MOE_FP32 && cfg->T >= kTiledMinT;
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
-  const bool wide = tiled && wide_tiles(*cfg);
-  a.by_rows = wide ? wide_by_rows(*cfg) : tiled && tiles_by_rows(*cfg);
+  const FfnRoute r = ffn_route(*cfg, routed, run_shared != 0, device_cu_count());
+  a.by_rows = r.by_rows;
   auto launch = [&](StreamMode mode) {
-    return wide ? launch_wide(mode, a, s) : (tiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s));
+    if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
+    return r.kernel == kFfnTiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s);
   };
   {
     ProfScope ps(kProfFfnGateUp, s);

@@ -1,0 +1,96 @@
+#include "ffn_route.h"
+
+namespace mm {
+namespace {
+
+struct Work {
+  long long weight_rows;             // gate rows of all weights of the layer
+  long long rows;                    // token rows x weight rows, with the mean of the two expert counts per token
+};
+Work layer_work(const moe_config& c) {
+  long long sh = 0;
+  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
+  return {(long long)c.E * c.I + sh, (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh};
+}
+
+// Whole bf16 steps whose weight rows meet this many token rows on average run on 256 x 256 tiles
+// (ffn_wide.hip), smaller ones on 128 x 256 (ffn_tiled.hip), whose two extra waves per SIMD hide the
+// loads of short tiles better.  Many experts are hit unevenly, so that half of them still have short
+// tiles at a mean where few experts have none; the full groups of shared experts come in between.
+// gate+up + down, us, 128 x 256 / 256 x 256: 8 experts of 14336, 192 rows 700 / 711, 215 rows 708 / 698,
+// 384 rows 1066 / 936; 64 of 1024, 281 rows 280 / 313, 384 rows 368 / 358; 64 of 1408 + 2 shared, 246
+// rows 379 / 373, 266 rows 409 / 408, 325 rows 435 / 389; 60 of 1408 + 5632 shared, 229 rows 363 / 375,
+// 241 rows 383 / 379, 273 rows 410 / 404, 448 rows 656 / 561.
+bool wide_whole(const moe_config& c) {
+  const Work w = layer_work(c);
+  return w.rows >= (c.E <= kFewExperts ? 208 : (c.n_shared > 0 ? 240 : 352)) * w.weight_rows;
+}
+
+// The shared experts alone are one or two groups of T rows: the wide tiles pay once there are 1.5 of them per
+// CU.  us, 128 x 256 / 256 x 256 (wide gate/up tiles): one of 5632, 1024 tokens (176) 95 / 105, 2200
+// (396) 200 / 190, 2800 (484) 218 / 199, 4096 (704) 340 / 278; two of 1408, 2048 tokens (176) 94 / 110,
+// 2500 (220) 110 / 112, 3500 (308) 144 / 147, 4096 (352) 160 / 158.
+bool wide_shared(const moe_config& c, int cus) {
+  long long panels = 0;
+  for (int s = 0; s < c.n_shared; ++s) panels += (c.shared_I[s] + kTiledPanel - 1) / kTiledPanel;
+  return 2 * panels * ((c.T + kWideRows - 1) / kWideRows) >= 3ll * cus;
+}
+
+// Order of the wide kernel's tiles in a whole step.  Contiguous ranges keep a group's token rows in one L2
+// and its weights in one range of memory; the order by rows gives every XCD the same mix of tile heights. With few experts
+// a range lies in one or two groups and its tiles are alike; with many, heights differ by the skew of the selection, and by the shared
+// experts' full groups until the experts have about as many rows as a tile.  gate+up + down, us, mean of six random
+// layers, contiguous / by rows (rows per expert): 8 experts of 14336, 1150 tokens 698 / 722, 2048 tokens
+// 952 / 957, 4096 tokens 1697 / 1715; 64 of 1024, 3000 tokens 300 / 296, 4096 tokens 356 / 352; 64 of
+// 1408 + 2 shared, 2500 (176) 398 / 389, 3000 (211) 400 / 433, 4096 (288) 504 / 516; 60 of 1408 + 5632
+// shared, 2500 (125) 474 / 415, 4096 (205) 559 / 539.  Ranges of equal estimated time instead of equal tile
+// counts: the last 531, but 2500 434 and the 64 experts 388.  Shared experts alone: one of 5632, 2800
+// tokens 199 / 217, 4096 tokens 278 / 286.
+constexpr long long kContiguousMinRows = 208;
+bool wide_by_rows(const moe_config& c) {
+  if (c.E <= kFewExperts) return false;
+  return c.n_shared == 0 || (long long)c.T * (c.k_big + c.k_little) < 2 * kContiguousMinRows * c.E;
+}
+
+// Order of the 128 x 256 tiles.  By rows pays for narrow weights in steps of few rows and few tiles per
+// workgroup.  gate+up + down, us, contiguous / by rows: 8-bit, 64 experts of 1024, 777 tokens 196 / 173,
+// 2048 tokens 266 / 251; 60 of 1408 + 5632 shared, 400 tokens 249 / 206, 1000 tokens 275 / 277; 64 of
+// 1408 + 2 shared, 600 tokens 252 / 230, 900 tokens 257 / 263; MXFP4, 60 experts, 600 tokens 222 / 200,
+// 64 of 1024, 777 tokens 165 / 163, 2048 tokens 235 / 238.  With bf16 weights, twice the bytes per tile,
+// mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more
+// panels than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
+// In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is:
+// fallback passes, 64 of 1024, 8-bit 300 tokens 98 / 98, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of
+// 14336 416 / 415, but 60 of 1408, 8-bit 134 / 138, MXFP4 128 / 133, 64 of 1024, MXFP4 98 / 104; the shared
+// experts alone, MXFP4, 300 tokens 65 / 68.
+bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cus) {
+  if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
+  const bool w8_alone = c.dtype == MOE_BF16_W8 && c.n_shared == 0;
+  if (!run_routed || (!run_shared && !w8_alone)) return false;
+  const Work w = layer_work(c);
+  return w.rows < (w8_alone ? 208 : 88) * w.weight_rows && w.weight_rows < 3ll * kTiledPanel * cus;
+}
+
+}  // namespace
+
+// A call that runs the routed part alone is taken for a part of a step: a fallback pass (some ranks of the
+// rejected tokens), or the experts of one wave of an offloaded layer.  Its rows are known to the
+// device only, and by the layer's own sizes they would be overrated: it stays on the smaller tiles.  (Fallback pass,
+// 20 % of the tokens, gate+up + down, us, 128 x 256 / 256 x 256: 60 experts of 1408, 2500 tokens 213 / 245,
+// 4096 tokens 219 / 251, 50 % of them 232 / 272; 64 of 1408, 3000 tokens 222 / 245; 8 of 14336, 1200 tokens
+// 549 / 598, 4000 tokens 639 / 664.  All pairs of 60 experts of 1408 without the shared one, 4096 tokens 342 / 338.)
+FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus) {
+  FfnRoute r = {kFfnStream, false};
+  if (c.dtype == MOE_FP32 || c.T < kTiledMinT) return r;
+  const bool whole = run_routed && run_shared;
+  if (c.dtype == MOE_BF16 && (whole ? wide_whole(c) : !run_routed && wide_shared(c, cus))) {
+    r.kernel = kFfnWide;
+    r.by_rows = whole && wide_by_rows(c);
+  } else {
+    r.kernel = kFfnTiled;
+    r.by_rows = tiled_by_rows(c, run_routed, run_shared, cus);
+  }
+  return r;
+}
+
+}  // namespace mm

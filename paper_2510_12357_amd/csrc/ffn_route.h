@@ -1,0 +1,26 @@
+// Which kernel a call of moe_expert_ffn runs on, and in which order its tiles: plain host C++ (no HIP), from
+// sizes alone, so that the rules can be checked without a GPU.
+#pragma once
+
+#include "mobile_moe.h"
+
+namespace mm {
+
+// Steps of this many tokens and more run the LDS-tiled kernels (bf16 activations): the experts see
+// enough rows for MFMA tiles.  Below that the weights are streamed once through the skinny kernel.
+constexpr int kTiledMinT = 256;
+constexpr int kTiledPanel = 128;     // gate/up output columns of a tile of either tiled kernel
+constexpr int kWideRows = 256;       // token rows of a tile of the wide kernel
+constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles lies in one or two experts
+
+enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
+struct FfnRoute {
+  FfnKernel kernel;
+  bool by_rows;                      // StreamArgs::by_rows
+};
+
+// run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;
+// cus: compute units of the device.
+FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus);
+
+}  // namespace mm

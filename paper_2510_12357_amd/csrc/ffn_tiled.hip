@@ -167,7 +167,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   //     their weights;
   //   * a.by_rows: a list per XCD, panel n of group g on XCD (n + g) % 8, groups with most rows first: every
   //     XCD has the same work, which counts where a workgroup has only two or three tiles (see
-  //     launch_tiled for the rule).
+  //     ffn_route for the rule).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslots = gridDim.x >> 3;
   const bool by_rows = a.by_rows != 0;
   constexpr int kPerThread = (kMaxGroups + kThreads - 1) / kThreads;
@@ -564,25 +564,9 @@ int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
 #define MOE_TILED_SHAPE 2, 2, 2, 4
 #endif
 typedef Shape<MOE_TILED_SHAPE> DefaultShape;
+static_assert(DefaultShape::BNR / 2 == kTiledPanel, "panels of the dispatch rules");
 
 }  // namespace
-
-// The order by rows pays for narrow weights in steps of few rows and few tiles per workgroup (a.by_rows).
-// gate+up + down, us, contiguous / by rows: 8-bit, 64 experts of 1024, 777 tokens 201 / 181, 2048 tokens
-// 285 / 270; 60 of 1408 + 5632 shared, 400 tokens 251 / 206, 1000 tokens 275 / 277; 64 of 1408 + 2 shared,
-// 600 tokens 256 / 233, 900 tokens 257 / 263; MXFP4, 60 experts, 600 tokens 225 / 200, 64 of 1024, 777
-// tokens 165 / 163, 2048 tokens 235 / 238.  With bf16 weights, twice the bytes per tile, mixing the two
-// kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more panels
-// than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
-bool tiles_by_rows(const moe_config& c) {
-  if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
-  long long sh = 0;
-  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
-  const long long weight_rows = (long long)c.E * c.I + sh;
-  const long long work = (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh;
-  const long long limit = c.dtype == MOE_BF16_W8 && c.n_shared == 0 ? 208 : 88;
-  return work < limit * weight_rows && weight_rows < 3ll * (DefaultShape::BNR / 2) * device_cu_count();
-}
 
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (weight_format == 2) {

@@ -49,6 +49,7 @@ constexpr int kThreadsW = 256;
 constexpr int kBuckets = 7;             // groups by their token rows, most first
 constexpr int kGrpC = (kMaxGroups + 63) / 64;
 constexpr int kOutCols(int mode) { return mode == kGateUp ? 128 : 256; }
+static_assert(kOutCols(kGateUp) == kTiledPanel && kSlotRows == kWideRows, "tiles of the dispatch rules");
 constexpr int kA = 8, kB = 8;           // loads of a wave per token / weight chunk
 constexpr int kLoads = (kA + kB) / 4;   // ... per k-step
 constexpr int kLdsBytes = (SA + SB) * kSlotB;
@@ -573,21 +574,6 @@ int launch_wide_mode(const StreamArgs& a, hipStream_t s) {
 }
 
 }  // namespace
-
-// Contiguous ranges keep a group's token rows in one L2 and its weights in one range of memory; the order by rows
-// (a.by_rows) gives every XCD the same mix of tile heights.  With few experts a range lies in one or two groups and its
-// tiles are alike; with many, heights differ by the skew of the selection, and by the shared experts'
-// full groups until the experts have about as many rows as a tile.  gate+up + down, us, mean of six random
-// layers, contiguous / by rows (rows per expert): 8 experts of 14336, 1150 tokens 698 / 722, 2048 tokens
-// 952 / 957, 4096 tokens 1697 / 1715; 64 of 1024, 3000 tokens 300 / 296, 4096 tokens 356 / 352; 64 of
-// 1408 + 2 shared, 2500 (176) 398 / 389, 3000 (211) 400 / 433, 4096 (288) 504 / 516; 60 of 1408 + 5632
-// shared, 2500 (125) 474 / 415, 4096 (205) 559 / 539.  Ranges of equal estimated time instead of equal tile
-// counts: the last 531, but 2500 434 and the 64 experts 388.
-constexpr long long kContiguousMinRows = 208;
-bool wide_by_rows(const moe_config& c) {
-  if (c.E <= kFewExperts) return false;
-  return c.n_shared == 0 || (long long)c.T * (c.k_big + c.k_little) < 2 * kContiguousMinRows * c.E;
-}
 
 int launch_wide(StreamMode mode, const StreamArgs& a, hipStream_t s) {
   return mode == kGateUp ? launch_wide_mode<kGateUp>(a, s) : launch_wide_mode<kDown>(a, s);

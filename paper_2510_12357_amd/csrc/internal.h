@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "mobile_moe.h"
+#include "ffn_route.h"
 
 namespace mm {
 
@@ -75,7 +76,7 @@ struct StreamArgs {
   const int32_t* offsets;             // device [E+1]
   const int32_t* sorted_token;        // device [T*k_big]
   int max_pairs;                      // T * k_big
-  int by_rows;                        // tiled and wide kernels: order of their tiles
+  int by_rows;                        // tiled and wide kernels: order of their tiles (ffn_route)
   const void* x;                      // [T,H]
   void* h_routed;                     // [T*k_big, I]   SwiGLU activations (storage dtype)
   void* h_shared[MOE_MAX_SHARED];     // [T, I_s]
@@ -95,12 +96,9 @@ int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, h
 // ---- large-m grouped GEMM on LDS-tiled MFMA (prefill regime; bf16 activations) ---------------
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
-bool tiles_by_rows(const moe_config& c);   // value of StreamArgs::by_rows for a step
 
 // the same with bf16 weights on 256 x 256 tiles, for large groups (ffn_wide.hip)
-constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles lies in one or two experts
 int launch_wide(StreamMode mode, const StreamArgs& a, hipStream_t s);
-bool wide_by_rows(const moe_config& c);    // value of StreamArgs::by_rows for a step
 
 // ---- a whole decode step in one launch (decode_step.hip) -------------------------------------
 constexpr int kDecodeMaxTokens = 64;

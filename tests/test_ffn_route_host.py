@@ -1,0 +1,88 @@
+"""The rules that choose the kernel of a moe_expert_ffn call (csrc/ffn_route.cpp: plain host C++) without a GPU:
+a call that runs a part of a step is judged by that part, and the GPU tests of a kernel's edges have
+sizes that reach the kernel and the tile order they name."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_kernel_edges as edges
+from paper_2510_12357_amd import workloads as wl
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2510_12357_amd", "csrc")
+CUS = 256
+DTYPES = {"bf16": 0, "fp32": 1, "bf16w8": 2, "bf16mx4": 3}
+STREAM, TILED, WIDE = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def route(tmp_path_factory):
+    cxx = shutil.which(os.environ.get("CXX", "g++"))
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    out = str(tmp_path_factory.mktemp("route") / "ffn_route_check")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-static-libasan", "-static-libubsan", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-I",
+                    os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host", "ffn_route_check.cpp"),
+                    os.path.join(CSRC, "ffn_route.cpp"), "-o", out], check=True)
+    env = dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0")
+    env.pop("LD_PRELOAD", None)
+
+    def ask(cfg, routed=True, shared=True):
+        v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
+             int(routed), int(shared), CUS]
+        r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True, env=env)
+        return tuple(map(int, r.stdout.split()))
+    return ask
+
+
+LAYERS = ["fine60_decode", "fine64_prefill", "shared2_offload", "coarse8"]
+
+
+@pytest.mark.parametrize("layer", LAYERS)
+@pytest.mark.parametrize("T", [256, 700, 2500, 4096])
+def test_a_part_of_a_step_is_judged_by_itself(route, layer, T):
+    """Fallback passes and waves (routed part alone) have rows that only the device knows: bf16 stays on
+    the 128 x 256 tiles, and so do shared experts alone while there are fewer than 1.5 wide tiles per CU.
+    Their tiles are alike, so the contiguous order stays, but for 8-bit experts that are all there is."""
+    cfg = wl.CONFIGS[layer].with_(T=T)
+    assert route(cfg, True, False) == (TILED, 0)
+    assert route(cfg.with_(dtype="bf16mx4"), True, False) == (TILED, 0)
+    assert route(cfg.with_(dtype="bf16w8"), True, False)[1] == int(layer == "fine64_prefill" and T < 2500)
+    if cfg.shared_I:
+        tiles = sum(-(-i // 128) for i in cfg.shared_I) * -(-T // 256)
+        assert route(cfg, False, True) == (WIDE if tiles >= 1.5 * CUS else TILED, 0)
+        for narrow in ("bf16w8", "bf16mx4"):
+            assert route(cfg.with_(dtype=narrow), False, True) == (TILED, 0)
+
+
+def test_whole_steps(route):
+    c = {k: wl.CONFIGS[k] for k in LAYERS + ["tiny_fp32"]}
+    assert route(c["coarse8"].with_(T=4096)) == (WIDE, 0) and route(c["coarse8"].with_(T=1000)) == (TILED, 0)
+    assert route(c["fine60_decode"].with_(T=4096)) == (WIDE, 1) and route(c["fine60_decode"].with_(T=2000)) == (TILED, 0)
+    assert route(c["shared2_offload"].with_(T=2500)) == (WIDE, 1) and route(c["shared2_offload"].with_(T=3300)) == (WIDE, 0)
+    assert route(c["fine64_prefill"].with_(T=4096)) == (WIDE, 1) and route(c["fine64_prefill"].with_(T=3000)) == (TILED, 0)
+    assert route(c["fine64_prefill"].with_(T=777, dtype="bf16w8")) == (TILED, 1)
+    assert route(c["fine60_decode"].with_(T=600, dtype="bf16mx4")) == (TILED, 1)
+    assert route(c["fine60_decode"].with_(T=255)) == (STREAM, 0) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
+
+
+def _cases(test):
+    return [tuple(a) for m in test.pytestmark if m.name == "parametrize" for a in m.args[1]]
+
+
+def _edge_config(counts, H, I, shared=(), dtype="bf16"):
+    return wl.LayerConfig("edge", T=sum(counts), H=H, E=len(counts), I=I, k_big=1, k_little=1, shared_I=shared, dtype=dtype)
+
+
+def test_edge_tests_reach_the_kernels_they_name(route):
+    wide = [route(_edge_config(*c)) for c in _cases(edges.test_wide_tiles)]
+    assert all(r[0] == WIDE for r in wide) and {r[1] for r in wide} == {0, 1}
+    for c in map(lambda c: _edge_config(*c), _cases(edges.test_parts_of_a_step_have_the_bits_of_the_whole)):
+        assert route(c)[0] == WIDE and route(c, True, False)[0] == TILED and route(c, False, True)[0] == TILED
+    assert all(route(_edge_config(*c)) == (TILED, 0) for c in _cases(edges.test_tiled_bf16_weights_read_once))
+    assert all(route(_edge_config(*c))[0] == STREAM for c in _cases(edges.test_streamed_items_of_64_rows))
+    mx4 = [route(_edge_config(*c, dtype="bf16mx4")) for c in _cases(edges.test_tiled_mxfp4_orders)]
+    assert all(r[0] == TILED for r in mx4) and {r[1] for r in mx4} == {0, 1}

@@ -86,6 +86,28 @@ def test_wide_tiles(counts, H, I, shared):
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 40, 128, 129, 193, 257, 300] + [3] * 10, 200, 264, (1512,)),
+    ([400] * 15 + [900, 1, 0], 64, 296, ()),
+    ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),
+])
+def test_parts_of_a_step_have_the_bits_of_the_whole(counts, H, I, shared):
+    """A whole step on 256 x 256 tiles; the routed part alone (as a fallback pass or a wave of an offloaded
+    layer calls it) and the shared experts alone on 128 x 256 tiles.  Both kernels add the products of a
+    row in the same order, so every bit agrees."""
+    cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=3)
+    b.y.fill_(7.0)
+    mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
+    y, out = b.y.clone(), None if b.shared_out is None else b.shared_out.clone()
+    b.y.fill_(7.0)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
+    assert torch.equal(b.y, y) and bool((y != 7.0).any())
+    if shared:
+        b.shared_out.fill_(7.0)
+        mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, None, sh, False, True, b.y, b.shared_out, b.fws, b.fws_bytes)
+        assert torch.equal(b.shared_out, out)
+
+
+@pytest.mark.parametrize("counts,H,I,shared", [
     ([0, 1, 40, 127, 128, 129, 1], 200, 264, ()),                  # one token tile per panel, and two
     ([90, 64, 128, 31], 72, 136, (264,)),                          # a shared expert of three token tiles
 ])
