@@ -333,6 +333,7 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
   const FfnRoute r = ffn_route(*cfg, routed, run_shared != 0, device_cu_count());
+  a.two_tiles = r.two_tiles;
   a.by_rows = r.by_rows;
   auto launch = [&](StreamMode mode) {
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);

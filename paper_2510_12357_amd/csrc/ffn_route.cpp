@@ -71,6 +71,23 @@ bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cu
   return w.rows < (w8_alone ? 208 : 88) * w.weight_rows && w.weight_rows < 3ll * kTiledPanel * cus;
 }
 
+// Token tiles per computer of the streaming kernel (stream_lds.hip).  bf16 has the registers for two (110 of a
+// computer's 128); the narrower formats, at 114 and 125 with one, have not.  Two pay where groups have more
+// than 32 rows, whose weights then pass once per 64; elsewhere they only cost: the token rows of 33 .. 64
+// rows, whose loads queue behind the weight stream, are then fetched by one workgroup instead of two.  gate+up + down, us,
+// one / two: 8 experts of 14336, 65 tokens 453 / 456, 100 tokens 464 / 464, 130 tokens 557 / 515, 200 tokens
+// 789 / 597, 255 tokens 976 / 664.  With many experts it is the shared experts and the most wanted ones that have such
+// groups: 60 of 1408 + 5632 shared, 65 tokens 194 / 204, 90 tokens 208 / 213, 120 tokens 228 / 228, 130 tokens 238 / 232,
+// 255 tokens 281 / 269; 64 of 1024, 80 tokens 103 / 109, 120 tokens 119 / 122, 140 tokens 126 / 122, 230 tokens 161 / 152,
+// 255 tokens 169 / 172; 64 of 1408 + 2 shared, 100 tokens 207 / 215, 120 tokens 212 / 225, 140 tokens
+// 223 / 222, 230 tokens 253 / 248.  Fallback passes: 60 experts, 65 tokens 84 / 87, 255 tokens 148 / 148; 64 of
+// 1024, 100 tokens 90 / 92; 8 of 14336, 255 tokens 442 / 444.  The shared expert of 5632 alone, 65 tokens 53 / 61,
+// 200 tokens 93 / 97, 255 tokens 105 / 98.
+bool two_tiles(const moe_config& c, bool whole) {
+  if (c.dtype != MOE_BF16) return false;
+  return c.E <= kFewExperts ? c.T > 64 : whole && c.T > 128;
+}
+
 }  // namespace
 
 // A call that runs the routed part alone is taken for a part of a step: a fallback pass (some ranks of the
@@ -80,9 +97,12 @@ bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cu
 // 4096 tokens 219 / 251, 50 % of them 232 / 272; 64 of 1408, 3000 tokens 222 / 245; 8 of 14336, 1200 tokens
 // 549 / 598, 4000 tokens 639 / 664.  All pairs of 60 experts of 1408 without the shared one, 4096 tokens 342 / 338.)
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus) {
-  FfnRoute r = {kFfnStream, false};
-  if (c.dtype == MOE_FP32 || c.T < kTiledMinT) return r;
   const bool whole = run_routed && run_shared;
+  FfnRoute r = {kFfnStream, false, false};
+  if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
+    r.two_tiles = two_tiles(c, whole);
+    return r;
+  }
   if (c.dtype == MOE_BF16 && (whole ? wide_whole(c) : !run_routed && wide_shared(c, cus))) {
     r.kernel = kFfnWide;
     r.by_rows = whole && wide_by_rows(c);

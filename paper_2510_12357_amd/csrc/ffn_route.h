@@ -16,6 +16,7 @@ constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles 
 enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
 struct FfnRoute {
   FfnKernel kernel;
+  bool two_tiles;                    // StreamArgs::two_tiles
   bool by_rows;                      // StreamArgs::by_rows
 };
 

@@ -76,6 +76,7 @@ struct StreamArgs {
   const int32_t* offsets;             // device [E+1]
   const int32_t* sorted_token;        // device [T*k_big]
   int max_pairs;                      // T * k_big
+  int two_tiles;                      // streaming kernel, bf16: token tiles per computer two instead of one (ffn_route)
   int by_rows;                        // tiled and wide kernels: order of their tiles (ffn_route)
   const void* x;                      // [T,H]
   void* h_routed;                     // [T*k_big, I]   SwiGLU activations (storage dtype)

@@ -90,7 +90,7 @@ template <int WB> struct Fmt {
 
 // Token rows per item of a group with m rows; TT: token tiles (of 16 rows) that a computer can hold.
 // Every item streams its weights again (through L2), so steps with large groups take two tiles per
-// computer and items of up to 64 rows (see launch_stream_lds).
+// computer and items of up to 64 rows (ffn_route.cpp).
 template <int TT>
 __device__ __forceinline__ int item_rows(int m) { return TT == 2 && m > 32 ? 64 : 32; }
 
@@ -649,17 +649,9 @@ int launch_lds_typed(const StreamArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Token tiles per computer.  bf16 has the registers for two (110 of a computer's 128); the narrower
-// formats, at 114 and 125 with one, have not.  Up to 64 tokens one tile is as fast or faster: the token
-// rows of 33 .. 64 rows, whose loads queue behind the weight stream, are then fetched by two
-// workgroups (60 experts, 64 tokens, gate+up 124 us, with two tiles 131; down at 8 tokens 26.5 / 28.4).
-// Above: 8 experts of 14336, 200 tokens, gate+up 518 us with one tile, 394 with two, down 265 / 202; 64
-// experts of 1024, 200 tokens 98 / 92; 60 experts, 250 tokens 177 / 172 and 102 / 98.
-constexpr int kOneTileMaxT = 64;
-
 int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (weight_format == 2) {
-    const bool two = a.T > kOneTileMaxT;
+    const bool two = a.two_tiles != 0;
     if (mode == kGateUp) return two ? launch_lds_typed<kGateUp, 2, 2>(a, s) : launch_lds_typed<kGateUp, 2, 1>(a, s);
     if (mode == kDown) return two ? launch_lds_typed<kDown, 2, 2>(a, s) : launch_lds_typed<kDown, 2, 1>(a, s);
   } else if (weight_format == 1) {

@@ -34,7 +34,9 @@ def route(tmp_path_factory):
         v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
              int(routed), int(shared), CUS]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True, env=env)
-        return tuple(map(int, r.stdout.split()))
+        kernel, by_rows, two = map(int, r.stdout.split())
+        assert not two or kernel == STREAM
+        return (STREAM, two) if kernel == STREAM else (kernel, by_rows)
     return ask
 
 
@@ -66,7 +68,19 @@ def test_whole_steps(route):
     assert route(c["fine64_prefill"].with_(T=4096)) == (WIDE, 1) and route(c["fine64_prefill"].with_(T=3000)) == (TILED, 0)
     assert route(c["fine64_prefill"].with_(T=777, dtype="bf16w8")) == (TILED, 1)
     assert route(c["fine60_decode"].with_(T=600, dtype="bf16mx4")) == (TILED, 1)
-    assert route(c["fine60_decode"].with_(T=255)) == (STREAM, 0) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
+    assert route(c["fine60_decode"].with_(T=255)) == (STREAM, 1) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
+
+
+def test_two_token_tiles_where_groups_are_large(route):
+    """Streaming kernel, bf16: steps of more than 64 tokens over few experts, whole steps of more than 128 over
+    many.  The parts of a step over many experts, and the narrower formats, stay with one tile."""
+    few, many = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]
+    for T in (1, 64, 65, 128, 129, 255):
+        for routed, shared in ((True, True), (True, False), (False, True)):
+            assert route(few.with_(T=T), routed, shared) == (STREAM, int(T > 64))
+            assert route(many.with_(T=T), routed, shared) == (STREAM, int(T > 128 and routed and shared))
+        for dtype in ("bf16w8", "bf16mx4", "fp32"):
+            assert route(few.with_(T=T, dtype=dtype)) == (STREAM, 0)
 
 
 def _cases(test):
@@ -83,6 +97,6 @@ def test_edge_tests_reach_the_kernels_they_name(route):
     for c in map(lambda c: _edge_config(*c), _cases(edges.test_parts_of_a_step_have_the_bits_of_the_whole)):
         assert route(c)[0] == WIDE and route(c, True, False)[0] == TILED and route(c, False, True)[0] == TILED
     assert all(route(_edge_config(*c)) == (TILED, 0) for c in _cases(edges.test_tiled_bf16_weights_read_once))
-    assert all(route(_edge_config(*c))[0] == STREAM for c in _cases(edges.test_streamed_items_of_64_rows))
+    assert all(route(_edge_config(*c)) == (STREAM, 1) for c in _cases(edges.test_streamed_items_of_64_rows))
     mx4 = [route(_edge_config(*c, dtype="bf16mx4")) for c in _cases(edges.test_tiled_mxfp4_orders)]
     assert all(r[0] == TILED for r in mx4) and {r[1] for r in mx4} == {0, 1}
