@@ -205,21 +205,14 @@ extern "C" int moe_route(const moe_config* cfg, const void* x, const void* Wg, c
     return fail(MOE_E_BADARG, "moe_route: logits/topk_idx/topk_w/important/k_t must not be NULL");
   if (!logits_given && (!x || !Wg)) return fail(MOE_E_BADARG, "moe_route: x and Wg are needed unless logits_given");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // decode sizes: plain-FMA GEMV spread over many waves; larger T: MFMA router GEMM
-  constexpr int kGemvMaxT = 256;
-  // decode batches: logits and selection of a token in one workgroup, one launch.  Every workgroup reads the
-  // whole gate matrix, so above 64 tokens only while that is small (60 x 2048, 200 tokens: two
-  // launches 10.3 us, one 8.5; the four-token blocks of the GEMV read a large matrix a quarter as often)
-  constexpr int kOneLaunchMaxT = 64;
-  constexpr long long kOneLaunchGate = 1 << 18;
-  const bool one_launch = cfg->T <= kOneLaunchMaxT || (cfg->T <= kGemvMaxT && (long long)cfg->E * cfg->H <= kOneLaunchGate);
-  if (!logits_given && one_launch) {
+  const RouterKernel router = router_kernel(*cfg);
+  if (!logits_given && router == kRouterOneLaunch) {
     ProfScope ps(kProfRouteTopk, s);
     return launch_gate_route(*cfg, x, Wg, gate_bias, conf, logits, topk_idx, topk_w, important, k_t, s);
   }
   if (!logits_given) {
     ProfScope ps(kProfRouterGemm, s);
-    if (cfg->T <= kGemvMaxT) {
+    if (router == kRouterGemv) {
       rc = launch_gate_gemv(*cfg, x, Wg, gate_bias, logits, s);
     } else {
       StreamArgs a = {};

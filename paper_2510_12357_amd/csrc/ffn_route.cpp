@@ -113,4 +113,22 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   return r;
 }
 
+// Decode batches take one launch.  Every workgroup of it reads the whole gate matrix for its one token, and its
+// waves the experts one after the other, so above 64 tokens only while there are few experts and the reads
+// of all tokens together stay small (the GEMV's four-token blocks read a matrix a quarter as often, on as
+// many waves as there are experts).  us, two launches / one, on a card that launches fast: bf16, 8 x 4096, 256
+// tokens 10.8 / 8.3, 60 x 2048, 200 tokens 10.7 / 8.3, 64 x 2048, 256 tokens (64 MB) 10.7 / 9.1, 64 x 4096,
+// 200 tokens (100 MB) 11.9 / 11.8, 256 tokens (128 MB) 11.8 / 12.4, 32 x 8192, 128 tokens (64 MB) 12.1 / 10.4;
+// fp32, 60 x 2048, 128 tokens (60 MB) 10.7 / 9.4, 200 tokens (94 MB) 10.6 / 10.5, 64 x 2048, 128 tokens (64
+// MB) 10.8 / 11.0.  Many experts, on a slower one: 128 x 2048, 65 tokens, bf16 11.8 / 11.8, fp32 11.8 /
+// 15.1, 256 x 256 bf16 12.1 / 16.9.
+RouterKernel router_kernel(const moe_config& c) {
+  constexpr int kOneLaunchMaxT = 64, kGemvMaxT = 256, kOneLaunchExperts = 64;
+  if (c.T <= kOneLaunchMaxT) return kRouterOneLaunch;
+  if (c.T > kGemvMaxT) return kRouterGemm;
+  const bool fp32 = c.dtype == MOE_FP32;
+  const long long reads = (long long)c.T * c.E * c.H * (fp32 ? 4 : 2), limit = (fp32 ? 60ll : 100ll) << 20;
+  return c.E <= kOneLaunchExperts && reads <= limit ? kRouterOneLaunch : kRouterGemv;
+}
+
 }  // namespace mm

@@ -1,5 +1,5 @@
-// Which kernel a call of moe_expert_ffn runs on, and in which order its tiles: plain host C++ (no HIP), from
-// sizes alone, so that the rules can be checked without a GPU.
+// Which kernel a call of moe_route or moe_expert_ffn runs on, and in which order its tiles: plain host C++ (no
+// HIP), from sizes alone, so that the rules can be checked without a GPU.
 #pragma once
 
 #include "mobile_moe.h"
@@ -23,5 +23,10 @@ struct FfnRoute {
 // run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;
 // cus: compute units of the device.
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus);
+
+// Router logits of a step.  kRouterOneLaunch: logits and selection of a token in one workgroup; kRouterGemv:
+// plain-FMA GEMV over many waves, then the selection; kRouterGemm: MFMA GEMM, then the selection.
+enum RouterKernel { kRouterOneLaunch = 0, kRouterGemv = 1, kRouterGemm = 2 };
+RouterKernel router_kernel(const moe_config& c);
 
 }  // namespace mm

@@ -1,4 +1,4 @@
-"""The rules that choose the kernel of a moe_expert_ffn call (csrc/ffn_route.cpp: plain host C++) without a GPU:
+"""The rules that choose the kernel of a moe_route or moe_expert_ffn call (csrc/ffn_route.cpp: plain host C++) without a GPU:
 a call that runs a part of a step is judged by that part, and the GPU tests of a kernel's edges have
 sizes that reach the kernel and the tile order they name."""
 import os
@@ -15,6 +15,7 @@ CSRC = os.path.join(ROOT, "paper_2510_12357_amd", "csrc")
 CUS = 256
 DTYPES = {"bf16": 0, "fp32": 1, "bf16w8": 2, "bf16mx4": 3}
 STREAM, TILED, WIDE = 0, 1, 2
+ONE_LAUNCH, GEMV, GEMM = 0, 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -30,13 +31,17 @@ def route(tmp_path_factory):
     env = dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0")
     env.pop("LD_PRELOAD", None)
 
-    def ask(cfg, routed=True, shared=True):
+    def run(cfg, routed, shared):
         v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
              int(routed), int(shared), CUS]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True, env=env)
-        kernel, by_rows, two = map(int, r.stdout.split())
+        return tuple(map(int, r.stdout.split()))
+
+    def ask(cfg, routed=True, shared=True):
+        kernel, by_rows, two, _ = run(cfg, routed, shared)
         assert not two or kernel == STREAM
         return (STREAM, two) if kernel == STREAM else (kernel, by_rows)
+    ask.router = lambda cfg: run(cfg, True, True)[3]
     return ask
 
 
@@ -81,6 +86,21 @@ def test_two_token_tiles_where_groups_are_large(route):
             assert route(many.with_(T=T), routed, shared) == (STREAM, int(T > 128 and routed and shared))
         for dtype in ("bf16w8", "bf16mx4", "fp32"):
             assert route(few.with_(T=T, dtype=dtype)) == (STREAM, 0)
+
+
+def test_router_in_one_launch_while_its_reads_are_small(route):
+    """Up to 64 tokens always; up to 256 with at most 64 experts while the gate matrix, read once per
+    token, comes to no more than 100 MB, 60 MB in fp32."""
+    def router(E, H, T, dtype="bf16"):
+        return route.router(wl.LayerConfig("r", T=T, H=H, E=E, I=8, k_big=1, k_little=1, dtype=dtype))
+    for E, H in ((8, 4096), (60, 2048), (256, 8192)):
+        assert [router(E, H, T) for T in (1, 64, 257)] == [ONE_LAUNCH, ONE_LAUNCH, GEMM]
+    for E, H, T, dtype in ((60, 2048, 200, "bf16"), (64, 2048, 256, "bf16"), (64, 4096, 200, "bf16"), (8, 4096, 256, "fp32"),
+                           (60, 2048, 128, "fp32"), (33, 72, 256, "fp32")):
+        assert router(E, H, T, dtype) == ONE_LAUNCH
+    for E, H, T, dtype in ((65, 64, 65, "bf16"), (128, 2048, 65, "bf16"), (256, 256, 65, "bf16"), (64, 4096, 201, "bf16"),
+                           (64, 2048, 128, "fp32"), (60, 2048, 200, "fp32"), (32, 8192, 65, "fp32"), (256, 1024, 256, "bf16")):
+        assert router(E, H, T, dtype) == GEMV
 
 
 def _cases(test):
