@@ -327,17 +327,18 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
   const FfnRoute r = ffn_route(*cfg, routed, run_shared != 0, device_cu_count());
   a.two_tiles = r.two_tiles;
-  a.by_rows = r.by_rows;
   auto launch = [&](StreamMode mode) {
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
     return r.kernel == kFfnTiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s);
   };
   {
     ProfScope ps(kProfFfnGateUp, s);
+    a.by_rows = r.by_rows_gate_up;
     rc = launch(kGateUp);
     if (rc) return rc;
   }
   ProfScope ps(kProfFfnDown, s);
+  a.by_rows = r.by_rows_down;
   return launch(kDown);
 }
 

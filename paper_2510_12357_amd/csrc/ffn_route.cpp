@@ -59,6 +59,9 @@ bool wide_by_rows(const moe_config& c) {
 // 64 of 1024, 777 tokens 165 / 163, 2048 tokens 235 / 238.  With bf16 weights, twice the bytes per tile,
 // mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more
 // panels than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
+// Every XCD then has the same number of tiles, so that a handful too many for whole rounds costs each of
+// them a round, which the ranges, at different points anyway, absorb: gate/up of 64 of 1408 + 2 shared, contiguous / by rows, 256
+// tokens (748 tiles) 102 / 97, 280 .. 384 tokens (770) 107 / 119, 8-bit 116 / 123, 400 tokens (792) 128 / 119.
 // In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is:
 // fallback passes, 64 of 1024, 8-bit 300 tokens 98 / 98, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of
 // 14336 416 / 415, but 60 of 1408, 8-bit 134 / 138, MXFP4 128 / 133, 64 of 1024, MXFP4 98 / 104; the shared
@@ -88,6 +91,14 @@ bool two_tiles(const moe_config& c, bool whole) {
   return c.E <= kFewExperts ? c.T > 64 : whole && c.T > 128;
 }
 
+bool few_tiles_left(const moe_config& c, int cus) {
+  const long long rows = ((long long)c.T * (c.k_big + c.k_little) / 2 + c.E - 1) / c.E;   // of an expert, on average
+  const auto up = [](long long n, int per) { return (n + per - 1) / per; };
+  long long tiles = c.E * up(c.I, kTiledPanel) * up(rows, kTiledRows);
+  for (int s = 0; s < c.n_shared; ++s) tiles += up(c.shared_I[s], kTiledPanel) * up(c.T, kTiledRows);
+  return tiles % cus > 0 && tiles % cus <= cus / 16;
+}
+
 }  // namespace
 
 // A call that runs the routed part alone is taken for a part of a step: a fallback pass (some ranks of the
@@ -98,17 +109,18 @@ bool two_tiles(const moe_config& c, bool whole) {
 // 549 / 598, 4000 tokens 639 / 664.  All pairs of 60 experts of 1408 without the shared one, 4096 tokens 342 / 338.)
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   const bool whole = run_routed && run_shared;
-  FfnRoute r = {kFfnStream, false, false};
+  FfnRoute r = {kFfnStream, false, false, false};
   if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
     r.two_tiles = two_tiles(c, whole);
     return r;
   }
   if (c.dtype == MOE_BF16 && (whole ? wide_whole(c) : !run_routed && wide_shared(c, cus))) {
     r.kernel = kFfnWide;
-    r.by_rows = whole && wide_by_rows(c);
+    r.by_rows_gate_up = r.by_rows_down = whole && wide_by_rows(c);
   } else {
     r.kernel = kFfnTiled;
-    r.by_rows = tiled_by_rows(c, run_routed, run_shared, cus);
+    r.by_rows_down = tiled_by_rows(c, run_routed, run_shared, cus);
+    r.by_rows_gate_up = r.by_rows_down && !(whole && few_tiles_left(c, cus));
   }
   return r;
 }

@@ -10,6 +10,7 @@ namespace mm {
 // enough rows for MFMA tiles.  Below that the weights are streamed once through the skinny kernel.
 constexpr int kTiledMinT = 256;
 constexpr int kTiledPanel = 128;     // gate/up output columns of a tile of either tiled kernel
+constexpr int kTiledRows = 128;      // token rows of a tile of the 128 x 256 kernel
 constexpr int kWideRows = 256;       // token rows of a tile of the wide kernel
 constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles lies in one or two experts
 
@@ -17,7 +18,7 @@ enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
 struct FfnRoute {
   FfnKernel kernel;
   bool two_tiles;                    // StreamArgs::two_tiles
-  bool by_rows;                      // StreamArgs::by_rows
+  bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches
 };
 
 // run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;

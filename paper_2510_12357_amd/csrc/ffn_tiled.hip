@@ -564,7 +564,7 @@ int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
 #define MOE_TILED_SHAPE 2, 2, 2, 4
 #endif
 typedef Shape<MOE_TILED_SHAPE> DefaultShape;
-static_assert(DefaultShape::BNR / 2 == kTiledPanel, "panels of the dispatch rules");
+static_assert(DefaultShape::BNR / 2 == kTiledPanel && DefaultShape::BM == kTiledRows, "tiles of the dispatch rules");
 
 }  // namespace
 

@@ -38,10 +38,10 @@ def route(tmp_path_factory):
         return tuple(map(int, r.stdout.split()))
 
     def ask(cfg, routed=True, shared=True):
-        kernel, by_rows, two, _ = run(cfg, routed, shared)
+        kernel, gate_up, down, two, _ = run(cfg, routed, shared)
         assert not two or kernel == STREAM
-        return (STREAM, two) if kernel == STREAM else (kernel, by_rows)
-    ask.router = lambda cfg: run(cfg, True, True)[3]
+        return (STREAM, two) if kernel == STREAM else (kernel, down if gate_up == down else (gate_up, down))
+    ask.router = lambda cfg: run(cfg, True, True)[4]
     return ask
 
 
@@ -74,6 +74,15 @@ def test_whole_steps(route):
     assert route(c["fine64_prefill"].with_(T=777, dtype="bf16w8")) == (TILED, 1)
     assert route(c["fine60_decode"].with_(T=600, dtype="bf16mx4")) == (TILED, 1)
     assert route(c["fine60_decode"].with_(T=255)) == (STREAM, 1) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
+
+
+def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):
+    """By rows every XCD has the same number of tiles: 770 of them on 256 CUs are three rounds and a
+    nearly empty one.  The down projection's tiles are others."""
+    for dtype in ("bf16w8", "bf16mx4"):
+        at = {T: route(wl.CONFIGS["shared2_offload"].with_(T=T, dtype=dtype)) for T in (256, 257, 384, 385, 600)}
+        assert at == {256: (TILED, 1), 257: (TILED, (0, 1)), 384: (TILED, (0, 1)), 385: (TILED, 1), 600: (TILED, 1)}
+        assert all(route(wl.CONFIGS["fine60_decode"].with_(T=T, dtype=dtype)) == (TILED, 1) for T in (256, 300, 500, 700))
 
 
 def test_two_token_tiles_where_groups_are_large(route):
