@@ -136,23 +136,32 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gate_route_kernel(const S* _
 
 // conf[t] = 1 / sum_v exp(z_tv - max_v z_tv): one workgroup per token, one sweep over the row.
 // Bound: a single CU's share of the work, since a row stays in one workgroup (the call has no
-// workspace through which several could meet): the 16-byte loads of a row, kConfUnroll of them in
-// flight per thread, and one v_exp_f32 per logit.  Every thread keeps a running maximum m and
-// s = sum exp(z - m) over the values seen, rescaled when a batch of loads raises m, so the row is
-// read once.  exp(z - m) is exp2((z - m) log2 e): its error is below the two-sweep version's, whose
-// chains of additions were four times as long.
-// T = 64, V = 131072: 207 us with one 4-byte load in flight per thread and two sweeps, 9.5 us so
-// (rel. error 4.1e-7 -> 5.9e-8).
+// workspace through which several could meet): one v_exp_f32 and a few more vector instructions per
+// logit, under 16-byte loads, kConfUnroll of them in flight per thread.  Every thread keeps a running
+// maximum m and s = sum exp(z - m) over the values seen, rescaled when a batch of loads raises m, so the row is
+// read once.  T = 64, V = 131072: 206 us with one 4-byte load in flight per thread and two sweeps, 10.4 us so.
 constexpr int kConfUnroll = 8;
 
 struct ExpSum { float m, s; };                          // s = sum exp(z - m)
 
-__device__ __forceinline__ float conf_exp(float d) { return __builtin_amdgcn_exp2f(d * 1.44269504088896341f); }
+// exp(d), d <= 0, is e = exp2(p) with p = d log2 e rounded: off by about |d| 2^-24 of it, on top of the
+// hardware's own error.  EXACT adds up e times the low half of d log2 e in `low`: e + ln 2 low has expf's error.
+constexpr float kLog2eHi = 1.44269504088896341f, kLog2eLo = 1.92596299e-8f;
+template <bool EXACT>
+__device__ __forceinline__ float conf_exp(float d) { return EXACT ? expf(d) : __builtin_amdgcn_exp2f(d * kLog2eHi); }
+template <bool EXACT>
+__device__ __forceinline__ void conf_add(float d, float& sum, float& low) {
+  const float p = d * kLog2eHi, e = __builtin_amdgcn_exp2f(p);
+  sum += e;
+  // -inf: e is 0 and the low half NaN, which the median turns into a number
+  if (EXACT) low = fmaf(e, __builtin_amdgcn_fmed3f(fmaf(d, kLog2eLo, fmaf(d, kLog2eHi, -p)), -1.f, 1.f), low);
+}
 // nothing but -inf seen yet: every term is exp(-inf) = 0
 __device__ __forceinline__ float conf_base(float m) { return m == -INFINITY ? 0.f : m; }
-__device__ __forceinline__ float conf_rescale(ExpSum a, float m) { return a.m == m ? a.s : a.s * conf_exp(a.m - m); }
+template <bool EXACT>
+__device__ __forceinline__ float conf_rescale(ExpSum a, float m) { return a.m == m ? a.s : a.s * conf_exp<EXACT>(a.m - m); }
 
-template <int THREADS>
+template <int THREADS, bool EXACT>
 __global__ __launch_bounds__(THREADS) void confidence_kernel(const float* __restrict__ z, int V,
                                                               float* __restrict__ conf) {
   constexpr int kWaves = THREADS / 64;
@@ -174,33 +183,45 @@ __global__ __launch_bounds__(THREADS) void confidence_kernel(const float* __rest
     float m = a.m;
 #pragma unroll
     for (int u = 0; u < kConfUnroll; ++u) m = fmaxf(fmaxf(fmaxf(m, v[u].x), fmaxf(v[u].y, v[u].z)), v[u].w);
-    a.s = conf_rescale(a, m);
+    a.s = conf_rescale<EXACT>(a, m);
     a.m = m;
     const float mb = conf_base(m);
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    float part[4] = {0.f, 0.f, 0.f, 0.f}, low[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < kConfUnroll; ++u) {
-      part[0] += conf_exp(v[u].x - mb); part[1] += conf_exp(v[u].y - mb);
-      part[2] += conf_exp(v[u].z - mb); part[3] += conf_exp(v[u].w - mb);
+      conf_add<EXACT>(v[u].x - mb, part[0], low[0]); conf_add<EXACT>(v[u].y - mb, part[1], low[1]);
+      conf_add<EXACT>(v[u].z - mb, part[2], low[2]); conf_add<EXACT>(v[u].w - mb, part[3], low[3]);
     }
-    a.s += (part[0] + part[1]) + (part[2] + part[3]);
+    a.s += fmaf((low[0] + low[1]) + (low[2] + low[3]), 0.693147180559945309f, (part[0] + part[1]) + (part[2] + part[3]));
   }
   const int extra = tid < head ? tid : tail + tid - head;   // at most 3 + 3 single values
   if (extra < V && tid < head + (V - tail)) {
     const float x = row[extra], m = fmaxf(a.m, x);
-    a.s = conf_rescale(a, m);
+    a.s = conf_rescale<EXACT>(a, m);
     a.m = m;
-    a.s += conf_exp(x - conf_base(m));
+    a.s += conf_exp<EXACT>(x - conf_base(m));
   }
-  // the workgroup's maximum, then every thread's sum brought to it
+  // the workgroup's maximum, then every thread's sum brought to it (EXACT: in one step, with one rounding less)
   const float wm = wave_max(a.m);
-  const float ws = wave_sum(conf_rescale(a, wm));
-  if (lane == 0) { s_m[wave] = wm; s_s[wave] = ws; }
-  __syncthreads();
-  if (wave != 0) return;
-  const ExpSum w = {lane < kWaves ? s_m[lane] : -INFINITY, lane < kWaves ? s_s[lane] : 0.f};
-  const float m = wave_max(w.m);
-  const float tot = wave_sum(conf_rescale(w, m));
+  float m, tot;
+  if constexpr (EXACT) {
+    if (lane == 0) s_m[wave] = wm;
+    __syncthreads();
+    m = wave_max(lane < kWaves ? s_m[lane] : -INFINITY);
+    const float ws = wave_sum(conf_rescale<EXACT>(a, m));
+    if (lane == 0) s_s[wave] = ws;
+    __syncthreads();
+    if (wave != 0) return;
+    tot = wave_sum(lane < kWaves ? s_s[lane] : 0.f);
+  } else {
+    const float ws = wave_sum(conf_rescale<EXACT>(a, wm));
+    if (lane == 0) { s_m[wave] = wm; s_s[wave] = ws; }
+    __syncthreads();
+    if (wave != 0) return;
+    const ExpSum w = {lane < kWaves ? s_m[lane] : -INFINITY, lane < kWaves ? s_s[lane] : 0.f};
+    m = wave_max(w.m);
+    tot = wave_sum(conf_rescale<EXACT>(w, m));
+  }
   if (lane != 0) return;
   conf[blockIdx.x] = m == -INFINITY ? NAN : 1.f / tot;   // a row of -inf has no distribution
 }
@@ -252,12 +273,21 @@ int launch_gate_gemv(const moe_config& c, const void* x, const void* Wg, const f
   return hip_fail(hipGetLastError(), "gate_gemv_kernel launch");
 }
 
+// Long rows do without the low halves: error against 64 bits there is below that of the two sweeps with expf that
+// this kernel replaced, whose chains of additions grew with the row, while the low halves cost four more
+// vector instructions per logit (64 rows of 131072 9.4 -> 13.3 us).  RMS of the relative error, 1e-8, two sweeps /
+// without / with: random rows of 1000 6.0 / 6.4 / 5.8, 8193 6.0 / 6.5 / 5.3, 32768 7.7 / 6.8 / 5.2, 50257 7.8 / 6.9,
+// 131072 15 / 7.5; rows of one value beside a larger one, 1000 8.6 / 9.9 / 5.3, 8192 28 / 16 / 6, 65536 175 / 21.
+// Up to 36864 values with them take the time without: 64 rows of 32001 6.8 us (two sweeps 35.3).
+constexpr int kConfExactMaxV = 36864;
+
 int launch_confidence(const float* z, int T, int V, float* conf, hipStream_t s) {
   if (T == 0) return MOE_OK;
   // a row of at most 8192 values is one batch of loads of 256 threads; a larger workgroup would only add waves
   // without a load to the reduction (T = 64, both about 7.4 us, the rate of launches)
-  if (V <= 8192) hipLaunchKernelGGL(confidence_kernel<256>, dim3((unsigned)T), dim3(256), 0, s, z, V, conf);
-  else hipLaunchKernelGGL(confidence_kernel<1024>, dim3((unsigned)T), dim3(1024), 0, s, z, V, conf);
+  if (V <= 8192) hipLaunchKernelGGL((confidence_kernel<256, true>), dim3((unsigned)T), dim3(256), 0, s, z, V, conf);
+  else if (V <= kConfExactMaxV) hipLaunchKernelGGL((confidence_kernel<1024, true>), dim3((unsigned)T), dim3(1024), 0, s, z, V, conf);
+  else hipLaunchKernelGGL((confidence_kernel<1024, false>), dim3((unsigned)T), dim3(1024), 0, s, z, V, conf);
   return hip_fail(hipGetLastError(), "confidence_kernel launch");
 }
 
