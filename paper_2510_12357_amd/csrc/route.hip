@@ -8,8 +8,8 @@
 //
 // Kernels:
 //   gate_route_kernel router logits and selection of one token per workgroup (small steps)
-//   gate_gemv_kernel  router logits alone (up to 256 tokens): plain fp32 FMAs, one wave per
-//                     small block of logits, so that even one token spreads over E waves
+//   gate_gemv_kernel  router logits alone (65 to 256 tokens that the former is not for): plain fp32
+//                     FMAs, one wave per block of 2 experts x 4 tokens
 //   route_kernel      softmax / importance / top-k on given logits
 #include "internal.h"
 #include "route_device.h"
@@ -32,8 +32,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void route_kernel(const float*
 }
 
 // One wave per block of TE experts x TT tokens: the lanes split the hidden dimension, every
-// operand chunk is a 16/32-byte load, and the block's sums are reduced with shuffles.  Decode
-// batches give E*T/(TE*TT) waves, enough to pull the gate matrix at full speed.
+// operand chunk is a 16/32-byte load, and the block's sums are reduced with shuffles.
 constexpr int kGemvWaves = 4;
 
 template <typename S, int TE, int TT>
@@ -263,13 +262,7 @@ int launch_gate_gemv(const moe_config& c, const void* x, const void* Wg, const f
                      hipStream_t s) {
   if (c.T == 0) return MOE_OK;
   const bool bf = c.dtype != MOE_FP32;
-  if (c.T <= 4) {
-    if (bf) launch_gemv<uint16_t, 1, 1>(c, x, Wg, bias, logits, s); else launch_gemv<float, 1, 1>(c, x, Wg, bias, logits, s);
-  } else if (c.T <= 32) {
-    if (bf) launch_gemv<uint16_t, 1, 4>(c, x, Wg, bias, logits, s); else launch_gemv<float, 1, 4>(c, x, Wg, bias, logits, s);
-  } else {
-    if (bf) launch_gemv<uint16_t, 2, 4>(c, x, Wg, bias, logits, s); else launch_gemv<float, 2, 4>(c, x, Wg, bias, logits, s);
-  }
+  if (bf) launch_gemv<uint16_t, 2, 4>(c, x, Wg, bias, logits, s); else launch_gemv<float, 2, 4>(c, x, Wg, bias, logits, s);
   return hip_fail(hipGetLastError(), "gate_gemv_kernel launch");
 }
 
