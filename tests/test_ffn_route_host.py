@@ -8,6 +8,7 @@ import subprocess
 import pytest
 
 import test_gpu_kernel_edges as edges
+import test_gpu_parity as parity
 from paper_2510_12357_amd import workloads as wl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -112,6 +113,17 @@ def test_router_in_one_launch_while_its_reads_are_small(route):
         assert router(E, H, T, dtype) == GEMV
 
 
+def test_router_tests_reach_both_kernels(route):
+    """The 100-token steps that the parity test compares with one launch run on the logits kernel for every
+    data type, with odd expert counts too; so do tests of the logits against the oracle."""
+    two = [(d, E) for d, _, E, _ in _cases(parity.test_one_launch_router_equals_the_two_kernels)
+           if route.router(wl.LayerConfig("r", T=100, H=264, E=E, I=8, k_big=1, k_little=1, dtype=d)) == GEMV]
+    assert {d for d, _ in two} == {"bf16", "fp32"} and any(E % 2 for _, E in two) and any(E == 256 for _, E in two)
+    gemv = [c for c in _cases(parity.test_gate_logits)
+            if route.router(wl.LayerConfig("r", T=c[1], H=c[2], E=c[3], I=8, k_big=1, k_little=1, dtype=c[0])) == GEMV]
+    assert {c[0] for c in gemv} == {"bf16", "fp32"} and any(c[1] % 4 for c in gemv)
+
+
 def _cases(test):
     return [tuple(a) for m in test.pytestmark if m.name == "parametrize" for a in m.args[1]]
 
@@ -123,6 +135,9 @@ def _edge_config(counts, H, I, shared=(), dtype="bf16"):
 def test_edge_tests_reach_the_kernels_they_name(route):
     wide = [route(_edge_config(*c)) for c in _cases(edges.test_wide_tiles)]
     assert all(r[0] == WIDE for r in wide) and {r[1] for r in wide} == {0, 1}
+    many = [_edge_config(*c[:4]) for c in _cases(edges.test_wide_tiles_of_many_groups)]
+    assert [route(c) for c in many] == [(WIDE, 1), (WIDE, 0), (WIDE, 1), (WIDE, 1)]
+    assert all(route(c, True, False) == (TILED, 0) and c.E + len(c.shared_I) > 64 for c in many)
     for c in map(lambda c: _edge_config(*c), _cases(edges.test_parts_of_a_step_have_the_bits_of_the_whole)):
         assert route(c)[0] == WIDE and route(c, True, False)[0] == TILED and route(c, False, True)[0] == TILED
     assert all(route(_edge_config(*c)) == (TILED, 0) for c in _cases(edges.test_tiled_bf16_weights_read_once))

@@ -101,6 +101,45 @@ def test_wide_tiles(counts, H, I, shared):
     _check_assigned(counts, H, I, shared)
 
 
+def _counts(n, rows, rest):
+    """n experts with `rows` tokens each but for those named in `rest`."""
+    return [rest.get(e, rows) for e in range(n)]
+
+
+@pytest.mark.parametrize("counts,H,I,shared,null", [
+    # 66 groups, by rows: a shared expert's groups first, then experts without rows on both sides of a word of 64 groups
+    (_counts(64, 9, {0: 0, 61: 0, 62: 0, 63: 200, 5: 130, 40: 65}), 64, 40, (1512, 1512), [30, 63]),
+    # 66 groups, contiguous ranges, the first expert of the second word missing
+    (_counts(64, 212, {3: 0, 61: 1, 62: 500, 63: 300}), 64, 40, (72, 40), [62]),
+    # 130 and 256 groups, by rows
+    (_counts(130, 360, {0: 1500, 62: 33, 63: 0, 64: 0, 65: 700, 127: 0, 128: 900, 129: 129}), 64, 40, (), [127, 129]),
+    (_counts(256, 370, {0: 0, 63: 0, 64: 1000, 127: 64, 128: 0, 191: 0, 192: 257, 254: 700, 255: 1}), 72, 136, (), [64, 254]),
+])
+def test_wide_tiles_of_many_groups(counts, H, I, shared, null):
+    """More groups than a wave has lanes: the tile list's words of 64 groups, experts without rows at their
+    ends, experts without weights (their rows of y stay as they are).  Bar as for the wide tiles; and
+    the routed part alone, on 128 x 256 tiles, has the same bits."""
+    cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=len(counts))
+    table[torch.tensor(null)] = 0
+    b.y.fill_(7.0)
+    mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
+    off, st, y = b.expert_offsets.tolist(), b.sorted_token.long(), b.y.clone()
+    assert [off[e + 1] - off[e] for e in range(cfg.E)] == list(counts)
+    for e in range(cfg.E):
+        got = y[off[e]:off[e + 1]]
+        if e in null:
+            assert bool((got == 7.0).all())
+        elif counts[e]:
+            ref = _ffn32(experts[e], H, I, x[st[off[e]:off[e + 1]]])
+            assert ((got - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2, e
+    if shared:
+        ref = sum(_ffn32(w, H, i, x) for w, i in zip(sh, shared))
+        assert ((b.shared_out.sum(0) - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+    b.y.fill_(7.0)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
+    assert torch.equal(b.y, y)
+
+
 @pytest.mark.parametrize("counts,H,I,shared", [
     ([0, 1, 40, 128, 129, 193, 257, 300] + [3] * 10, 200, 264, (1512,)),
     ([400] * 15 + [900, 1, 0], 64, 296, ()),

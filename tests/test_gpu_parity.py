@@ -61,7 +61,8 @@ def test_route_bit_exact_on_given_logits(T, E, kb, kl, renorm):
 
 
 @pytest.mark.parametrize("dtype,T,H,E", [("bf16", 64, 2048, 60), ("bf16", 300, 264, 10), ("fp32", 64, 256, 8),
-                                         ("bf16", 1, 2048, 64), ("fp32", 130, 72, 33)])
+                                         ("bf16", 1, 2048, 64), ("fp32", 130, 72, 33),
+                                         ("fp32", 130, 72, 133), ("bf16", 255, 264, 255), ("bf16", 200, 8192, 64)])
 def test_gate_logits(dtype, T, H, E):
     cfg = wl.LayerConfig("g", T=T, H=H, E=E, I=8, k_big=1, k_little=1, dtype=dtype, gate_std=0.1,
                          gate_bias_std=1.0)
@@ -472,11 +473,13 @@ def test_many_experts_and_largest_top_k():
 
 
 @pytest.mark.parametrize("dtype,T,E,kb", [("bf16", 40, 60, 4), ("fp32", 40, 60, 4), ("bf16", 64, 256, 16),
-                                          ("bf16", 1, 7, 3)])
+                                          ("bf16", 1, 7, 3), ("bf16", 40, 65, 4), ("fp32", 40, 101, 4), ("fp32", 64, 256, 16),
+                                          ("bf16", 1, 70, 3)])
 def test_one_launch_router_equals_the_two_kernels(dtype, T, E, kb):
-    """Steps of at most 64 tokens compute router logits and selection in one launch; larger steps use
-    the separate logits kernel and the selection kernel.  Same rows in: bit-identical logits and
-    selections out, and the selections are the oracle's on those logits."""
+    """Steps of at most 64 tokens compute router logits and selection in one launch; larger steps with more
+    than 64 experts use the separate logits kernel and the selection kernel (with fewer experts, here, the one
+    launch again).  Same rows in: bit-identical logits and selections out, and the selections are
+    the oracle's on those logits."""
     cfg = cfg_small(T=T, E=E, k_big=kb, k_little=max(1, kb // 2), dtype=dtype, gate_bias_std=0.5,
                     fallback_ratio=0.4)
     layer = wl.make_layer(cfg, seed=12, experts=False)
