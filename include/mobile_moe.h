@@ -120,6 +120,19 @@ int moe_profile_read(int kind, int64_t* launches, double* total_ms);
  * published peak.  `sink` is a device int32 the kernel may write (it does not for ordinary data). */
 int moe_profile_plain_read(const void* buf, size_t bytes, int32_t* sink, void* stream);
 
+/* Measurement and test aid: moe_expert_ffn (below, same arguments and results) on a kernel of the caller's
+ * choice instead of the one that its rules pick from the sizes.
+ *   kernel 0  weights streamed; variant 1 or 2: tiles of 16 tokens per wave (2: MOE_BF16 only); fewer than
+ *             256 tokens unless MOE_FP32
+ *   kernel 1  tiles of 128 x 256, kernel 2 of 256 x 256 (MOE_BF16 only); 256 tokens and more, not
+ *             MOE_FP32; variant 0: tiles in contiguous ranges, 1: by rows
+ * Anything else is MOE_E_UNSUPPORTED. */
+int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
+                           const int32_t* expert_offsets, const int32_t* sorted_token,
+                           const void* const* expert_w, const void* const* shared_w, int run_routed,
+                           int run_shared, float* y, float* shared_out, void* ws, size_t ws_bytes,
+                           void* stream);
+
 /* ------------------------------------------------------------------------------------------
  * Selection stage (Sec. II-A) with the big-little rule (Sec. III-A, Alg. 1).
  *

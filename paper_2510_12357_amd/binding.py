@@ -25,8 +25,8 @@ MOE_OK = 0
 ERRORS = {-1: "MOE_E_BADARG", -2: "MOE_E_SHAPE", -3: "MOE_E_UNSUPPORTED", -4: "MOE_E_HIP",
           -5: "MOE_E_CACHE_FULL", -6: "MOE_E_WORKSPACE"}
 
-EXPORTS = ("moe_last_error", "moe_device_info", "moe_profile_enable", "moe_profile_read", "moe_profile_plain_read", "moe_route", "moe_token_confidence",
-           "moe_dispatch_workspace_bytes", "moe_dispatch", "moe_dispatch_from", "moe_combine_add",
+EXPORTS = ("moe_last_error", "moe_device_info", "moe_profile_enable", "moe_profile_read", "moe_profile_plain_read", "moe_profile_expert_ffn", "moe_route",
+           "moe_token_confidence", "moe_dispatch_workspace_bytes", "moe_dispatch", "moe_dispatch_from", "moe_combine_add",
            "moe_expert_ffn_workspace_bytes", "moe_expert_blob_bytes",
            "moe_shared_out_slabs", "moe_layer_decode_workspace_bytes", "moe_layer_decode_init",
            "moe_layer_decode_status", "moe_layer_decode", "moe_expert_ffn", "moe_expert_ffn_static", "moe_expert_ffn_static_max_bytes",
@@ -76,6 +76,9 @@ def load_library() -> ctypes.CDLL:
     lib.moe_profile_read.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_int64),
                                      ctypes.POINTER(ctypes.c_double)]
     lib.moe_profile_plain_read.argtypes = [vp, sz, vp, vp]
+    lib.moe_profile_expert_ffn.argtypes = [cfgp, ctypes.c_int, ctypes.c_int, vp, vp, vp, vp, ctypes.POINTER(vp), ctypes.c_int,
+                                           ctypes.c_int, vp, vp, vp, sz, vp]
+    lib.moe_profile_expert_ffn.restype = ctypes.c_int
     lib.moe_route.argtypes = [cfgp, vp, vp, vp, vp, vp, ctypes.c_int, vp, vp, vp, vp, vp]
     lib.moe_token_confidence.argtypes = [vp, i32, i32, vp, vp]
     lib.moe_dispatch_workspace_bytes.argtypes = [cfgp]
@@ -262,6 +265,17 @@ def moe_expert_ffn(cfg: moe_config, x, expert_offsets, sorted_token, expert_w, s
                                          _ptr(sorted_token), ew, sw, int(bool(run_routed)),
                                          int(bool(run_shared)), _ptr(y), _ptr(shared_out), _ptr(ws),
                                          ws_bytes, _stream(stream)))
+
+
+def moe_profile_expert_ffn(cfg: moe_config, kernel: int, variant: int, x, expert_offsets, sorted_token, expert_w,
+                           shared_w: Sequence, run_routed, run_shared, y, shared_out, ws, ws_bytes: int, stream=None) -> None:
+    """moe_expert_ffn on a given kernel: 0 streamed (variant: token tiles per wave), 1 tiles of 128 x 256, 2 of
+    256 x 256 (variant 1: by rows)."""
+    sw = (ctypes.c_void_p * max(1, len(shared_w)))(*[t.data_ptr() for t in shared_w])
+    ew = ctypes.c_void_p(expert_w) if isinstance(expert_w, int) else _ptr(expert_w)
+    _check(load_library().moe_profile_expert_ffn(ctypes.byref(cfg), kernel, variant, _ptr(x), _ptr(expert_offsets),
+                                                 _ptr(sorted_token), ew, sw, int(bool(run_routed)), int(bool(run_shared)),
+                                                 _ptr(y), _ptr(shared_out), _ptr(ws), ws_bytes, _stream(stream)))
 
 
 def moe_layer_decode_workspace_bytes(cfg: moe_config) -> int:

@@ -278,10 +278,10 @@ extern "C" size_t moe_expert_ffn_workspace_bytes(const moe_config* cfg) {
   return ffn_layout(*cfg).total;
 }
 
-extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_t* expert_offsets,
-                              const int32_t* sorted_token, const void* const* expert_w,
-                              const void* const* shared_w, int run_routed, int run_shared, float* y,
-                              float* shared_out, void* ws, size_t ws_bytes, void* stream) {
+namespace {
+int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, const int32_t* expert_offsets,
+               const int32_t* sorted_token, const void* const* expert_w, const void* const* shared_w,
+               int run_routed, int run_shared, float* y, float* shared_out, void* ws, size_t ws_bytes, void* stream) {
   int rc = validate_config(cfg);
   if (rc) return rc;
   const bool routed = run_routed != 0;
@@ -325,7 +325,7 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   for (int i = 0; i < a.n_slabs; ++i) { a.slab_shared[i] = plan.slab_shared[i]; a.slab_chunk[i] = plan.slab_chunk[i]; }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
-  const FfnRoute r = ffn_route(*cfg, routed, run_shared != 0, device_cu_count());
+  const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, device_cu_count());
   a.two_tiles = r.two_tiles;
   auto launch = [&](StreamMode mode) {
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
@@ -340,6 +340,34 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
   ProfScope ps(kProfFfnDown, s);
   a.by_rows = r.by_rows_down;
   return launch(kDown);
+}
+}  // namespace
+
+extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_t* expert_offsets,
+                              const int32_t* sorted_token, const void* const* expert_w,
+                              const void* const* shared_w, int run_routed, int run_shared, float* y,
+                              float* shared_out, void* ws, size_t ws_bytes, void* stream) {
+  return expert_ffn(cfg, nullptr, x, expert_offsets, sorted_token, expert_w, shared_w, run_routed, run_shared, y,
+                    shared_out, ws, ws_bytes, stream);
+}
+
+extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
+                                      const int32_t* expert_offsets, const int32_t* sorted_token,
+                                      const void* const* expert_w, const void* const* shared_w, int run_routed,
+                                      int run_shared, float* y, float* shared_out, void* ws, size_t ws_bytes,
+                                      void* stream) {
+  int rc = validate_config(cfg);
+  if (rc) return rc;
+  const bool fp32 = cfg->dtype == MOE_FP32, bf16 = cfg->dtype == MOE_BF16, many = cfg->T >= kTiledMinT;
+  const bool ok = kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16))
+                                       : (kernel == kFfnTiled || (kernel == kFfnWide && bf16)) && !fp32 && many && (variant == 0 || variant == 1);
+  if (!ok) return fail(MOE_E_UNSUPPORTED, "moe_profile_expert_ffn: kernel %d, variant %d with T=%d, dtype %d", kernel, variant, cfg->T, cfg->dtype);
+  FfnRoute r = {};
+  r.kernel = (FfnKernel)kernel;
+  r.two_tiles = kernel == kFfnStream && variant == 2;
+  r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && variant == 1;
+  return expert_ffn(cfg, &r, x, expert_offsets, sorted_token, expert_w, shared_w, run_routed, run_shared, y, shared_out,
+                    ws, ws_bytes, stream);
 }
 
 extern "C" int moe_combine(const moe_config* cfg, const float* y, const float* topk_w,

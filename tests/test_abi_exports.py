@@ -54,3 +54,20 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=120)
     assert r.returncode != 0 and "single-GPU" in (r.stderr + r.stdout)
+
+
+def test_kernel_choice_is_refused_where_the_kernel_does_not_apply():
+    if not os.path.exists(mm.LIB_PATH):
+        pytest.skip("libmobile_moe.so not built")
+    lib = mm.load_library()
+
+    def code(cfg, kernel, variant):
+        c = mm.make_config(cfg)
+        return lib.moe_profile_expert_ffn(ctypes.byref(c), kernel, variant, None, None, None, None, (ctypes.c_void_p * 1)(), 1, 0,
+                                          None, None, None, 0, None)
+    few, many = wl.CONFIGS["fine60_decode"].with_(T=255), wl.CONFIGS["fine60_decode"].with_(T=256)
+    for args in ((many, 0, 1), (few, 1, 0), (few, 2, 0), (many.with_(dtype="bf16w8"), 2, 0), (many.with_(dtype="bf16mx4"), 2, 1),
+                 (few.with_(dtype="bf16w8"), 0, 2), (many.with_(dtype="fp32"), 1, 0), (few.with_(dtype="fp32"), 0, 2), (few, 0, 0),
+                 (few, 0, 3), (many, 1, 2), (many, 2, -1), (many, 3, 0), (many, -1, 0)):
+        assert code(*args) == -3, args
+    assert code(many, 2, 0) == -1                                # the other checks are moe_expert_ffn's: x is NULL

@@ -1,13 +1,11 @@
 """The rules that choose the kernel of a moe_route or moe_expert_ffn call (csrc/ffn_route.cpp: plain host C++) without a GPU:
-a call that runs a part of a step is judged by that part, and the GPU tests of a kernel's edges have
-sizes that reach the kernel and the tile order they name."""
+a call that runs a part of a step is judged by that part."""
 import os
 import shutil
 import subprocess
 
 import pytest
 
-import test_gpu_kernel_edges as edges
 import test_gpu_parity as parity
 from paper_2510_12357_amd import workloads as wl
 
@@ -126,21 +124,3 @@ def test_router_tests_reach_both_kernels(route):
 
 def _cases(test):
     return [tuple(a) for m in test.pytestmark if m.name == "parametrize" for a in m.args[1]]
-
-
-def _edge_config(counts, H, I, shared=(), dtype="bf16"):
-    return wl.LayerConfig("edge", T=sum(counts), H=H, E=len(counts), I=I, k_big=1, k_little=1, shared_I=shared, dtype=dtype)
-
-
-def test_edge_tests_reach_the_kernels_they_name(route):
-    wide = [route(_edge_config(*c)) for c in _cases(edges.test_wide_tiles)]
-    assert all(r[0] == WIDE for r in wide) and {r[1] for r in wide} == {0, 1}
-    many = [_edge_config(*c[:4]) for c in _cases(edges.test_wide_tiles_of_many_groups)]
-    assert [route(c) for c in many] == [(WIDE, 1), (WIDE, 0), (WIDE, 1), (WIDE, 1)]
-    assert all(route(c, True, False) == (TILED, 0) and c.E + len(c.shared_I) > 64 for c in many)
-    for c in map(lambda c: _edge_config(*c), _cases(edges.test_parts_of_a_step_have_the_bits_of_the_whole)):
-        assert route(c)[0] == WIDE and route(c, True, False)[0] == TILED and route(c, False, True)[0] == TILED
-    assert all(route(_edge_config(*c)) == (TILED, 0) for c in _cases(edges.test_tiled_bf16_weights_read_once))
-    assert all(route(_edge_config(*c)) == (STREAM, 1) for c in _cases(edges.test_streamed_items_of_64_rows))
-    mx4 = [route(_edge_config(*c, dtype="bf16mx4")) for c in _cases(edges.test_tiled_mxfp4_orders)]
-    assert all(r[0] == TILED for r in mx4) and {r[1] for r in mx4} == {0, 1}

@@ -72,17 +72,32 @@ def _ffn32(w, H, I, x):
     return h @ w[2 * H * I:].view(H, I).t()
 
 
-def _check_assigned(counts, H, I, shared):
-    cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=len(counts) * 7 + H)
+STREAM, TILED, WIDE = 0, 1, 2                  # moe_profile_expert_ffn
+
+
+def _run_on(kernel, variant, b, x, table, sh, routed=True, shared=True):
     b.y.fill_(7.0)
+    if b.shared_out is not None:
+        b.shared_out.fill_(7.0)
+    mm.moe_profile_expert_ffn(b.c, kernel, variant, x, b.expert_offsets, b.sorted_token, table, sh, routed, shared, b.y,
+                              b.shared_out, b.fws, b.fws_bytes)
+    return b.y.clone(), None if b.shared_out is None else b.shared_out.clone()
+
+
+def _check_assigned(counts, H, I, shared, kernel, variants):
+    """Every variant of the kernel on the layer, against fp32 products; the results of the last."""
+    cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=len(counts) * 7 + H)
     mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
     off, st = b.expert_offsets.tolist(), b.sorted_token.long()
     assert [off[e + 1] - off[e] for e in range(cfg.E)] == list(counts)
     ref = torch.cat([_ffn32(experts[e], H, I, x[st[off[e]:off[e + 1]]]) for e in range(cfg.E)])
-    assert ((b.y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
-    if shared:
-        ref = sum(_ffn32(w, H, i, x) for w, i in zip(sh, shared))
-        assert ((b.shared_out.sum(0) - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+    for variant in variants:
+        y, out = _run_on(kernel, variant, b, x, table, sh)
+        assert ((y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2, variant
+        if shared:
+            ref_sh = sum(_ffn32(w, H, i, x) for w, i in zip(sh, shared))
+            assert ((out.sum(0) - ref_sh).abs().max() / ref_sh.pow(2).mean().sqrt()).item() <= 2e-2, variant
+    return x, sh, table, b, y, out
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
@@ -90,15 +105,19 @@ def _check_assigned(counts, H, I, shared):
     ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),    # one chunk of K, padded to the ring's length
     ([400, 512, 31, 450], 576, 128, (1512, 8)),                     # shared experts cut along K; whole tiles
     ([1300], 128, 40, ()),                                          # one group, fewer panels than XCDs
-    ([0, 1, 40, 128, 129, 193, 257, 300] + [3] * 10, 200, 264, (1512,)),  # few rows beside a shared expert: by rows
-    ([400] * 15 + [900, 1, 0], 64, 296, ()),                        # many experts: by rows
-    ([300], 64, 40, (72, 2048)),                                    # by groups, fewer tiles than workgroups
+    ([0, 1, 40, 128, 129, 193, 257, 300] + [3] * 10, 200, 264, (1512,)),  # few rows beside a shared expert
+    ([400] * 15 + [900, 1, 0], 64, 296, ()),                        # many experts
+    ([300], 64, 40, (72, 2048)),                                    # fewer tiles than workgroups
 ])
 def test_wide_tiles(counts, H, I, shared):
     """256 x 256 tiles against fp32 products of the same bf16 operands: the activations h round to
     bf16 on both sides, where fp32 sums in another order may fall to the neighbouring value (2^-8 of one of
-    I terms), so rows agree far inside the bf16 bar of 2e-2 of the tensor's RMS."""
-    _check_assigned(counts, H, I, shared)
+    I terms), so rows agree far inside the bf16 bar of 2e-2 of the tensor's RMS.  Both orders of the tiles; and
+    either kernel adds up a row's products in the same order, so every bit is that of the 128 x 256
+    tiles."""
+    x, sh, table, b, y, out = _check_assigned(counts, H, I, shared, WIDE, (0, 1))
+    y1, out1 = _run_on(TILED, 0, b, x, table, sh)
+    assert torch.equal(y, y1) and (out is None or torch.equal(out, out1))
 
 
 def _counts(n, rows, rest):
@@ -107,24 +126,22 @@ def _counts(n, rows, rest):
 
 
 @pytest.mark.parametrize("counts,H,I,shared,null", [
-    # 66 groups, by rows: a shared expert's groups first, then experts without rows on both sides of a word of 64 groups
+    # 66 groups: the shared experts' first, then experts without rows on both sides of a word of 64 groups
     (_counts(64, 9, {0: 0, 61: 0, 62: 0, 63: 200, 5: 130, 40: 65}), 64, 40, (1512, 1512), [30, 63]),
-    # 66 groups, contiguous ranges, the first expert of the second word missing
     (_counts(64, 212, {3: 0, 61: 1, 62: 500, 63: 300}), 64, 40, (72, 40), [62]),
-    # 130 and 256 groups, by rows
+    # 130 and 256 groups
     (_counts(130, 360, {0: 1500, 62: 33, 63: 0, 64: 0, 65: 700, 127: 0, 128: 900, 129: 129}), 64, 40, (), [127, 129]),
     (_counts(256, 370, {0: 0, 63: 0, 64: 1000, 127: 64, 128: 0, 191: 0, 192: 257, 254: 700, 255: 1}), 72, 136, (), [64, 254]),
 ])
 def test_wide_tiles_of_many_groups(counts, H, I, shared, null):
     """More groups than a wave has lanes: the tile list's words of 64 groups, experts without rows at their
-    ends, experts without weights (their rows of y stay as they are).  Bar as for the wide tiles; and
-    the routed part alone, on 128 x 256 tiles, has the same bits."""
+    ends, experts without weights (their rows of y stay as they are).  Bar and bits as for the wide tiles."""
     cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=len(counts))
     table[torch.tensor(null)] = 0
-    b.y.fill_(7.0)
     mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
-    off, st, y = b.expert_offsets.tolist(), b.sorted_token.long(), b.y.clone()
+    off, st = b.expert_offsets.tolist(), b.sorted_token.long()
     assert [off[e + 1] - off[e] for e in range(cfg.E)] == list(counts)
+    y, out = _run_on(WIDE, 0, b, x, table, sh)
     for e in range(cfg.E):
         got = y[off[e]:off[e + 1]]
         if e in null:
@@ -134,10 +151,10 @@ def test_wide_tiles_of_many_groups(counts, H, I, shared, null):
             assert ((got - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2, e
     if shared:
         ref = sum(_ffn32(w, H, i, x) for w, i in zip(sh, shared))
-        assert ((b.shared_out.sum(0) - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
-    b.y.fill_(7.0)
-    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
-    assert torch.equal(b.y, y)
+        assert ((out.sum(0) - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+    for kernel, variant in ((WIDE, 1), (TILED, 0), (TILED, 1)):
+        y1, out1 = _run_on(kernel, variant, b, x, table, sh)
+        assert torch.equal(y, y1) and (out is None or torch.equal(out, out1)), (kernel, variant)
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
@@ -145,21 +162,18 @@ def test_wide_tiles_of_many_groups(counts, H, I, shared, null):
     ([400] * 15 + [900, 1, 0], 64, 296, ()),
     ([0, 1, 40, 128, 129, 193, 257, 520, 900], 64, 328, (72,)),
 ])
-def test_parts_of_a_step_have_the_bits_of_the_whole(counts, H, I, shared):
-    """A whole step on 256 x 256 tiles; the routed part alone (as a fallback pass or a wave of an offloaded
-    layer calls it) and the shared experts alone on 128 x 256 tiles.  Both kernels add the products of a
-    row in the same order, so every bit agrees."""
+@pytest.mark.parametrize("kernel,variant", [(TILED, 0), (TILED, 1), (WIDE, 0), (WIDE, 1)])
+def test_parts_of_a_step_have_the_bits_of_the_whole(counts, H, I, shared, kernel, variant):
+    """The routed part alone (as a fallback pass or a wave of an offloaded layer calls it) and the shared
+    experts alone: the bits of a whole step, and nothing of the other part is written."""
     cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=3)
-    b.y.fill_(7.0)
     mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
     y, out = b.y.clone(), None if b.shared_out is None else b.shared_out.clone()
-    b.y.fill_(7.0)
-    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
-    assert torch.equal(b.y, y) and bool((y != 7.0).any())
+    y1, out1 = _run_on(kernel, variant, b, x, table, (), shared=False)
+    assert torch.equal(y1, y) and (out1 is None or bool((out1 == 7.0).all()))
     if shared:
-        b.shared_out.fill_(7.0)
-        mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, None, sh, False, True, b.y, b.shared_out, b.fws, b.fws_bytes)
-        assert torch.equal(b.shared_out, out)
+        y1, out1 = _run_on(kernel, variant, b, x, None, sh, routed=False)
+        assert torch.equal(out1, out) and bool((y1 == 7.0).all())
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
@@ -169,8 +183,7 @@ def test_parts_of_a_step_have_the_bits_of_the_whole(counts, H, I, shared):
 def test_tiled_bf16_weights_read_once(counts, H, I, shared):
     """Prefill with few rows per expert: panels of one token tile load their weights past the caches, the
     others through them.  Bar as for the wide tiles."""
-    assert sum(counts) >= 256
-    _check_assigned(counts, H, I, shared)
+    _check_assigned(counts, H, I, shared, TILED, (0, 1))
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
@@ -179,14 +192,14 @@ def test_tiled_bf16_weights_read_once(counts, H, I, shared):
     ([65], 64, 40, ()),
 ])
 def test_streamed_items_of_64_rows(counts, H, I, shared):
-    """Steps of 65 .. 255 tokens: groups of more than 32 rows in items of 64.  Bar as for the wide tiles."""
-    assert 64 < sum(counts) < 256
-    _check_assigned(counts, H, I, shared)
+    """Steps of 65 .. 255 tokens: groups of more than 32 rows in items of 64, and of 32.  Bar as for the wide
+    tiles."""
+    _check_assigned(counts, H, I, shared, STREAM, (2, 1))
 
 
 @pytest.mark.parametrize("counts,H,I", [
-    ([0, 5, 128, 129, 1, 40, 64, 33], 256, 384),                   # tiles listed by rows: few rows per expert
-    ([300, 0, 290, 400], 128, 256),                                # contiguous ranges: many rows per expert
+    ([0, 5, 128, 129, 1, 40, 64, 33], 256, 384),                   # few rows per expert
+    ([300, 0, 290, 400], 128, 256),                                # many rows per expert
     ([1] * 200 + [100], 128, 128),                                 # more groups than a wave has lanes
 ])
 def test_tiled_mxfp4_orders(counts, H, I):
@@ -212,7 +225,9 @@ def test_tiled_mxfp4_orders(counts, H, I):
     mm.layer_step(b, x, None, None, None, table, [], logits_given=True)
     off, st = b.expert_offsets.tolist(), b.sorted_token.long()
     ref = torch.cat([_ffn32(dense[e], H, I, x[st[off[e]:off[e + 1]]]) for e in range(E)])
-    assert ((b.y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+    y, _ = _run_on(TILED, 0, b, x, table, [])
+    assert ((y - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= 2e-2
+    assert torch.equal(y, _run_on(TILED, 1, b, x, table, [])[0])
 
 
 @pytest.mark.parametrize("T,E,K", [(1, 1, 1), (63, 5, 3), (64, 60, 4), (65, 256, 16), (255, 7, 7), (256, 256, 16),
