@@ -3,14 +3,27 @@
 namespace mm {
 namespace {
 
+long long ceil_div(long long n, int per) { return (n + per - 1) / per; }
+
 struct Work {
   long long weight_rows;             // gate rows of all weights of the layer
   long long rows;                    // token rows x weight rows, with the mean of the two expert counts per token
+  long long expert_rows;             // token rows of an expert, on average
 };
 Work layer_work(const moe_config& c) {
   long long sh = 0;
   for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
-  return {(long long)c.E * c.I + sh, (long long)c.T * (c.k_big + c.k_little) * c.I / 2 + (long long)c.T * sh};
+  const long long pairs = (long long)c.T * (c.k_big + c.k_little) / 2;
+  return {(long long)c.E * c.I + sh, pairs * c.I + (long long)c.T * sh, ceil_div(pairs, c.E)};
+}
+// bf16 bytes of the layer's weights
+long long layer_bytes(const moe_config& c) { return 6ll * c.H * layer_work(c).weight_rows; }
+
+// Gate/up tiles of a step, `rows` token rows each; every expert taken for hit
+long long gate_up_tiles(const moe_config& c, int rows) {
+  long long n = c.E * ceil_div(c.I, kTiledPanel) * ceil_div(layer_work(c).expert_rows, rows);
+  for (int s = 0; s < c.n_shared; ++s) n += ceil_div(c.shared_I[s], kTiledPanel) * ceil_div(c.T, rows);
+  return n;
 }
 
 // Whole bf16 steps whose weight rows meet this many token rows on average run on 256 x 256 tiles
@@ -20,20 +33,32 @@ Work layer_work(const moe_config& c) {
 // gate+up + down, us, 128 x 256 / 256 x 256: 8 experts of 14336, 192 rows 700 / 711, 215 rows 708 / 698,
 // 384 rows 1066 / 936; 64 of 1024, 281 rows 280 / 313, 384 rows 368 / 358; 64 of 1408 + 2 shared, 246
 // rows 379 / 373, 266 rows 409 / 408, 325 rows 435 / 389; 60 of 1408 + 5632 shared, 229 rows 363 / 375,
-// 241 rows 383 / 379, 273 rows 410 / 404, 448 rows 656 / 561.
-bool wide_whole(const moe_config& c) {
+// 241 rows 383 / 379, 273 rows 410 / 404, 448 rows 656 / 561; 64 of 1536 + 3072 shared, hidden 4096, 295 rows 852 / 773; 160 of
+// them, hidden 5120, 241 rows 2530 / 2056.
+// That holds for large layers.  In smaller ones there are so few wide tiles per CU that the last round decides, or
+// K is too short for a pipeline that one wave per SIMD has to hide: 8 of 512, hidden 512, 768 rows 38 / 50;
+// 32 of 512, hidden 1024, 384 rows 71 / 77; 8 of 2048 + 2048 shared, 225 rows 101 / 109; 16 of 1408, 562 rows 166 / 186, 768
+// rows 224 / 247, 1125 rows 311 / 280; 64 of 1024, hidden 512, 384 rows 128 / 130; 12 of 4096, 312 rows 228 / 264, 512 rows
+// 316 / 293, 750 rows 397 / 456; 24 of 2048, 375 rows 278 / 293.  And with few experts, fewer than five tiles
+// per CU want full ones: 8 of 4096, hidden 4096, 281 rows 229 / 241, 412 rows 315 / 293; 8 of 8192, 281 rows 269 / 280.
+constexpr long long kLargeLayer = 6ll << 27;         // bytes: 8 x 4096 x 4096 or 64 x 1024 x 2048, gate, up and down
+bool wide_whole(const moe_config& c, int cus) {
   const Work w = layer_work(c);
-  return w.rows >= (c.E <= kFewExperts ? 208 : (c.n_shared > 0 ? 240 : 352)) * w.weight_rows;
+  if (layer_bytes(c) < kLargeLayer) return false;
+  if (c.E > kFewExperts) return w.rows >= (c.n_shared > 0 ? 240 : 352) * w.weight_rows;
+  return w.rows >= (gate_up_tiles(c, kWideRows) >= 5ll * cus ? 208 : 400) * w.weight_rows;
 }
 
 // The shared experts alone are one or two groups of T rows: the wide tiles pay once there are 1.5 of them per
 // CU.  us, 128 x 256 / 256 x 256 (wide gate/up tiles): one of 5632, 1024 tokens (176) 95 / 105, 2200
 // (396) 200 / 190, 2800 (484) 218 / 199, 4096 (704) 340 / 278; two of 1408, 2048 tokens (176) 94 / 110,
-// 2500 (220) 110 / 112, 3500 (308) 144 / 147, 4096 (352) 160 / 158.
+// 2500 (220) 110 / 112, 3500 (308) 144 / 147, 4096 (352) 160 / 158.  Short rows want five of them: one of 4096, hidden
+// 512, 4096 tokens (512) 86 / 100, hidden 1024 140 / 140; one of 14336, hidden 1024, 2048 tokens (896) 203 / 215,
+// 3000 tokens (1344) 324 / 288.
 bool wide_shared(const moe_config& c, int cus) {
-  long long panels = 0;
-  for (int s = 0; s < c.n_shared; ++s) panels += (c.shared_I[s] + kTiledPanel - 1) / kTiledPanel;
-  return 2 * panels * ((c.T + kWideRows - 1) / kWideRows) >= 3ll * cus;
+  long long tiles = 0;
+  for (int s = 0; s < c.n_shared; ++s) tiles += ceil_div(c.shared_I[s], kTiledPanel) * ceil_div(c.T, kWideRows);
+  return 2 * tiles >= (c.H >= 2048 ? 3ll : 10ll) * cus;
 }
 
 // Order of the wide kernel's tiles in a whole step.  Contiguous ranges keep a group's token rows in one L2
@@ -92,11 +117,8 @@ bool two_tiles(const moe_config& c, bool whole) {
 }
 
 bool few_tiles_left(const moe_config& c, int cus) {
-  const long long rows = ((long long)c.T * (c.k_big + c.k_little) / 2 + c.E - 1) / c.E;   // of an expert, on average
-  const auto up = [](long long n, int per) { return (n + per - 1) / per; };
-  long long tiles = c.E * up(c.I, kTiledPanel) * up(rows, kTiledRows);
-  for (int s = 0; s < c.n_shared; ++s) tiles += up(c.shared_I[s], kTiledPanel) * up(c.T, kTiledRows);
-  return tiles % cus > 0 && tiles % cus <= cus / 16;
+  const long long left = gate_up_tiles(c, kTiledRows) % cus;
+  return left > 0 && left <= cus / 16;
 }
 
 }  // namespace
@@ -114,7 +136,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
     r.two_tiles = two_tiles(c, whole);
     return r;
   }
-  if (c.dtype == MOE_BF16 && (whole ? wide_whole(c) : !run_routed && wide_shared(c, cus))) {
+  if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {
     r.kernel = kFfnWide;
     r.by_rows_gate_up = r.by_rows_down = whole && wide_by_rows(c);
   } else {

@@ -75,6 +75,26 @@ def test_whole_steps(route):
     assert route(c["fine60_decode"].with_(T=255)) == (STREAM, 1) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
 
 
+def _layer(H, E, I, k, T, shared=(), dtype="bf16"):
+    return wl.LayerConfig("r", T=T, H=H, E=E, I=I, k_big=k, k_little=max(1, k // 2), shared_I=shared, dtype=dtype)
+
+
+def test_wide_tiles_in_large_layers_only(route):
+    """Below 805 MB of weights there are few wide tiles per CU or short rows; with few experts, fewer than five
+    tiles per CU want 400 rows.  Shared experts alone want as many where their rows are shorter than 2048."""
+    for H, E, I, k, shared in ((512, 8, 512, 2, ()), (512, 16, 256, 2, (512,)), (1024, 32, 512, 4, ()), (2048, 8, 2048, 2, (2048,)),
+                               (2048, 16, 1408, 4, ()), (512, 64, 1024, 8, ()), (2048, 12, 4096, 2, ()), (2048, 24, 2048, 2, ()),
+                               (520, 64, 264, 6, (1000,))):
+        assert all(route(_layer(H, E, I, k, T, shared))[0] == TILED for T in (256, 1200, 2500, 4096, 6000, 12000))
+    assert [route(_layer(4096, 8, 4096, 2, T))[0] for T in (1500, 2200, 4096)] == [TILED, WIDE, WIDE]
+    assert [route(_layer(2048, 8, 8192, 2, T))[0] for T in (1500, 4096)] == [TILED, WIDE]
+    assert [route(_layer(6144, 8, 16384, 2, T))[0] for T in (1000, 1500)] == [TILED, WIDE]
+    assert [route(_layer(4096, 64, 1536, 6, T, (3072,)))[0] for T in (2200, 3000)] == [TILED, WIDE]
+    assert route(_layer(512, 16, 256, 2, 8192, (4096,)), False, True)[0] == TILED
+    assert [route(_layer(1024, 16, 256, 2, T, (14336,)), False, True)[0] for T in (2048, 3000)] == [TILED, WIDE]
+    assert route(_layer(4096, 16, 256, 2, 3072, (4096,)), False, True)[0] == WIDE
+
+
 def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):
     """By rows every XCD has the same number of tiles: 770 of them on 256 CUs are three rounds and a
     nearly empty one.  The down projection's tiles are others."""
