@@ -327,6 +327,7 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
   const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, device_cu_count());
   a.two_tiles = r.two_tiles;
+  a.weights_once = r.weights_once;
   auto launch = [&](StreamMode mode) {
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
     return r.kernel == kFfnTiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s);
@@ -360,12 +361,14 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   if (rc) return rc;
   const bool fp32 = cfg->dtype == MOE_FP32, bf16 = cfg->dtype == MOE_BF16, many = cfg->T >= kTiledMinT;
   const bool ok = kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16))
-                                       : (kernel == kFfnTiled || (kernel == kFfnWide && bf16)) && !fp32 && many && (variant == 0 || variant == 1);
+                                       : (kernel == kFfnTiled || (kernel == kFfnWide && bf16)) && !fp32 && many &&
+                                             variant >= 0 && variant < (kernel == kFfnTiled && bf16 ? 4 : 2);
   if (!ok) return fail(MOE_E_UNSUPPORTED, "moe_profile_expert_ffn: kernel %d, variant %d with T=%d, dtype %d", kernel, variant, cfg->T, cfg->dtype);
   FfnRoute r = {};
   r.kernel = (FfnKernel)kernel;
   r.two_tiles = kernel == kFfnStream && variant == 2;
-  r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && variant == 1;
+  r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
+  r.weights_once = kernel == kFfnTiled && variant >= 2;
   return expert_ffn(cfg, &r, x, expert_offsets, sorted_token, expert_w, shared_w, run_routed, run_shared, y, shared_out,
                     ws, ws_bytes, stream);
 }

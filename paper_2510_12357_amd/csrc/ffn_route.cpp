@@ -116,6 +116,16 @@ bool two_tiles(const moe_config& c, bool whole) {
   return c.E <= kFewExperts ? c.T > 64 : whole && c.T > 128;
 }
 
+// bf16 weights that are read once in a launch need no place in the caches, which then hold the token rows longer.
+// gate+up + down, us, through the caches / past them: 64 of 1024, 300 tokens 146 / 133, 777 tokens 208 / 200, 16 of
+// 1024, hidden 4096 (403 MB), 600 tokens 119 / 111, 24 of 2048 (604 MB), 1200 tokens 179 / 171, 32 of 1024 + 2048 (428 MB),
+// 256 tokens 142 / 129.  A layer that can stay in the 256 MB behind the L2s from one step to the next loses, though one that
+// has left them in between gains (second pair): 32 of 512, hidden 1024 (101 MB), 256 tokens 34 / 41, 41 / 39, 8 of
+// 2048 + 2048 (226 MB), 256 tokens 66 / 81, 84 / 75, 16 of 1408 (277 MB), 600 tokens 87 / 94, 93 / 91.  Narrow weights lose, their chunks
+// being half a cache line and less (MXFP4, 60 experts, 600 tokens, gate+up 123 / 147).
+constexpr long long kPastCaches = 384ll << 20;
+bool weights_once(const moe_config& c) { return c.dtype == MOE_BF16 && layer_bytes(c) >= kPastCaches; }
+
 bool few_tiles_left(const moe_config& c, int cus) {
   const long long left = gate_up_tiles(c, kTiledRows) % cus;
   return left > 0 && left <= cus / 16;
@@ -131,7 +141,7 @@ bool few_tiles_left(const moe_config& c, int cus) {
 // 549 / 598, 4000 tokens 639 / 664.  All pairs of 60 experts of 1408 without the shared one, 4096 tokens 342 / 338.)
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   const bool whole = run_routed && run_shared;
-  FfnRoute r = {kFfnStream, false, false, false};
+  FfnRoute r = {};
   if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
     r.two_tiles = two_tiles(c, whole);
     return r;
@@ -141,6 +151,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
     r.by_rows_gate_up = r.by_rows_down = whole && wide_by_rows(c);
   } else {
     r.kernel = kFfnTiled;
+    r.weights_once = weights_once(c);
     r.by_rows_down = tiled_by_rows(c, run_routed, run_shared, cus);
     r.by_rows_gate_up = r.by_rows_down && !(whole && few_tiles_left(c, cus));
   }

@@ -18,6 +18,7 @@ enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
 struct FfnRoute {
   FfnKernel kernel;
   bool two_tiles;                    // StreamArgs::two_tiles
+  bool weights_once;                 // StreamArgs::weights_once
   bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches
 };
 

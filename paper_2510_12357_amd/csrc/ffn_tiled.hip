@@ -169,7 +169,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   //     XCD has the same work, which counts where a workgroup has only two or three tiles (see
   //     ffn_route for the rule).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslots = gridDim.x >> 3;
-  const bool by_rows = a.by_rows != 0;
+  const bool by_rows = a.by_rows != 0, weights_once = a.weights_once != 0;
   constexpr int kPerThread = (kMaxGroups + kThreads - 1) / kThreads;
   int my_tiles[kPerThread], my_rank[kPerThread];
   if (by_rows) {
@@ -292,11 +292,8 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         bcol[p] = (ld_pcw ^ WF::key(br)) * WF::kPerCol;
         boff[p] = (n < G.N ? (unsigned)n * WF::bytes((unsigned)G.ldw) + extra : kOob) + WF::bytes((unsigned)bcol[p]);
       }
-      // The bf16 weights of a panel with one token tile are read once and need no place in the caches, which
-      // then hold the token rows longer.  gate+up, us, 64 experts of 1024: 300 tokens 93 -> 82, 777 tokens
-      // 136 -> 128, 2048 tokens 151 -> 146; 8 of 14336, 700 tokens 377 -> 357.  Narrow weights lose by it,
-      // their chunks being half a cache line and less (MXFP4, 60 experts, 600 tokens 123 -> 147).
-      const bool once = WB == 2 && mt == 1;
+      // The weights of a panel with one token tile are read once in the launch (a.weights_once)
+      const bool once = WB == 2 && mt == 1 && weights_once;
       // chunk `kt` into stage `st`, then step the offsets to the next chunk
       auto issue = [&](int st, int kt) {
         char* const sa = s_tiles + st * kStageBytes + (lw * kInsA) * 1024;

@@ -78,6 +78,7 @@ struct StreamArgs {
   int max_pairs;                      // T * k_big
   int two_tiles;                      // streaming kernel, bf16: token tiles per computer two instead of one (ffn_route)
   int by_rows;                        // tiled and wide kernels: order of their tiles (ffn_route)
+  int weights_once;                   // tiled kernel, bf16: weights read once go past the caches (ffn_route)
   const void* x;                      // [T,H]
   void* h_routed;                     // [T*k_big, I]   SwiGLU activations (storage dtype)
   void* h_shared[MOE_MAX_SHARED];     // [T, I_s]

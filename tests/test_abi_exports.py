@@ -68,6 +68,6 @@ def test_kernel_choice_is_refused_where_the_kernel_does_not_apply():
     few, many = wl.CONFIGS["fine60_decode"].with_(T=255), wl.CONFIGS["fine60_decode"].with_(T=256)
     for args in ((many, 0, 1), (few, 1, 0), (few, 2, 0), (many.with_(dtype="bf16w8"), 2, 0), (many.with_(dtype="bf16mx4"), 2, 1),
                  (few.with_(dtype="bf16w8"), 0, 2), (many.with_(dtype="fp32"), 1, 0), (few.with_(dtype="fp32"), 0, 2), (few, 0, 0),
-                 (few, 0, 3), (many, 1, 2), (many, 2, -1), (many, 3, 0), (many, -1, 0)):
+                 (few, 0, 3), (many, 1, 4), (many, 2, 2), (many.with_(dtype="bf16w8"), 1, 2), (many, 2, -1), (many, 3, 0), (many, -1, 0)):
         assert code(*args) == -3, args
     assert code(many, 2, 0) == -1                                # the other checks are moe_expert_ffn's: x is NULL

@@ -37,10 +37,12 @@ def route(tmp_path_factory):
         return tuple(map(int, r.stdout.split()))
 
     def ask(cfg, routed=True, shared=True):
-        kernel, gate_up, down, two, _ = run(cfg, routed, shared)
+        kernel, gate_up, down, two, _, once = run(cfg, routed, shared)
         assert not two or kernel == STREAM
+        assert not once or kernel == TILED
         return (STREAM, two) if kernel == STREAM else (kernel, down if gate_up == down else (gate_up, down))
     ask.router = lambda cfg: run(cfg, True, True)[4]
+    ask.weights_once = lambda cfg, routed=True: run(cfg, routed, True)[5]
     return ask
 
 
@@ -93,6 +95,17 @@ def test_wide_tiles_in_large_layers_only(route):
     assert route(_layer(512, 16, 256, 2, 8192, (4096,)), False, True)[0] == TILED
     assert [route(_layer(1024, 16, 256, 2, T, (14336,)), False, True)[0] for T in (2048, 3000)] == [TILED, WIDE]
     assert route(_layer(4096, 16, 256, 2, 3072, (4096,)), False, True)[0] == WIDE
+
+
+def test_weights_go_past_the_caches_where_the_layer_cannot_stay_in_them(route):
+    for H, E, I, k, shared, once in ((2048, 64, 1024, 8, (), 1), (2048, 60, 1408, 4, (5632,), 1), (4096, 16, 1024, 2, (), 1),
+                                     (4096, 15, 1024, 2, (), 0), (2048, 32, 1024, 4, (2048,), 1), (2048, 16, 1408, 4, (), 0),
+                                     (2048, 8, 2048, 2, (2048,), 0), (1024, 32, 512, 4, (), 0)):
+        for T in (256, 1000):
+            assert route.weights_once(_layer(H, E, I, k, T, shared)) == once
+            assert route.weights_once(_layer(H, E, I, k, T, shared), routed=False) == once
+        for dtype in ("bf16w8", "bf16mx4"):
+            assert not route.weights_once(_layer(H, E, I, k, 256, shared, dtype))
 
 
 def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):

@@ -182,8 +182,10 @@ def test_parts_of_a_step_have_the_bits_of_the_whole(counts, H, I, shared, kernel
 ])
 def test_tiled_bf16_weights_read_once(counts, H, I, shared):
     """Prefill with few rows per expert: panels of one token tile load their weights past the caches, the
-    others through them.  Bar as for the wide tiles."""
-    _check_assigned(counts, H, I, shared, TILED, (0, 1))
+    others through them; the bits are the same.  Bar as for the wide tiles."""
+    x, sh, table, b, y, out = _check_assigned(counts, H, I, shared, TILED, (0, 1, 2, 3))
+    y0, out0 = _run_on(TILED, 0, b, x, table, sh)
+    assert torch.equal(y, y0) and (out is None or torch.equal(out, out0))
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
