@@ -99,21 +99,29 @@ bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cu
   return w.rows < (w8_alone ? 208 : 88) * w.weight_rows && w.weight_rows < 3ll * kTiledPanel * cus;
 }
 
-// Token tiles per computer of the streaming kernel (stream_lds.hip).  bf16 has the registers for two (110 of a
-// computer's 128); the narrower formats, at 114 and 125 with one, have not.  Two pay where groups have more
-// than 32 rows, whose weights then pass once per 64; elsewhere they only cost: the token rows of 33 .. 64
-// rows, whose loads queue behind the weight stream, are then fetched by one workgroup instead of two.  gate+up + down, us,
-// one / two: 8 experts of 14336, 65 tokens 453 / 456, 100 tokens 464 / 464, 130 tokens 557 / 515, 200 tokens
-// 789 / 597, 255 tokens 976 / 664.  With many experts it is the shared experts and the most wanted ones that have such
-// groups: 60 of 1408 + 5632 shared, 65 tokens 194 / 204, 90 tokens 208 / 213, 120 tokens 228 / 228, 130 tokens 238 / 232,
-// 255 tokens 281 / 269; 64 of 1024, 80 tokens 103 / 109, 120 tokens 119 / 122, 140 tokens 126 / 122, 230 tokens 161 / 152,
-// 255 tokens 169 / 172; 64 of 1408 + 2 shared, 100 tokens 207 / 215, 120 tokens 212 / 225, 140 tokens
-// 223 / 222, 230 tokens 253 / 248.  Fallback passes: 60 experts, 65 tokens 84 / 87, 255 tokens 148 / 148; 64 of
-// 1024, 100 tokens 90 / 92; 8 of 14336, 255 tokens 442 / 444.  The shared expert of 5632 alone, 65 tokens 53 / 61,
-// 200 tokens 93 / 97, 255 tokens 105 / 98.
-bool two_tiles(const moe_config& c, bool whole) {
+// Token tiles per computer of the streaming kernel (stream_lds.hip) in a whole step.  bf16 has the registers for two
+// (110 of a computer's 128); the narrower formats, at 114 and 125 with one, have not.  Two pay where groups have more
+// than 32 rows, whose weights then pass once per 64; elsewhere they cost: the token rows of 33 .. 64 rows, whose
+// loads queue behind the weight stream, are fetched by one workgroup instead of two, and a small layer has half the
+// items for its CUs.  gate+up + down, us, one / two:
+//   * large layers of few experts, which the weight stream bounds: 8 of 14336, 65 tokens 453 / 456, 100 tokens 464 / 464
+//     (half of them with all ranks 553 / 511), 130 tokens 557 / 515, 200 tokens 789 / 597; 4 of 11008, 128 tokens
+//     311 / 250; 8 of 4096, hidden 4096, 80 tokens 153 / 154, 170 tokens 197 / 174.
+//   * large layers of many, whose shared and most wanted experts have such groups once the mean is half of one: 60 of 1408 +
+//     5632, 65 tokens (mean 7) 194 / 204, 120 tokens (13) 228 / 228, 200 tokens (22) 262 / 262, 255 tokens (28) 281 / 269; 64 of
+//     1408 + 2 shared, 120 tokens (12) 212 / 225, 230 tokens (23) 253 / 248; 64 of 1536 + 3072, 80 tokens (8) 413 / 436,
+//     170 tokens (17) 476 / 438; 256 of 512 + 512, 255 tokens (7) 288 / 310.
+//   * smaller ones (experts' rows): 8 of 1024, hidden 1024, 170 tokens (32) 26 / 27, 220 tokens (41) 32 / 30; 8 of 2048 + 2048,
+//     170 tokens (32) 82 / 85, 220 tokens (41) 100 / 88; 16 of 1408, 128 tokens (24) 69 / 70, 220 tokens (41) 98 / 82;
+//     16 of 1024, hidden 4096, 255 tokens (24) 87 / 89.  Below 32 MB never: 8 of 512, hidden 512, 170 tokens (32)
+//     18.5 / 19.8, 16 of 256 + 512, 220 tokens (21) 22.5 / 25.0, 64 of 264 + 1000, hidden 520, 255 tokens (18) 40 / 42.
+// Parts of a step have few rows or few groups: fallback passes, 60 experts, 65 tokens 84 / 87, 255 tokens 148 / 148;
+// 64 of 1024, 100 tokens 90 / 92; the shared expert of 5632 alone, 65 tokens 53 / 61, 200 tokens 93 / 97, 255 tokens 105 / 98.
+bool two_tiles(const moe_config& c) {
   if (c.dtype != MOE_BF16) return false;
-  return c.E <= kFewExperts ? c.T > 64 : whole && c.T > 128;
+  const Work w = layer_work(c);
+  if (layer_bytes(c) >= kLargeLayer) return c.E <= kFewExperts ? c.T > 64 : w.rows >= 16 * w.weight_rows;
+  return layer_bytes(c) >= 32ll << 20 && w.expert_rows >= 36;
 }
 
 // bf16 weights that are read once in a launch need no place in the caches, which then hold the token rows longer.
@@ -143,7 +151,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   const bool whole = run_routed && run_shared;
   FfnRoute r = {};
   if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
-    r.two_tiles = two_tiles(c, whole);
+    r.two_tiles = whole && two_tiles(c);
     return r;
   }
   if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {

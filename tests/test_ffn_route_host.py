@@ -118,15 +118,24 @@ def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):
 
 
 def test_two_token_tiles_where_groups_are_large(route):
-    """Streaming kernel, bf16: steps of more than 64 tokens over few experts, whole steps of more than 128 over
-    many.  The parts of a step over many experts, and the narrower formats, stay with one tile."""
+    """Streaming kernel, bf16, whole steps: large layers of few experts from 65 tokens on, of many where their weights meet
+    16 rows on average; smaller layers where an expert has 36.  Parts of a step, small layers and the
+    narrower formats stay with one tile."""
     few, many = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]
-    for T in (1, 64, 65, 128, 129, 255):
-        for routed, shared in ((True, True), (True, False), (False, True)):
-            assert route(few.with_(T=T), routed, shared) == (STREAM, int(T > 64))
-            assert route(many.with_(T=T), routed, shared) == (STREAM, int(T > 128 and routed and shared))
+    for T in (1, 64, 65, 128, 146, 147, 255):
+        for routed, shared in ((True, False), (False, True)):
+            assert route(few.with_(T=T), routed, shared) == route(many.with_(T=T), routed, shared) == (STREAM, 0)
+        assert route(few.with_(T=T)) == (STREAM, int(T > 64))
+        assert route(many.with_(T=T)) == (STREAM, int(T > 146))
         for dtype in ("bf16w8", "bf16mx4", "fp32"):
             assert route(few.with_(T=T, dtype=dtype)) == (STREAM, 0)
+    for H, E, I, k, shared, lines in ((1024, 8, 1024, 2, (), {187: 0, 188: 1}), (2048, 8, 2048, 2, (2048,), {170: 0, 188: 1}),
+                                      (2048, 16, 1408, 4, (), {128: 0, 187: 1}), (4096, 16, 1024, 2, (), {255: 0}),
+                                      (512, 8, 512, 2, (), {255: 0}), (512, 16, 256, 2, (512,), {255: 0}), (520, 64, 264, 6, (1000,), {255: 0}),
+                                      (2048, 256, 512, 8, (512,), {255: 0}), (1024, 128, 768, 8, (), {255: 0}),
+                                      (4096, 64, 1536, 6, (3072,), {130: 0, 170: 1})):
+        for T, two in lines.items():
+            assert route(_layer(H, E, I, k, T, shared)) == (STREAM, two), (H, E, I, T)
 
 
 def test_router_in_one_launch_while_its_reads_are_small(route):
