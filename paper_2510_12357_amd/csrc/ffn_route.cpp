@@ -78,10 +78,15 @@ bool wide_by_rows(const moe_config& c) {
 }
 
 // Order of the 128 x 256 tiles.  By rows pays for narrow weights in steps of few rows and few tiles per
-// workgroup.  gate+up + down, us, contiguous / by rows: 8-bit, 64 experts of 1024, 777 tokens 196 / 173,
-// 2048 tokens 266 / 251; 60 of 1408 + 5632 shared, 400 tokens 249 / 206, 1000 tokens 275 / 277; 64 of
-// 1408 + 2 shared, 600 tokens 252 / 230, 900 tokens 257 / 263; MXFP4, 60 experts, 600 tokens 222 / 200,
-// 64 of 1024, 777 tokens 165 / 163, 2048 tokens 235 / 238.  With bf16 weights, twice the bytes per tile,
+// workgroup where tiles differ: beside shared experts, whose groups are full, and where the selection is skewed.
+// gate+up + down, us, contiguous / by rows: 60 of 1408 + 5632 shared, 8-bit, 400 tokens 249 / 206, 1000 tokens 275 / 277, MXFP4,
+// 600 tokens 222 / 200; 64 of 1408 + 2 shared, 8-bit, 600 tokens 252 / 230, 900 tokens 257 / 263; 32 of 2048 +
+// 4096, 8-bit, 256 tokens 294 / 263, MXFP4 295 / 268; 48 of 1408 + 2816, 8-bit, 320 tokens 185 / 156, MXFP4 148 / 132.
+// 64 of 1024 without shared ones, 8-bit, skewed, 777 tokens 196 / 173, 2048 tokens 266 / 251, unskewed, 400 tokens 128 / 129,
+// 800 tokens 155 / 160, 2000 tokens 284 / 293.  Alike tiles of MXFP4, which are the shortest, lose more: 64 of 1024,
+// unskewed, 600 tokens 106 / 113, skewed 140 / 134, 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096, 800 tokens
+// 90 / 99.  So do small layers: 64 of 256 + 1024, hidden 512, 256 tokens, 8-bit 59 / 62, MXFP4 41 / 47, 32 of 512, hidden
+// 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122.  With bf16 weights, twice the bytes per tile,
 // mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more
 // panels than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
 // Every XCD then has the same number of tiles, so that a handful too many for whole rounds costs each of
@@ -93,10 +98,11 @@ bool wide_by_rows(const moe_config& c) {
 // experts alone, MXFP4, 300 tokens 65 / 68.
 bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
-  const bool w8_alone = c.dtype == MOE_BF16_W8 && c.n_shared == 0;
-  if (!run_routed || (!run_shared && !w8_alone)) return false;
+  const bool alone = c.n_shared == 0;
+  if (!run_routed || (!run_shared && !alone)) return false;
+  if (alone ? c.dtype != MOE_BF16_W8 || layer_bytes(c) < kLargeLayer : layer_bytes(c) < 192ll << 20) return false;
   const Work w = layer_work(c);
-  return w.rows < (w8_alone ? 208 : 88) * w.weight_rows && w.weight_rows < 3ll * kTiledPanel * cus;
+  return w.rows < (alone ? 208 : 88) * w.weight_rows && w.weight_rows < 3ll * kTiledPanel * cus;
 }
 
 // Token tiles per computer of the streaming kernel (stream_lds.hip) in a whole step.  bf16 has the registers for two
