@@ -127,7 +127,9 @@ int moe_profile_plain_read(const void* buf, size_t bytes, int32_t* sink, void* s
  *   kernel 1  tiles of 128 x 256, kernel 2 of 256 x 256 (MOE_BF16 only); 256 tokens and more, not
  *             MOE_FP32; variant 0: tiles in contiguous ranges, 1: by rows; 2, 3 (kernel 1, MOE_BF16): the same
  *             with the weights of panels of one token tile loaded past the caches
- * Anything else is MOE_E_UNSUPPORTED. */
+ * Anything else is MOE_E_UNSUPPORTED.  moe_profile_expert_ffn_kernel returns the kernel (0, 1 or 2) that
+ * moe_expert_ffn picks for such a call, or a negative code. */
+int moe_profile_expert_ffn_kernel(const moe_config* cfg, int run_routed, int run_shared);
 int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
                            const int32_t* expert_offsets, const int32_t* sorted_token,
                            const void* const* expert_w, const void* const* shared_w, int run_routed,
@@ -172,8 +174,8 @@ int moe_token_confidence(const float* lm_logits, int32_t T, int32_t V, float* co
  *   sorted_token   device [T*k_big]    token of the pair at each position, -1 beyond P
  *   sorted_rank    device [T*k_big]    rank j of that pair,                -1 beyond P
  *   inv_pos        device [T,k_big]    position of pair (t,j),             -1 for j >= k_t[t]
- * Integer-only and deterministic: the order comes from scans and prefix sums (the only atomics
- * are LDS integer additions into histograms, whose result does not depend on their order).
+ * Integer-only and deterministic: the order comes from token masks and prefix sums (the only atomics
+ * are LDS integer additions and ORs, whose result does not depend on their order).
  * Precondition: the experts topk_idx names for one token (ranks below k_t) are distinct, as
  * moe_route produces them; for a selection that repeats an expert within a token the positions of
  * the repeated entries are unspecified.

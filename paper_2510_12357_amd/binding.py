@@ -25,7 +25,7 @@ MOE_OK = 0
 ERRORS = {-1: "MOE_E_BADARG", -2: "MOE_E_SHAPE", -3: "MOE_E_UNSUPPORTED", -4: "MOE_E_HIP",
           -5: "MOE_E_CACHE_FULL", -6: "MOE_E_WORKSPACE"}
 
-EXPORTS = ("moe_last_error", "moe_device_info", "moe_profile_enable", "moe_profile_read", "moe_profile_plain_read", "moe_profile_expert_ffn", "moe_route",
+EXPORTS = ("moe_last_error", "moe_device_info", "moe_profile_enable", "moe_profile_read", "moe_profile_plain_read", "moe_profile_expert_ffn", "moe_profile_expert_ffn_kernel", "moe_route",
            "moe_token_confidence", "moe_dispatch_workspace_bytes", "moe_dispatch", "moe_dispatch_from", "moe_combine_add",
            "moe_expert_ffn_workspace_bytes", "moe_expert_blob_bytes",
            "moe_shared_out_slabs", "moe_layer_decode_workspace_bytes", "moe_layer_decode_init",
@@ -79,6 +79,8 @@ def load_library() -> ctypes.CDLL:
     lib.moe_profile_expert_ffn.argtypes = [cfgp, ctypes.c_int, ctypes.c_int, vp, vp, vp, vp, ctypes.POINTER(vp), ctypes.c_int,
                                            ctypes.c_int, vp, vp, vp, sz, vp]
     lib.moe_profile_expert_ffn.restype = ctypes.c_int
+    lib.moe_profile_expert_ffn_kernel.argtypes = [cfgp, ctypes.c_int, ctypes.c_int]
+    lib.moe_profile_expert_ffn_kernel.restype = ctypes.c_int
     lib.moe_route.argtypes = [cfgp, vp, vp, vp, vp, vp, ctypes.c_int, vp, vp, vp, vp, vp]
     lib.moe_token_confidence.argtypes = [vp, i32, i32, vp, vp]
     lib.moe_dispatch_workspace_bytes.argtypes = [cfgp]
@@ -276,6 +278,13 @@ def moe_profile_expert_ffn(cfg: moe_config, kernel: int, variant: int, x, expert
     _check(load_library().moe_profile_expert_ffn(ctypes.byref(cfg), kernel, variant, _ptr(x), _ptr(expert_offsets),
                                                  _ptr(sorted_token), ew, sw, int(bool(run_routed)), int(bool(run_shared)),
                                                  _ptr(y), _ptr(shared_out), _ptr(ws), ws_bytes, _stream(stream)))
+
+
+def moe_profile_expert_ffn_kernel(cfg: moe_config, run_routed=True, run_shared=True) -> int:
+    rc = load_library().moe_profile_expert_ffn_kernel(ctypes.byref(cfg), int(bool(run_routed)), int(bool(run_shared)))
+    if rc < 0:
+        _check(rc)
+    return rc
 
 
 def moe_layer_decode_workspace_bytes(cfg: moe_config) -> int:

@@ -352,6 +352,11 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
                     shared_out, ws, ws_bytes, stream);
 }
 
+extern "C" int moe_profile_expert_ffn_kernel(const moe_config* cfg, int run_routed, int run_shared) {
+  const int rc = validate_config(cfg);
+  return rc ? rc : ffn_route(*cfg, run_routed != 0, run_shared != 0, device_cu_count()).kernel;
+}
+
 extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
                                       const int32_t* expert_offsets, const int32_t* sorted_token,
                                       const void* const* expert_w, const void* const* shared_w, int run_routed,

@@ -26,7 +26,7 @@ __device__ __forceinline__ unsigned long long lanemask_lt(int lane) {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// expert of pair i of the chunk that starts at token t0, -1 if it is none
+// expert of rank j of token t, at idx[at]; -1 if that is no pair
 __device__ __forceinline__ int pair_expert(const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t,
                                            int j_lo, int t, int j, size_t at, int E, int K) {
   int kt = k_t[t];

@@ -3,11 +3,12 @@
 //
 // What bounds it: a 128 x 256 tile moves 36 KB through LDS (24 KB of fragment reads, 12 KB of loads
 // landing) per 256 cycles of MFMAs, more than the 128 bytes a cycle that LDS delivers.  A 256 x 256
-// tile on four waves of 128 x 128 needs 48 KB per 512 cycles.  Its 256 accumulators and the
-// fragments of two k-steps take a wave's whole 512 registers, so there is one wave per SIMD, no room
-// for waves that only load, and nothing that would hide a stall: every k-step is one asm block in
-// which the MFMAs, the fragment reads of the next k-step and the loads into LDS alternate, and which
-// ends with the wait for its own reads.
+// tile on four waves of 128 x 128 needs 48 KB per 512 cycles.  Its 256 accumulators, the fragments of
+// two k-steps (64) and the tile list take 468 of the 512 registers that a wave can have, so there is
+// one wave per SIMD, no room for waves that only load, and nothing that would hide a stall: every
+// k-step is one asm block in which the MFMAs, the fragment reads of the next k-step and the loads
+// into LDS alternate, and which ends with the wait for its own reads.  (About 100 scalars live in lanes of
+// vector registers; they are fetched where a tile begins and ends, not between the blocks.)
 //
 //   * 4 waves, one workgroup per CU.  Tiles of more than 128 tokens: waves in a 2 x 2 grid, each up to 4
 //     blocks of 32 tokens x 4 of 32 weight rows.  Smaller tiles: the waves split the weight rows
@@ -22,13 +23,13 @@
 //     whose rows were looked up one tile earlier, and the epilogue's stores drain under its MFMAs.
 //   * Groups are split into token tiles of nearly equal height: the tiles of a weight panel run side
 //     by side on one XCD, and tiles of equal length keep step, so that the panel is fetched once for all
-//     of them.  (8 experts of 14336, 4096 tokens, gate+up: whole tiles first and the remainders last
-//     1152 us, remainder next to the whole tiles 1057, even heights 1045; ffn_tiled.hip 1137 .. 1177.)
+//     of them.  (8 experts of 14336, 4096 tokens, gate+up, on one card: whole tiles first and the remainders
+//     last 1152 us, remainder next to the whole tiles 1057, even heights 1045; ffn_tiled.hip 1137.)
 //
-// Measured, ffn_tiled.hip -> this kernel, us (gate+up / down): 8 experts of 14336, 4096 tokens 1137 / 636
-// -> 1077 / 597, 2048 tokens 668 / 415 -> 641 / 320; 60 experts of 1408 + 5632 shared, 4096 tokens
-// 394 / 266 -> 350 / 204; 64 of 1408 + 2 shared, 4096 tokens 326 / 221 -> 304 / 192.  The MFMAs alone (no
-// loads, no fragment reads) take 747 of the 1077 us.
+// Measured, ffn_tiled.hip -> this kernel, us (gate+up / down), in turn on another card: 8 experts of 14336, 4096
+// tokens 1160 / 638 -> 1079 / 589, 2048 tokens 669 / 416 -> 630 / 314; 60 experts of 1408 + 5632 shared, 4096
+// tokens 389 / 261 -> 339 / 206; 64 of 1408 + 2 shared, 3300 tokens 279 / 175 -> 254 / 166.  The MFMAs alone
+// (no loads, no fragment reads) of the first take 747 us.
 #include <atomic>
 #include <type_traits>
 
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   // Two orders of the tiles.  By rows: panel n (kOut output columns) of group g belongs to XCD (n + g) % 8 and
   // each XCD has a list of its own; otherwise one list by groups, cut into 8 contiguous ranges.  Tile height: 256 rows use
   // LDS best, but a few large tiles can leave the last round half empty (8 experts of 614 rows,
-  // down: 48 tiles of 205 rows on 32 CUs take 632 us, 64 of 160 rows 570); the height with the
+  // down: 48 tiles of 224 rows on 32 CUs take 632 us, 64 of 160 rows 570); the height with the
   // smallest estimate of the list's time is taken.
   int gm[kGrpC], gp[kGrpC];
   int R = 256;

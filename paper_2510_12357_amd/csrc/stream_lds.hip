@@ -12,10 +12,11 @@
 //
 // A workgroup has two kinds of waves:
 //   * waves 0..3, loaders: issue the global->LDS loads of the weight chunks and nothing else.  A
-//     work item is 32 weight rows (16 gate + 16 up rows, or 32 down rows) x all of K for up to 32 (64)
-//     token rows, cut into chunks of 256 k (bf16; the narrower formats take 64 rows, see below);
-//     one chunk = 32 rows x 512 B = one 16 KB stage = 4 load instructions per loader.  The chunks of all items of the workgroup form one stream, so the
-//     ring never drains at an item boundary.  A loader issues exactly 4 loads per iteration (a
+//     work item is 32 weight rows (16 gate + 16 up rows, or 32 down rows) x all of K for up to 32
+//     token rows (64 with two token tiles per computer, TT = 2, in groups of more than 32 rows), cut into
+//     chunks of 256 k (bf16; the narrower formats take 64 rows, see below); one chunk = 32 rows x 512 B
+//     = one 16 KB stage = 4 load instructions per loader.  The chunks of all items of the workgroup
+//     form one stream, so the ring never drains at an item boundary.  A loader issues exactly 4 loads per iteration (a
 //     slot without a chunk issues 4 loads with out-of-range offsets, which the hardware turns
 //     into zero fills without memory traffic), so its hand-counted s_waitcnt vmcnt(12) means:
 //     the chunk issued three iterations ago has landed.  It decodes its next item while its
@@ -24,7 +25,8 @@
 //     (MFMA "B" operand, from L2) one chunk ahead into registers with ordinary loads (issued
 //     right behind the MFMAs, so that they arrive during the barrier waits), run the
 //     MFMAs, reduce the K split through LDS, apply the epilogue (SwiGLU) and store.  Computer c
-//     owns token tile c & 1 (16 token rows) and the k-steps of parity c >> 1.
+//     owns token tile c & 1 (16 token rows), with TT = 2 also tile (c & 1) + 2, and the k-steps of parity
+//     c >> 1.
 //   * Two workgroup barriers per iteration: "landed" (the chunk issued three iterations ago is in
 //     LDS for every wave) and "free" (the stage just consumed may be refilled; partial sums of an
 //     item that ended are complete).  Loaders and computers execute the same number of iterations: the number of

@@ -329,8 +329,8 @@ def test_fine64_prefill_full_size_sampled():
 
 
 def test_coarse8_full_size_sampled_prefill_and_single_token():
-    """The 8-expert layer with 14336-wide experts at full size: a 4096-token prefill step (tiled MFMA
-    kernels) checked on sampled tokens, and a one-token decode step (streaming kernels)."""
+    """The 8-expert layer with 14336-wide experts at full size: a 4096-token prefill step (256 x 256
+    tiles) checked on sampled tokens, and a one-token decode step (streaming kernels)."""
     cfg = wl.CONFIGS["coarse8"]
     layer = wl.make_layer(cfg, seed=0)
     dl = DeviceLayer(layer)
