@@ -23,7 +23,7 @@ struct FfnRoute {
 };
 
 // run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;
-// cus: compute units of the device.
+// cus: compute units of the device (only used from kTiledMinT tokens on).
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus);
 
 // Router logits of a step.  kRouterOneLaunch: logits and selection of a token in one workgroup; kRouterGemv:
