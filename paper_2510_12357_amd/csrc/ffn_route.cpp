@@ -135,10 +135,17 @@ bool two_tiles(const moe_config& c) {
 // 1024, hidden 4096 (403 MB), 600 tokens 119 / 111, 24 of 2048 (604 MB), 1200 tokens 179 / 171, 32 of 1024 + 2048 (428 MB),
 // 256 tokens 142 / 129.  A layer that can stay in the 256 MB behind the L2s from one step to the next loses, though one that
 // has left them in between gains (second pair): 32 of 512, hidden 1024 (101 MB), 256 tokens 34 / 41, 41 / 39, 8 of
-// 2048 + 2048 (226 MB), 256 tokens 66 / 81, 84 / 75, 16 of 1408 (277 MB), 600 tokens 87 / 94, 93 / 91.  Narrow weights lose, their chunks
-// being half a cache line and less (MXFP4, 60 experts, 600 tokens, gate+up 123 / 147).
+// 2048 + 2048 (226 MB), 256 tokens 66 / 81, 84 / 75, 16 of 1408 (277 MB), 600 tokens 87 / 94, 93 / 91.  A chunk has to be a
+// cache line: of rows that are not whole lines its pieces share lines with the next chunk's, which then come twice (64 of
+// 1968 + 2064, hidden 3256, 3424 tokens 894 / 1064, 64 of 1864, hidden 3104, fallback pass of 273 tokens 436 / 502), and
+// narrow weights have half a line and less (MXFP4, 60 experts, 600 tokens, gate+up 123 / 147).
 constexpr long long kPastCaches = 384ll << 20;
-bool weights_once(const moe_config& c) { return c.dtype == MOE_BF16 && layer_bytes(c) >= kPastCaches; }
+constexpr int kLineWeights = 64;                     // bf16 weights in a cache line of 128 bytes
+bool weights_once(const moe_config& c) {
+  bool lines = c.H % kLineWeights == 0 && c.I % kLineWeights == 0;
+  for (int s = 0; s < c.n_shared; ++s) lines = lines && c.shared_I[s] % kLineWeights == 0;
+  return c.dtype == MOE_BF16 && lines && layer_bytes(c) >= kPastCaches;
+}
 
 bool few_tiles_left(const moe_config& c, int cus) {
   const long long left = gate_up_tiles(c, kTiledRows) % cus;

@@ -1,5 +1,5 @@
 """The rules that choose the kernel of a moe_route or moe_expert_ffn call (csrc/ffn_route.cpp: plain host C++) without a GPU:
-a call that runs a part of a step is judged by that part."""
+a call that runs a part of a step goes by that part."""
 import os
 import shutil
 import subprocess
@@ -51,7 +51,7 @@ LAYERS = ["fine60_decode", "fine64_prefill", "shared2_offload", "coarse8"]
 
 @pytest.mark.parametrize("layer", LAYERS)
 @pytest.mark.parametrize("T", [256, 700, 2500, 4096])
-def test_a_part_of_a_step_is_judged_by_itself(route, layer, T):
+def test_a_part_of_a_step_goes_by_what_it_runs(route, layer, T):
     """Fallback passes and waves (routed part alone) have rows that only the device knows: bf16 stays on
     the 128 x 256 tiles, and so do shared experts alone while there are fewer than 1.5 wide tiles per CU.
     Their tiles are alike, so the contiguous order stays, but for 8-bit experts that are all there is."""
@@ -106,6 +106,8 @@ def test_weights_go_past_the_caches_where_the_layer_cannot_stay_in_them(route):
             assert route.weights_once(_layer(H, E, I, k, T, shared), routed=False) == once
         for dtype in ("bf16w8", "bf16mx4"):
             assert not route.weights_once(_layer(H, E, I, k, 256, shared, dtype))
+    for H, I, shared in ((2048, 1032, ()), (2080, 1024, ()), (2048, 1024, (2064,))):       # rows that are not whole lines of 128 bytes
+        assert not route.weights_once(_layer(H, 64, I, 8, 256, shared))
 
 
 def test_narrow_weights_by_rows_where_tiles_differ(route):
