@@ -292,7 +292,9 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         bcol[p] = (ld_pcw ^ WF::key(br)) * WF::kPerCol;
         boff[p] = (n < G.N ? (unsigned)n * WF::bytes((unsigned)G.ldw) + extra : kOob) + WF::bytes((unsigned)bcol[p]);
       }
-      // The weights of a panel with one token tile are read once in the launch (a.weights_once)
+      // The weights of a panel with one token tile are read once in the launch (a.weights_once).  One branch for
+      // a chunk's loads: one for each of them costs small launches up to a quarter (8 experts of 392, hidden 3008, a
+      // fallback pass of 444 tokens, gate+up 37 us, 31 so).
       const bool once = WB == 2 && mt == 1 && weights_once;
       // chunk `kt` into stage `st`, then step the offsets to the next chunk
       auto issue = [&](int st, int kt) {
@@ -305,12 +307,20 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
           __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(sa + p * 1024), 16, (int)off, 0, 0, 0);
           aoff[p] += kRowB;
         }
+        unsigned off[kInsB];
 #pragma unroll
         for (int p = 0; p < kInsB; ++p) {
-          const unsigned off = full ? boff[p] : ((kt * BK + bcol[p] < K) ? boff[p] : kOob);
-          if (once) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off, 0, 0, kStreamOnce);
-          else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off, 0, 0, 0);
+          off[p] = full ? boff[p] : ((kt * BK + bcol[p] < K) ? boff[p] : kOob);
           boff[p] += kRowBW;
+        }
+        if (once) {
+#pragma unroll
+          for (int p = 0; p < kInsB; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off[p], 0, 0, kStreamOnce);
+        } else {
+#pragma unroll
+          for (int p = 0; p < kInsB; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off[p], 0, 0, 0);
         }
       };
       // wait until at most `pending` whole chunks of this wave's loads are still in flight
