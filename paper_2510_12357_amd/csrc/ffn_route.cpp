@@ -16,7 +16,9 @@ Work layer_work(const moe_config& c) {
   const long long pairs = (long long)c.T * (c.k_big + c.k_little) / 2;
   return {(long long)c.E * c.I + sh, pairs * c.I + (long long)c.T * sh, ceil_div(pairs, c.E)};
 }
-// bf16 bytes of the layer's weights
+// bf16 bytes of the layer's weights, and the sizes that the rules tell apart
+constexpr long long kLargeLayer = 6ll << 27;         // 8 x 4096 x 4096 or 64 x 1024 x 2048, gate, up and down
+constexpr long long kMediumLayer = 384ll << 20;      // what cannot stay in the 256 MB behind the L2s
 long long layer_bytes(const moe_config& c) { return 6ll * c.H * layer_work(c).weight_rows; }
 
 // Gate/up tiles of a step, `rows` token rows each; every expert taken for hit
@@ -41,7 +43,6 @@ long long gate_up_tiles(const moe_config& c, int rows) {
 // rows 224 / 247, 1125 rows 311 / 280; 64 of 1024, hidden 512, 384 rows 128 / 130; 12 of 4096, 312 rows 228 / 264, 512 rows
 // 316 / 293, 750 rows 397 / 456; 24 of 2048, 375 rows 278 / 293.  And with few experts, fewer than five tiles
 // per CU want full ones: 8 of 4096, hidden 4096, 281 rows 229 / 241, 412 rows 315 / 293; 8 of 8192, 281 rows 269 / 280.
-constexpr long long kLargeLayer = 6ll << 27;         // bytes: 8 x 4096 x 4096 or 64 x 1024 x 2048, gate, up and down
 bool wide_whole(const moe_config& c, int cus) {
   const Work w = layer_work(c);
   if (layer_bytes(c) < kLargeLayer) return false;
@@ -86,7 +87,8 @@ bool wide_by_rows(const moe_config& c) {
 // 800 tokens 155 / 160, 2000 tokens 284 / 293.  Alike tiles of MXFP4, which are the shortest, lose more: 64 of 1024,
 // unskewed, 600 tokens 106 / 113, skewed 140 / 134, 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096, 800 tokens
 // 90 / 99.  So do small layers: 64 of 256 + 1024, hidden 512, 256 tokens, 8-bit 59 / 62, MXFP4 41 / 47, 32 of 512, hidden
-// 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122.  With bf16 weights, twice the bytes per tile,
+// 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122, 128 of 496 + 784, hidden 592, 828 tokens, 8-bit
+// 64 / 77, 64 of 640 + 2176, hidden 1408, 381 tokens, MXFP4 54 / 62.  With bf16 weights, twice the bytes per tile,
 // mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more
 // panels than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
 // Every XCD then has the same number of tiles, so that a handful too many for whole rounds costs each of
@@ -100,7 +102,7 @@ bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cu
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
   const bool alone = c.n_shared == 0;
   if (!run_routed || (!run_shared && !alone)) return false;
-  if (alone ? c.dtype != MOE_BF16_W8 || layer_bytes(c) < kLargeLayer : layer_bytes(c) < 192ll << 20) return false;
+  if (alone ? c.dtype != MOE_BF16_W8 || layer_bytes(c) < kLargeLayer : layer_bytes(c) < kMediumLayer) return false;
   const Work w = layer_work(c);
   return w.rows < (alone ? 208 : 88) * w.weight_rows && w.weight_rows < 3ll * kTiledPanel * cus;
 }
@@ -139,12 +141,11 @@ bool two_tiles(const moe_config& c) {
 // cache line: of rows that are not whole lines its pieces share lines with the next chunk's, which then come twice (64 of
 // 1968 + 2064, hidden 3256, 3424 tokens 894 / 1064, 64 of 1864, hidden 3104, fallback pass of 273 tokens 436 / 502), and
 // narrow weights have half a line and less (MXFP4, 60 experts, 600 tokens, gate+up 123 / 147).
-constexpr long long kPastCaches = 384ll << 20;
 constexpr int kLineWeights = 64;                     // bf16 weights in a cache line of 128 bytes
 bool weights_once(const moe_config& c) {
   bool lines = c.H % kLineWeights == 0 && c.I % kLineWeights == 0;
   for (int s = 0; s < c.n_shared; ++s) lines = lines && c.shared_I[s] % kLineWeights == 0;
-  return c.dtype == MOE_BF16 && lines && layer_bytes(c) >= kPastCaches;
+  return c.dtype == MOE_BF16 && lines && layer_bytes(c) >= kMediumLayer;
 }
 
 bool few_tiles_left(const moe_config& c, int cus) {

@@ -111,12 +111,13 @@ def test_weights_go_past_the_caches_where_the_layer_cannot_stay_in_them(route):
 
 
 def test_narrow_weights_by_rows_where_tiles_differ(route):
-    """Beside shared experts in layers of 200 MB (of bf16) and more; alone 8-bit experts in large layers."""
+    """Beside shared experts in layers of 403 MB (of bf16) and more; alone 8-bit experts in large layers."""
     for dtype in ("bf16w8", "bf16mx4"):
         for H, E, I, k, shared in ((2048, 60, 1408, 4, (5632,)), (4096, 32, 2048, 4, (4096,)), (2048, 48, 1408, 4, (2816,))):
             assert route(_layer(H, E, I, k, 256, shared, dtype)) == (TILED, 1)
         for H, E, I, k, shared in ((512, 64, 256, 6, (1024,)), (512, 16, 256, 2, (512,)), (1024, 32, 512, 4, ()), (2048, 24, 2048, 2, ()),
-                                   (4096, 16, 1024, 2, ()), (1024, 8, 1024, 2, ())):
+                                   (4096, 16, 1024, 2, ()), (1024, 8, 1024, 2, ()), (640, 128, 512, 1, (768,)),
+                                   (1408, 64, 640, 6, (2176,))):
             assert all(route(_layer(H, E, I, k, T, shared, dtype)) == (TILED, 0) for T in (256, 400, 800))
         for T in (256, 777, 2000):
             assert route(_layer(2048, 64, 1024, 8, T, (), dtype)) == (TILED, int(dtype == "bf16w8"))
