@@ -331,7 +331,8 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   a.weights_once = r.weights_once;
   auto launch = [&](StreamMode mode) {
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
-    return r.kernel == kFfnTiled ? launch_tiled(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s);
+    if (r.kernel == kFfnTiled) return launch_tiled(mode, wfmt, a, s);
+    return r.panels ? launch_stream_panels(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s);
   };
   {
     ProfScope ps(kProfFfnGateUp, s);
@@ -366,12 +367,13 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   int rc = validate_config(cfg);
   if (rc) return rc;
   const bool fp32 = cfg->dtype == MOE_FP32, bf16 = cfg->dtype == MOE_BF16, many = cfg->T >= kTiledMinT;
-  const bool ok = kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16))
+  const bool ok = kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16) || (variant == 4 && !fp32))
                                        : (kernel == kFfnTiled || (kernel == kFfnWide && bf16)) && !fp32 && many &&
                                              variant >= 0 && variant < (kernel == kFfnTiled && bf16 ? 4 : 2);
   if (!ok) return fail(MOE_E_UNSUPPORTED, "moe_profile_expert_ffn: kernel %d, variant %d with T=%d, dtype %d", kernel, variant, cfg->T, cfg->dtype);
   FfnRoute r = {};
   r.kernel = (FfnKernel)kernel;
+  r.panels = kernel == kFfnStream && variant == 4;
   r.two_tiles = kernel == kFfnStream && variant == 2;
   r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
   r.weights_once = kernel == kFfnTiled && variant >= 2;

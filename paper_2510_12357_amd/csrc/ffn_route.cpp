@@ -18,6 +18,7 @@ Work layer_work(const moe_config& c) {
 }
 // bf16 bytes of the layer's weights, and the sizes that the rules tell apart
 constexpr long long kLargeLayer = 6ll << 27;         // 8 x 4096 x 4096 or 64 x 1024 x 2048, gate, up and down
+constexpr int kScanExperts = 64;                     // one for each lane of a wave
 constexpr long long kMediumLayer = 384ll << 20;      // what cannot stay in the 256 MB behind the L2s
 long long layer_bytes(const moe_config& c) { return 6ll * c.H * layer_work(c).weight_rows; }
 
@@ -132,6 +133,33 @@ bool two_tiles(const moe_config& c) {
   return layer_bytes(c) >= 32ll << 20 && w.expert_rows >= 36;
 }
 
+// The streaming kernel whose waves stream rows of their own (stream_panels.hip) instead of the one with loader waves
+// (stream_lds.hip): large layers.  Setting its panels up takes a microsecond longer per launch, which a small layer
+// does not bring back, and its waves want a tile of rows each.  gate+up + down, us, stream_lds / stream_panels:
+//   * by size: bf16, 8 of 512, hidden 512, 33 tokens 17.4 / 20.4, 8 of 1024, hidden 1024, 130 tokens 29.5 / 31.9, 16 of 1024, hidden
+//     4096 (403 MB), 65 tokens 77 / 80, 20 of 4096 (1 GB), 65 tokens 178 / 167, 64 of 1024, 65 tokens 144 / 143, 255 tokens
+//     176 / 155; 8-bit, 64 of 256 + 1024, hidden 512, 130 tokens 31.5 / 35.2, 8 of 2048 + 2048 (226 MB), 65 tokens 47.8 / 50.7, 16 of 1024,
+//     hidden 4096, 1 token 1.11 times as fast, 255 tokens 1.26 times, MXFP4 1.21 and 1.38 times.
+//   * bf16, few experts: long groups stream as well through stream_lds.hip, whose loads are 512 bytes of a row, while
+//     they have few rows: 8 of 14336, 4 tokens 214 / 218, 64 tokens 448 / 453, 128 tokens 505 / 467, 255 tokens 657 / 488.
+//   * bf16, few rows of weights hit, counted for the down projection: 20 of 4096, 1 token (2 x 2048 rows) 28.6 / 33.0, 3
+//     tokens (6 x 2048) 62.8 / 59.0; 60 of 1408 + 5632, 1 token (8 x 2048) 41.1 / 38.7.  Fallback passes hit fewer still: 60 of
+//     1408, 3 tokens 27.9 / 30.1, 9 tokens 44.9 / 41.2.
+//   * many experts have to be looked through: 256 of 512 + 512, 1 token 31.2 / 33.4, 8-bit, 3 tokens 35.3 / 37.4, fallback
+//     27.5 / 32.2, 9 tokens 57.1 / 54.5, 33 tokens 121 / 108; 128 of 768, hidden 1024, 8-bit, 3 tokens, fallback 23.4 / 25.9.
+bool stream_panels(const moe_config& c, bool run_routed, bool run_shared) {
+  if (!run_routed) return false;       // the shared experts alone: few rows per wave
+  const bool narrow = c.dtype == MOE_BF16_W8 || c.dtype == MOE_BF16_MXFP4;
+  if (c.dtype != MOE_BF16 && !narrow) return false;
+  if (layer_bytes(c) < (narrow ? kMediumLayer : kLargeLayer)) return false;
+  if (c.E > kScanExperts && c.T < (run_shared ? 8 : 16)) return false;
+  if (narrow) return true;
+  long long sh = 0;
+  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
+  const long long pairs = (long long)c.T * c.k_big, hit = (pairs < c.E ? pairs : c.E) + (run_shared ? sh / c.I : 0);
+  return c.E <= kFewExperts ? c.T > 64 : hit * c.H >= 16384 && (run_shared || c.T >= 8);
+}
+
 // bf16 weights that are read once in a launch need no place in the caches, which then hold the token rows longer.
 // gate+up + down, us, through the caches / past them: 64 of 1024, 300 tokens 146 / 133, 777 tokens 208 / 200, 16 of
 // 1024, hidden 4096 (403 MB), 600 tokens 119 / 111, 24 of 2048 (604 MB), 1200 tokens 179 / 171, 32 of 1024 + 2048 (428 MB),
@@ -166,6 +194,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   FfnRoute r = {};
   if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
     r.two_tiles = whole && two_tiles(c);
+    r.panels = c.T < kTiledMinT && stream_panels(c, run_routed, run_shared);
     return r;
   }
   if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {

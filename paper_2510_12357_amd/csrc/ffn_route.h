@@ -17,7 +17,8 @@ constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles 
 enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
 struct FfnRoute {
   FfnKernel kernel;
-  bool two_tiles;                    // StreamArgs::two_tiles
+  bool panels;                       // kFfnStream: stream_panels.hip instead of stream_lds.hip
+  bool two_tiles;                    // StreamArgs::two_tiles (stream_lds.hip)
   bool weights_once;                 // StreamArgs::weights_once
   bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches
 };

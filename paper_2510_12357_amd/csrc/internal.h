@@ -94,6 +94,8 @@ int launch_stream(StreamMode mode, int dtype, const StreamArgs& a, hipStream_t s
 // scales) streamed through an LDS ring (stream_lds.hip)
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4
 int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
+// the same for large layers, fewer than 256 tokens: every wave streams rows of its own (stream_panels.hip)
+int launch_stream_panels(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
 
 // ---- large-m grouped GEMM on LDS-tiled MFMA (prefill regime; bf16 activations) ---------------
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4

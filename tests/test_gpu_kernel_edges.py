@@ -199,6 +199,46 @@ def test_streamed_items_of_64_rows(counts, H, I, shared):
     _check_assigned(counts, H, I, shared, STREAM, (2, 1))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "bf16w8", "bf16mx4"])
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 2, 16, 17, 43, 44, 64], 128, 384, ()),                 # blocks of token rows, their remainders; one k unit and less
+    ([65, 0, 129, 1], 1152, 256, (640, 128)),                      # several blocks; K in parts of a unit; shared experts cut along K
+    ([1], 2048, 128, (128,)),                                      # more waves than rows
+    ([3] * 63 + [0, 2, 1, 4] + [0] * 133 + [5], 128, 128, ()),     # experts behind every word of 64 lanes
+    ([30] * 8, 256, 16384, ()),                                    # more rounds than one
+    ([1] * 255 + [0], 128, 4224, (256,)),                          # more panels in a workgroup than lanes in a wave
+])
+def test_streamed_by_waves(counts, H, I, shared, dtype):
+    """Every wave with rows of its own: the bits of the kernel with loader waves, which the tests against the oracle
+    cover, in y and in the shared experts' outputs; rows that belong to nobody stay as they are."""
+    T, E = sum(counts), len(counts)
+    cfg = wl.LayerConfig("edge", T=T, H=H, E=E, I=I, k_big=1, k_little=1, shared_I=tuple(shared), dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+
+    def blob(i):
+        n = 3 * H * i
+        codes = torch.randint(0, 256, (n,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
+        if dtype == "bf16":
+            return (torch.randn(n, generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+        if dtype == "bf16w8":
+            scale = torch.rand(2 * i + H, generator=g, device="cuda") * 1e-3
+            return torch.cat([codes & 0xf7, scale.view(torch.uint8)])                      # no NaN codes
+        return torch.cat([codes[:n // 2], torch.randint(117, 122, (n // 32,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)])
+
+    experts, sh = [blob(I) for _ in range(E)], [blob(i) for i in shared]
+    table = torch.tensor([w.data_ptr() for w in experts], dtype=torch.int64, device="cuda")
+    x = torch.randn(T, H, generator=g, device="cuda").to(torch.bfloat16)
+    b = mm.StepBuffers(cfg)
+    of = torch.repeat_interleave(torch.arange(E), torch.tensor(counts))[torch.randperm(T, generator=torch.Generator().manual_seed(T))]
+    b.logits.fill_(0.0)
+    b.logits[torch.arange(T), of.cuda()] = 4.0
+    mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
+    for routed, with_shared in ((True, True), (True, False)) + (((False, True),) if shared else ()):
+        y1, out1 = _run_on(STREAM, 1, b, x, table, sh, routed, with_shared)
+        y4, out4 = _run_on(STREAM, 4, b, x, table, sh, routed, with_shared)
+        assert torch.isfinite(y1).all() and torch.equal(y1, y4) and (out1 is None or torch.equal(out1, out4))
+
+
 @pytest.mark.parametrize("counts,H,I", [
     ([0, 5, 128, 129, 1, 40, 64, 33], 256, 384),                   # few rows per expert
     ([300, 0, 290, 400], 128, 256),                                # many rows per expert
