@@ -951,7 +951,7 @@ def main():
         roofline = dict(bound="hbm", achieved=ach, peak=HBM_PEAK_GBS, unit="GB/s", frac=ach / HBM_PEAK_GBS,
                         traffic=stored_traffic(args.workload))
     roofline["kernel"] = ("decode_step_kernel (the whole step)" if fused else
-                          ("stream_kernel" if cfg.dtype == "fp32" else ("stream_lds_kernel", "tiled_kernel", "wide_kernel")[
+                          ("stream_kernel" if cfg.dtype == "fp32" else ("stream_panel_kernel/stream_lds_kernel", "tiled_kernel", "wide_kernel")[
                               mm.moe_profile_expert_ffn_kernel(mm.make_config(cfg))]) + "<kGateUp> (ffn_gate_up)")
     roofline["traffic_source"] = traffic_source(args.workload)
     roofline["avg_us"] = gu["avg_us"]

@@ -271,7 +271,7 @@ def moe_expert_ffn(cfg: moe_config, x, expert_offsets, sorted_token, expert_w, s
 
 def moe_profile_expert_ffn(cfg: moe_config, kernel: int, variant: int, x, expert_offsets, sorted_token, expert_w,
                            shared_w: Sequence, run_routed, run_shared, y, shared_out, ws, ws_bytes: int, stream=None) -> None:
-    """moe_expert_ffn on a given kernel: 0 streamed (variant: token tiles per wave; 4: rows of its own per wave), 1 tiles of 128 x 256, 2 of
+    """moe_expert_ffn on a given kernel: 0 streamed (variant: token tiles per wave; 4, 5: rows of its own per wave, one or two tiles of them), 1 tiles of 128 x 256, 2 of
     256 x 256 (variant 1: by rows)."""
     sw = (ctypes.c_void_p * max(1, len(shared_w)))(*[t.data_ptr() for t in shared_w])
     ew = ctypes.c_void_p(expert_w) if isinstance(expert_w, int) else _ptr(expert_w)

@@ -328,11 +328,13 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   const int cus = cfg->T >= kTiledMinT ? device_cu_count() : 0;   // a runtime call, which small steps feel
   const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, cus);
   a.two_tiles = r.two_tiles;
+  a.wide_panels = r.wide_panels;
   a.weights_once = r.weights_once;
   auto launch = [&](StreamMode mode) {
+    if (r.panels) return launch_stream_panels(mode, wfmt, a, s);
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
     if (r.kernel == kFfnTiled) return launch_tiled(mode, wfmt, a, s);
-    return r.panels ? launch_stream_panels(mode, wfmt, a, s) : launch_stream(mode, cfg->dtype, a, s);
+    return launch_stream(mode, cfg->dtype, a, s);
   };
   {
     ProfScope ps(kProfFfnGateUp, s);
@@ -356,7 +358,9 @@ extern "C" int moe_expert_ffn(const moe_config* cfg, const void* x, const int32_
 
 extern "C" int moe_profile_expert_ffn_kernel(const moe_config* cfg, int run_routed, int run_shared) {
   const int rc = validate_config(cfg);
-  return rc ? rc : ffn_route(*cfg, run_routed != 0, run_shared != 0, device_cu_count()).kernel;
+  if (rc) return rc;
+  const FfnRoute r = ffn_route(*cfg, run_routed != 0, run_shared != 0, device_cu_count());
+  return r.panels ? kFfnStream : r.kernel;
 }
 
 extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
@@ -367,13 +371,16 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   int rc = validate_config(cfg);
   if (rc) return rc;
   const bool fp32 = cfg->dtype == MOE_FP32, bf16 = cfg->dtype == MOE_BF16, many = cfg->T >= kTiledMinT;
-  const bool ok = kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16) || (variant == 4 && !fp32))
+  const bool panels = kernel == kFfnStream && (variant == 4 || (variant == 5 && !bf16));
+  const bool ok = panels ? !fp32 && cfg->T <= kPanelsMaxT
+                  : kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16))
                                        : (kernel == kFfnTiled || (kernel == kFfnWide && bf16)) && !fp32 && many &&
                                              variant >= 0 && variant < (kernel == kFfnTiled && bf16 ? 4 : 2);
   if (!ok) return fail(MOE_E_UNSUPPORTED, "moe_profile_expert_ffn: kernel %d, variant %d with T=%d, dtype %d", kernel, variant, cfg->T, cfg->dtype);
   FfnRoute r = {};
   r.kernel = (FfnKernel)kernel;
-  r.panels = kernel == kFfnStream && variant == 4;
+  r.panels = panels;
+  r.wide_panels = panels && variant == 5;
   r.two_tiles = kernel == kFfnStream && variant == 2;
   r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
   r.weights_once = kernel == kFfnTiled && variant >= 2;

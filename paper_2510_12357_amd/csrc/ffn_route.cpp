@@ -160,6 +160,60 @@ bool stream_panels(const moe_config& c, bool run_routed, bool run_shared) {
   return c.E <= kFewExperts ? c.T > 64 : hit * c.H >= 16384 && (run_shared || c.T >= 8);
 }
 
+// The same kernel for prefill of few rows per expert, where the tiled kernels' blocks of 128 token rows are mostly
+// padding: narrow weights that meet fewer token rows on average than `most` (there is as little to set up in proportion
+// that layers of any size gain), bf16 weights of up to kFewExperts experts.  Above, a panel's passes of 64 token rows over its
+// weights are more and the tiled kernels' 128 are full.  gate+up + down, us, tiled / panels (wide panels where the next rule
+// wants them), token rows per weight row in brackets:
+//   * few experts, alike: 8 of 14336, 8-bit, 256 tokens (48) 424 / 325, 370 tokens (69) 438 / 415, 400 tokens (75) 442 / 447; MXFP4,
+//     256 tokens (48) 451 / 280, 400 tokens (75) 510 / 370, 680 tokens (127) 564 / 619; 16 of 1408, 600 tokens (56) 1.24 times as
+//     fast, 860 tokens (81) 0.97 times; 8 of 512, hidden 512, 256 tokens, 8-bit 43 / 23, MXFP4 31 / 21.
+//   * many: 60 of 1408 + 5632, 8-bit, 256 tokens (28) 183 / 149, 777 tokens (85) 242 / 231, 940 tokens (103) 268 / 262; MXFP4, 256
+//     tokens 172 / 114, 777 tokens 215 / 204, 940 tokens 225 / 225; 64 of 1408 + 2 shared, 8-bit, 777 tokens (77) 254 / 202, MXFP4,
+//     777 tokens 215 / 195, 940 tokens (93) 218 / 238; 20 of 4096, 8-bit, 860 tokens (64) 1.24 times, 1200 tokens (90) 0.88 times.
+//   * many of up to 1024, which the tiled kernels waste less on, and where one expert of more than 64 rows can make a round
+//     of the panels: 64 of 1024, skewed selection (mean of four), 8-bit, 300 tokens (28) 122 / 109, 380 tokens (36) 124 / 125, 520 tokens
+//     (49) 133 / 133, one of them 125 / 141, 600 tokens (56) 148 / 141, 720 tokens (68) 172 / 142, 820 tokens (77) 182 / 185; MXFP4, 256 tokens 113 / 80, 777 tokens 165 / 129, 940 tokens (88) 171 / 156; unskewed, 8-bit,
+//     420 tokens 1.34 times, 777 tokens 1.1 times, MXFP4, 420 tokens 1.02 times, 777 tokens 0.92 times, 860 tokens 0.92 times.
+//     Smaller layers of them: 32 of 1024, 8-bit, 640 tokens (60) 1.14 times, 700 tokens (66) 0.84 times, MXFP4, 420
+//     tokens (39) 0.91 times; 64 of 512, hidden 1024, 8-bit, 600 tokens (56) 0.98 times, MXFP4, 330 tokens (31) 1.19 times, 420
+//     tokens (39) 0.89 times.
+//   * bf16, 8 of 14336, 256 tokens (48) 548 / 488, 330 tokens (62) 563 / 503, 420 tokens (79) 578 / 707; 4 of 11008, 256 tokens
+//     (64) 336 / 309; 16 of 1024, hidden 4096, 600 tokens (56) 95 / 88, 860 tokens (81) 98 / 128; but 20 of 4096, 420 tokens (32)
+//     179 / 184, 60 of 1408 + 5632, 256 tokens (28) 204 / 238, 8 of 2048 + 2048 (226 MB), 256 tokens (71) 70 / 80.
+//   * fallback passes (20 % of the tokens) gain more: 60 of 1408, 256 tokens, 8-bit 1.46 times as fast, MXFP4 1.76 times.  The
+//     line is that of the whole step all the same, for a part may have all of its rows.
+bool prefill_panels(const moe_config& c, bool run_routed) {
+  if (!run_routed || c.T > kPanelsMaxT) return false;
+  const Work w = layer_work(c);
+  const bool w8 = c.dtype == MOE_BF16_W8;
+  if (c.dtype == MOE_BF16) return c.E <= kFewExperts && layer_bytes(c) >= kMediumLayer && w.rows < 60 * w.weight_rows;
+  if (!w8 && c.dtype != MOE_BF16_MXFP4) return false;
+  const int most = c.E <= kFewExperts ? (w8 ? 70 : 76) : c.I > 1024 ? 84 : layer_bytes(c) >= kLargeLayer ? 76 : 36;
+  if (w8 && c.E > kFewExperts && c.I <= 1024 && w.rows >= 36 * w.weight_rows && w.rows < 54 * w.weight_rows) return false;
+  return w.rows < most * w.weight_rows;
+}
+
+// Two tiles of weight rows per wave, which share the token rows' fragments, instead of one.  A tile of narrow weights
+// is computed from LDS slower than it comes from HBM once it meets several tiles of token rows, and half of the reads are
+// the token rows'.  With fewer rows the larger panels leave more of the last round empty.  gate+up + down, us, one / two:
+//   * MXFP4, 60 of 1408 + 5632, 200 tokens (22 rows per weight row) 105 / 107, 255 tokens (28) 121 / 114; 64 of 1408 + 2 shared,
+//     255 tokens (25) 108 / 114, 420 tokens (41) 160 / 138; 8 of 14336, 128 tokens (24) 197 / 206, 200 tokens (38) 268 / 246.
+//   * 8-bit: 60 of 1408 + 5632, 256 tokens (28) 149 / 152, 420 tokens (46) 181 / 171; 64 of 1024, 540 tokens (51) 130 / 144, 680
+//     tokens (64) 156 / 143; 64 of 1408 + 2 shared, 420 tokens (41) 158 / 160, 540 tokens (53) 188 / 174; 8 of 14336, 256 tokens
+//     (48) 325 / 326, 330 tokens (62) 433 / 381.  bf16 weights: 8 of 14336, 256 tokens 484 / 494.
+//   * Parts of a step have fewer rows than that: 60 of 1408, fallback pass, 420 tokens, 8-bit 1.41 / 1.33 times the tiled
+//     kernel's rate.  There they pay where they make one round over the CUs of two: 64 of 272, hidden 528, 256 tokens 29.2 / 25.4.
+bool wide_panels(const moe_config& c, bool run_shared, int cus) {
+  if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
+  if (!run_shared) {
+    constexpr int kColumns = 64;       // gate/up columns of a panel of one tile per wave
+    return c.T >= kTiledMinT && c.E * ceil_div(c.I, kColumns) > cus && c.E * ceil_div(c.I, 2 * kColumns) <= cus;
+  }
+  const Work w = layer_work(c);
+  return w.rows >= (c.dtype == MOE_BF16_W8 ? 52 : 27) * w.weight_rows;
+}
+
 // bf16 weights that are read once in a launch need no place in the caches, which then hold the token rows longer.
 // gate+up + down, us, through the caches / past them: 64 of 1024, 300 tokens 146 / 133, 777 tokens 208 / 200, 16 of
 // 1024, hidden 4096 (403 MB), 600 tokens 119 / 111, 24 of 2048 (604 MB), 1200 tokens 179 / 171, 32 of 1024 + 2048 (428 MB),
@@ -195,6 +249,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
     r.two_tiles = whole && two_tiles(c);
     r.panels = c.T < kTiledMinT && stream_panels(c, run_routed, run_shared);
+    r.wide_panels = r.panels && wide_panels(c, run_shared, cus);
     return r;
   }
   if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {
@@ -205,6 +260,8 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
     r.weights_once = weights_once(c);
     r.by_rows_down = tiled_by_rows(c, run_routed, run_shared, cus);
     r.by_rows_gate_up = r.by_rows_down && !(whole && few_tiles_left(c, cus));
+    r.panels = prefill_panels(c, run_routed);
+    r.wide_panels = r.panels && wide_panels(c, run_shared, cus);
   }
   return r;
 }

@@ -6,9 +6,10 @@
 
 namespace mm {
 
-// Steps of this many tokens and more run the LDS-tiled kernels (bf16 activations): the experts see
-// enough rows for MFMA tiles.  Below that the weights are streamed once through the skinny kernel.
+// Steps of this many tokens and more run the LDS-tiled kernels (bf16 activations) where the experts see
+// enough rows for MFMA tiles.  Below that the weights are streamed once through a skinny kernel.
 constexpr int kTiledMinT = 256;
+constexpr int kPanelsMaxT = 65535;   // tokens that stream_panels.hip can number
 constexpr int kTiledPanel = 128;     // gate/up output columns of a tile of either tiled kernel
 constexpr int kTiledRows = 128;      // token rows of a tile of the 128 x 256 kernel
 constexpr int kWideRows = 256;       // token rows of a tile of the wide kernel
@@ -17,7 +18,8 @@ constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles 
 enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
 struct FfnRoute {
   FfnKernel kernel;
-  bool panels;                       // kFfnStream: stream_panels.hip instead of stream_lds.hip
+  bool panels;                       // stream_panels.hip instead of that (never where it is kFfnWide)
+  bool wide_panels;                  // StreamArgs::wide_panels (stream_panels.hip)
   bool two_tiles;                    // StreamArgs::two_tiles (stream_lds.hip)
   bool weights_once;                 // StreamArgs::weights_once
   bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches

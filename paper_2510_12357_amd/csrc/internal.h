@@ -77,6 +77,7 @@ struct StreamArgs {
   const int32_t* sorted_token;        // device [T*k_big]
   int max_pairs;                      // T * k_big
   int two_tiles;                      // streaming kernel, bf16: token tiles per computer two instead of one (ffn_route)
+  int wide_panels;                    // stream_panels.hip: tiles of weight rows per wave two instead of one (ffn_route)
   int by_rows;                        // tiled and wide kernels: order of their tiles (ffn_route)
   int weights_once;                   // tiled kernel, bf16: weights read once go past the caches (ffn_route)
   const void* x;                      // [T,H]
@@ -94,7 +95,7 @@ int launch_stream(StreamMode mode, int dtype, const StreamArgs& a, hipStream_t s
 // scales) streamed through an LDS ring (stream_lds.hip)
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4
 int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
-// the same for large layers, fewer than 256 tokens: every wave streams rows of its own (stream_panels.hip)
+// the same for large layers and for prefill of few rows per expert: every wave streams rows of its own (stream_panels.hip)
 int launch_stream_panels(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
 
 // ---- large-m grouped GEMM on LDS-tiled MFMA (prefill regime; bf16 activations) ---------------

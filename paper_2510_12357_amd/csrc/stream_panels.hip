@@ -1,6 +1,6 @@
-// Skinny grouped GEMM for the decode regime of large layers (fewer than 256 tokens; bf16 activations; bf16, 8-bit or
-// MXFP4 weights): the operation and, per element, the order of additions of stream_lds.hip, so that either kernel gives
-// the same bits.
+// Skinny grouped GEMM for the decode regime of large layers and for prefill of few rows per expert (bf16 activations; bf16,
+// 8-bit or MXFP4 weights): the operation and, per element, the order of additions of stream_lds.hip, so that either
+// kernel gives the same bits, and any split of a step into smaller ones.
 //
 //   kGateUp  h = silu(W_gate x) * (W_up x)     (execution stage of Sec. II-A, SwiGLU)
 //   kDown    y = W_down h
@@ -22,6 +22,13 @@
 //     rounds than the largest, so that every workgroup ends at the same time: 1342 panels of 32 quads on 256 CUs
 //     are 5.2 rounds, 1525 of 28.2 fill six (60 experts, 64 tokens, gate/up: the last workgroup ended 27 us behind the
 //     median, now 7).
+//   * With many token rows it is the reads from LDS that bound the narrow formats: 16 KB of a panel's token rows for every 4 KB of
+//     weights.  RT = 2 makes a wave's share two tiles of up to four quads, whose products share the fragments of the token rows:
+//     8 experts of 14336, MXFP4, 256 tokens, gate/up + down 336 / 280, 8-bit 330 tokens 433 / 381, 60 of 1408 + 5632, MXFP4 420 tokens
+//     155 / 152, 8-bit 181 / 171.  The 16 quads' accumulators still fit 256 registers at 64 rows.
+//   * Steps of 256 tokens and more (MANY) have token numbers of two bytes, too many for LDS at once: the workgroup
+//     looks them up for 32 of its panels at a time.  Their weights pass the caches as well: loaded through them the steps
+//     were slower.
 //   * Groups of more token rows are several blocks of even length, whose panels over the same weights are eight places
 //     apart, i.e. on one XCD at one time.
 //   * The two sums per output (even and odd groups of four 16-byte columns) are those of the two k parts in stream_lds.hip.
@@ -32,7 +39,7 @@
 // bf16 431 + 227 / 320 + 168, 8-bit 334 + 187 / 199 + 109, MXFP4 294 + 177 / 187 + 151.  MXFP4 at 64 tokens: 187 MB in 42 us behind the
 // first load; without the products 36, without the token rows too 33.
 // Measured and not kept: contiguous ranges of quads per workgroup (pieces of groups that a wave has little of last as
-// long as whole ones); slices of half a unit; two tiles per wave and panel (as fast, the rounds balance worse); three or four
+// long as whole ones); slices of half a unit; two tiles per wave and panel for bf16 weights (as fast, the rounds balance worse); three or four
 // token buffers with a mark per load (1 - 2 % slower: the counts are no constants any more); weights and token rows
 // read in one go (MXFP4 5 % slower: the next load waits for the token rows); units of 1 or 2 quads and 4 or 2 times the k for
 // panels of few quads (8 experts, 1 token, down 51 -> 42, everything else 1 % slower).
@@ -50,9 +57,9 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kWaves = 8;
 constexpr int kThreadsP = kWaves * 64;
-constexpr int kPanelQuads = 4 * kWaves;                   // quads of a panel, at most: a tile of 16 rows per wave
+constexpr int kPanelsMany = 32;                           // panels that a workgroup of a step of 256 tokens and more looks up at a time
 constexpr int kIndexMax = (kTiledMinT - 1) * MOE_MAX_TOPK;
-static_assert(kTiledMinT <= 256, "a token's number and a group's rows fit a byte");
+static_assert(kTiledMinT <= 256, "the token numbers of such a step fit a byte");
 
 // WB as in groups.h: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4
 template <int WB> struct Unit {
@@ -100,6 +107,11 @@ __device__ __forceinline__ unsigned lds_read_u8(unsigned addr) {
   asm volatile("ds_read_u8 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
   return v;
 }
+__device__ __forceinline__ unsigned lds_read_u16(unsigned addr) {
+  unsigned v;
+  asm volatile("ds_read_u16 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
+  return v;
+}
 #define MM_RD(D, A, O) "ds_read_b128 %" #D ", %" #A " offset:" #O "\n\t"
 #define MM_RD4(D0, D1, D2, D3, A0, A1, A2, A3, O) MM_RD(D0, A0, O) MM_RD(D1, A1, O) MM_RD(D2, A2, O) MM_RD(D3, A3, O)
 #define MM_OUT4(V) "=&v"((V)[0]), "=&v"((V)[1]), "=&v"((V)[2]), "=&v"((V)[3])
@@ -131,13 +143,18 @@ template <int WB>
 struct __attribute__((aligned(1024))) SmemP {
   char tok[2][Unit<WB>::kBuffer];     // in front of the ring: reads for tokens that do not exist run into it
   char ring[kWaves][Unit<WB>::kStages * Unit<WB>::kBytes];
-  unsigned char index[kIndexMax];     // token of each dispatch position (gate/up)
+  union {
+    unsigned char index[kIndexMax];   // fewer than 256 tokens: token of each dispatch position (gate/up)
+    unsigned short rows[kPanelsMany][64];   // more: token of each row of the workgroup's panels
+  };
 };
 
-template <int MODE, int WB>
+// MANY: 256 tokens and more; RT: tiles of four quads of a wave in a panel, at most
+template <int MODE, int WB, bool MANY, int RT>
 __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2))) void stream_panel_kernel(const StreamArgs a) {
   typedef Unit<WB> U;
   constexpr int OQ = MODE == kGateUp ? 2 : 4;            // output columns per quad
+  constexpr int kPanelQuads = 4 * RT * kWaves;           // quads of a panel, at most
   __shared__ SmemP<WB> sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int q = lane >> 4, c16 = lane & 15;
@@ -146,16 +163,16 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
 
   // ---- routed experts: expert 64 j + lane in this lane ----
   constexpr int NE = MOE_MAX_EXPERTS / 64;
-  int v_end[NE], v_src[NE], v_lo[NE], v_hi[NE];          // token blocks up to and with the expert; rows | first dispatch position << 8; weights
+  int v_end[NE], v_m[NE], v_row0[NE], v_lo[NE], v_hi[NE];   // token blocks up to and with the expert; rows, first dispatch position; weights
   int routed_blocks = 0;
 #pragma unroll
   for (int j = 0; j < NE; ++j) {
-    v_end[j] = v_src[j] = v_lo[j] = v_hi[j] = 0;
+    v_end[j] = v_m[j] = v_row0[j] = v_lo[j] = v_hi[j] = 0;
     if (64 * j < a.n_routed) {
       int nb = 0;
       if (64 * j + lane < a.n_routed) {
         const GroupSrc src = load_group_src<MODE>(a, n_sh + 64 * j + lane);
-        v_src[j] = src.m | src.row0 << 8;
+        v_m[j] = src.m; v_row0[j] = src.row0;
         v_lo[j] = (int)(uint64_t)src.blob; v_hi[j] = (int)((uint64_t)src.blob >> 32);
         nb = token_blocks<WB>(src.m);
       }
@@ -168,7 +185,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
       routed_blocks = __builtin_amdgcn_readlane(v_end[j], 63);
     }
   }
-  if (MODE == kGateUp && a.n_routed)
+  if (!MANY && MODE == kGateUp && a.n_routed)
     for (int i = tid; i < a.max_pairs; i += kThreadsP) sm.index[i] = (unsigned char)clampi(a.sorted_token[i], 0, a.T - 1);
 
   // ---- panels: every group's quads in panels of at most `per`, the smallest size that needs no more rounds of workgroups ----
@@ -183,7 +200,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
   int per;
   {
     const int rounds = (panels_with(kPanelQuads) + grid - 1) / grid;
-    const uint64_t fits = __ballot(lane < kPanelQuads && panels_with(lane + 1) <= rounds * grid);
+    const uint64_t fits = __ballot(panels_with(min(lane + 1, kPanelQuads)) <= rounds * grid);
     per = uniform((int)__builtin_ctzll(fits | 1ull << (kPanelQuads - 1)) + 1);
   }
   const int npr = (Qr + per - 1) / per;
@@ -199,11 +216,12 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
     b_rd[j] = tok + (unsigned)((c16 << U::kRowShift) + ((low ^ c16) << 4));
   }
 
+  constexpr int kLook = MANY ? kPanelsMany : 64;
 #pragma unroll 1
-  for (int first = blockIdx.x; first < total; first += 64 * grid) {
+  for (int first = blockIdx.x; first < total; first += kLook * grid) {
     // ---- panels first, first + grid, ..: one per lane ----
-    const int np = min(64, (total - first + grid - 1) / grid);
-    int p_g = 0, p_qa = 0, p_n = 0, p_r0 = 0, p_rows = 0, p_src = a.T, p_lo = 0, p_hi = 0;
+    const int np = min(kLook, (total - first + grid - 1) / grid);
+    int p_g = 0, p_qa = 0, p_n = 0, p_r0 = 0, p_rows = 0, p_m = a.T, p_row0 = 0, p_lo = 0, p_hi = 0;
     {
       int item = first + min(lane, np - 1) * grid, nb = sh_blocks, panels = npr, Q = Qr;
       const bool sh = item < total_sh;
@@ -219,7 +237,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
         item -= total_sh;
       }
       const int blk = sh ? 0 : item / npr;               // the expert that holds this block: the first whose blocks end behind it
-      int e = 0, v = 0, lo = 0, hi = 0, end = 0;
+      int e = 0, m = a.T, row0 = 0, lo = 0, hi = 0, end = 0;
 #pragma unroll
       for (int j = 0; j < NE; ++j) {
         if (64 * j < a.n_routed) {
@@ -229,17 +247,17 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
             if (__shfl(v_end[j], at + d - 1) <= blk) at += d;
           const bool here = j == 0 || e == 64 * j;       // every expert of the sets before ends in front of the block
           const int l = min(at, 63);
-          const int nv = __shfl(v_src[j], l), nlo = __shfl(v_lo[j], l), nhi = __shfl(v_hi[j], l), nend = __shfl(v_end[j], l);
-          if (here) { e = 64 * j + (__shfl(v_end[j], 63) <= blk ? 64 : at); v = nv; lo = nlo; hi = nhi; end = nend; }
+          const int nm = __shfl(v_m[j], l), nrow0 = __shfl(v_row0[j], l), nlo = __shfl(v_lo[j], l), nhi = __shfl(v_hi[j], l), nend = __shfl(v_end[j], l);
+          if (here) { e = 64 * j + (__shfl(v_end[j], 63) <= blk ? 64 : at); m = nm; row0 = nrow0; lo = nlo; hi = nhi; end = nend; }
         }
       }
       if (!sh) {
-        p_g = n_sh + min(e, a.n_routed - 1); p_src = v; p_lo = lo; p_hi = hi;
-        nb = token_blocks<WB>(v & 255);
+        p_g = n_sh + min(e, a.n_routed - 1); p_m = m; p_row0 = row0; p_lo = lo; p_hi = hi;
+        nb = token_blocks<WB>(m);
         item -= (end - nb) * npr;
       }
       // all token blocks of panel 8 b + i are 8 panels apart: at the same time on one XCD
-      const int m = p_src & 255;
+      m = p_m;
       int tb = 0, panel = item;
       if (nb > 1) {
         const int b8 = item / (8 * nb), rem = item - b8 * 8 * nb, w8 = min(8, panels - 8 * b8);
@@ -253,30 +271,44 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
     struct Panel { int qa, n, r0, rows; };
     auto get_panel = [&](int i, Group& G) -> Panel {
       Panel p;
-      const int g = __builtin_amdgcn_readlane(p_g, i), v = __builtin_amdgcn_readlane(p_src, i);
+      const int g = __builtin_amdgcn_readlane(p_g, i);
       p.qa = __builtin_amdgcn_readlane(p_qa, i); p.n = __builtin_amdgcn_readlane(p_n, i);
       p.r0 = __builtin_amdgcn_readlane(p_r0, i); p.rows = __builtin_amdgcn_readlane(p_rows, i);
       GroupSrc src;
-      src.m = v & 255; src.row0 = v >> 8;
+      src.m = __builtin_amdgcn_readlane(p_m, i); src.row0 = __builtin_amdgcn_readlane(p_row0, i);
       src.blob = (const void*)(((uint64_t)(unsigned)__builtin_amdgcn_readlane(p_hi, i) << 32) | (unsigned)__builtin_amdgcn_readlane(p_lo, i));
       G = make_group<uint16_t, MODE, WB>(a, g, src);
       return p;
     };
+    if (MANY && MODE == kGateUp) {
+      for (int i = wave; i < np; i += kWaves) {
+        const int r0 = __builtin_amdgcn_readlane(p_r0, i), rows = __builtin_amdgcn_readlane(p_rows, i);
+        if (__builtin_amdgcn_readlane(p_g, i) >= n_sh && lane < rows)
+          sm.rows[i][lane] = (unsigned short)clampi(a.sorted_token[__builtin_amdgcn_readlane(p_row0, i) + r0 + lane], 0, a.T - 1);
+      }
+    }
     // a panel's quads are dealt to the waves in contiguous parts that differ by one at most
     auto wave_part = [&](const Panel& p, int i, int& wa, int& wn) {
       const int w = (wave + 3 * i) & (kWaves - 1), more = p.n & (kWaves - 1);
       wn = p.n / kWaves + (w < more ? 1 : 0);
       wa = p.qa + (p.n / kWaves) * w + min(w, more);
     };
+    // a wave's quads as one tile of up to four, or two even ones
+    auto tiles_of = [](int wn) -> int { return RT > 1 && wn > 4 ? 2 : 1; };
+    auto tile_start = [](int wn, int r) -> int { return r == 0 ? 0 : (RT > 1 && wn > 4 && r == 1 ? (wn + 1) / 2 : wn); };
     auto slice_rows = [](const Panel& p) -> int { return (p.rows + U::kRowsPerLoad - 1) & ~(U::kRowsPerLoad - 1); };
     // units per slice of token rows
     auto slice_units = [&](const Panel& p, int nu) -> int { return min(nu, (U::kBuffer >> U::kRowShift) / slice_rows(p)); };
 
     // ---- weight cursor ----
-    int w_p = -1, w_u = 0, w_nu = 0, w_left = 0, w_n = 0, slot = 0;
-    unsigned addr[4], s_addr = 0;
+    int w_p = -1, w_u = 0, w_nu = 0, w_left = 0, w_n = 0, w_tile = 0, w_tiles = 1, slot = 0;
+    unsigned addr[RT][4], s_addr[RT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) addr[i] = 0;
+    for (int r = 0; r < RT; ++r) {
+      s_addr[r] = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) addr[r][i] = 0;
+    }
     __amdgpu_buffer_rsrc_t rw = make_rsrc(a.x, 0), rsc = rw;
     auto next_weights = [&]() {
       w_u = 0; w_n = 0; w_nu = 1 << 30;                  // nothing is left: loads that only fill LDS with zeros
@@ -290,41 +322,60 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
         const unsigned ld = WB ? (unsigned)G.ldw * WB : (unsigned)G.ldw / 2u;
         rw = make_rsrc(G.w0, G.wbytes);
         w_left = G.K; w_nu = (G.K + U::kK - 1) / U::kK;
-        const int n0 = wa * OQ;
+        w_tiles = tiles_of(w_n);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // quad i of the tile: gate/up: rows n, n + 1 of W_gate and the same of W_up behind it
-          const int n = MODE == kGateUp ? n0 + 2 * i + (q & 1) + ((q & 2) ? G.N : 0) : n0 + 4 * i + q;
-          addr[i] = ((unsigned)n * ld + (unsigned)((c16 ^ (4 * i + q)) << 4)) | (i < w_n ? 0u : kOob);
-        }
-        if (WB == 0) {
-          const unsigned lds = (unsigned)G.ldw >> 5;
-          rsc = make_rsrc(G.scale, (unsigned)((MODE == kGateUp ? 2 : 1) * G.N - 1) * lds + ((unsigned)G.K >> 5));
-          const int row = lane >> 2;                     // one dword = four blocks of one row
-          const int n = MODE == kGateUp ? n0 + 2 * (row >> 2) + (row & 1) + ((row & 2) ? G.N : 0) : n0 + row;
-          s_addr = ((unsigned)n * lds + 4u * (lane & 3)) | ((row >> 2) < w_n ? 0u : kOob);
+        for (int r = 0; r < RT; ++r) {
+          const int n0 = (wa + tile_start(w_n, r)) * OQ, tn = tile_start(w_n, r + 1) - tile_start(w_n, r);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            // quad i of the tile: gate/up: rows n, n + 1 of W_gate and the same of W_up behind it
+            const int n = MODE == kGateUp ? n0 + 2 * i + (q & 1) + ((q & 2) ? G.N : 0) : n0 + 4 * i + q;
+            addr[r][i] = ((unsigned)n * ld + (unsigned)((c16 ^ (4 * i + q)) << 4)) | (i < tn ? 0u : kOob);
+          }
+          if (WB == 0) {
+            const unsigned lds = (unsigned)G.ldw >> 5;
+            rsc = make_rsrc(G.scale, (unsigned)((MODE == kGateUp ? 2 : 1) * G.N - 1) * lds + ((unsigned)G.K >> 5));
+            const int row = lane >> 2;                   // one dword = four blocks of one row
+            const int n = MODE == kGateUp ? n0 + 2 * (row >> 2) + (row & 1) + ((row & 2) ? G.N : 0) : n0 + row;
+            s_addr[r] = ((unsigned)n * lds + 4u * (lane & 3)) | ((row >> 2) < tn ? 0u : kOob);
+          }
         }
       } else {
+        w_tiles = 1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) addr[i] = kOob;
-        s_addr = kOob;
+        for (int r = 0; r < RT; ++r) {
+          s_addr[r] = kOob;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) addr[r][i] = kOob;
+        }
       }
+      w_tile = 0;
     };
     auto issue = [&]() {
       char* const st = sm.ring[wave] + slot * U::kBytes;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const bool ok = (c16 ^ (4 * i + q)) * U::kPerColumn < w_left;            // k behind the row's end: out of range
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(st + i * 1024), 16, (int)(addr[i] | (ok ? 0u : kOob)), 0, 0, kStreamOnce);
-        addr[i] += 256u;                                 // kOob + a row stays out of range
+        const unsigned at = RT > 1 && w_tile ? addr[RT - 1][i] : addr[0][i];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(st + i * 1024), 16, (int)(at | (ok ? 0u : kOob)), 0, 0, kStreamOnce);
       }
       if (WB == 0) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsc, (lds_void*)(st + 4096), 4, (int)(s_addr | ((lane & 3) * 128 < w_left ? 0u : kOob)), 0, 0, 0);
-        s_addr += 16u;
+        const unsigned at = RT > 1 && w_tile ? s_addr[RT - 1] : s_addr[0];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsc, (lds_void*)(st + 4096), 4, (int)(at | ((lane & 3) * 128 < w_left ? 0u : kOob)), 0, 0, 0);
       }
       slot = slot + 1 == U::kStages ? 0 : slot + 1;
-      w_left -= U::kK;
-      if (++w_u == w_nu) next_weights();
+      if (RT > 1 && w_tile + 1 < w_tiles) w_tile = 1;
+      else {
+        w_tile = 0;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) addr[r][i] += 256u;              // kOob + a row stays out of range
+          s_addr[r] += 16u;
+        }
+        w_left -= U::kK;
+        if (++w_u == w_nu) next_weights();
+      }
     };
 
     // ---- token cursor ----
@@ -353,7 +404,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
           constexpr int cols = 16 * U::kParts;
           const int row = U::kRowsPerLoad * r + lane / cols, kk = u * U::kK + (((lane % cols) ^ (row & 15)) << 3);
           int src = t_r0 + min(row, t_rows - 1);
-          if (t_gather) src = (int)lds_read_u8(s_index + (unsigned)(t_row0 + src));
+          if (t_gather) src = MANY ? (int)lds_read_u16(s_index + (unsigned)(t_p * 64 + min(row, t_rows - 1)) * 2u) : (int)lds_read_u8(s_index + (unsigned)(t_row0 + src));
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_void*)(dst + i * 1024), 16,
               (int)(((unsigned)src * t_ld + (unsigned)kk * 2u) | (row < t_rows && kk < t_K ? 0u : kOob)), 0, 0, 0);
           ++issued;
@@ -381,9 +432,12 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
       wave_part(p, ip, wa, wn);
       const int nt = (p.rows + 15) >> 4, nu = (G.K + U::kK - 1) / U::kK, us = slice_units(p, nu);
       const unsigned unit_bytes = (unsigned)slice_rows(p) << U::kRowShift;
-      f32x4 acc[U::kTiles][2];                 // two sums per token tile: even and odd groups of four columns
+      f32x4 acc[RT][U::kTiles][2];             // two sums per token tile: even and odd groups of four columns
 #pragma unroll
-      for (int t = 0; t < U::kTiles; ++t) acc[t][0] = acc[t][1] = f32x4{0, 0, 0, 0};
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int t = 0; t < U::kTiles; ++t) acc[r][t][0] = acc[r][t][1] = f32x4{0, 0, 0, 0};
+      const bool both = RT > 1 && wn > 4;
 #pragma unroll 1
       for (int u0 = 0; u0 < nu; u0 += us) {
         if (since <= U::kStages) wait_units<U::kLoads>(since);          // this wave's part of the slice has landed
@@ -397,55 +451,97 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
         for (int j = 0; j < 4; ++j) ab[j] = b_rd[j] + (unsigned)(buf * U::kBuffer);
 #pragma unroll 1
         for (int u = u0; u < u1; ++u) {
-          // the units issued in front of the slice's token rows may have those behind them as well
-          if (since < U::kStages) wait_vm<(U::kStages - 1) * U::kLoads>(extra); else MM_WAIT_VM((U::kStages - 1) * U::kLoads);
-          const unsigned so = (unsigned)(slot * U::kBytes);
-          const unsigned aw[4] = {a_rd[0] + so, a_rd[1] + so, a_rd[2] + so, a_rd[3] + so};
-          i32x4 w[4], sc4;
-          if constexpr (WB == 0) read_weights(w, sc4, aw, ring + so + 4096u + (unsigned)c16 * 16u);
-          else read_weights(w, aw);
-          issue();
-          ++since;
-          bf16x8 f[U::kParts][4];              // weights of the k-steps
-#pragma unroll
-          for (int part = 0; part < U::kParts; ++part) {
-            const float sv = WB == 0 ? e8m0_to_f32(((unsigned)sc4[part] >> (8 * q)) & 0xffu) : 0.f;
+          i32x4 w[RT][4], sc4[RT];
+          auto take_unit = [&](int r) {
+            // the units issued in front of the slice's token rows may have those behind them as well
+            if (since < U::kStages) wait_vm<(U::kStages - 1) * U::kLoads>(extra); else MM_WAIT_VM((U::kStages - 1) * U::kLoads);
+            const unsigned so = (unsigned)(slot * U::kBytes);
+            const unsigned aw[4] = {a_rd[0] + so, a_rd[1] + so, a_rd[2] + so, a_rd[3] + so};
+            if constexpr (WB == 0) read_weights(w[r], sc4[r], aw, ring + so + 4096u + (unsigned)c16 * 16u);
+            else read_weights(w[r], aw);
+            issue();
+            ++since;
+          };
+          take_unit(0);
+          if constexpr (RT > 1) if (both) take_unit(1);
+          // weights of the k-steps of a part of unit r
+          auto widen = [&](int r, int part, bf16x8 (&f)[4]) {
+            const float sv = WB == 0 ? e8m0_to_f32(((unsigned)sc4[r][part] >> (8 * q)) & 0xffu) : 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              if constexpr (WB == 2) f[part][j] = __builtin_bit_cast(bf16x8, w[j]);
-              else if constexpr (WB == 1) f[part][j] = widen_e4m3(w[2 * part + (j >> 1)][2 * (j & 1)], w[2 * part + (j >> 1)][2 * (j & 1) + 1]);
-              else f[part][j] = widen_mx4(w[part][j], sv);
-            }
-          }
-          auto token_tile = [&](auto tc) {
-            constexpr int t = decltype(tc)::value;
-            if constexpr (t < U::kTiles) {
-              if (t < nt) {
-                constexpr unsigned far = (unsigned)t << (U::kRowShift + 4);
-                const unsigned at[4] = {ab[0] + far, ab[1] + far, ab[2] + far, ab[3] + far};
-                i32x4 b[U::kParts][4];
-                read_tokens(b, at);
-#pragma unroll
-                for (int part = 0; part < U::kParts; ++part)
-#pragma unroll
-                  for (int j = 0; j < 4; ++j) {
-                    const int odd = WB == 2 ? j & 1 : (WB == 1 ? j >> 1 : part & 1);
-                    acc[t][odd] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[part][j], __builtin_bit_cast(bf16x8, b[part][j]), acc[t][odd], 0, 0, 0);
-                  }
-              }
+              if constexpr (WB == 2) f[j] = __builtin_bit_cast(bf16x8, w[r][j]);
+              else if constexpr (WB == 1) f[j] = widen_e4m3(w[r][2 * part + (j >> 1)][2 * (j & 1)], w[r][2 * part + (j >> 1)][2 * (j & 1) + 1]);
+              else f[j] = widen_mx4(w[r][part][j], sv);
             }
           };
-          token_tile(std::integral_constant<int, 0>{});
-          token_tile(std::integral_constant<int, 1>{});
-          token_tile(std::integral_constant<int, 2>{});
-          token_tile(std::integral_constant<int, 3>{});
+          auto multiply = [&](int r, int t, int part, const bf16x8 (&f)[4], const i32x4 (&b)[4]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int odd = WB == 2 ? j & 1 : (WB == 1 ? j >> 1 : part & 1);
+              acc[r][t][odd] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j], __builtin_bit_cast(bf16x8, b[j]), acc[r][t][odd], 0, 0, 0);
+            }
+          };
+          if constexpr (RT == 1 || WB != 0) {
+            bf16x8 f[RT][U::kParts][4];
+#pragma unroll
+            for (int part = 0; part < U::kParts; ++part) widen(0, part, f[0][part]);
+            if constexpr (RT > 1) {
+              if (both) {
+#pragma unroll
+                for (int part = 0; part < U::kParts; ++part) widen(1, part, f[1][part]);
+              }
+            }
+            auto token_tile = [&](auto tc) {
+              constexpr int t = decltype(tc)::value;
+              if constexpr (t < U::kTiles) {
+                if (t < nt) {
+                  constexpr unsigned far = (unsigned)t << (U::kRowShift + 4);
+                  const unsigned at[4] = {ab[0] + far, ab[1] + far, ab[2] + far, ab[3] + far};
+                  i32x4 b[U::kParts][4];
+                  read_tokens(b, at);
+#pragma unroll
+                  for (int part = 0; part < U::kParts; ++part) multiply(0, t, part, f[0][part], b[part]);
+                  if constexpr (RT > 1) {
+                    if (both) {
+#pragma unroll
+                      for (int part = 0; part < U::kParts; ++part) multiply(1, t, part, f[1][part], b[part]);
+                    }
+                  }
+                }
+              }
+            };
+            token_tile(std::integral_constant<int, 0>{});
+            token_tile(std::integral_constant<int, 1>{});
+            token_tile(std::integral_constant<int, 2>{});
+            token_tile(std::integral_constant<int, 3>{});
+          } else {
+#pragma unroll
+            for (int part = 0; part < U::kParts; ++part) {
+              bf16x8 f[RT][4];
+              widen(0, part, f[0]);
+              if (both) widen(1, part, f[RT - 1]);
+#pragma unroll
+              for (int t = 0; t < U::kTiles; ++t) {
+                if (t < nt) {
+                  const unsigned far = ((unsigned)t << (U::kRowShift + 4)) + 256u * part;
+                  const unsigned at[4] = {ab[0] + far, ab[1] + far, ab[2] + far, ab[3] + far};
+                  i32x4 b[1][4];
+                  read_tokens(b, at);
+                  multiply(0, t, part, f[0], b[0]);
+                  if (both) multiply(1, t, part, f[RT - 1], b[0]);
+                }
+              }
+            }
+          }
 #pragma unroll
           for (int j = 0; j < 4; ++j) ab[j] += unit_bytes;
         }
       }
       // ---- epilogue ----
-      if (wn > 0) {
-        const int n0 = wa * OQ;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const int tn = tile_start(wn, r + 1) - tile_start(wn, r), n0 = (wa + tile_start(wn, r)) * OQ;
+        if (tn <= 0) continue;
         float sc[4] = {1.f, 1.f, 1.f, 1.f};
         if (WB == 1) {
           typedef const __attribute__((address_space(4))) float* cfloat;
@@ -462,15 +558,15 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
         }
 #pragma unroll
         for (int t = 0; t < U::kTiles; ++t) {
-          const int r = 16 * t + c16;
-          if (r < p.rows && q < wn) {
+          const int row = 16 * t + c16;
+          if (row < p.rows && q < tn) {
             float val[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              val[v] = acc[t][0][v] + acc[t][1][v];
+              val[v] = acc[r][t][0][v] + acc[r][t][1][v];
               if (WB == 1) val[v] *= sc[v];
             }
-            const size_t ro = (size_t)(p.r0 + r);
+            const size_t ro = (size_t)(p.r0 + row);
             if (MODE == kGateUp) {
               typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
               float h[2];
@@ -489,28 +585,35 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
   }
 }
 
-template <int MODE, int WB>
+template <int MODE, int WB, bool MANY, int RT>
 int launch_panels_typed(const StreamArgs& a, hipStream_t s) {
-  if (a.T >= kTiledMinT) return fail(MOE_E_UNSUPPORTED, "stream_panel_kernel: T=%d", a.T);
+  if (a.T > kPanelsMaxT) return fail(MOE_E_UNSUPPORTED, "stream_panel_kernel: T=%d", a.T);
   const long items = item_upper_bound((StreamMode)MODE, a, 32);
   if (items <= 0) return MOE_OK;
   long grid = device_cu_count();                          // 158 KB of LDS: one workgroup per CU
   if (grid > items) grid = items;
-  hipLaunchKernelGGL((stream_panel_kernel<MODE, WB>), dim3((unsigned)grid), dim3(kThreadsP), 0, s, a);
+  hipLaunchKernelGGL((stream_panel_kernel<MODE, WB, MANY, RT>), dim3((unsigned)grid), dim3(kThreadsP), 0, s, a);
   return hip_fail(hipGetLastError(), "stream_panel_kernel launch");
+}
+template <int MODE, int WB>
+int launch_panels(const StreamArgs& a, hipStream_t s) {
+  const bool many = a.T >= kTiledMinT;
+  if constexpr (WB != 2)                       // bf16 weights: never faster (ffn_route)
+    if (a.wide_panels) return many ? launch_panels_typed<MODE, WB, true, 2>(a, s) : launch_panels_typed<MODE, WB, false, 2>(a, s);
+  return many ? launch_panels_typed<MODE, WB, true, 1>(a, s) : launch_panels_typed<MODE, WB, false, 1>(a, s);
 }
 
 }  // namespace
 
 int launch_stream_panels(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (mode == kGateUp) {
-    if (weight_format == 2) return launch_panels_typed<kGateUp, 2>(a, s);
-    if (weight_format == 1) return launch_panels_typed<kGateUp, 1>(a, s);
-    return launch_panels_typed<kGateUp, 0>(a, s);
+    if (weight_format == 2) return launch_panels<kGateUp, 2>(a, s);
+    if (weight_format == 1) return launch_panels<kGateUp, 1>(a, s);
+    return launch_panels<kGateUp, 0>(a, s);
   }
-  if (weight_format == 2) return launch_panels_typed<kDown, 2>(a, s);
-  if (weight_format == 1) return launch_panels_typed<kDown, 1>(a, s);
-  return launch_panels_typed<kDown, 0>(a, s);
+  if (weight_format == 2) return launch_panels<kDown, 2>(a, s);
+  if (weight_format == 1) return launch_panels<kDown, 1>(a, s);
+  return launch_panels<kDown, 0>(a, s);
 }
 
 }  // namespace mm

@@ -1,4 +1,4 @@
-"""The rule that lets a step of few tokens stream its weights in panels (csrc/ffn_route.cpp) without a GPU."""
+"""The rules that let a step of few token rows per expert stream its weights in panels (csrc/ffn_route.cpp) without a GPU."""
 import os
 import shutil
 import subprocess
@@ -6,7 +6,7 @@ import subprocess
 import pytest
 
 from paper_2510_12357_amd import workloads as wl
-from test_ffn_route_host import CSRC, DTYPES, ROOT, STREAM
+from test_ffn_route_host import CSRC, DTYPES, ROOT, WIDE
 
 
 @pytest.fixture(scope="module")
@@ -23,9 +23,10 @@ def panels(tmp_path_factory):
         v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
              int(routed), int(shared)]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True)
-        kernel, yes = map(int, r.stdout.split())
-        assert not yes or kernel == STREAM
-        return bool(yes)
+        kernel, yes, wide = map(int, r.stdout.split())
+        assert not yes or kernel != WIDE
+        assert not wide or (yes and cfg.dtype in ("bf16w8", "bf16mx4"))
+        return yes + wide
     return ask
 
 
@@ -47,3 +48,28 @@ def test_large_layers_stream_in_panels(panels):
         assert not panels(_layer(4096, 16, 1024, 2, T))
         assert panels(_layer(2048, 256, 512, 8, T, (512,))) == (T >= 8)
     assert not panels(many.with_(T=256)) and not panels(_layer(2048, 20, 4096, 2, 1)) and panels(_layer(2048, 20, 4096, 2, 4))
+
+
+def test_prefill_of_few_rows_streams_in_panels(panels):
+    """0: tiled; 1, 2: panels of one and two tiles per wave.  Narrow formats of any size while the weights meet few token rows
+    (fewer in smaller layers of many small experts), bf16 only with few experts; the same line for parts of a step."""
+    few, many, small = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"], _layer(512, 8, 512, 2, 256)
+    many_small, smaller = _layer(2048, 64, 1024, 8, 256), _layer(1024, 64, 512, 8, 256)
+    for cfg, dtype, expect in (
+            (few, "bf16", ((256, 1), (319, 1), (320, 0), (4096, 0))), (many, "bf16", ((256, 0), (600, 0))),
+            (small, "bf16", ((256, 0),)), (small.with_(T=256, H=65536), "bf16", ((256, 1),)),
+            (few, "bf16w8", ((277, 1), (278, 2), (373, 2), (374, 0))), (many, "bf16w8", ((256, 1), (475, 1), (476, 2), (767, 2), (768, 0))),
+            (few, "bf16mx4", ((144, 2), (143, 1), (405, 2), (406, 0))), (many, "bf16mx4", ((246, 1), (247, 2), (767, 2), (768, 0))),
+            (small, "bf16w8", ((255, 0), (256, 1), (512, 0))), (small, "bf16mx4", ((255, 0), (256, 2), (512, 0))),
+            (many_small, "bf16w8", ((383, 1), (384, 0), (575, 0), (576, 2), (810, 2), (811, 0))), (many_small, "bf16mx4", ((287, 1), (288, 2), (811, 0))),
+            (smaller, "bf16w8", ((383, 1), (384, 0), (600, 0))), (smaller, "bf16mx4", ((383, 2), (384, 0))),
+            (few, "fp32", ((256, 0),)), (_layer(512, 4096, 4096, 1, 1), "bf16w8", ((65535, 1), (65536, 0)))):
+        for T, want in expect:
+            assert panels(cfg.with_(T=T, dtype=dtype)) == want, (cfg, T)
+            assert not panels(cfg.with_(T=T, dtype=dtype), False, True)
+            if T >= 256:
+                assert (panels(cfg.with_(T=T, dtype=dtype), True, False) > 0) == (want > 0)
+    # a fallback pass: two tiles where they make one round over the CUs of two
+    assert panels(_layer(528, 64, 272, 6, 256, (992,), "bf16w8"), True, False) == 2
+    assert panels(_layer(512, 64, 256, 4, 256, (1024,), "bf16w8"), True, False) == 1
+    assert panels(few.with_(T=400, dtype="bf16mx4"), True, False) == 1

@@ -199,18 +199,8 @@ def test_streamed_items_of_64_rows(counts, H, I, shared):
     _check_assigned(counts, H, I, shared, STREAM, (2, 1))
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "bf16w8", "bf16mx4"])
-@pytest.mark.parametrize("counts,H,I,shared", [
-    ([0, 1, 2, 16, 17, 43, 44, 64], 128, 384, ()),                 # blocks of token rows, their remainders; one k unit and less
-    ([65, 0, 129, 1], 1152, 256, (640, 128)),                      # several blocks; K in parts of a unit; shared experts cut along K
-    ([1], 2048, 128, (128,)),                                      # more waves than rows
-    ([3] * 63 + [0, 2, 1, 4] + [0] * 133 + [5], 128, 128, ()),     # experts behind every word of 64 lanes
-    ([30] * 8, 256, 16384, ()),                                    # more rounds than one
-    ([1] * 255 + [0], 128, 4224, (256,)),                          # more panels in a workgroup than lanes in a wave
-])
-def test_streamed_by_waves(counts, H, I, shared, dtype):
-    """Every wave with rows of its own: the bits of the kernel with loader waves, which the tests against the oracle
-    cover, in y and in the shared experts' outputs; rows that belong to nobody stay as they are."""
+def _coded_layer(counts, H, I, shared, dtype):
+    """_assigned_layer's selection with random weights of any stored format, all of them finite."""
     T, E = sum(counts), len(counts)
     cfg = wl.LayerConfig("edge", T=T, H=H, E=E, I=I, k_big=1, k_little=1, shared_I=tuple(shared), dtype=dtype)
     g = torch.Generator(device="cuda").manual_seed(T + H)
@@ -228,15 +218,69 @@ def test_streamed_by_waves(counts, H, I, shared, dtype):
     experts, sh = [blob(I) for _ in range(E)], [blob(i) for i in shared]
     table = torch.tensor([w.data_ptr() for w in experts], dtype=torch.int64, device="cuda")
     x = torch.randn(T, H, generator=g, device="cuda").to(torch.bfloat16)
-    b = mm.StepBuffers(cfg)
     of = torch.repeat_interleave(torch.arange(E), torch.tensor(counts))[torch.randperm(T, generator=torch.Generator().manual_seed(T))]
+    return cfg, experts, sh, table, x, of.cuda()
+
+
+def _assigned_step(cfg, x, table, sh, of):
+    """Buffers of a step whose token t goes to expert of[t]."""
+    b = mm.StepBuffers(cfg)
     b.logits.fill_(0.0)
-    b.logits[torch.arange(T), of.cuda()] = 4.0
+    b.logits[torch.arange(cfg.T), of] = 4.0
     mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
+    return b
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16w8", "bf16mx4"])
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 2, 16, 17, 43, 44, 64], 128, 384, ()),                 # blocks of token rows, their remainders; one k unit and less
+    ([65, 0, 129, 1], 1152, 256, (640, 128)),                      # several blocks; K in parts of a unit; shared experts cut along K
+    ([1], 2048, 128, (128,)),                                      # more waves than rows
+    ([3] * 63 + [0, 2, 1, 4] + [0] * 133 + [5], 128, 128, ()),     # experts behind every word of 64 lanes
+    ([30] * 8, 256, 16384, ()),                                    # more rounds than one
+    ([1] * 255 + [0], 128, 4224, (256,)),                          # more panels in a workgroup than lanes in a wave
+])
+def test_streamed_by_waves(counts, H, I, shared, dtype):
+    """Every wave with rows of its own: the bits of the kernel with loader waves, which the tests against the oracle
+    cover, in y and in the shared experts' outputs; rows that belong to nobody stay as they are."""
+    cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
+    b = _assigned_step(cfg, x, table, sh, of)
     for routed, with_shared in ((True, True), (True, False)) + (((False, True),) if shared else ()):
         y1, out1 = _run_on(STREAM, 1, b, x, table, sh, routed, with_shared)
-        y4, out4 = _run_on(STREAM, 4, b, x, table, sh, routed, with_shared)
-        assert torch.isfinite(y1).all() and torch.equal(y1, y4) and (out1 is None or torch.equal(out1, out4))
+        for variant in (4,) if dtype == "bf16" else (4, 5):
+            y4, out4 = _run_on(STREAM, variant, b, x, table, sh, routed, with_shared)
+            assert torch.isfinite(y1).all() and torch.equal(y1, y4) and (out1 is None or torch.equal(out1, out4))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16w8", "bf16mx4"])
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 43, 44, 64, 65, 129, 200], 128, 384, ()),              # blocks of token rows, their remainders
+    ([256, 0, 1], 1152, 256, (640, 128)),                          # more shared rows than a byte numbers; K in parts of a unit
+    ([1] * 253 + [3, 0, 0], 256, 128, (128,)),                     # four groups of experts to look through
+    ([300, 2400], 128, 4224, (256,)),                              # blocks of one expert in several rounds; many panels in a workgroup
+])
+def test_prefill_streamed_by_waves(counts, H, I, shared, dtype):
+    """Steps of 256 tokens and more, one and two tiles of rows per wave: an output's sum does not depend on the step, so the
+    bits of the kernel with loader waves on parts of at most 255 tokens; rows of the part not asked for stay as they are."""
+    cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
+    b = _assigned_step(cfg, x, table, sh, of)
+    y_tok, outs = torch.empty(cfg.T, H, device="cuda"), []
+    for lo in range(0, cfg.T, 255):
+        hi = min(lo + 255, cfg.T)
+        part = _assigned_step(cfg.with_(T=hi - lo), x[lo:hi].contiguous(), table, sh, of[lo:hi])
+        y1, out1 = _run_on(STREAM, 1, part, x[lo:hi].contiguous(), table, sh)
+        y_tok[lo + part.sorted_token[:hi - lo].long()] = y1
+        outs.append(out1)
+    ref, ref_out = y_tok[b.sorted_token.long()], torch.cat(outs, 1) if shared else None
+    assert torch.isfinite(ref).all()
+    for variant in (4,) if dtype == "bf16" else (4, 5):
+        y, out = _run_on(STREAM, variant, b, x, table, sh)
+        assert torch.equal(y, ref) and (not shared or torch.equal(out, ref_out)), variant
+        y, out = _run_on(STREAM, variant, b, x, table, sh, shared=False)
+        assert torch.equal(y, ref) and (out is None or bool((out == 7.0).all())), variant
+        if shared:
+            y, out = _run_on(STREAM, variant, b, x, table, sh, routed=False)
+            assert torch.equal(out, ref_out) and bool((y == 7.0).all()), variant
 
 
 @pytest.mark.parametrize("counts,H,I", [
