@@ -325,15 +325,15 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   for (int i = 0; i < a.n_slabs; ++i) { a.slab_shared[i] = plan.slab_shared[i]; a.slab_chunk[i] = plan.slab_chunk[i]; }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
-  const int cus = cfg->T >= kTiledMinT ? device_cu_count() : 0;   // a runtime call, which small steps feel
+  const int cus = cfg->T > kCuMinT ? device_cu_count() : 0;   // a runtime call, which small steps feel
   const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, cus);
   a.two_tiles = r.two_tiles;
   a.wide_panels = r.wide_panels;
-  a.weights_once = r.weights_once;
+  a.weights_once = r.weights_once || r.tiled_gate_up;
   auto launch = [&](StreamMode mode) {
-    if (r.panels) return launch_stream_panels(mode, wfmt, a, s);
+    if (r.panels && !(r.tiled_gate_up && mode == kGateUp)) return launch_stream_panels(mode, wfmt, a, s);
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
-    if (r.kernel == kFfnTiled) return launch_tiled(mode, wfmt, a, s);
+    if (r.kernel == kFfnTiled || r.tiled_gate_up) return launch_tiled(mode, wfmt, a, s);
     return launch_stream(mode, cfg->dtype, a, s);
   };
   {
@@ -371,7 +371,7 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   int rc = validate_config(cfg);
   if (rc) return rc;
   const bool fp32 = cfg->dtype == MOE_FP32, bf16 = cfg->dtype == MOE_BF16, many = cfg->T >= kTiledMinT;
-  const bool panels = kernel == kFfnStream && (variant == 4 || (variant == 5 && !bf16));
+  const bool panels = kernel == kFfnStream && (variant == 4 || (variant == 5 && !bf16) || (variant == 6 && bf16));
   const bool ok = panels ? !fp32 && cfg->T <= kPanelsMaxT
                   : kernel == kFfnStream ? (fp32 || !many) && (variant == 1 || (variant == 2 && bf16))
                                        : (kernel == kFfnTiled || (kernel == kFfnWide && bf16)) && !fp32 && many &&
@@ -381,6 +381,7 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   r.kernel = (FfnKernel)kernel;
   r.panels = panels;
   r.wide_panels = panels && variant == 5;
+  r.tiled_gate_up = panels && variant == 6;
   r.two_tiles = kernel == kFfnStream && variant == 2;
   r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
   r.weights_once = kernel == kFfnTiled && variant >= 2;

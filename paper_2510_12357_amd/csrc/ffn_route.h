@@ -9,6 +9,7 @@ namespace mm {
 // Steps of this many tokens and more run the LDS-tiled kernels (bf16 activations) where the experts see
 // enough rows for MFMA tiles.  Below that the weights are streamed once through a skinny kernel.
 constexpr int kTiledMinT = 256;
+constexpr int kCuMinT = 64;          // up to here no rule asks for the device's compute units
 constexpr int kPanelsMaxT = 65535;   // tokens that stream_panels.hip can number
 constexpr int kTiledPanel = 128;     // gate/up output columns of a tile of either tiled kernel
 constexpr int kTiledRows = 128;      // token rows of a tile of the 128 x 256 kernel
@@ -19,6 +20,7 @@ enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
 struct FfnRoute {
   FfnKernel kernel;
   bool panels;                       // stream_panels.hip instead of that (never where it is kFfnWide)
+  bool tiled_gate_up;                // with panels: the gate/up launch on 128 x 256 tiles, past the caches
   bool wide_panels;                  // StreamArgs::wide_panels (stream_panels.hip)
   bool two_tiles;                    // StreamArgs::two_tiles (stream_lds.hip)
   bool weights_once;                 // StreamArgs::weights_once
@@ -26,7 +28,7 @@ struct FfnRoute {
 };
 
 // run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;
-// cus: compute units of the device (only used from kTiledMinT tokens on).
+// cus: compute units of the device (only used above kCuMinT tokens).
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus);
 
 // Router logits of a step.  kRouterOneLaunch: logits and selection of a token in one workgroup; kRouterGemv:

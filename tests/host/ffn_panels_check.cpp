@@ -1,7 +1,7 @@
 // Prints whether a call of moe_expert_ffn streams its weights in panels (csrc/ffn_route.cpp, no HIP).
 //
 // stdin:   dtype T H E I k_big k_little n_shared shared_I_0 ... run_routed run_shared     (one line per call)
-// stdout:  kernel panels wide_panels
+// stdout:  kernel panels wide_panels tiled_gate_up
 #include <stdio.h>
 
 #include "ffn_route.h"
@@ -14,6 +14,6 @@ int main() {
       if (s >= MOE_MAX_SHARED || scanf("%d", &c.shared_I[s]) != 1) return 2;
     if (scanf("%d %d", &routed, &shared) != 2) return 2;
     const mm::FfnRoute r = mm::ffn_route(c, routed != 0, shared != 0, 256);
-    printf("%d %d %d\n", (int)r.kernel, (int)r.panels, (int)r.wide_panels);
+    printf("%d %d %d %d\n", (int)r.kernel, (int)r.panels, (int)r.wide_panels, (int)r.tiled_gate_up);
   }
 }

@@ -23,10 +23,11 @@ def panels(tmp_path_factory):
         v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
              int(routed), int(shared)]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True)
-        kernel, yes, wide = map(int, r.stdout.split())
+        kernel, yes, wide, tiled = map(int, r.stdout.split())
         assert not yes or kernel != WIDE
         assert not wide or (yes and cfg.dtype in ("bf16w8", "bf16mx4"))
-        return yes + wide
+        assert not tiled or (yes and cfg.dtype == "bf16" and 64 < cfg.T < 256 and routed and shared)
+        return yes + wide + 4 * tiled
     return ask
 
 
@@ -39,7 +40,7 @@ def test_large_layers_stream_in_panels(panels):
     hit, fallback passes from 8 tokens on; many experts from 8 (16) tokens on; never the shared experts alone."""
     few, many = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]
     for T in (1, 2, 64, 65, 255):
-        assert panels(many.with_(T=T)) and panels(few.with_(T=T)) == (T > 64)
+        assert panels(many.with_(T=T)) == (1 if T < 129 else 5) and panels(few.with_(T=T)) == (T > 64)
         assert panels(many.with_(T=T), True, False) == (T >= 8)
         assert not panels(many.with_(T=T), False, True) and not panels(many.with_(T=T, dtype="fp32"))
         for dtype in ("bf16w8", "bf16mx4"):
@@ -73,3 +74,14 @@ def test_prefill_of_few_rows_streams_in_panels(panels):
     assert panels(_layer(528, 64, 272, 6, 256, (992,), "bf16w8"), True, False) == 2
     assert panels(_layer(512, 64, 256, 4, 256, (1024,), "bf16w8"), True, False) == 1
     assert panels(few.with_(T=400, dtype="bf16mx4"), True, False) == 1
+
+
+def test_gate_up_on_tiles_where_the_panels_need_more_rounds(panels):
+    """More than two rounds of panels over the CUs for one of tiles; rows that are whole cache lines only."""
+    for layer, expect in ((_layer(2048, 64, 1408, 6, 1, (1408, 1408)), {64: 1, 128: 1, 129: 5, 255: 5}),
+                          (_layer(2048, 64, 1408, 6, 1, (2816,)), {128: 1, 129: 5, 255: 5}),
+                          (_layer(2048, 64, 1400, 6, 1, (2800,)), {255: 1}),                  # rows that are no whole cache lines
+                          (_layer(2048, 64, 1024, 8, 1), {255: 1}), (_layer(4096, 64, 1536, 6, 1, (3072,)), {255: 1}),
+                          (_layer(2048, 128, 768, 8, 1, (768,)), {255: 1})):
+        for T, want in expect.items():
+            assert panels(layer.with_(T=T)) == want, (layer, T)

@@ -252,6 +252,16 @@ def test_streamed_by_waves(counts, H, I, shared, dtype):
             assert torch.isfinite(y1).all() and torch.equal(y1, y4) and (out1 is None or torch.equal(out1, out4))
 
 
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 32, 33, 64, 65, 50], 200, 264, ()),
+    ([1, 127, 0, 1, 126], 1032, 72, (520,)),                       # 255 tokens: a shared expert of two row blocks
+    ([129], 64, 40, (128, 72)),
+])
+def test_streamed_with_gate_up_on_tiles(counts, H, I, shared):
+    """Gate/up on tiles of 128 token rows, the down projection streamed, fewer than 256 tokens.  Bar as for the wide tiles."""
+    _check_assigned(counts, H, I, shared, STREAM, (6,))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "bf16w8", "bf16mx4"])
 @pytest.mark.parametrize("counts,H,I,shared", [
     ([0, 1, 43, 44, 64, 65, 129, 200], 128, 384, ()),              # blocks of token rows, their remainders
