@@ -1,4 +1,5 @@
-// Grouped expert GEMM for the prefill regime (many tokens per expert): LDS-tiled bf16 MFMA.
+// Grouped expert GEMM for the prefill regime (many tokens per expert) and for bf16 gate/up of steps whose shared experts have more
+// than 128 token rows: LDS-tiled bf16 MFMA.
 //
 //   kGateUp  h[r][i] = silu(sum_k x[tok(r)][k] Wgate[i][k]) * (sum_k x[tok(r)][k] Wup[i][k])
 //   kDown    y[r][c] = sum_i h[r][i] Wdown[c][i]

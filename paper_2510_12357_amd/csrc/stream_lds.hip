@@ -1,4 +1,4 @@
-// Skinny grouped GEMM for the decode regime with the weights streamed from HBM directly into
+// Skinny grouped GEMM for the decode regime (layers too small for stream_panels.hip) with the weights streamed from HBM directly into
 // LDS (bf16 activations; bf16 weights, or 8-bit E4M3 weights with fp32 row scales; same
 // operation, groups and work items as stream_gemm.hip).
 //
