@@ -1,6 +1,7 @@
 // Skinny grouped GEMM for the decode regime of large layers and for prefill of few rows per expert (bf16 activations; bf16,
-// 8-bit or MXFP4 weights): the operation and, per element, the order of additions of stream_lds.hip, so that either
-// kernel gives the same bits, and any split of a step into smaller ones.
+// 8-bit or MXFP4 weights): the operation and, per element, the order of additions of the kernel that it stands in for, so that
+// either gives the same bits, and a step has the same ones whether it is issued whole or in parts: fewer than 256 tokens
+// those of stream_lds.hip, from there on (MANY) those of ffn_tiled.hip and ffn_wide.hip.
 //
 //   kGateUp  h = silu(W_gate x) * (W_up x)     (execution stage of Sec. II-A, SwiGLU)
 //   kDown    y = W_down h
@@ -32,6 +33,8 @@
 //   * Groups of more token rows are several blocks of even length, whose panels over the same weights are eight places
 //     apart, i.e. on one XCD at one time.
 //   * The two sums per output (even and odd groups of four 16-byte columns) are those of the two k parts in stream_lds.hip.
+//     The one sum of MANY is that of the tiled kernels: a product of 32 k adds up as two of theirs of 16 k do, and tile_order()
+//     gives it the k of those two.
 //
 // us, gate/up + down, stream_lds / here.  60 experts of 1408 + 5632: bf16, 1 token 25 + 15 / 20 + 15, 64 tokens 124 + 67 / 120 + 63,
 // 255 tokens 171 + 98 / 153 + 83; 8-bit, 16 tokens 40 + 25 / 36 + 24, 64 tokens 71 + 44 / 69 + 42, 255 tokens 107 + 67 / 94 + 55;
@@ -137,6 +140,26 @@ __device__ __forceinline__ void read_tokens(i32x4 (&b)[4][4], const unsigned (&a
                : MM_OUT4(b[0]), MM_OUT4(b[1]), MM_OUT4(b[2]), MM_OUT4(b[3]) : MM_IN4(ab) : "memory");
 }
 
+// Brings the codes of four 16-byte columns of a weight row, one in the lanes of each q, into the order in which the tiled
+// kernel takes their k: q and q + 2 exchange halves of their columns.
+//   8-bit (64 k = 8 groups of 8): products of the groups 0, 2, 1, 3 and 4, 6, 5, 7 (from the lanes of q = 0, 1, 2, 3)
+//   MXFP4 (128 k = 16 groups):    of 0, 4, 1, 5, of 2, 6, 3, 7, of 8, 12, 9, 13 and of 10, 14, 11, 15
+template <int WB>
+__device__ __forceinline__ void tile_order(i32x4& w) {
+  constexpr int far = WB == 1 ? 2 : 1;
+  const auto a = __builtin_amdgcn_permlane32_swap((unsigned)w[0], (unsigned)w[far], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap((unsigned)w[3 - far], (unsigned)w[3], false, false);
+  w = i32x4{(int)a[0], (int)b[0], (int)a[1], (int)b[1]};
+}
+
+// Column c of a token row sits at c ^ token_key(row & 15).  A read is free of bank conflicts while the lanes of neighbouring q
+// take columns whose numbers differ in a bit that the keys of rows 0 .. 3, 12 .. 15 and of rows 4 .. 11 do not differ in alone: 4 columns
+// apart (MXFP4 in the tiles' order) want the bits 1 and 2 of the row exchanged.
+template <int WB, bool MANY>
+__device__ __forceinline__ int token_key(int row) {
+  return WB == 0 && MANY ? (row & 9) | (row & 2) << 1 | (row & 4) >> 1 : row;
+}
+
 template <int WB> __device__ __forceinline__ int token_blocks(int m) { return (m + Unit<WB>::kBlock - 1) / Unit<WB>::kBlock; }
 
 template <int WB>
@@ -212,8 +235,9 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     a_rd[j] = ring + (unsigned)(c16 * 256 + (((4 * j + q) ^ c16) << 4));
-    const int low = WB == 2 ? 4 * j + q : (WB == 1 ? 8 * (j >> 1) + 2 * q + (j & 1) : 4 * q + j);
-    b_rd[j] = tok + (unsigned)((c16 << U::kRowShift) + ((low ^ c16) << 4));
+    int low = WB == 2 ? 4 * j + q : (WB == 1 ? 8 * (j >> 1) + 2 * q + (j & 1) : 4 * q + j);
+    if (MANY && WB != 2) low = 8 * (j >> 1) + (WB == 1 ? 4 : 2) * (j & 1) + (WB == 1 ? 2 : 4) * (q & 1) + (q >> 1);   // tile_order()
+    b_rd[j] = tok + (unsigned)((c16 << U::kRowShift) + ((low ^ token_key<WB, MANY>(c16)) << 4));
   }
 
   constexpr int kLook = MANY ? kPanelsMany : 64;
@@ -402,7 +426,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
         for (int i = wave; i < n; i += kWaves, r += kWaves) {
           while (r >= t_loads) { r -= t_loads; ++u; }
           constexpr int cols = 16 * U::kParts;
-          const int row = U::kRowsPerLoad * r + lane / cols, kk = u * U::kK + (((lane % cols) ^ (row & 15)) << 3);
+          const int row = U::kRowsPerLoad * r + lane / cols, kk = u * U::kK + (((lane % cols) ^ token_key<WB, MANY>(row & 15)) << 3);
           int src = t_r0 + min(row, t_rows - 1);
           if (t_gather) src = MANY ? (int)lds_read_u16(s_index + (unsigned)(t_p * 64 + min(row, t_rows - 1)) * 2u) : (int)lds_read_u8(s_index + (unsigned)(t_row0 + src));
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_void*)(dst + i * 1024), 16,
@@ -432,11 +456,12 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
       wave_part(p, ip, wa, wn);
       const int nt = (p.rows + 15) >> 4, nu = (G.K + U::kK - 1) / U::kK, us = slice_units(p, nu);
       const unsigned unit_bytes = (unsigned)slice_rows(p) << U::kRowShift;
-      f32x4 acc[RT][U::kTiles][2];             // two sums per token tile: even and odd groups of four columns
+      constexpr int kSums = MANY ? 1 : 2;      // per token tile; two: even and odd groups of four columns
+      f32x4 acc[RT][U::kTiles][kSums];
 #pragma unroll
       for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int t = 0; t < U::kTiles; ++t) acc[r][t][0] = acc[r][t][1] = f32x4{0, 0, 0, 0};
+        for (int t = 0; t < U::kTiles; ++t) acc[r][t][0] = acc[r][t][kSums - 1] = f32x4{0, 0, 0, 0};
       const bool both = RT > 1 && wn > 4;
 #pragma unroll 1
       for (int u0 = 0; u0 < nu; u0 += us) {
@@ -459,6 +484,10 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
             const unsigned aw[4] = {a_rd[0] + so, a_rd[1] + so, a_rd[2] + so, a_rd[3] + so};
             if constexpr (WB == 0) read_weights(w[r], sc4[r], aw, ring + so + 4096u + (unsigned)c16 * 16u);
             else read_weights(w[r], aw);
+            if constexpr (MANY && WB != 2) {
+#pragma unroll
+              for (int j = 0; j < 4; ++j) tile_order<WB>(w[r][j]);
+            }
             issue();
             ++since;
           };
@@ -466,18 +495,22 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
           if constexpr (RT > 1) if (both) take_unit(1);
           // weights of the k-steps of a part of unit r
           auto widen = [&](int r, int part, bf16x8 (&f)[4]) {
-            const float sv = WB == 0 ? e8m0_to_f32(((unsigned)sc4[r][part] >> (8 * q)) & 0xffu) : 0.f;
+            float s0 = WB == 0 ? e8m0_to_f32(((unsigned)sc4[r][part] >> (8 * q)) & 0xffu) : 0.f, s1 = s0;
+            if (WB == 0 && MANY) {                       // behind tile_order(): of the blocks q & 1 and 2 + (q & 1)
+              const auto both_halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0), __float_as_uint(s0), false, false);
+              s0 = __uint_as_float(both_halves[0]); s1 = __uint_as_float(both_halves[1]);
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
               if constexpr (WB == 2) f[j] = __builtin_bit_cast(bf16x8, w[r][j]);
               else if constexpr (WB == 1) f[j] = widen_e4m3(w[r][2 * part + (j >> 1)][2 * (j & 1)], w[r][2 * part + (j >> 1)][2 * (j & 1) + 1]);
-              else f[j] = widen_mx4(w[r][part][j], sv);
+              else f[j] = widen_mx4(w[r][part][j], j < 2 ? s0 : s1);
             }
           };
           auto multiply = [&](int r, int t, int part, const bf16x8 (&f)[4], const i32x4 (&b)[4]) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              const int odd = WB == 2 ? j & 1 : (WB == 1 ? j >> 1 : part & 1);
+              const int odd = MANY ? 0 : (WB == 2 ? j & 1 : (WB == 1 ? j >> 1 : part & 1));
               acc[r][t][odd] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j], __builtin_bit_cast(bf16x8, b[j]), acc[r][t][odd], 0, 0, 0);
             }
           };
@@ -563,7 +596,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
             float val[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              val[v] = acc[r][t][0][v] + acc[r][t][1][v];
+              val[v] = MANY ? acc[r][t][0][v] : acc[r][t][0][v] + acc[r][t][kSums - 1][v];
               if (WB == 1) val[v] *= sc[v];
             }
             const size_t ro = (size_t)(p.r0 + row);

@@ -270,18 +270,11 @@ def test_streamed_with_gate_up_on_tiles(counts, H, I, shared):
     ([300, 2400], 128, 4224, (256,)),                              # blocks of one expert in several rounds; many panels in a workgroup
 ])
 def test_prefill_streamed_by_waves(counts, H, I, shared, dtype):
-    """Steps of 256 tokens and more, one and two tiles of rows per wave: an output's sum does not depend on the step, so the
-    bits of the kernel with loader waves on parts of at most 255 tokens; rows of the part not asked for stay as they are."""
+    """Steps of 256 tokens and more, one and two tiles of rows per wave: the bits of the tiled kernel, which the tests against
+    the oracle cover; rows of the part not asked for stay as they are."""
     cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
     b = _assigned_step(cfg, x, table, sh, of)
-    y_tok, outs = torch.empty(cfg.T, H, device="cuda"), []
-    for lo in range(0, cfg.T, 255):
-        hi = min(lo + 255, cfg.T)
-        part = _assigned_step(cfg.with_(T=hi - lo), x[lo:hi].contiguous(), table, sh, of[lo:hi])
-        y1, out1 = _run_on(STREAM, 1, part, x[lo:hi].contiguous(), table, sh)
-        y_tok[lo + part.sorted_token[:hi - lo].long()] = y1
-        outs.append(out1)
-    ref, ref_out = y_tok[b.sorted_token.long()], torch.cat(outs, 1) if shared else None
+    ref, ref_out = _run_on(TILED, 0, b, x, table, sh)
     assert torch.isfinite(ref).all()
     for variant in (4,) if dtype == "bf16" else (4, 5):
         y, out = _run_on(STREAM, variant, b, x, table, sh)
@@ -291,6 +284,26 @@ def test_prefill_streamed_by_waves(counts, H, I, shared, dtype):
         if shared:
             y, out = _run_on(STREAM, variant, b, x, table, sh, routed=False)
             assert torch.equal(out, ref_out) and bool((y == 7.0).all()), variant
+
+
+@pytest.mark.parametrize("counts,H,I,shared,dtype", [
+    ([32] * 8, 512, 512, (512,), "bf16w8"),                        # whole on panels, the shared expert alone on tiles
+    ([32] * 8, 512, 512, (512,), "bf16mx4"),
+    ([13] * 20 + [1, 0, 70, 40], 528, 272, (992, 48), "bf16w8"),
+])
+def test_parts_through_the_rules_have_the_bits_of_the_whole(counts, H, I, shared, dtype):
+    """A step issued in parts (shared experts on a stream of their own, an offloaded layer's waves) on whatever kernels the
+    rules pick for them."""
+    cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
+    b = _assigned_step(cfg, x, table, sh, of)
+
+    def run(routed, with_shared):
+        b.y.fill_(7.0)
+        b.shared_out.fill_(7.0)
+        mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, sh, routed, with_shared, b.y, b.shared_out, b.fws, b.fws_bytes)
+        return b.y.clone(), b.shared_out.clone()
+    y, out = run(True, True)
+    assert torch.isfinite(y).all() and torch.equal(run(True, False)[0], y) and torch.equal(run(False, True)[1], out)
 
 
 @pytest.mark.parametrize("counts,H,I", [
