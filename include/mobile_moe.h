@@ -124,7 +124,7 @@ int moe_profile_plain_read(const void* buf, size_t bytes, int32_t* sink, void* s
  * choice instead of the one that its rules pick from the sizes.
  *   kernel 0  weights streamed; variant 1 or 2: tiles of 16 tokens per wave (2: MOE_BF16 only), fewer than 256
  *             tokens unless MOE_FP32; 4 or 5: every wave streams rows of its own, tiles of 16 rows per wave one
- *             or two (5: not MOE_BF16), up to 65535 tokens, not MOE_FP32; 6 (MOE_BF16): 4 with gate/up on kernel 1
+ *             or two (5: not MOE_BF16), up to 65535 tokens, not MOE_FP32; 6 (MOE_BF16): 4 with gate/up on tiles
  *   kernel 1  tiles of 128 x 256, kernel 2 of 256 x 256 (MOE_BF16 only); 256 tokens and more, not
  *             MOE_FP32; variant 0: tiles in contiguous ranges, 1: by rows; 2, 3 (kernel 1, MOE_BF16): the same
  *             with the weights of panels of one token tile loaded past the caches

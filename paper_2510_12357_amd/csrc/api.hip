@@ -330,6 +330,7 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   a.two_tiles = r.two_tiles;
   a.wide_panels = r.wide_panels;
   a.weights_once = r.weights_once || r.tiled_gate_up;
+  a.two_sums = r.tiled_gate_up && cfg->T < kTiledMinT;
   auto launch = [&](StreamMode mode) {
     if (r.panels && !(r.tiled_gate_up && mode == kGateUp)) return launch_stream_panels(mode, wfmt, a, s);
     if (r.kernel == kFfnWide) return launch_wide(mode, a, s);

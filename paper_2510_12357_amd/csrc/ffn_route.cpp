@@ -230,14 +230,12 @@ bool weights_once(const moe_config& c) {
   return c.dtype == MOE_BF16 && lines && layer_bytes(c) >= kMediumLayer;
 }
 
-// Gate/up of a step that streams in panels on the 128 x 256 tiles, whose blocks of 128 token rows pass half as often over the
+// Gate/up of a step that streams in panels on the tiled kernel, whose blocks of 128 token rows pass half as often over the
 // weights of the shared experts: where the panels, 64 columns wide at most, need more than two rounds over the CUs for each round of
-// tiles, 128 columns wide.  (Routed experts counted with one block each.)  gate/up, us, panels / tiles, rounds in brackets: 60 of
-// 1408 + 5632, 65 .. 128 tokens (6 / 3) 118 / 117, 124 / 123, 160 tokens (7 / 3) 148 / 119, 255 tokens (7 / 3) 153 / 121; 64 of
-// 1408 + 2 shared, 128 tokens (6 / 3) 130 / 127, 160 tokens (7 / 3) 136 / 127, 255 tokens (7 / 3) 145 / 128; but 64 of 1024 (4 / 2) 93 / 99, 64 of 1536 + 3072, hidden 4096, 128 tokens (7 / 4) 271 / 287, 128 of 768
-// + 768, 255 tokens (7 / 4) 143 / 172, 24 of 2048 + 2048, 128 tokens (4 / 2) 73 / 77.  The down projection has half as many
-// columns as gate/up and more of K: 60 of 1408 + 5632, 160 tokens 76 / 79, 64 of 1408 + 2 shared, 255 tokens 79 / 84.
-// Up to 64 tokens the steps keep the bits of the one-launch kernel.
+// 128 columns.  (Routed experts counted with one block each.)  gate/up, us, panels / tiles, rounds in brackets: 60 of
+// 1408 + 5632, 128 tokens (6 / 3) 128 / 141, 160 tokens (7 / 3) 150 / 126, 255 tokens (7 / 3) 153 / 127; 64 of
+// 1408 + 2 shared, 160 tokens (7 / 3) 138 / 130, 255 tokens (7 / 3) 148 / 132; 64 of 1536 + 3072, hidden 4096, 128 tokens (7 / 4)
+// 270 / 288.  The down projection, with half as many columns as gate/up and more of K, stays in panels.
 bool tiled_gate_up(const moe_config& c, int cus) {
   if (c.dtype != MOE_BF16 || c.T <= kCuMinT || !weights_once(c)) return false;
   constexpr int kColumns = 64, kPanelRows = 64;

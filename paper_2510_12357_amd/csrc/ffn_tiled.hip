@@ -28,6 +28,11 @@
 //     the XCDs by panels (two orders, below); either way
 //     the token tiles that share a weight panel are adjacent in the list, so a panel is fetched
 //     from HBM once and re-read from that XCD's L2.
+//   * Steps of fewer than 256 tokens (a.two_sums: bf16 gate/up beside shared experts of more than 128 rows) keep the streaming
+//     kernels' bits, which have two sums per output, of the even and of the odd blocks of 32 k: two accumulators each, hence
+//     tiles of half as many weight rows (128 tokens x 128, four stages of 32 KB).  A product of 16 k adds up as half of one of
+//     32 k, so nothing else differs.  gate/up, us, panels / these tiles / one sum and 256 rows: 60 experts of 1408 + 5632, 160 tokens
+//     150 / 126 / 121, 255 tokens 153 / 127 / 122; 64 of 1408 + 2 shared, 255 tokens 148 / 132 / 125.  Three stages: 131, 136.
 //   * 8-bit weights (WB = 1: E4M3 codes with one fp32 scale per weight row): the weight rows of a
 //     tile are 64 bytes in LDS (half the loads and half the LDS of a bf16 panel), 16 rows per load
 //     instruction, swizzled with the key (row >> 2) & 3 so that a 16-byte fragment read of 16 rows
@@ -66,12 +71,10 @@ typedef uint16_t S;
 #endif
 constexpr int BK = MOE_TILED_BK;   // K chunk, elements (32 or 64)
 constexpr int kRowB = BK * 2;      // bytes of a tile row in LDS
-constexpr int kStages = MOE_TILED_STAGES;
 constexpr int kCols = BK / 8;                  // 16-byte columns of a tile row
 constexpr int kRowsPerIns = 1024 / kRowB;      // tile rows that one load instruction fills
 constexpr int kKeyShift = BK == 64 ? 1 : 2;    // rows per 256 bytes of LDS = 1 << kKeyShift
 static_assert(BK == 32 || BK == 64, "K chunk of 32 or 64");
-static_assert(MOE_TILED_STAGES >= 3, "the pipeline needs at least three stages");
 // swizzle key of a tile row: rows that share 256 bytes of LDS get the same key, the next ones the next
 __device__ __forceinline__ constexpr int row_key(int row) { return (row >> kKeyShift) & (kCols - 1); }
 
@@ -122,10 +125,12 @@ __device__ __forceinline__ void frag_wait(bf16x8 (&f)[N]) {
 #define MOE_TILED_ATTR
 #endif
 
-// WM x WN waves; each wave TM x TN MFMA tiles of 32 x 32.
-template <int WM_, int WN_, int TM_, int TN_>
+// WM x WN waves; each wave TM x TN MFMA tiles of 32 x 32, SUMS accumulators per output (2: even and odd blocks of 32 k).
+template <int WM_, int WN_, int TM_, int TN_, int STAGES_ = MOE_TILED_STAGES, int SUMS_ = 1>
 struct Shape {
-  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, kStages = STAGES_, SUMS = SUMS_;
+  static_assert(kStages >= 3, "the pipeline needs at least three stages");
+  static_assert(SUMS == 1 || BK == 64, "a chunk is an even and an odd block of 32 k");
   static constexpr int kWaves = WM * WN;              // computing waves, and as many loader waves
   static constexpr int kThreads = 2 * kWaves * 64;
   static constexpr int BM = WM * TM * 32;            // tokens per tile
@@ -140,7 +145,8 @@ struct Shape {
 template <int MODE, typename SH, int WB>
 __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(const StreamArgs a) {
   typedef WFmt<WB> WF;
-  constexpr int BM = SH::BM, BNR = SH::BNR, TM = SH::TM, TN = SH::TN;
+  constexpr int BM = SH::BM, BNR = SH::BNR, TM = SH::TM, TN = SH::TN, kStages = SH::kStages, SUMS = SH::SUMS;
+  static_assert(SUMS == 1 || WB == 2, "two sums are those of the streaming kernels for bf16 weights");
   constexpr int kThreads = SH::kThreads, kInsA = SH::kInsA, kInsB = SH::template ins_b<WB>();
   constexpr int kStageBytes = SH::template stage_bytes<WB>();
   constexpr int kRowBW = WF::kRowB;                                // bytes of a weight tile row
@@ -346,13 +352,15 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
     }
 
     // ================= computing waves: fragment reads, MFMAs, barriers, epilogue =================
-    f32x16 acc[TM][TN];
+    f32x16 acc[SUMS][TM][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int u = 0; u < SUMS; ++u)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[u][i][j][v] = 0.f;
 
     // 32-token blocks of this wave that hold rows of the group: a group's last token tile is
     // mostly empty when the group is small against BM, and a block without rows is neither read
@@ -444,7 +452,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         const int st_nx = st + 1 == kStages ? 0 : st + 1;  // stage of chunk kt+1
 #pragma unroll
         for (int kk = 0; kk < kParts; ++kk) {
-          const int cur = kk & 1, nxt = (kk + 1) & 1;      // kParts is even: set 0 again holds k-step 0 of the next chunk
+          const int cur = kk & 1, nxt = (kk + 1) & 1, u = SUMS == 1 ? 0 : kk >> 1;   // kParts is even: set 0 again holds k-step 0 of the next chunk
           int st_rd = st, kk_rd = kk + 1;
           if (kk + 1 == kParts) {
             lds_barrier();                                 // barrier kt+1
@@ -457,7 +465,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
             for (int i = 0; i < NB; ++i)
 #pragma unroll
               for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
+                acc[u][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[u][i][j], 0, 0, 0);
             frag_wait(fa[nxt]); frag_wait(fb[nxt]);
           } else {
             // fr holds the codes of kPer k-steps.  In the last of them fr is free (everything widened)
@@ -468,7 +476,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
             if (kRead) read_b(st_rd, kk_rd / kPer, fr);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-              acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][j], acc[0][j], 0, 0, 0);
+              acc[u][0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][j], acc[u][0][j], 0, 0, 0);
             frag_wait(fa[nxt]);
             if (kRead) frag_wait(fr);
             if constexpr (WB == 0) {
@@ -479,7 +487,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
             for (int i = 1; i < NB; ++i)
 #pragma unroll
               for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
+                acc[u][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[u][i][j], 0, 0, 0);
           }
           __builtin_amdgcn_sched_barrier(0);               // keep the steps apart; free order inside a step
         }
@@ -518,6 +526,12 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         }
       }
     }
+    if constexpr (SUMS == 2) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[0][i][j] += acc[1][i][j];
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -529,8 +543,8 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
           for (int j = 0; j < TN / 2; ++j) {
             const int col = n0 + wn * (TN / 2) * 32 + j * 32 + (lane & 31);
             if (col < G.N) {
-              const float gte = WB == 1 ? acc[i][j][v] * wsc[j] : acc[i][j][v];
-              const float upv = WB == 1 ? acc[i][j + TN / 2][v] * wsc[j + TN / 2] : acc[i][j + TN / 2][v];
+              const float gte = WB == 1 ? acc[0][i][j][v] * wsc[j] : acc[0][i][j][v];
+              const float upv = WB == 1 ? acc[0][i][j + TN / 2][v] * wsc[j + TN / 2] : acc[0][i][j + TN / 2][v];
               const float hv = gte / (1.f + __expf(-gte)) * upv;
               const __bf16 o = (__bf16)hv;
               static_cast<S*>(G.out)[(size_t)r * G.N + col] = __builtin_bit_cast(uint16_t, o);
@@ -540,7 +554,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             const int col = n0 + wn * TN * 32 + j * 32 + (lane & 31);
-            if (col < G.N) static_cast<float*>(G.out)[(size_t)r * a.H + col] = WB == 1 ? acc[i][j][v] * wsc[j] : acc[i][j][v];
+            if (col < G.N) static_cast<float*>(G.out)[(size_t)r * a.H + col] = WB == 1 ? acc[0][i][j][v] * wsc[j] : acc[0][i][j][v];
           }
         }
       }
@@ -549,7 +563,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
 
 template <int MODE, typename SH, int WB>
 int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
-  constexpr size_t kLds = (size_t)kStages * SH::template stage_bytes<WB>();
+  constexpr size_t kLds = (size_t)SH::kStages * SH::template stage_bytes<WB>();
   static std::atomic<int> cached{0};
   int per_cu = cached.load(std::memory_order_relaxed);
   if (per_cu == 0) {
@@ -572,12 +586,14 @@ int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
 #define MOE_TILED_SHAPE 2, 2, 2, 4
 #endif
 typedef Shape<MOE_TILED_SHAPE> DefaultShape;
+typedef Shape<2, 2, 2, 2, 4, 2> TwoSumShape;
 static_assert(DefaultShape::BNR / 2 == kTiledPanel && DefaultShape::BM == kTiledRows, "tiles of the dispatch rules");
 
 }  // namespace
 
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (weight_format == 2) {
+    if (mode == kGateUp && a.two_sums) return launch_tiled_shape<kGateUp, TwoSumShape, 2>(a, s);
     if (mode == kGateUp) return launch_tiled_shape<kGateUp, DefaultShape, 2>(a, s);
     if (mode == kDown) return launch_tiled_shape<kDown, DefaultShape, 2>(a, s);
   }

@@ -258,8 +258,11 @@ def test_streamed_by_waves(counts, H, I, shared, dtype):
     ([129], 64, 40, (128, 72)),
 ])
 def test_streamed_with_gate_up_on_tiles(counts, H, I, shared):
-    """Gate/up on tiles of 128 token rows, the down projection streamed, fewer than 256 tokens.  Bar as for the wide tiles."""
-    _check_assigned(counts, H, I, shared, STREAM, (6,))
+    """Gate/up on tiles of 128 token rows, the down projection streamed, fewer than 256 tokens.  Bar as for the wide tiles, and
+    the bits of the streaming kernel."""
+    x, sh, table, b, y, out = _check_assigned(counts, H, I, shared, STREAM, (6,))
+    y1, out1 = _run_on(STREAM, 1, b, x, table, sh)
+    assert torch.equal(y, y1) and (out is None or torch.equal(out, out1))
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "bf16w8", "bf16mx4"])
@@ -290,6 +293,7 @@ def test_prefill_streamed_by_waves(counts, H, I, shared, dtype):
     ([32] * 8, 512, 512, (512,), "bf16w8"),                        # whole on panels, the shared expert alone on tiles
     ([32] * 8, 512, 512, (512,), "bf16mx4"),
     ([13] * 20 + [1, 0, 70, 40], 528, 272, (992, 48), "bf16w8"),
+    ([3] * 50 + [5] * 10, 2048, 1408, (5632,), "bf16"),            # whole with gate/up on tiles, in parts streamed
 ])
 def test_parts_through_the_rules_have_the_bits_of_the_whole(counts, H, I, shared, dtype):
     """A step issued in parts (shared experts on a stream of their own, an offloaded layer's waves) on whatever kernels the
