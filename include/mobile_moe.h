@@ -129,7 +129,7 @@ int moe_profile_plain_read(const void* buf, size_t bytes, int32_t* sink, void* s
  *             MOE_FP32; variant 0: tiles in contiguous ranges, 1: by rows; 2, 3 (kernel 1, MOE_BF16): the same
  *             with the weights of panels of one token tile loaded past the caches
  * Anything else is MOE_E_UNSUPPORTED.  moe_profile_expert_ffn_kernel returns the kernel (0, 1 or 2) that
- * moe_expert_ffn picks for such a call, or a negative code. */
+ * moe_expert_ffn picks for gate/up of such a call, or a negative code. */
 int moe_profile_expert_ffn_kernel(const moe_config* cfg, int run_routed, int run_shared);
 int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
                            const int32_t* expert_offsets, const int32_t* sorted_token,

@@ -329,13 +329,15 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, cus);
   a.two_tiles = r.two_tiles;
   a.wide_panels = r.wide_panels;
-  a.weights_once = r.weights_once || r.tiled_gate_up;
-  a.two_sums = r.tiled_gate_up && cfg->T < kTiledMinT;
+  a.weights_once = r.weights_once;
+  a.two_sums = r.gate_up == kFfnTiled && cfg->T < kTiledMinT;
   auto launch = [&](StreamMode mode) {
-    if (r.panels && !(r.tiled_gate_up && mode == kGateUp)) return launch_stream_panels(mode, wfmt, a, s);
-    if (r.kernel == kFfnWide) return launch_wide(mode, a, s);
-    if (r.kernel == kFfnTiled || r.tiled_gate_up) return launch_tiled(mode, wfmt, a, s);
-    return launch_stream(mode, cfg->dtype, a, s);
+    switch (mode == kGateUp ? r.gate_up : r.down) {
+      case kFfnPanels: return launch_stream_panels(mode, wfmt, a, s);
+      case kFfnWide: return launch_wide(mode, a, s);
+      case kFfnTiled: return launch_tiled(mode, wfmt, a, s);
+      default: return launch_stream(mode, cfg->dtype, a, s);
+    }
   };
   {
     ProfScope ps(kProfFfnGateUp, s);
@@ -361,7 +363,7 @@ extern "C" int moe_profile_expert_ffn_kernel(const moe_config* cfg, int run_rout
   const int rc = validate_config(cfg);
   if (rc) return rc;
   const FfnRoute r = ffn_route(*cfg, run_routed != 0, run_shared != 0, device_cu_count());
-  return r.panels ? kFfnStream : r.kernel;
+  return r.gate_up == kFfnPanels ? kFfnStream : r.gate_up;      // variants of the same kernel 0
 }
 
 extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int variant, const void* x,
@@ -379,13 +381,12 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
                                              variant >= 0 && variant < (kernel == kFfnTiled && bf16 ? 4 : 2);
   if (!ok) return fail(MOE_E_UNSUPPORTED, "moe_profile_expert_ffn: kernel %d, variant %d with T=%d, dtype %d", kernel, variant, cfg->T, cfg->dtype);
   FfnRoute r = {};
-  r.kernel = (FfnKernel)kernel;
-  r.panels = panels;
+  r.gate_up = r.down = panels ? kFfnPanels : (FfnKernel)kernel;
   r.wide_panels = panels && variant == 5;
-  r.tiled_gate_up = panels && variant == 6;
+  if (panels && variant == 6) r.gate_up = kFfnTiled;
   r.two_tiles = kernel == kFfnStream && variant == 2;
   r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
-  r.weights_once = kernel == kFfnTiled && variant >= 2;
+  r.weights_once = r.gate_up == kFfnTiled && variant >= 2;
   return expert_ffn(cfg, &r, x, expert_offsets, sorted_token, expert_w, shared_w, run_routed, run_shared, y, shared_out,
                     ws, ws_bytes, stream);
 }

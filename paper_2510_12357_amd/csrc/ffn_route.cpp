@@ -260,24 +260,23 @@ bool few_tiles_left(const moe_config& c, int cus) {
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   const bool whole = run_routed && run_shared;
   FfnRoute r = {};
-  if (c.dtype == MOE_FP32 || c.T < kTiledMinT) {
-    r.two_tiles = whole && two_tiles(c);
-    r.panels = c.T < kTiledMinT && stream_panels(c, run_routed, run_shared);
-    r.wide_panels = r.panels && wide_panels(c, run_shared, cus);
-    r.tiled_gate_up = r.panels && whole && tiled_gate_up(c, cus);
-    return r;
-  }
-  if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {
-    r.kernel = kFfnWide;
+  if (c.dtype == MOE_FP32) return r;
+  if (c.T < kTiledMinT) {
+    r.gate_up = r.down = stream_panels(c, run_routed, run_shared) ? kFfnPanels : kFfnStream;
+    if (r.gate_up == kFfnPanels && whole && tiled_gate_up(c, cus)) r.gate_up = kFfnTiled;
+  } else if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {
+    r.gate_up = r.down = kFfnWide;
     r.by_rows_gate_up = r.by_rows_down = whole && wide_by_rows(c);
   } else {
-    r.kernel = kFfnTiled;
-    r.weights_once = weights_once(c);
-    r.by_rows_down = tiled_by_rows(c, run_routed, run_shared, cus);
-    r.by_rows_gate_up = r.by_rows_down && !(whole && few_tiles_left(c, cus));
-    r.panels = prefill_panels(c, run_routed);
-    r.wide_panels = r.panels && wide_panels(c, run_shared, cus);
+    r.gate_up = r.down = prefill_panels(c, run_routed) ? kFfnPanels : kFfnTiled;
+    const bool by_rows = tiled_by_rows(c, run_routed, run_shared, cus);
+    r.by_rows_down = r.down == kFfnTiled && by_rows;
+    r.by_rows_gate_up = r.gate_up == kFfnTiled && by_rows && !(whole && few_tiles_left(c, cus));
   }
+  auto any = [&](FfnKernel k) { return r.gate_up == k || r.down == k; };
+  r.two_tiles = any(kFfnStream) && whole && two_tiles(c);
+  r.wide_panels = any(kFfnPanels) && wide_panels(c, run_shared, cus);
+  r.weights_once = any(kFfnTiled) && weights_once(c);
   return r;
 }
 

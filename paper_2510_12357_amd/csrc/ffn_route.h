@@ -16,15 +16,16 @@ constexpr int kTiledRows = 128;      // token rows of a tile of the 128 x 256 ke
 constexpr int kWideRows = 256;       // token rows of a tile of the wide kernel
 constexpr int kFewExperts = 16;      // up to here one of eight ranges of tiles lies in one or two experts
 
-enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2 };
+// stream_gemm.hip and stream_lds.hip; ffn_tiled.hip; ffn_wide.hip; stream_panels.hip
+enum FfnKernel { kFfnStream = 0, kFfnTiled = 1, kFfnWide = 2, kFfnPanels = 3 };
+// Which kernel a launch runs on does not show in its results: below kTiledMinT tokens all have two sums per output, from there on one.
 struct FfnRoute {
-  FfnKernel kernel;
-  bool panels;                       // stream_panels.hip instead of that (never where it is kFfnWide)
-  bool tiled_gate_up;                // with panels: the gate/up launch on 128 x 256 tiles, past the caches
+  FfnKernel gate_up, down;
+  // false where no launch runs on the kernel in question
   bool wide_panels;                  // StreamArgs::wide_panels (stream_panels.hip)
   bool two_tiles;                    // StreamArgs::two_tiles (stream_lds.hip)
-  bool weights_once;                 // StreamArgs::weights_once
-  bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches
+  bool weights_once;                 // StreamArgs::weights_once (ffn_tiled.hip)
+  bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches (ffn_tiled.hip, ffn_wide.hip)
 };
 
 // run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;

@@ -71,8 +71,10 @@ def test_kernel_choice_is_refused_where_the_kernel_does_not_apply():
                  (few, 0, 3), (many, 1, 4), (many, 2, 2), (many.with_(dtype="bf16w8"), 1, 2), (many, 2, -1), (many, 3, 0), (many, -1, 0)):
         assert code(*args) == -3, args
     assert code(many, 2, 0) == -1                                # the other checks are moe_expert_ffn's: x is NULL
-    for cfg, kernel in ((few, 0), (many, 1), (few.with_(T=4096), 2), (few.with_(T=4096, dtype="bf16w8"), 1), (many.with_(dtype="fp32"), 0)):
+    # gate/up of a whole step, of its routed part alone; panels count as kernel 0
+    for cfg, whole, routed in ((few.with_(T=128), 0, 0), (few, 1, 0), (many, 1, 1), (few.with_(T=4096), 2, 1), (many.with_(dtype="bf16w8"), 0, 0),
+                               (few.with_(T=4096, dtype="bf16w8"), 1, 1), (many.with_(dtype="fp32"), 0, 0)):
         c = mm.make_config(cfg)
-        assert lib.moe_profile_expert_ffn_kernel(ctypes.byref(c), 1, 1) == kernel
-        assert lib.moe_profile_expert_ffn_kernel(ctypes.byref(c), 1, 0) == min(kernel, 1)
+        assert lib.moe_profile_expert_ffn_kernel(ctypes.byref(c), 1, 1) == whole
+        assert lib.moe_profile_expert_ffn_kernel(ctypes.byref(c), 1, 0) == routed
     assert lib.moe_profile_expert_ffn_kernel(ctypes.byref(mm.make_config(few.with_(k_little=5))), 1, 1) == -2

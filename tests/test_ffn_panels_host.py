@@ -1,33 +1,18 @@
 """The rules that let a step of few token rows per expert stream its weights in panels (csrc/ffn_route.cpp) without a GPU."""
-import os
-import shutil
-import subprocess
-
 import pytest
 
 from paper_2510_12357_amd import workloads as wl
-from test_ffn_route_host import CSRC, DTYPES, ROOT, WIDE
+from test_ffn_route_host import PANELS, TILED, route  # noqa: F401
 
 
 @pytest.fixture(scope="module")
-def panels(tmp_path_factory):
-    cxx = shutil.which(os.environ.get("CXX", "g++"))
-    if cxx is None:
-        pytest.skip("no host C++ compiler")
-    out = str(tmp_path_factory.mktemp("panels") / "ffn_panels_check")
-    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
-                    os.path.join(ROOT, "tests", "host", "ffn_panels_check.cpp"), os.path.join(CSRC, "ffn_route.cpp"), "-o", out],
-                   check=True)
-
+def panels(route):  # noqa: F811
     def ask(cfg, routed=True, shared=True):
-        v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
-             int(routed), int(shared)]
-        r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True)
-        kernel, yes, wide, tiled = map(int, r.stdout.split())
-        assert not yes or kernel != WIDE
-        assert not wide or (yes and cfg.dtype in ("bf16w8", "bf16mx4"))
-        assert not tiled or (yes and cfg.dtype == "bf16" and 64 < cfg.T < 256 and routed and shared)
-        return yes + wide + 4 * tiled
+        gate_up, down, _, _, _, wide, _, _ = route.raw(cfg, routed, shared)
+        tiled = gate_up == TILED and down == PANELS
+        assert not tiled or (cfg.dtype == "bf16" and 64 < cfg.T < 256 and routed and shared)
+        assert not wide or cfg.dtype in ("bf16w8", "bf16mx4")
+        return (down == PANELS) + wide + 4 * tiled
     return ask
 
 

@@ -13,7 +13,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2510_12357_amd", "csrc")
 CUS = 256
 DTYPES = {"bf16": 0, "fp32": 1, "bf16w8": 2, "bf16mx4": 3}
-STREAM, TILED, WIDE = 0, 1, 2
+STREAM, TILED, WIDE, PANELS = 0, 1, 2, 3
 ONE_LAUNCH, GEMV, GEMM = 0, 1, 2
 
 
@@ -37,12 +37,18 @@ def route(tmp_path_factory):
         return tuple(map(int, r.stdout.split()))
 
     def ask(cfg, routed=True, shared=True):
-        kernel, gate_up, down, two, _, once = run(cfg, routed, shared)
-        assert not two or kernel == STREAM
-        assert not once or kernel == TILED
-        return (STREAM, two) if kernel == STREAM else (kernel, down if gate_up == down else (gate_up, down))
-    ask.router = lambda cfg: run(cfg, True, True)[4]
-    ask.weights_once = lambda cfg, routed=True: run(cfg, routed, True)[5]
+        """Kernel of both launches with what it is told: token tiles two (STREAM), order of tiles (TILED, WIDE), row tiles
+        two (PANELS); (gate/up's, down's) where they differ."""
+        gate_up, down, rows_gate_up, rows_down, two, wide, once, _ = run(cfg, routed, shared)
+        assert (not two or STREAM in (gate_up, down)) and (not once or TILED in (gate_up, down)) and (not wide or PANELS in (gate_up, down))
+        told = {STREAM: (two, two), PANELS: (wide, wide)}
+        g, d = ((k, told.get(k, (rows_gate_up, rows_down))[i]) for i, k in enumerate((gate_up, down)))
+        if gate_up == down:
+            return gate_up, (g[1] if g[1] == d[1] else (g[1], d[1]))
+        return g, d
+    ask.raw = run
+    ask.router = lambda cfg: run(cfg, True, True)[7]
+    ask.weights_once = lambda cfg, routed=True: run(cfg, routed, True)[6]
     return ask
 
 
@@ -54,11 +60,13 @@ LAYERS = ["fine60_decode", "fine64_prefill", "shared2_offload", "coarse8"]
 def test_a_part_of_a_step_goes_by_what_it_runs(route, layer, T):
     """Fallback passes and waves (routed part alone) have rows that only the device knows: bf16 stays on
     the 128 x 256 tiles, and so do shared experts alone while there are fewer than 1.5 wide tiles per CU.
-    Their tiles are alike, so the contiguous order stays, but for 8-bit experts that are all there is."""
+    Their tiles are alike, so the contiguous order stays, but for 8-bit experts that are all there is.  Few rows
+    stream in panels."""
     cfg = wl.CONFIGS[layer].with_(T=T)
-    assert route(cfg, True, False) == (TILED, 0)
-    assert route(cfg.with_(dtype="bf16mx4"), True, False) == (TILED, 0)
-    assert route(cfg.with_(dtype="bf16w8"), True, False)[1] == int(layer == "fine64_prefill" and T < 2500)
+    few = T == 256 or (T == 700 and layer != "coarse8")
+    assert route(cfg, True, False) == (PANELS if layer == "coarse8" and T == 256 else TILED, 0)
+    assert route(cfg.with_(dtype="bf16mx4"), True, False) == (PANELS if few else TILED, 0)
+    assert route(cfg.with_(dtype="bf16w8"), True, False) == ((PANELS, 0) if few else (TILED, int(layer == "fine64_prefill" and T < 2500)))
     if cfg.shared_I:
         tiles = sum(-(-i // 128) for i in cfg.shared_I) * -(-T // 256)
         assert route(cfg, False, True) == (WIDE if tiles >= 1.5 * CUS else TILED, 0)
@@ -72,9 +80,9 @@ def test_whole_steps(route):
     assert route(c["fine60_decode"].with_(T=4096)) == (WIDE, 1) and route(c["fine60_decode"].with_(T=2000)) == (TILED, 0)
     assert route(c["shared2_offload"].with_(T=2500)) == (WIDE, 1) and route(c["shared2_offload"].with_(T=3300)) == (WIDE, 0)
     assert route(c["fine64_prefill"].with_(T=4096)) == (WIDE, 1) and route(c["fine64_prefill"].with_(T=3000)) == (TILED, 0)
-    assert route(c["fine64_prefill"].with_(T=777, dtype="bf16w8")) == (TILED, 1)
-    assert route(c["fine60_decode"].with_(T=600, dtype="bf16mx4")) == (TILED, 1)
-    assert route(c["fine60_decode"].with_(T=255)) == (STREAM, 1) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
+    assert route(c["fine64_prefill"].with_(T=777, dtype="bf16w8")) == (PANELS, 1) and route(c["fine64_prefill"].with_(T=900, dtype="bf16w8")) == (TILED, 1)
+    assert route(c["fine60_decode"].with_(T=600, dtype="bf16mx4")) == (PANELS, 1) and route(c["fine60_decode"].with_(T=780, dtype="bf16mx4")) == (TILED, 1)
+    assert route(c["fine60_decode"].with_(T=255)) == ((TILED, 0), (PANELS, 0)) and route(c["tiny_fp32"].with_(T=512)) == (STREAM, 0)
 
 
 def _layer(H, E, I, k, T, shared=(), dtype="bf16"):
@@ -87,7 +95,7 @@ def test_wide_tiles_in_large_layers_only(route):
     for H, E, I, k, shared in ((512, 8, 512, 2, ()), (512, 16, 256, 2, (512,)), (1024, 32, 512, 4, ()), (2048, 8, 2048, 2, (2048,)),
                                (2048, 16, 1408, 4, ()), (512, 64, 1024, 8, ()), (2048, 12, 4096, 2, ()), (2048, 24, 2048, 2, ()),
                                (520, 64, 264, 6, (1000,))):
-        assert all(route(_layer(H, E, I, k, T, shared))[0] == TILED for T in (256, 1200, 2500, 4096, 6000, 12000))
+        assert all(route(_layer(H, E, I, k, T, shared))[0] == TILED for T in (1200, 2500, 4096, 6000, 12000))
     assert [route(_layer(4096, 8, 4096, 2, T))[0] for T in (1500, 2200, 4096)] == [TILED, WIDE, WIDE]
     assert [route(_layer(2048, 8, 8192, 2, T))[0] for T in (1500, 4096)] == [TILED, WIDE]
     assert [route(_layer(6144, 8, 16384, 2, T))[0] for T in (1000, 1500)] == [TILED, WIDE]
@@ -101,7 +109,7 @@ def test_weights_go_past_the_caches_where_the_layer_cannot_stay_in_them(route):
     for H, E, I, k, shared, once in ((2048, 64, 1024, 8, (), 1), (2048, 60, 1408, 4, (5632,), 1), (4096, 16, 1024, 2, (), 1),
                                      (4096, 15, 1024, 2, (), 0), (2048, 32, 1024, 4, (2048,), 1), (2048, 16, 1408, 4, (), 0),
                                      (2048, 8, 2048, 2, (2048,), 0), (1024, 32, 512, 4, (), 0)):
-        for T in (256, 1000):
+        for T in (700, 1000):
             assert route.weights_once(_layer(H, E, I, k, T, shared)) == once
             assert route.weights_once(_layer(H, E, I, k, T, shared), routed=False) == once
         for dtype in ("bf16w8", "bf16mx4"):
@@ -113,42 +121,39 @@ def test_weights_go_past_the_caches_where_the_layer_cannot_stay_in_them(route):
 def test_narrow_weights_by_rows_where_tiles_differ(route):
     """Beside shared experts in layers of 403 MB (of bf16) and more; alone 8-bit experts in large layers."""
     for dtype in ("bf16w8", "bf16mx4"):
-        for H, E, I, k, shared in ((2048, 60, 1408, 4, (5632,)), (4096, 32, 2048, 4, (4096,)), (2048, 48, 1408, 4, (2816,))):
-            assert route(_layer(H, E, I, k, 256, shared, dtype)) == (TILED, 1)
+        for H, E, I, k, shared, T in ((2048, 60, 1408, 4, (5632,), 780), (4096, 32, 2048, 4, (4096,), 580), (2048, 48, 1408, 4, (2816,), 840)):
+            assert route(_layer(H, E, I, k, T, shared, dtype)) == (TILED, 1)
         for H, E, I, k, shared in ((512, 64, 256, 6, (1024,)), (512, 16, 256, 2, (512,)), (1024, 32, 512, 4, ()), (2048, 24, 2048, 2, ()),
                                    (4096, 16, 1024, 2, ()), (1024, 8, 1024, 2, ()), (640, 128, 512, 1, (768,)),
                                    (1408, 64, 640, 6, (2176,))):
-            assert all(route(_layer(H, E, I, k, T, shared, dtype)) == (TILED, 0) for T in (256, 400, 800))
-        for T in (256, 777, 2000):
+            on = [route(_layer(H, E, I, k, T, shared, dtype)) for T in (256, 400, 800, 1500, 2000)]
+            assert (TILED, 0) in on and all(r == (TILED, 0) or r[0] == PANELS for r in on)
+        for T in (900, 2000):
             assert route(_layer(2048, 64, 1024, 8, T, (), dtype)) == (TILED, int(dtype == "bf16w8"))
 
 
 def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):
-    """By rows every XCD has the same number of tiles: 770 of them on 256 CUs are three rounds and a
+    """By rows every XCD has the same number of tiles: 528 of them on 256 CUs are two rounds and a
     nearly empty one.  The down projection's tiles are others."""
-    for dtype in ("bf16w8", "bf16mx4"):
-        at = {T: route(wl.CONFIGS["shared2_offload"].with_(T=T, dtype=dtype)) for T in (256, 257, 384, 385, 600)}
-        assert at == {256: (TILED, 1), 257: (TILED, (0, 1)), 384: (TILED, (0, 1)), 385: (TILED, 1), 600: (TILED, 1)}
-        assert all(route(wl.CONFIGS["fine60_decode"].with_(T=T, dtype=dtype)) == (TILED, 1) for T in (256, 300, 500, 700))
+    at = {T: route(_layer(2048, 64, 1024, 6, T, (512,), "bf16w8")) for T in (470, 512, 513, 600)}
+    assert at == {470: (TILED, (0, 1)), 512: (TILED, (0, 1)), 513: (TILED, 1), 600: (TILED, 1)}
 
 
 def test_two_token_tiles_where_groups_are_large(route):
-    """Streaming kernel, bf16, whole steps: large layers of few experts from 65 tokens on, of many where their weights meet
-    16 rows on average; smaller layers where an expert has 36.  Parts of a step, small layers and the
-    narrower formats stay with one tile."""
-    few, many = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]
+    """Streaming kernel, bf16, whole steps of layers below 805 MB (above, such steps run in panels) where an expert has 36 rows.
+    Parts of a step, small layers and the narrower formats stay with one tile."""
+    few, many, medium = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"], _layer(2048, 16, 1408, 4, 1)
     for T in (1, 64, 65, 128, 146, 147, 255):
-        for routed, shared in ((True, False), (False, True)):
-            assert route(few.with_(T=T), routed, shared) == route(many.with_(T=T), routed, shared) == (STREAM, 0)
-        assert route(few.with_(T=T)) == (STREAM, int(T > 64))
-        assert route(many.with_(T=T)) == (STREAM, int(T > 146))
-        for dtype in ("bf16w8", "bf16mx4", "fp32"):
-            assert route(few.with_(T=T, dtype=dtype)) == (STREAM, 0)
+        assert route(few.with_(T=T), False, True) == route(many.with_(T=T), False, True) == (STREAM, 0)
+        assert route(medium.with_(T=T), True, False) == route(medium.with_(T=T), False, True) == (STREAM, 0)
+        assert route(few.with_(T=T)) == (PANELS if T > 64 else STREAM, 0)
+        assert route(few.with_(T=T, dtype="fp32")) == (STREAM, 0)
+        for dtype in ("bf16w8", "bf16mx4"):
+            assert route(medium.with_(T=T, dtype=dtype)) == (STREAM, 0)
     for H, E, I, k, shared, lines in ((1024, 8, 1024, 2, (), {187: 0, 188: 1}), (2048, 8, 2048, 2, (2048,), {170: 0, 188: 1}),
                                       (2048, 16, 1408, 4, (), {128: 0, 187: 1}), (4096, 16, 1024, 2, (), {255: 0}),
                                       (512, 8, 512, 2, (), {255: 0}), (512, 16, 256, 2, (512,), {255: 0}), (520, 64, 264, 6, (1000,), {255: 0}),
-                                      (2048, 256, 512, 8, (512,), {255: 0}), (1024, 128, 768, 8, (), {255: 0}),
-                                      (4096, 64, 1536, 6, (3072,), {130: 0, 170: 1})):
+                                      (1024, 128, 768, 8, (), {255: 0})):
         for T, two in lines.items():
             assert route(_layer(H, E, I, k, T, shared)) == (STREAM, two), (H, E, I, T)
 
