@@ -113,13 +113,9 @@ bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cu
 // than 32 rows, whose weights then pass once per 64; elsewhere they cost: the token rows of 33 .. 64 rows, whose
 // loads queue behind the weight stream, are fetched by one workgroup instead of two, and a small layer has half the
 // items for its CUs.  gate+up + down, us, one / two:
-//   * large layers of few experts, which the weight stream bounds: 8 of 14336, 65 tokens 453 / 456, 100 tokens 464 / 464
-//     (half of them with all ranks 553 / 511), 130 tokens 557 / 515, 200 tokens 789 / 597; 4 of 11008, 128 tokens
-//     311 / 250; 8 of 4096, hidden 4096, 80 tokens 153 / 154, 170 tokens 197 / 174.
-//   * large layers of many, whose shared and most wanted experts have such groups once the mean is half of one: 60 of 1408 +
-//     5632, 65 tokens (mean 7) 194 / 204, 120 tokens (13) 228 / 228, 200 tokens (22) 262 / 262, 255 tokens (28) 281 / 269; 64 of
-//     1408 + 2 shared, 120 tokens (12) 212 / 225, 230 tokens (23) 253 / 248; 64 of 1536 + 3072, 80 tokens (8) 413 / 436,
-//     170 tokens (17) 476 / 438; 256 of 512 + 512, 255 tokens (7) 288 / 310.
+//   * large layers of few experts, which the weight stream bounds (from 20 rows per expert on they run in panels): 8 of 14336, 65
+//     tokens 453 / 456, 100 tokens 464 / 464, half of them with all ranks 553 / 511.  Large layers of many run in panels wherever
+//     their groups have that many rows.
 //   * smaller ones (experts' rows): 8 of 1024, hidden 1024, 170 tokens (32) 26 / 27, 220 tokens (41) 32 / 30; 8 of 2048 + 2048,
 //     170 tokens (32) 82 / 85, 220 tokens (41) 100 / 88; 16 of 1408, 128 tokens (24) 69 / 70, 220 tokens (41) 98 / 82;
 //     16 of 1024, hidden 4096, 255 tokens (24) 87 / 89.  Below 32 MB never: 8 of 512, hidden 512, 170 tokens (32)
@@ -128,36 +124,77 @@ bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cu
 // 64 of 1024, 100 tokens 90 / 92; the shared expert of 5632 alone, 65 tokens 53 / 61, 200 tokens 93 / 97, 255 tokens 105 / 98.
 bool two_tiles(const moe_config& c) {
   if (c.dtype != MOE_BF16) return false;
-  const Work w = layer_work(c);
-  if (layer_bytes(c) >= kLargeLayer) return c.E <= kFewExperts ? c.T > 64 : w.rows >= 16 * w.weight_rows;
-  return layer_bytes(c) >= 32ll << 20 && w.expert_rows >= 36;
+  if (layer_bytes(c) >= kLargeLayer) return c.E <= kFewExperts && c.T > 64;
+  return layer_bytes(c) >= 32ll << 20 && layer_work(c).expert_rows >= 36;
 }
 
 // The streaming kernel whose waves stream rows of their own (stream_panels.hip) instead of the one with loader waves
-// (stream_lds.hip): large layers.  Setting its panels up takes a microsecond longer per launch, which a small layer
-// does not bring back, and its waves want a tile of rows each.  gate+up + down, us, stream_lds / stream_panels:
-//   * by size: bf16, 8 of 512, hidden 512, 33 tokens 17.4 / 20.4, 8 of 1024, hidden 1024, 130 tokens 29.5 / 31.9, 16 of 1024, hidden
-//     4096 (403 MB), 65 tokens 77 / 80, 20 of 4096 (1 GB), 65 tokens 178 / 167, 64 of 1024, 65 tokens 144 / 143, 255 tokens
-//     176 / 155; 8-bit, 64 of 256 + 1024, hidden 512, 130 tokens 31.5 / 35.2, 8 of 2048 + 2048 (226 MB), 65 tokens 47.8 / 50.7, 16 of 1024,
-//     hidden 4096, 1 token 1.11 times as fast, 255 tokens 1.26 times, MXFP4 1.21 and 1.38 times.
-//   * bf16, few experts: long groups stream as well through stream_lds.hip, whose loads are 512 bytes of a row, while
-//     they have few rows: 8 of 14336, 4 tokens 214 / 218, 64 tokens 448 / 453, 128 tokens 505 / 467, 255 tokens 657 / 488.
-//   * bf16, few rows of weights hit, counted for the down projection: 20 of 4096, 1 token (2 x 2048 rows) 28.6 / 33.0, 3
-//     tokens (6 x 2048) 62.8 / 59.0; 60 of 1408 + 5632, 1 token (8 x 2048) 41.1 / 38.7.  Fallback passes hit fewer still: 60 of
-//     1408, 3 tokens 27.9 / 30.1, 9 tokens 44.9 / 41.2.
-//   * many experts have to be looked through: 256 of 512 + 512, 1 token 31.2 / 33.4, 8-bit, 3 tokens 35.3 / 37.4, fallback
-//     27.5 / 32.2, 9 tokens 57.1 / 54.5, 33 tokens 121 / 108; 128 of 768, hidden 1024, 8-bit, 3 tokens, fallback 23.4 / 25.9.
-bool stream_panels(const moe_config& c, bool run_routed, bool run_shared) {
+// (stream_lds.hip), for each launch by itself.  Setting its panels up takes a microsecond longer, which a small layer does not
+// bring back; its waves want a tile of rows each, and a group of several token tiles passes its weights once where the other
+// kernel's items fetch them again.  Rates below: stream_lds' time / stream_panels', geometric mean of four or five selections;
+// layers as experts of I (+ shared), hidden 2048 unless named.
+//   * Size: bf16, 8 of 512, hidden 512, 33 tokens 0.85, 16 of 1024, hidden 4096 (403 MB), 65 tokens 0.96; 8-bit, 64 of 256 + 1024, hidden
+//     512, 130 tokens 0.89, 8 of 2048 + 2048 (226 MB), 65 tokens 0.94.
+//   * Narrow formats (gate/up, down): 60 of 1408 + 5632, 8-bit 1.03 .. 1.16, 1.02 .. 1.20, MXFP4 1.08 .. 1.24, 1.09 .. 1.18; 8 of 14336 0.99
+//     .. 1.8, 0.99 .. 1.8.  8-bit layers of up to 64 experts of up to 1024 with short rows lose while an expert has about half a
+//     token tile, some of them more than one: 64 of 1024, 64 tokens 0.96, 0.97, 96 tokens 0.95, 0.97, but 48 tokens 1.01, 1.00, 160 tokens 1.04,
+//     1.03; 32 of 1024 + 2048, 64 tokens 0.92, 0.96, 128 tokens 0.89, 0.95, 32 tokens 1.07, 1.09, 160 tokens 1.00, 1.05; hidden 4096, 16 of
+//     1024, 64 tokens 1.03, 1.06.
+//   * Many experts have to be looked through: 256 of 512 + 512, 8-bit, 3 tokens 0.95, fallback passes of 8 tokens 0.98, 0.86, 16 tokens
+//     0.95, 0.89, 32 tokens 1.05, 0.94, 64 tokens 1.07, 0.99; 128 of 768 + 768, 8 tokens 1.03, 0.94, 16 tokens 1.10, 0.98.
+bool narrow_panels(const moe_config& c, bool run_shared) {
+  if (layer_bytes(c) < kMediumLayer) return false;
+  if (c.E > kScanExperts) return c.T >= (run_shared ? 8 : c.E > 2 * kScanExperts ? 32 : 16);
+  const long long rows = layer_work(c).expert_rows;
+  return !(c.dtype == MOE_BF16_W8 && run_shared && c.E > kFewExperts && c.I <= 1024 && c.H <= 2048 && rows >= 5 && rows < 14);
+}
+//   * bf16, whole steps, gate/up.  60 of 1408 + 5632 1.03 .. 1.16; 64 of 1408 + 2 shared 1 .. 8 tokens 1.02 .. 1.16, above 1.00 .. 1.04; 48 of
+//     1408 + 2816 0.99 .. 1.21.  Without shared experts, or with rows of 4096, only while few experts are hit, or again where groups
+//     are of several token tiles: 64 of 1024, skewed, 1 token 0.96, 3 tokens 1.12, 8 tokens 1.05, 32 tokens 1.01, 64 tokens 0.96, 128 tokens
+//     1.08; 64 of 1408 alone, 3 tokens 1.11, 6 tokens 0.97, 16 .. 128 tokens 0.95 .. 0.99; 64 of 1536 + 3072, hidden 4096, 1 token 0.96, 8 tokens
+//     1.04, 24 tokens 0.97, 65 tokens 1.01, 128 tokens 1.04; 32 of 2048 + 4096, hidden 4096, 1 token 0.89, 24 tokens 0.97, 48 tokens 1.13, 128
+//     tokens 1.05; 24 of 4096, hidden 4096, 4 tokens 0.97, 64 tokens 0.95.  Long groups of short rows gain: 20 and 32 of 4096, 2 .. 128 tokens
+//     1.03 .. 1.24, 1 token 0.95.  Many experts lose until their shared ones weigh: 128 of 768 + 768, 16 .. 128 tokens 0.95 .. 0.99, 256 of 512 +
+//     512 0.94 .. 0.99, 160 of 1408 + 2 shared, 32 tokens 0.95, 128 tokens 0.99.
+//   * bf16, whole steps, down.  With few rows of weights hit (mean selection x hidden + shared) below 13000: 64 of 1024, 1 token (6 x 2048) 0.90;
+//     20 of 4096, 4 tokens (6 x 2048) 0.85, 6 tokens (9 x 2048) 1.01; 24 of 4096, hidden 4096, 1 token (3 x 4096) 0.88; 60 of 1408 + 5632, 1
+//     token (7 x 2048) 1.01; 64 of 1408, 1 token 0.91, 2 tokens (9 x 2048) 1.03.  Above: 60 of 1408 + 5632 1.02 .. 1.15; 64 of 1408 + 2 shared 1.00
+//     .. 1.13; 64 of 1024 0.97 .. 1.06; 24 of 4096, hidden 4096 1.12 .. 1.24; 256 of 512 + 512 1.06 .. 1.12.  32 of 2048 + 4096, hidden 4096, loses
+//     at 6 .. 48 tokens, 0.94 .. 0.97.
+//   * bf16, few experts: long groups stream as well through stream_lds.hip, whose loads are 512 bytes of a row, while they have few
+//     rows: 8 of 14336, gate/up, down, 65 tokens 0.98, 0.94, 96 tokens (18 rows) 1.01, 0.97, 128 tokens (24) 1.06, 1.02, 255 tokens 1.33,
+//     1.26; 8 of 8192 + 8192, 65 tokens 1.27, 1.14.
+//   * bf16, fallback passes (20 % of the tokens), whose rows the host does not know.  gate/up: 60 of 1408, 8 tokens 0.99, 12 .. 64 tokens 1.01
+//     .. 1.15, 128 tokens 0.97; 64 of 1024, 8 tokens 0.97, 12 .. 96 tokens 1.03 .. 1.14, 160 tokens 0.98; 64 of 1408, 12 tokens 1.15, 24 .. 96
+//     tokens 0.97 .. 1.02; 20 and 32 of 4096, 8 .. 255 tokens 1.00 .. 1.21; 128 of 768, 16 tokens 1.11, 64 tokens 1.00, 96 tokens 0.97; 256 of
+//     512 0.92 .. 0.99; 8 of 14336 0.97; 8 of 8192 0.95.  down: 60 of 1408, 16 tokens (k_big x tokens = 64) 0.97, 24 tokens 1.07; 20 of 4096, 24 tokens
+//     (48) 0.97, 48 tokens 1.05; 64 of 1024, 8 tokens (64) 0.93, 12 tokens 1.04; 256 of 512, 16 tokens (128) 0.95, 32 tokens 1.01; hidden 4096, 32 of
+//     2048 0.91 .. 0.96, 64 of 1536 0.97 .. 1.00; 8 of 14336 0.95 .. 0.98.
+bool bf16_panels(const moe_config& c, bool run_shared, bool gate_up) {
+  if (layer_bytes(c) < kLargeLayer) return false;
+  const bool many = c.E > kScanExperts, short_rows = c.H <= 2048, long_groups = c.I >= 2 * c.H;
+  const Work w = layer_work(c);
+  const long long sh = w.weight_rows - (long long)c.E * c.I;
+  if (!run_shared) {
+    if (c.E <= kFewExperts) return false;
+    if (!gate_up) return short_rows && c.T * c.k_big >= (many ? 130 : 65);
+    if (long_groups) return c.T >= 8;
+    return many ? c.T >= 16 && c.T <= 64 && c.I >= 768 : c.T >= 12 && c.T < 128;
+  }
+  if (c.E <= kFewExperts) return c.T > 64 && (sh > 0 || w.expert_rows >= 20);
+  if (many && c.T < 8) return false;
+  const long long pairs = (long long)c.T * (c.k_big + c.k_little) / 2;
+  if (!gate_up) return c.T > 64 || ((pairs < c.E ? pairs : c.E) + sh / c.I) * c.H >= 13000;
+  // token tiles of 16 rows that the weight rows meet, in sixteenths
+  const long long tiles = c.E * (long long)c.I * (w.expert_rows > 16 ? w.expert_rows : 16) + 16 * sh * ceil_div(c.T, 16);
+  if (100 * tiles >= 16 * w.weight_rows * (many ? 115 : 110)) return true;
+  if (many) return false;
+  if (c.T == 1) return sh > 0 && short_rows;
+  return (sh > 0 && short_rows) || long_groups || 4 * pairs <= 3 * c.E;
+}
+bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool gate_up) {
   if (!run_routed) return false;       // the shared experts alone: few rows per wave
-  const bool narrow = c.dtype == MOE_BF16_W8 || c.dtype == MOE_BF16_MXFP4;
-  if (c.dtype != MOE_BF16 && !narrow) return false;
-  if (layer_bytes(c) < (narrow ? kMediumLayer : kLargeLayer)) return false;
-  if (c.E > kScanExperts && c.T < (run_shared ? 8 : 16)) return false;
-  if (narrow) return true;
-  long long sh = 0;
-  for (int s = 0; s < c.n_shared; ++s) sh += c.shared_I[s];
-  const long long pairs = (long long)c.T * c.k_big, hit = (pairs < c.E ? pairs : c.E) + (run_shared ? sh / c.I : 0);
-  return c.E <= kFewExperts ? c.T > 64 : hit * c.H >= 16384 && (run_shared || c.T >= 8);
+  return c.dtype == MOE_BF16 ? bf16_panels(c, run_shared, gate_up) : narrow_panels(c, run_shared);
 }
 
 // The same kernel for prefill of few rows per expert, where the tiled kernels' blocks of 128 token rows are mostly
@@ -262,7 +299,8 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   FfnRoute r = {};
   if (c.dtype == MOE_FP32) return r;
   if (c.T < kTiledMinT) {
-    r.gate_up = r.down = stream_panels(c, run_routed, run_shared) ? kFfnPanels : kFfnStream;
+    auto kernel = [&](bool gate_up) { return stream_panels(c, run_routed, run_shared, gate_up) ? kFfnPanels : kFfnStream; };
+    r.gate_up = kernel(true); r.down = kernel(false);
     if (r.gate_up == kFfnPanels && whole && tiled_gate_up(c, cus)) r.gate_up = kFfnTiled;
   } else if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {
     r.gate_up = r.down = kFfnWide;

@@ -2,17 +2,16 @@
 import pytest
 
 from paper_2510_12357_amd import workloads as wl
-from test_ffn_route_host import PANELS, TILED, route  # noqa: F401
+from test_ffn_route_host import route  # noqa: F401
 
 
 @pytest.fixture(scope="module")
 def panels(route):  # noqa: F811
+    """Kernels of gate/up and the down projection: S, T, W or P; with a 2 where panels hold two tiles per wave."""
     def ask(cfg, routed=True, shared=True):
         gate_up, down, _, _, _, wide, _, _ = route.raw(cfg, routed, shared)
-        tiled = gate_up == TILED and down == PANELS
-        assert not tiled or (cfg.dtype == "bf16" and 64 < cfg.T < 256 and routed and shared)
         assert not wide or cfg.dtype in ("bf16w8", "bf16mx4")
-        return (down == PANELS) + wide + 4 * tiled
+        return "STWP"[gate_up] + "STWP"[down] + "2" * wide
     return ask
 
 
@@ -21,24 +20,58 @@ def _layer(H, E, I, k, T, shared=(), dtype="bf16"):
 
 
 def test_large_layers_stream_in_panels(panels):
-    """Large layers (narrow formats: medium ones too); bf16 with few experts from 65 tokens on and where enough rows are
-    hit, fallback passes from 8 tokens on; many experts from 8 (16) tokens on; never the shared experts alone."""
+    """Large layers, narrow formats medium ones too; never the shared experts alone, nor many experts that few tokens hit."""
     few, many = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]
-    for T in (1, 2, 64, 65, 255):
-        assert panels(many.with_(T=T)) == (1 if T < 129 else 5) and panels(few.with_(T=T)) == (T > 64)
-        assert panels(many.with_(T=T), True, False) == (T >= 8)
-        assert not panels(many.with_(T=T), False, True) and not panels(many.with_(T=T, dtype="fp32"))
+    for T in (1, 2, 64, 65, 128):
+        assert panels(many.with_(T=T)) == "PP" and panels(few.with_(T=T)) == ("PP" if T > 106 else "SS")
+        assert panels(many.with_(T=T), False, True) == panels(many.with_(T=T, dtype="fp32")) == "SS"
         for dtype in ("bf16w8", "bf16mx4"):
-            assert panels(few.with_(T=T, dtype=dtype)) and panels(many.with_(T=T, dtype=dtype), True, False)
-            assert panels(_layer(4096, 16, 1024, 2, T, (), dtype)) and not panels(_layer(2048, 8, 2048, 2, T, (2048,), dtype))
-        assert not panels(_layer(4096, 16, 1024, 2, T))
-        assert panels(_layer(2048, 256, 512, 8, T, (512,))) == (T >= 8)
-    assert not panels(many.with_(T=256)) and not panels(_layer(2048, 20, 4096, 2, 1)) and panels(_layer(2048, 20, 4096, 2, 4))
+            assert panels(few.with_(T=T, dtype=dtype))[:2] == panels(many.with_(T=T, dtype=dtype), True, False) == "PP"
+            assert panels(_layer(4096, 16, 1024, 2, T, (), dtype))[:2] == "PP" and panels(_layer(2048, 8, 2048, 2, T, (2048,), dtype)) == "SS"
+        assert panels(_layer(4096, 16, 1024, 2, T)) == "SS"
+    assert panels(_layer(4096, 8, 8192, 2, 65, (8192,))) == "PP"
+    for dtype in ("bf16w8", "bf16mx4"):
+        for E, line in ((128, 16), (256, 32)):
+            layer = _layer(2048, E, 1024, 8, 1, (), dtype)
+            assert [panels(layer.with_(T=T)) for T in (7, 8)] == ["SS", "PP"]
+            assert [panels(layer.with_(T=T), True, False) for T in (line - 1, line)] == ["SS", "PP"]
+    # 8-bit, short rows: experts of 5 .. 13 rows
+    for layer in (_layer(2048, 64, 1024, 8, 1, (), "bf16w8"), _layer(2048, 32, 1024, 4, 1, (2048,), "bf16w8")):
+        per = layer.E * 2 / 3 / layer.k_little                # tokens per row of an expert
+        for rows, kernels in ((4, "PP"), (4.6, "SS"), (12.9, "SS"), (14, "PP")):
+            assert panels(layer.with_(T=int(rows * per))) == kernels, rows
+            assert panels(layer.with_(T=int(rows * per)), True, False) == panels(layer.with_(T=int(rows * per), dtype="bf16mx4"))[:2] == "PP"
+
+
+def test_bf16_launches_choose_by_themselves(panels):
+    """gate/up leaves the panels where its groups are of one token tile and many of them are hit, the down projection while few are."""
+    fine64, wide_rows = _layer(2048, 64, 1024, 8, 1), _layer(4096, 64, 1536, 6, 1, (3072,))
+    for layer, expect in ((fine64, {1: "SS", 2: "PP", 8: "PP", 9: "SP", 128: "SP"}),
+                          (wide_rows, {1: "SP", 2: "PP", 10: "PP", 11: "SP", 64: "SP", 65: "PP", 128: "PP"}),
+                          (wl.CONFIGS["shared2_offload"], {1: "PS", 2: "PP", 128: "PP"}),
+                          (_layer(2048, 20, 4096, 2, 1), {1: "SS", 2: "PS", 4: "PS", 5: "PP", 128: "PP"}),
+                          (_layer(2048, 128, 768, 8, 1, (768,)), {7: "SS", 8: "SP", 128: "SP"}),
+                          (_layer(2048, 160, 1408, 8, 1, (1408, 1408)), {8: "SP", 208: "SP", 209: "PP"}),
+                          (_layer(2048, 24, 2048, 2, 64, (2048,)), {64: "SS"})):
+        for T, want in expect.items():
+            assert panels(layer.with_(T=T)) == want, (layer, T)
+    for layer, expect in ((wl.CONFIGS["fine60_decode"], {11: "SS", 12: "PS", 16: "PS", 17: "PP", 33: "PP", 127: "PP", 128: "SP", 255: "SP"}),
+                          (wide_rows, {11: "SS", 12: "PS", 127: "PS", 128: "SS"}),
+                          (_layer(2048, 20, 4096, 2, 1), {7: "SS", 8: "PS", 32: "PS", 33: "PP", 255: "PP"}),
+                          (_layer(2048, 128, 768, 8, 1, (768,)), {15: "SS", 16: "PS", 17: "PP", 64: "PP", 65: "SP"}),
+                          (_layer(2048, 256, 512, 8, 1, (512,)), {16: "SS", 17: "SP", 255: "SP"}),
+                          (wl.CONFIGS["coarse8"], {8: "SS", 255: "SS"})):
+        for T, want in expect.items():
+            assert panels(layer.with_(T=T), True, False) == want, (layer, T)
 
 
 def test_prefill_of_few_rows_streams_in_panels(panels):
-    """0: tiled; 1, 2: panels of one and two tiles per wave.  Narrow formats of any size while the weights meet few token rows
-    (fewer in smaller layers of many small experts), bf16 only with few experts; the same line for parts of a step."""
+    """0: tiled or, below 256 tokens, streamed; 1, 2: panels of one and two tiles per wave.  Narrow formats of any size while the
+    weights meet few token rows (fewer in smaller layers of many small experts), bf16 only with few experts; the same line for
+    parts of a step."""
+    def number(*args):
+        kernels = panels(*args)
+        return len(kernels) - 1 if kernels[:2] == "PP" else 0
     few, many, small = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"], _layer(512, 8, 512, 2, 256)
     many_small, smaller = _layer(2048, 64, 1024, 8, 256), _layer(1024, 64, 512, 8, 256)
     for cfg, dtype, expect in (
@@ -51,22 +84,22 @@ def test_prefill_of_few_rows_streams_in_panels(panels):
             (smaller, "bf16w8", ((383, 1), (384, 0), (600, 0))), (smaller, "bf16mx4", ((383, 2), (384, 0))),
             (few, "fp32", ((256, 0),)), (_layer(512, 4096, 4096, 1, 1), "bf16w8", ((65535, 1), (65536, 0)))):
         for T, want in expect:
-            assert panels(cfg.with_(T=T, dtype=dtype)) == want, (cfg, T)
-            assert not panels(cfg.with_(T=T, dtype=dtype), False, True)
+            assert number(cfg.with_(T=T, dtype=dtype)) == want, (cfg, T)
+            assert not number(cfg.with_(T=T, dtype=dtype), False, True)
             if T >= 256:
-                assert (panels(cfg.with_(T=T, dtype=dtype), True, False) > 0) == (want > 0)
+                assert (number(cfg.with_(T=T, dtype=dtype), True, False) > 0) == (want > 0)
     # a fallback pass: two tiles where they make one round over the CUs of two
-    assert panels(_layer(528, 64, 272, 6, 256, (992,), "bf16w8"), True, False) == 2
-    assert panels(_layer(512, 64, 256, 4, 256, (1024,), "bf16w8"), True, False) == 1
-    assert panels(few.with_(T=400, dtype="bf16mx4"), True, False) == 1
+    assert number(_layer(528, 64, 272, 6, 256, (992,), "bf16w8"), True, False) == 2
+    assert number(_layer(512, 64, 256, 4, 256, (1024,), "bf16w8"), True, False) == 1
+    assert number(few.with_(T=400, dtype="bf16mx4"), True, False) == 1
 
 
 def test_gate_up_on_tiles_where_the_panels_need_more_rounds(panels):
     """More than two rounds of panels over the CUs for one of tiles; rows that are whole cache lines only."""
-    for layer, expect in ((_layer(2048, 64, 1408, 6, 1, (1408, 1408)), {64: 1, 128: 1, 129: 5, 255: 5}),
-                          (_layer(2048, 64, 1408, 6, 1, (2816,)), {128: 1, 129: 5, 255: 5}),
-                          (_layer(2048, 64, 1400, 6, 1, (2800,)), {255: 1}),                  # rows that are no whole cache lines
-                          (_layer(2048, 64, 1024, 8, 1), {255: 1}), (_layer(4096, 64, 1536, 6, 1, (3072,)), {255: 1}),
-                          (_layer(2048, 128, 768, 8, 1, (768,)), {255: 1})):
+    for layer, expect in ((_layer(2048, 64, 1408, 6, 1, (1408, 1408)), {64: "PP", 128: "PP", 129: "TP", 255: "TP"}),
+                          (_layer(2048, 64, 1408, 6, 1, (2816,)), {128: "PP", 129: "TP", 255: "TP"}),
+                          (_layer(2048, 64, 1400, 6, 1, (2800,)), {255: "PP"}),                  # rows that are no whole cache lines
+                          (_layer(2048, 64, 1024, 8, 1), {255: "PP"}), (_layer(4096, 64, 1536, 6, 1, (3072,)), {255: "PP"}),
+                          (_layer(2048, 128, 768, 8, 1, (768,)), {255: "SP"})):
         for T, want in expect.items():
             assert panels(layer.with_(T=T)) == want, (layer, T)

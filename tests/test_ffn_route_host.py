@@ -140,13 +140,14 @@ def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):
 
 
 def test_two_token_tiles_where_groups_are_large(route):
-    """Streaming kernel, bf16, whole steps of layers below 805 MB (above, such steps run in panels) where an expert has 36 rows.
+    """Streaming kernel, bf16, whole steps where an expert has 36 rows; in layers of 805 MB and more, which run in panels from
+    20 rows on, above 64 tokens.
     Parts of a step, small layers and the narrower formats stay with one tile."""
     few, many, medium = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"], _layer(2048, 16, 1408, 4, 1)
     for T in (1, 64, 65, 128, 146, 147, 255):
         assert route(few.with_(T=T), False, True) == route(many.with_(T=T), False, True) == (STREAM, 0)
         assert route(medium.with_(T=T), True, False) == route(medium.with_(T=T), False, True) == (STREAM, 0)
-        assert route(few.with_(T=T)) == (PANELS if T > 64 else STREAM, 0)
+        assert route(few.with_(T=T)) == ((PANELS, 0) if T > 106 else (STREAM, int(T > 64)))
         assert route(few.with_(T=T, dtype="fp32")) == (STREAM, 0)
         for dtype in ("bf16w8", "bf16mx4"):
             assert route(medium.with_(T=T, dtype=dtype)) == (STREAM, 0)
