@@ -325,7 +325,7 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
   for (int i = 0; i < a.n_slabs; ++i) { a.slab_shared[i] = plan.slab_shared[i]; a.slab_chunk[i] = plan.slab_chunk[i]; }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
-  const int cus = cfg->T > kCuMinT ? device_cu_count() : 0;   // a runtime call, which small steps feel
+  const int cus = cfg->T >= kTiledMinT ? device_cu_count() : 0;   // a runtime call, which small steps feel
   const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, cus);
   a.two_tiles = r.two_tiles;
   a.wide_panels = r.wide_panels;

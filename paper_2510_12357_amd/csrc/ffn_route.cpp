@@ -190,7 +190,7 @@ bool bf16_panels(const moe_config& c, bool run_shared, bool gate_up) {
   if (100 * tiles >= 16 * w.weight_rows * (many ? 115 : 110)) return true;
   if (many) return false;
   if (c.T == 1) return sh > 0 && short_rows;
-  return (sh > 0 && short_rows) || long_groups || 4 * pairs <= 3 * c.E;
+  return (short_rows && (sh > 0 || w.expert_rows >= 12)) || long_groups || 4 * pairs <= 3 * c.E;
 }
 bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool gate_up) {
   if (!run_routed) return false;       // the shared experts alone: few rows per wave
@@ -267,18 +267,18 @@ bool weights_once(const moe_config& c) {
   return c.dtype == MOE_BF16 && lines && layer_bytes(c) >= kMediumLayer;
 }
 
-// Gate/up of a step that streams in panels on the tiled kernel, whose blocks of 128 token rows pass half as often over the
-// weights of the shared experts: where the panels, 64 columns wide at most, need more than two rounds over the CUs for each round of
-// 128 columns.  (Routed experts counted with one block each.)  gate/up, us, panels / tiles, rounds in brackets: 60 of
-// 1408 + 5632, 128 tokens (6 / 3) 128 / 141, 160 tokens (7 / 3) 150 / 126, 255 tokens (7 / 3) 153 / 127; 64 of
-// 1408 + 2 shared, 160 tokens (7 / 3) 138 / 130, 255 tokens (7 / 3) 148 / 132; 64 of 1536 + 3072, hidden 4096, 128 tokens (7 / 4)
-// 270 / 288.  The down projection, with half as many columns as gate/up and more of K, stays in panels.
-bool tiled_gate_up(const moe_config& c, int cus) {
-  if (c.dtype != MOE_BF16 || c.T <= kCuMinT || !weights_once(c)) return false;
-  constexpr int kColumns = 64, kPanelRows = 64;
-  long long panels = c.E * ceil_div(c.I, kColumns);
-  for (int s = 0; s < c.n_shared; ++s) panels += ceil_div(c.shared_I[s], kColumns) * ceil_div(c.T, kPanelRows);
-  return ceil_div(panels, cus) > 2 * ceil_div(gate_up_tiles(c, kTiledRows), cus);
+// Gate/up of a whole step of 129 .. 255 tokens on the tiled kernel, past the caches, whose blocks of 128 token rows pass half as
+// often over the weights of the large groups.  At 128 tokens and less the shared experts' blocks are as many as the panels', and
+// with many experts so is everything that counts.  stream_lds' time / panels' / tiles', geometric mean of five selections:
+// 60 of 1408 + 5632, 128 tokens 1.15 / 1.03, 129 tokens 1.02 / 1.18, 255 tokens 1.11 / 1.36; 64 of 1408 + 2 shared 1.04 / 1.00, 1.03 / 1.10, 1.08 /
+// 1.22; 48 of 1408 + 2816 1.03 / 0.97, 1.04 / 1.05, 1.20 / 1.23; 64 of 1408 alone 0.96 / 1.03 at all three; 64 of 1024 1.08 / 1.10, 1.08 / 1.10,
+// 1.19 / 1.29; 20 of 4096 1.08 / 1.14, 1.08 / 1.14, 1.10 / 1.20; 8 of 14336 1.06 / 1.13, 1.06 / 1.14, 1.33 / 1.42; 8 of 8192 + 8192 1.16 / 1.12, 1.22 /
+// 1.41, 1.43 / 1.90; hidden 4096, 64 of 1536 + 3072 1.04 / 0.97, 1.06 / 1.07, 1.10 / 1.17, 32 of 2048 + 4096 1.05 / 0.96, 1.11 / 1.14, 1.16 / 1.30, 24 of 4096
+// 0.97 / 1.02, 255 tokens 1.13 / 1.20.  Many: 160 of 1408 + 2 shared, 129 tokens 0.99 / 0.99, 255 tokens 1.03 / 1.03; 128 of 768 + 768 0.92 / 0.99,
+// 0.96 / 0.97; 256 of 512 + 512 0.96 / 0.93, 0.96 / 0.97.  The down projection has half as many columns and more of K: on the tiles
+// of 256 rows, which have one sum, it gained only in 8 of 8192 + 8192 and 32 of 2048 + 4096 (255 tokens 132 / 115 us).
+bool tiled_gate_up(const moe_config& c) {
+  return c.T > kTiledRows && c.E <= kScanExperts && layer_bytes(c) >= kLargeLayer && weights_once(c);
 }
 
 bool few_tiles_left(const moe_config& c, int cus) {
@@ -301,7 +301,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   if (c.T < kTiledMinT) {
     auto kernel = [&](bool gate_up) { return stream_panels(c, run_routed, run_shared, gate_up) ? kFfnPanels : kFfnStream; };
     r.gate_up = kernel(true); r.down = kernel(false);
-    if (r.gate_up == kFfnPanels && whole && tiled_gate_up(c, cus)) r.gate_up = kFfnTiled;
+    if (whole && tiled_gate_up(c)) r.gate_up = kFfnTiled;
   } else if (c.dtype == MOE_BF16 && (whole ? wide_whole(c, cus) : !run_routed && wide_shared(c, cus))) {
     r.gate_up = r.down = kFfnWide;
     r.by_rows_gate_up = r.by_rows_down = whole && wide_by_rows(c);

@@ -9,7 +9,6 @@ namespace mm {
 // Steps of this many tokens and more run the LDS-tiled kernels (bf16 activations) where the experts see
 // enough rows for MFMA tiles.  Below that the weights are streamed once through a skinny kernel.
 constexpr int kTiledMinT = 256;
-constexpr int kCuMinT = 64;          // up to here no rule asks for the device's compute units
 constexpr int kPanelsMaxT = 65535;   // tokens that stream_panels.hip can number
 constexpr int kTiledPanel = 128;     // gate/up output columns of a tile of either tiled kernel
 constexpr int kTiledRows = 128;      // token rows of a tile of the 128 x 256 kernel
@@ -29,7 +28,7 @@ struct FfnRoute {
 };
 
 // run_routed, run_shared: as moe_expert_ffn gets them, also where the layer has no shared experts;
-// cus: compute units of the device (only used above kCuMinT tokens).
+// cus: compute units of the device (only used from kTiledMinT tokens on).
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus);
 
 // Router logits of a step.  kRouterOneLaunch: logits and selection of a token in one workgroup; kRouterGemv:

@@ -46,7 +46,7 @@ def test_large_layers_stream_in_panels(panels):
 def test_bf16_launches_choose_by_themselves(panels):
     """gate/up leaves the panels where its groups are of one token tile and many of them are hit, the down projection while few are."""
     fine64, wide_rows = _layer(2048, 64, 1024, 8, 1), _layer(4096, 64, 1536, 6, 1, (3072,))
-    for layer, expect in ((fine64, {1: "SS", 2: "PP", 8: "PP", 9: "SP", 128: "SP"}),
+    for layer, expect in ((fine64, {1: "SS", 2: "PP", 8: "PP", 9: "SP", 117: "SP", 118: "PP", 128: "PP"}),
                           (wide_rows, {1: "SP", 2: "PP", 10: "PP", 11: "SP", 64: "SP", 65: "PP", 128: "PP"}),
                           (wl.CONFIGS["shared2_offload"], {1: "PS", 2: "PP", 128: "PP"}),
                           (_layer(2048, 20, 4096, 2, 1), {1: "SS", 2: "PS", 4: "PS", 5: "PP", 128: "PP"}),
@@ -94,12 +94,11 @@ def test_prefill_of_few_rows_streams_in_panels(panels):
     assert number(few.with_(T=400, dtype="bf16mx4"), True, False) == 1
 
 
-def test_gate_up_on_tiles_where_the_panels_need_more_rounds(panels):
-    """More than two rounds of panels over the CUs for one of tiles; rows that are whole cache lines only."""
-    for layer, expect in ((_layer(2048, 64, 1408, 6, 1, (1408, 1408)), {64: "PP", 128: "PP", 129: "TP", 255: "TP"}),
-                          (_layer(2048, 64, 1408, 6, 1, (2816,)), {128: "PP", 129: "TP", 255: "TP"}),
-                          (_layer(2048, 64, 1400, 6, 1, (2800,)), {255: "PP"}),                  # rows that are no whole cache lines
-                          (_layer(2048, 64, 1024, 8, 1), {255: "PP"}), (_layer(4096, 64, 1536, 6, 1, (3072,)), {255: "PP"}),
-                          (_layer(2048, 128, 768, 8, 1, (768,)), {255: "SP"})):
-        for T, want in expect.items():
-            assert panels(layer.with_(T=T)) == want, (layer, T)
+def test_gate_up_on_tiles_above_128_tokens(panels):
+    """Whole bf16 steps of large layers of up to 64 experts; rows that are whole cache lines only.  Parts stay streamed."""
+    for layer in (_layer(2048, 64, 1408, 6, 1, (1408, 1408)), _layer(2048, 64, 1408, 6, 1), _layer(2048, 64, 1024, 8, 1), _layer(4096, 8, 8192, 2, 1, (8192,)),
+                  _layer(4096, 64, 1536, 6, 1, (3072,)), wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]):
+        assert [panels(layer.with_(T=T))[0] == "T" for T in (65, 128, 129, 255)] == [False, False, True, True], layer
+        assert "T" not in panels(layer.with_(T=200), True, False) + panels(layer.with_(T=200), False, True)
+    for layer in (_layer(2048, 64, 1400, 6, 1, (2800,)), _layer(2048, 160, 1408, 8, 1, (1408, 1408)), _layer(2048, 24, 2048, 2, 1, (2048,))):
+        assert "T" not in panels(layer.with_(T=65)) + panels(layer.with_(T=255))

@@ -147,7 +147,7 @@ def test_two_token_tiles_where_groups_are_large(route):
     for T in (1, 64, 65, 128, 146, 147, 255):
         assert route(few.with_(T=T), False, True) == route(many.with_(T=T), False, True) == (STREAM, 0)
         assert route(medium.with_(T=T), True, False) == route(medium.with_(T=T), False, True) == (STREAM, 0)
-        assert route(few.with_(T=T)) == ((PANELS, 0) if T > 106 else (STREAM, int(T > 64)))
+        assert route(few.with_(T=T)) == (((TILED, 0), (PANELS, 0)) if T > 128 else (PANELS, 0) if T > 106 else (STREAM, int(T > 64)))
         assert route(few.with_(T=T, dtype="fp32")) == (STREAM, 0)
         for dtype in ("bf16w8", "bf16mx4"):
             assert route(medium.with_(T=T, dtype=dtype)) == (STREAM, 0)
