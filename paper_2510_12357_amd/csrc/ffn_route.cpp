@@ -29,6 +29,15 @@ long long gate_up_tiles(const moe_config& c, int rows) {
   return n;
 }
 
+// Down tiles of a step on the 128 x 256 kernel: 256 output columns of an expert or of a K chunk of a shared expert
+long long down_tiles(const moe_config& c) {
+  const long long across = ceil_div(c.H, 2 * kTiledPanel);
+  long long n = c.E * across * ceil_div(layer_work(c).expert_rows, kTiledRows);
+  const int chunk = c.I > 1024 ? c.I : 1024;
+  for (int s = 0; s < c.n_shared; ++s) n += across * ceil_div(c.shared_I[s], chunk) * ceil_div(c.T, kTiledRows);
+  return n;
+}
+
 // Whole bf16 steps whose weight rows meet this many token rows on average run on 256 x 256 tiles
 // (ffn_wide.hip), smaller ones on 128 x 256 (ffn_tiled.hip), whose two extra waves per SIMD hide the
 // loads of short tiles better.  Many experts are hit unevenly, so that half of them still have short
@@ -200,35 +209,54 @@ bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool g
 // The same kernel for prefill of few rows per expert, where the tiled kernels' blocks of 128 token rows are mostly
 // padding: narrow weights that meet fewer token rows on average than `most` (there is as little to set up in proportion
 // that layers of any size gain), bf16 weights of up to kFewExperts experts.  Above, a panel's passes of 64 token rows over its
-// weights are more and the tiled kernels' 128 are full.  gate+up + down, us, tiled / panels (wide panels where the next rule
-// wants them), token rows per weight row in brackets:
-//   * few experts, alike: 8 of 14336, 8-bit, 256 tokens (48) 424 / 325, 370 tokens (69) 438 / 415, 400 tokens (75) 442 / 447; MXFP4,
-//     256 tokens (48) 451 / 280, 400 tokens (75) 510 / 370, 680 tokens (127) 564 / 619; 16 of 1408, 600 tokens (56) 1.24 times as
-//     fast, 860 tokens (81) 0.97 times; 8 of 512, hidden 512, 256 tokens, 8-bit 43 / 23, MXFP4 31 / 21.
-//   * many: 60 of 1408 + 5632, 8-bit, 256 tokens (28) 183 / 149, 777 tokens (85) 242 / 231, 940 tokens (103) 268 / 262; MXFP4, 256
-//     tokens 172 / 114, 777 tokens 215 / 204, 940 tokens 225 / 225; 64 of 1408 + 2 shared, 8-bit, 777 tokens (77) 254 / 202, MXFP4,
-//     777 tokens 215 / 195, 940 tokens (93) 218 / 238; 20 of 4096, 8-bit, 860 tokens (64) 1.24 times, 1200 tokens (90) 0.88 times.
-//   * many of up to 1024, which the tiled kernels waste less on, and where one expert of more than 64 rows can make a round
-//     of the panels: 64 of 1024, skewed selection (mean of four), 8-bit, 300 tokens (28) 122 / 109, 380 tokens (36) 124 / 125, 520 tokens
-//     (49) 133 / 133, one of them 125 / 141, 600 tokens (56) 148 / 141, 720 tokens (68) 172 / 142, 820 tokens (77) 182 / 185; MXFP4, 256 tokens 113 / 80, 777 tokens 165 / 129, 940 tokens (88) 171 / 156; unskewed, 8-bit,
-//     420 tokens 1.34 times, 777 tokens 1.1 times, MXFP4, 420 tokens 1.02 times, 777 tokens 0.92 times, 860 tokens 0.92 times.
-//     Smaller layers of them: 32 of 1024, 8-bit, 640 tokens (60) 1.14 times, 700 tokens (66) 0.84 times, MXFP4, 420
-//     tokens (39) 0.91 times; 64 of 512, hidden 1024, 8-bit, 600 tokens (56) 0.98 times, MXFP4, 330 tokens (31) 1.19 times, 420
-//     tokens (39) 0.89 times.
-//   * bf16, 8 of 14336, 256 tokens (48) 548 / 488, 330 tokens (62) 563 / 503, 420 tokens (79) 578 / 707; 4 of 11008, 256 tokens
-//     (64) 336 / 309; 16 of 1024, hidden 4096, 600 tokens (56) 95 / 88, 860 tokens (81) 98 / 128; but 20 of 4096, 420 tokens (32)
-//     179 / 184, 60 of 1408 + 5632, 256 tokens (28) 204 / 238, 8 of 2048 + 2048 (226 MB), 256 tokens (71) 70 / 80.
-//   * fallback passes (20 % of the tokens) gain more: 60 of 1408, 256 tokens, 8-bit 1.46 times as fast, MXFP4 1.76 times.  The
-//     line is that of the whole step all the same, for a part may have all of its rows.
-bool prefill_panels(const moe_config& c, bool run_routed) {
+// weights are more and the tiled kernels' 128 are full.  Each launch by itself: the down projection, with half the columns and
+// thus fewer tiles for the CUs, gains longer than gate/up.  Rates: the tiled kernel's time / the panels' (two tiles per wave where
+// the next rule wants them), gate/up, down, geometric mean of four selections; token rows per weight row in brackets:
+//   * few experts, alike: 8 of 14336, 8-bit, 256 tokens (48) 1.19, 1.61, 340 tokens (64) 1.11, 1.35, 420 tokens (79) 0.90, 0.87; MXFP4, 256
+//     tokens 1.28, 1.68, 380 tokens (71) 1.12, 1.94, 500 tokens (94) 0.96, 1.39; 8 of 512, hidden 512, 256 tokens, 8-bit 1.67, 2.1, MXFP4
+//     1.34, 1.42.  Where the panels fill one round of the CUs, but not two, a second block of 64 rows is another round, which the faster
+//     MXFP4 tiles do not lose: 16 of 1408, 560 tokens (52) 1.12, 1.10, 620 tokens (58) 0.82, 1.10, 8-bit 1.12, 1.59, 740 tokens (69) 1.12, 1.39.
+//   * many: 60 of 1408 + 5632, 8-bit, 256 tokens (28) 1.05, 1.46, 740 tokens (81) 1.01, 1.09, 900 tokens (99) 0.99, 1.16; MXFP4 1.33, 1.59, 1.07,
+//     0.95, 1.01, 0.93; 64 of 1408 + 2 shared, 8-bit, 800 tokens (79) 1.24, 1.32, MXFP4 1.07, 0.98; 20 of 4096, 8-bit, 900 tokens (68) 1.24, 1.25,
+//     MXFP4 1.12, 0.97.
+//   * many of up to 1024, with a selection skewed as by gate biases of a standard deviation of 0 / 1 / 2: 64 of 1024, 8-bit, gate/up, 300
+//     tokens (28) 1.28 / 0.98 / 0.96, 380 tokens (36) 1.26 / 0.99 / 0.93, 460 tokens (43) 1.34 / 0.82 / 1.03, 620 tokens (58) 1.11 / 0.90 / 0.78, 680
+//     tokens (64) 1.05 / 0.98 / 0.80, 740 tokens (69) 0.98 / 1.11 / 0.86, down 1.0 .. 1.5 throughout; MXFP4, gate/up, 500 tokens (47) 0.96 / 1.08 / 1.10, 620
+//     tokens 0.82 / 0.92 / 1.12, 740 tokens 0.87 / 1.14 / 0.86, down 1.04 / 1.11 / 1.14, 0.90 / 0.99 / 1.12, 0.94 / 1.18 / 0.90.  What gate/up
+//     loses at 36 .. 61 rows (8-bit) and from 56 on (MXFP4) it loses by its rounds: 1024 panels are four of 256 CUs exactly, so that
+//     every expert with a second block makes a fifth.  Where the last round has room it gains as before: 8-bit, 96 of 768 (4.5
+//     rounds), 800 tokens (37) 1.38, 128 of 768 + 768 (6.5), 740 tokens (40) 1.34, 64 of 1024 + 1024, hidden 4096 (4.4), 340 tokens (37) 1.28,
+//     560 tokens (60) 1.17, MXFP4 1.24, 680 tokens (73) 1.10.
+//     Smaller layers of them: 32 of 1024, 8-bit, 340 tokens (32) 1.07, 1.19, 740 tokens (69) 0.78, 1.00; MXFP4, 380 tokens (36) 1.12, 1.06, 460 tokens
+//     (43) 0.91, 0.96; 64 of 512, hidden 1024, MXFP4, 380 tokens (36) 1.10, 1.06, 460 tokens (43) 0.87, 0.95.
+//   * bf16, where the tiles leave part of the CUs idle in their rounds: 8 of 14336, 256 .. 319 tokens (48 .. 60), gate/up (896 tiles, 3.5 rounds) 1.03, down
+//     (128 tiles) 1.38, 380 tokens (71) 0.97, 0.88; 16 of 1024, hidden 4096, 256 tokens, gate/up (128) 1.24, down (256) 1.02, 560 tokens (52)
+//     1.11, 0.95; 16 of 4096, hidden 4096, gate/up (512) 0.95, down (256) 0.94 .. 0.98; but 20 of 4096, 420 tokens (32) 0.97, 60 of 1408
+//     + 5632, 256 tokens (28) 0.86, 8 of 4096 + 4096, hidden 4096, 300 tokens 0.90, 0.84.
+//   * fallback passes (20 % of the tokens) gain more: 60 of 1408, 8-bit 1.31 .. 1.45, 1.33 .. 1.41, MXFP4 1.8 .. 2.0, 1.55 .. 1.60; 64 of 1024, 8-bit 1.22 .. 1.49,
+//     1.40 .. 1.62, MXFP4 1.30 .. 1.87, 1.31 .. 1.69; bf16, 8 of 14336 1.03, 1.27, 16 of 4096 1.00 .. 1.04, 1.04 .. 1.10.  The lines by rows are
+//     those of the whole step all the same, for a part may have all of its rows; second blocks are rare in it.
+bool prefill_panels(const moe_config& c, bool run_routed, bool run_shared, bool gate_up, int cus) {
   if (!run_routed || c.T > kPanelsMaxT) return false;
   const Work w = layer_work(c);
-  const bool w8 = c.dtype == MOE_BF16_W8;
-  if (c.dtype == MOE_BF16) return c.E <= kFewExperts && layer_bytes(c) >= kMediumLayer && w.rows < 60 * w.weight_rows;
+  const bool w8 = c.dtype == MOE_BF16_W8, few = c.E <= kFewExperts, large = layer_bytes(c) >= kLargeLayer;
+  auto fewer_rows = [&](int than) { return w.rows < than * w.weight_rows; };
+  if (c.dtype == MOE_BF16) {
+    if (!few || layer_bytes(c) < kMediumLayer || !fewer_rows(60)) return false;
+    const long long tiles = gate_up ? gate_up_tiles(c, kTiledRows) : down_tiles(c);
+    return !run_shared || 8 * tiles <= 7 * cus * ceil_div(tiles, cus);
+  }
   if (!w8 && c.dtype != MOE_BF16_MXFP4) return false;
-  const int most = c.E <= kFewExperts ? (w8 ? 70 : 76) : c.I > 1024 ? 84 : layer_bytes(c) >= kLargeLayer ? 76 : 36;
-  if (w8 && c.E > kFewExperts && c.I <= 1024 && w.rows >= 36 * w.weight_rows && w.rows < 54 * w.weight_rows) return false;
-  return w.rows < most * w.weight_rows;
+  const int most = few ? (w8 ? 70 : 76) : c.I > 1024 ? 84 : large ? 76 : 36;
+  if (!fewer_rows(most)) return false;
+  if (!gate_up || !run_shared) return true;
+  constexpr int kColumns = 64, kPanelRows = 64;      // of a panel of one tile per wave
+  long long panels = c.E * ceil_div(c.I, kColumns);
+  for (int s = 0; s < c.n_shared; ++s) panels += ceil_div(c.shared_I[s], kColumns) * ceil_div(c.T, kPanelRows);
+  if (few) return w8 || large || fewer_rows(56) || 2 * panels <= cus;
+  const bool full_rounds = 16 * (cus * ceil_div(panels, cus) - panels) < panels;
+  if (c.I > 1024 || !full_rounds) return true;
+  return w8 ? fewer_rows(36) || !fewer_rows(62) : fewer_rows(56);
 }
 
 // Two tiles of weight rows per wave, which share the token rows' fragments, instead of one.  A tile of narrow weights
@@ -306,7 +334,8 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
     r.gate_up = r.down = kFfnWide;
     r.by_rows_gate_up = r.by_rows_down = whole && wide_by_rows(c);
   } else {
-    r.gate_up = r.down = prefill_panels(c, run_routed) ? kFfnPanels : kFfnTiled;
+    auto kernel = [&](bool gate_up) { return prefill_panels(c, run_routed, run_shared, gate_up, cus) ? kFfnPanels : kFfnTiled; };
+    r.gate_up = kernel(true); r.down = kernel(false);
     const bool by_rows = tiled_by_rows(c, run_routed, run_shared, cus);
     r.by_rows_down = r.down == kFfnTiled && by_rows;
     r.by_rows_gate_up = r.gate_up == kFfnTiled && by_rows && !(whole && few_tiles_left(c, cus));

@@ -66,32 +66,31 @@ def test_bf16_launches_choose_by_themselves(panels):
 
 
 def test_prefill_of_few_rows_streams_in_panels(panels):
-    """0: tiled or, below 256 tokens, streamed; 1, 2: panels of one and two tiles per wave.  Narrow formats of any size while the
-    weights meet few token rows (fewer in smaller layers of many small experts), bf16 only with few experts; the same line for
-    parts of a step."""
-    def number(*args):
-        kernels = panels(*args)
-        return len(kernels) - 1 if kernels[:2] == "PP" else 0
+    """Narrow formats of any size while the weights meet few token rows (fewer in smaller layers of many small experts), bf16
+    only with few experts and where the tiles leave CUs idle."""
     few, many, small = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"], _layer(512, 8, 512, 2, 256)
     many_small, smaller = _layer(2048, 64, 1024, 8, 256), _layer(1024, 64, 512, 8, 256)
     for cfg, dtype, expect in (
-            (few, "bf16", ((256, 1), (319, 1), (320, 0), (4096, 0))), (many, "bf16", ((256, 0), (600, 0))),
-            (small, "bf16", ((256, 0),)), (small.with_(T=256, H=65536), "bf16", ((256, 1),)),
-            (few, "bf16w8", ((277, 1), (278, 2), (373, 2), (374, 0))), (many, "bf16w8", ((256, 1), (475, 1), (476, 2), (767, 2), (768, 0))),
-            (few, "bf16mx4", ((144, 2), (143, 1), (405, 2), (406, 0))), (many, "bf16mx4", ((246, 1), (247, 2), (767, 2), (768, 0))),
-            (small, "bf16w8", ((255, 0), (256, 1), (512, 0))), (small, "bf16mx4", ((255, 0), (256, 2), (512, 0))),
-            (many_small, "bf16w8", ((383, 1), (384, 0), (575, 0), (576, 2), (810, 2), (811, 0))), (many_small, "bf16mx4", ((287, 1), (288, 2), (811, 0))),
-            (smaller, "bf16w8", ((383, 1), (384, 0), (600, 0))), (smaller, "bf16mx4", ((383, 2), (384, 0))),
-            (few, "fp32", ((256, 0),)), (_layer(512, 4096, 4096, 1, 1), "bf16w8", ((65535, 1), (65536, 0)))):
-        for T, want in expect:
-            assert number(cfg.with_(T=T, dtype=dtype)) == want, (cfg, T)
-            assert not number(cfg.with_(T=T, dtype=dtype), False, True)
-            if T >= 256:
-                assert (number(cfg.with_(T=T, dtype=dtype), True, False) > 0) == (want > 0)
+            (few, "bf16", {256: "PP", 319: "PP", 320: "TT", 4096: "WW"}), (many, "bf16", {256: "TT", 600: "TT"}), (small, "bf16", {256: "TT"}),
+            (_layer(4096, 16, 1024, 2, 1), "bf16", {256: "PT", 639: "PT", 640: "TT"}), (_layer(4096, 16, 4096, 2, 1), "bf16", {256: "TT"}),
+            (few, "bf16w8", {277: "PP", 278: "PP2", 373: "PP2", 374: "TT"}), (many, "bf16w8", {256: "PP", 475: "PP", 476: "PP2", 767: "PP2", 768: "TT"}),
+            (few, "bf16mx4", {144: "PP2", 143: "PP", 405: "PP2", 406: "TT"}), (many, "bf16mx4", {246: "PP", 247: "PP2", 767: "PP2", 768: "TT"}),
+            (small, "bf16w8", {255: "SS", 256: "PP", 512: "TT"}), (small, "bf16mx4", {255: "SS", 256: "PP2", 405: "PP2", 512: "TT"}),
+            (_layer(2048, 16, 1408, 2, 1), "bf16mx4", {597: "PP2", 598: "TP2", 810: "TP2", 811: "TT"}), (_layer(2048, 16, 1408, 2, 1), "bf16w8", {740: "PP2", 747: "TT"}),
+            (many_small, "bf16w8", {383: "PP", 384: "TP", 660: "TP2", 662: "PP2", 810: "PP2", 811: "TT"}),
+            (many_small, "bf16mx4", {287: "PP", 288: "PP2", 597: "PP2", 598: "TP2", 810: "TP2", 811: "TT"}),
+            (_layer(4096, 64, 1024, 8, 1, (1024,)), "bf16w8", {340: "PP", 560: "PP2"}), (_layer(4096, 64, 1024, 8, 1, (1024,)), "bf16mx4", {680: "PP2"}),
+            (smaller, "bf16w8", {383: "PP", 384: "TT", 600: "TT"}), (smaller, "bf16mx4", {383: "PP2", 384: "TT"}),
+            (few, "fp32", {256: "SS"}), (_layer(512, 4096, 4096, 1, 1), "bf16w8", {65535: "PP", 65536: "TT"})):
+        for T, want in expect.items():
+            assert panels(cfg.with_(T=T, dtype=dtype)) == want, (cfg, dtype, T)
+            assert "P" not in panels(cfg.with_(T=T, dtype=dtype), False, True)
+            if T >= 256 and dtype != "fp32":       # a part: both launches wherever the step's rows allow it
+                assert panels(cfg.with_(T=T, dtype=dtype), True, False)[:2] == ("PP" if "P" in want or (cfg.E, cfg.I, T) == (16, 4096, 256) else "TT")
     # a fallback pass: two tiles where they make one round over the CUs of two
-    assert number(_layer(528, 64, 272, 6, 256, (992,), "bf16w8"), True, False) == 2
-    assert number(_layer(512, 64, 256, 4, 256, (1024,), "bf16w8"), True, False) == 1
-    assert number(few.with_(T=400, dtype="bf16mx4"), True, False) == 1
+    assert panels(_layer(528, 64, 272, 6, 256, (992,), "bf16w8"), True, False) == "PP2"
+    assert panels(_layer(512, 64, 256, 4, 256, (1024,), "bf16w8"), True, False) == "PP"
+    assert panels(few.with_(T=400, dtype="bf16mx4"), True, False) == "PP"
 
 
 def test_gate_up_on_tiles_above_128_tokens(panels):
