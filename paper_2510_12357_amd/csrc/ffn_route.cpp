@@ -90,24 +90,17 @@ bool wide_by_rows(const moe_config& c) {
 
 // Order of the 128 x 256 tiles.  By rows pays for narrow weights in steps of few rows and few tiles per
 // workgroup where tiles differ: beside shared experts, whose groups are full, and where the selection is skewed.
-// gate+up + down, us, contiguous / by rows: 60 of 1408 + 5632 shared, 8-bit, 400 tokens 249 / 206, 1000 tokens 275 / 277, MXFP4,
-// 600 tokens 222 / 200; 64 of 1408 + 2 shared, 8-bit, 600 tokens 252 / 230, 900 tokens 257 / 263; 32 of 2048 +
-// 4096, 8-bit, 256 tokens 294 / 263, MXFP4 295 / 268; 48 of 1408 + 2816, 8-bit, 320 tokens 185 / 156, MXFP4 148 / 132.
-// 64 of 1024 without shared ones, 8-bit, skewed, 777 tokens 196 / 173, 2048 tokens 266 / 251, unskewed, 400 tokens 128 / 129,
-// 800 tokens 155 / 160, 2000 tokens 284 / 293.  Alike tiles of MXFP4, which are the shortest, lose more: 64 of 1024,
-// unskewed, 600 tokens 106 / 113, skewed 140 / 134, 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096, 800 tokens
-// 90 / 99.  So do small layers: 64 of 256 + 1024, hidden 512, 256 tokens, 8-bit 59 / 62, MXFP4 41 / 47, 32 of 512, hidden
-// 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122, 128 of 496 + 784, hidden 592, 828 tokens, 8-bit
-// 64 / 77, 64 of 640 + 2176, hidden 1408, 381 tokens, MXFP4 54 / 62.  With bf16 weights, twice the bytes per tile,
-// mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more
-// panels than three per CU the balance is there already (8 experts of 14336, 300 tokens 419 / 426).
-// Every XCD then has the same number of tiles, so that a handful too many for whole rounds costs each of
-// them a round, which the ranges, at different points anyway, absorb: gate/up of 64 of 1408 + 2 shared, contiguous / by rows, 256
-// tokens (748 tiles) 102 / 97, 280 .. 384 tokens (770) 107 / 119, 8-bit 116 / 123, 400 tokens (792) 128 / 119.
-// In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is:
-// fallback passes, 64 of 1024, 8-bit 300 tokens 98 / 98, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of
-// 14336 416 / 415, but 60 of 1408, 8-bit 134 / 138, MXFP4 128 / 133, 64 of 1024, MXFP4 98 / 104; the shared
-// experts alone, MXFP4, 300 tokens 65 / 68.
+// Contiguous order's rate of the order by rows', gate/up, down, geometric mean of four selections, at sizes that do not run in panels: 60 of
+// 1408 + 5632 shared, 8-bit, 770 tokens 0.90, 0.90, 810 tokens (88 rows) 0.93, 0.92, 1000 tokens 275 / 277 us, MXFP4 0.94, 0.96 and
+// 0.96, 0.98; 64 of 1408 + 2 shared, 8-bit, 870 tokens 0.98, 0.99, 900 tokens 257 / 263 us, MXFP4 0.97, 1.03; 32 of 1024 + 2048, 8-bit, 256 tokens 0.97, 0.98, 400 tokens 0.84,
+// 0.85, 580 tokens 0.91, 0.95, MXFP4 0.97, 1.02, 0.88, 0.91, 0.93, 0.95; 32 of 2048 + 4096, hidden 4096, 8-bit, 580 tokens 0.93, 0.92; 60 of 1024 + 1024, skewed, 8-bit, 700
+// tokens 0.91, 0.89.  Alone, 64 of 1024, 8-bit, skewed, 420 .. 1000 tokens (gate/up) 0.90 .. 0.93, 2000 tokens 0.95, 0.94, unskewed 1.02 .. 1.06.  Alike tiles
+// of MXFP4, which are the shortest, lose more, gate+up + down, us, contiguous / by rows: 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096,
+// 800 tokens 90 / 99.  So do small layers: 32 of 512, hidden 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122.
+// With bf16 weights, twice the bytes per tile, mixing the two kinds of tiles over the XCDs is worth more (60 experts,
+// 1000 tokens 286 / 312), and with more panels than three per CU the balance is there already.
+// In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is: fallback passes, 64 of 1024,
+// 8-bit, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of 14336 416 / 415.
 bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
   const bool alone = c.n_shared == 0;
@@ -309,11 +302,6 @@ bool tiled_gate_up(const moe_config& c) {
   return c.T > kTiledRows && c.E <= kScanExperts && layer_bytes(c) >= kLargeLayer && weights_once(c);
 }
 
-bool few_tiles_left(const moe_config& c, int cus) {
-  const long long left = gate_up_tiles(c, kTiledRows) % cus;
-  return left > 0 && left <= cus / 16;
-}
-
 }  // namespace
 
 // A call that runs the routed part alone is taken for a part of a step: a fallback pass (some ranks of the
@@ -338,7 +326,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
     r.gate_up = kernel(true); r.down = kernel(false);
     const bool by_rows = tiled_by_rows(c, run_routed, run_shared, cus);
     r.by_rows_down = r.down == kFfnTiled && by_rows;
-    r.by_rows_gate_up = r.gate_up == kFfnTiled && by_rows && !(whole && few_tiles_left(c, cus));
+    r.by_rows_gate_up = r.gate_up == kFfnTiled && by_rows;
   }
   auto any = [&](FfnKernel k) { return r.gate_up == k || r.down == k; };
   r.two_tiles = any(kFfnStream) && whole && two_tiles(c);

@@ -132,13 +132,6 @@ def test_narrow_weights_by_rows_where_tiles_differ(route):
             assert route(_layer(2048, 64, 1024, 8, T, (), dtype)) == (TILED, int(dtype == "bf16w8"))
 
 
-def test_gate_up_contiguous_where_a_few_tiles_are_left_over(route):
-    """By rows every XCD has the same number of tiles: 268 of them on 256 CUs are one round and a
-    nearly empty one.  The down projection's tiles are others."""
-    at = {T: route(_layer(2048, 32, 1024, 6, T, (512,), "bf16w8")) for T in (300, 512, 513, 560)}
-    assert at == {300: (TILED, (0, 1)), 512: (TILED, (0, 1)), 513: (TILED, 1), 560: (TILED, 1)}
-
-
 def test_two_token_tiles_where_groups_are_large(route):
     """Streaming kernel, bf16, whole steps where an expert has 36 rows; in layers of 805 MB and more, which run in panels from
     20 rows on, above 64 tokens.
