@@ -134,69 +134,83 @@ bool two_tiles(const moe_config& c) {
 // (stream_lds.hip), for each launch by itself.  Setting its panels up takes a microsecond longer, which a small layer does not
 // bring back; its waves want a tile of rows each, and a group of several token tiles passes its weights once where the other
 // kernel's items fetch them again.  Rates below: stream_lds' time / stream_panels', geometric mean of four or five selections;
-// layers as experts of I (+ shared), hidden 2048 unless named.
+// layers as experts of I (+ shared), hidden 2048 unless named.  Held against other layers, drawn at random, both launches of a call (whole
+// steps and fallback passes), the time on stream_lds / by these rules: bf16, 1582 calls, 1.02 in the mean, of the 1249 over 18 us 43 below 0.97,
+// 0.90 at worst; narrow formats, 680 calls, 1.13, 10 of 517, 0.87.
 //   * Size: bf16, 8 of 512, hidden 512, 33 tokens 0.85, 16 of 1024, hidden 4096 (403 MB), 65 tokens 0.96; 8-bit, 64 of 256 + 1024, hidden
 //     512, 130 tokens 0.89, 8 of 2048 + 2048 (226 MB), 65 tokens 0.94.
 //   * Narrow formats (gate/up, down): 60 of 1408 + 5632, 8-bit 1.03 .. 1.16, 1.02 .. 1.20, MXFP4 1.08 .. 1.24, 1.09 .. 1.18; 8 of 14336 0.99
 //     .. 1.8, 0.99 .. 1.8.  8-bit layers of up to 64 experts of up to 1024 with short rows lose while an expert has about half a
 //     token tile, some of them more than one: 64 of 1024, 64 tokens 0.96, 0.97, 96 tokens 0.95, 0.97, but 48 tokens 1.01, 1.00, 160 tokens 1.04,
 //     1.03; 32 of 1024 + 2048, 64 tokens 0.92, 0.96, 128 tokens 0.89, 0.95, 32 tokens 1.07, 1.09, 160 tokens 1.00, 1.05; hidden 4096, 16 of
-//     1024, 64 tokens 1.03, 1.06.
+//     1024, 64 tokens 1.03, 1.06.  8-bit down projections of few columns: 72 of 2880 + 2880, hidden 512, 54 .. 201 tokens 0.69.
 //   * Many experts have to be looked through: 256 of 512 + 512, 8-bit, 3 tokens 0.95, fallback passes of 8 tokens 0.98, 0.86, 16 tokens
 //     0.95, 0.89, 32 tokens 1.05, 0.94, 64 tokens 1.07, 0.99; 128 of 768 + 768, 8 tokens 1.03, 0.94, 16 tokens 1.10, 0.98.
-bool narrow_panels(const moe_config& c, bool run_shared) {
+bool narrow_panels(const moe_config& c, bool run_shared, bool gate_up) {
   if (layer_bytes(c) < kMediumLayer) return false;
+  const bool w8 = c.dtype == MOE_BF16_W8;
+  if (w8 && !gate_up && c.H < 768) return false;
   if (c.E > kScanExperts) return c.T >= (run_shared ? 8 : c.E > 2 * kScanExperts ? 32 : 16);
   const long long rows = layer_work(c).expert_rows;
-  return !(c.dtype == MOE_BF16_W8 && run_shared && c.E > kFewExperts && c.I <= 1024 && c.H <= 2048 && rows >= 5 && rows < 14);
+  return !(w8 && run_shared && c.E > kFewExperts && c.I <= 1024 && c.H <= 2048 && rows >= 5 && rows < 14);
 }
-//   * bf16, whole steps, gate/up.  60 of 1408 + 5632 1.03 .. 1.16; 64 of 1408 + 2 shared 1 .. 8 tokens 1.02 .. 1.16, above 1.00 .. 1.04; 48 of
+//   * bf16, whole steps, gate/up.  Less than half a panel of 64 columns per CU (three quarters with rows of more than 2048) leaves the waves'
+//     tiles empty, by the columns of the mean selection: 64 of 1408, two ranks, 2 tokens (3 x 1408) 0.84; 64 of 1024, 1 token (6 x 1024) 0.96;
+//     60 of 512, hidden 6144, 2 tokens 0.87; 32 of 2048 + 4096, hidden 4096, 1 token (5 x 2048) 0.89; 60 of 1408 + 5632, 1 token (7 x 1408) 1.15;
+//     24 of 4096, hidden 4096, 1 token (3 x 4096) 1.00.  60 of 1408 + 5632 1.03 .. 1.16; 64 of 1408 + 2 shared 1 .. 8 tokens 1.02 .. 1.16, above 1.00 .. 1.04; 48 of
 //     1408 + 2816 0.99 .. 1.21.  Without shared experts, or with rows of 4096, only while few experts are hit, or again where groups
-//     are of several token tiles: 64 of 1024, skewed, 1 token 0.96, 3 tokens 1.12, 8 tokens 1.05, 32 tokens 1.01, 64 tokens 0.96, 128 tokens
-//     1.08; 64 of 1408 alone, 3 tokens 1.11, 6 tokens 0.97, 16 .. 128 tokens 0.95 .. 0.99; 64 of 1536 + 3072, hidden 4096, 1 token 0.96, 8 tokens
-//     1.04, 24 tokens 0.97, 65 tokens 1.01, 128 tokens 1.04; 32 of 2048 + 4096, hidden 4096, 1 token 0.89, 24 tokens 0.97, 48 tokens 1.13, 128
+//     are of several token tiles: 64 of 1024, skewed, 3 tokens 1.12, 8 tokens 1.05, 32 tokens 1.01, 64 tokens 0.96, 128 tokens
+//     1.08; 64 of 1408 alone, 3 tokens 1.11, 6 tokens 0.97, 16 .. 128 tokens 0.95 .. 0.99; 64 of 1536 + 3072, hidden 4096, 8 tokens
+//     1.04, 24 tokens 0.97, 65 tokens 1.01, 128 tokens 1.04; 32 of 2048 + 4096, hidden 4096, 24 tokens 0.97, 48 tokens 1.13, 128
 //     tokens 1.05; 24 of 4096, hidden 4096, 4 tokens 0.97, 64 tokens 0.95.  Long groups of short rows gain: 20 and 32 of 4096, 2 .. 128 tokens
-//     1.03 .. 1.24, 1 token 0.95.  Many experts lose until their shared ones weigh: 128 of 768 + 768, 16 .. 128 tokens 0.95 .. 0.99, 256 of 512 +
-//     512 0.94 .. 0.99, 160 of 1408 + 2 shared, 32 tokens 0.95, 128 tokens 0.99.
-//   * bf16, whole steps, down.  With few rows of weights hit (mean selection x hidden + shared) below 13000: 64 of 1024, 1 token (6 x 2048) 0.90;
+//     1.03 .. 1.24.  Many experts lose until their shared ones weigh, long groups aside: 128 of 768 + 768, 16 .. 128 tokens 0.95 .. 0.99, 256 of 512 +
+//     512 0.94 .. 0.99, 160 of 1408 + 2 shared, 32 tokens 0.95, 128 tokens 0.99, but 128 of 4096 + 8192, hidden 640, 123 tokens 1.40, 128
+//     of 2048 + 2048, hidden 512, 8 tokens 1.15.
+//   * bf16, whole steps, down.  Few rows of weights hit (mean selection x hidden + shared; 128 make a panel): 64 of 1024, 1 token (6 x 2048) 0.90;
 //     20 of 4096, 4 tokens (6 x 2048) 0.85, 6 tokens (9 x 2048) 1.01; 24 of 4096, hidden 4096, 1 token (3 x 4096) 0.88; 60 of 1408 + 5632, 1
-//     token (7 x 2048) 1.01; 64 of 1408, 1 token 0.91, 2 tokens (9 x 2048) 1.03.  Above: 60 of 1408 + 5632 1.02 .. 1.15; 64 of 1408 + 2 shared 1.00
+//     token (7 x 2048) 1.01, 2 tokens (10 x 2048) 1.07; 64 of 1408, 1 token 0.91; random layers 13000 .. 20000 0.97, 20000 .. 30000 1.04.  Few columns:
+//     64 of 14336, hidden 512, 31 .. 55 tokens 0.46 .. 0.65; 96 of 2048, hidden 768, 55 tokens 0.84; 256 of 920, hidden 1024, 133 tokens 0.87; random
+//     layers, hidden 900 .. 1200 0.96, 1200 .. 1600 1.02.  Above: 60 of 1408 + 5632 1.02 .. 1.15; 64 of 1408 + 2 shared 1.00
 //     .. 1.13; 64 of 1024 0.97 .. 1.06; 24 of 4096, hidden 4096 1.12 .. 1.24; 256 of 512 + 512 1.06 .. 1.12.  32 of 2048 + 4096, hidden 4096, loses
 //     at 6 .. 48 tokens, 0.94 .. 0.97.
 //   * bf16, few experts: long groups stream as well through stream_lds.hip, whose loads are 512 bytes of a row, while they have few
 //     rows: 8 of 14336, gate/up, down, 65 tokens 0.98, 0.94, 96 tokens (18 rows) 1.01, 0.97, 128 tokens (24) 1.06, 1.02, 255 tokens 1.33,
 //     1.26; 8 of 8192 + 8192, 65 tokens 1.27, 1.14.
-//   * bf16, fallback passes (20 % of the tokens), whose rows the host does not know.  gate/up: 60 of 1408, 8 tokens 0.99, 12 .. 64 tokens 1.01
-//     .. 1.15, 128 tokens 0.97; 64 of 1024, 8 tokens 0.97, 12 .. 96 tokens 1.03 .. 1.14, 160 tokens 0.98; 64 of 1408, 12 tokens 1.15, 24 .. 96
-//     tokens 0.97 .. 1.02; 20 and 32 of 4096, 8 .. 255 tokens 1.00 .. 1.21; 128 of 768, 16 tokens 1.11, 64 tokens 1.00, 96 tokens 0.97; 256 of
+//   * bf16, fallback passes (20 % of the tokens), whose rows the host does not know.  gate/up (k_big x tokens x I in thousands): 60 of 1408, 8
+//     tokens (45) 0.99, 12 tokens (68) 1.08, 12 .. 64 tokens 1.01 .. 1.15, 128 tokens 0.97; 64 of 1024, 8 tokens (66) 0.97, 12 .. 96 tokens 1.03 .. 1.14, 160
+//     tokens 0.98; 64 of 1408, 8 tokens (68) 1.04, 12 tokens 1.15, 24 .. 96 tokens 0.97 .. 1.02; 32 of 2048, hidden 4096, 8 tokens (66) 0.89, 16 tokens 1.04; 48 of 2048, hidden 4096, 9
+//     tokens (147) 0.84; 60 of
+//     512, hidden 6144, 16 tokens (16) 0.90; more than 64 experts with rows of more than 2048 0.93 .. 0.98 below 48 tokens, 1.02 .. 1.05 above; 20 and 32 of 4096, 8 .. 255 tokens 1.00 .. 1.21; 128 of 768, 16 tokens 1.11, 64 tokens 1.00, 96 tokens 0.97; 256 of
 //     512 0.92 .. 0.99; 8 of 14336 0.97; 8 of 8192 0.95.  down: 60 of 1408, 16 tokens (k_big x tokens = 64) 0.97, 24 tokens 1.07; 20 of 4096, 24 tokens
-//     (48) 0.97, 48 tokens 1.05; 64 of 1024, 8 tokens (64) 0.93, 12 tokens 1.04; 256 of 512, 16 tokens (128) 0.95, 32 tokens 1.01; hidden 4096, 32 of
+//     (48) 0.97, 64 tokens 1.14; 64 of 1024, 8 tokens (64) 0.93, 16 tokens 1.05; 256 of 512, 16 tokens (128) 0.95, 32 tokens 1.01; random layers 65 .. 130 0.99,
+//     hidden below 1300 65 .. 300 0.95, above 1.03; hidden 4096, 32 of
 //     2048 0.91 .. 0.96, 64 of 1536 0.97 .. 1.00; 8 of 14336 0.95 .. 0.98.
 bool bf16_panels(const moe_config& c, bool run_shared, bool gate_up) {
   if (layer_bytes(c) < kLargeLayer) return false;
-  const bool many = c.E > kScanExperts, short_rows = c.H <= 2048, long_groups = c.I >= 2 * c.H;
+  const bool many = c.E > kScanExperts, short_rows = c.H <= 2048, long_groups = c.I >= 2 * c.H, few_columns = c.H < 1280;
   const Work w = layer_work(c);
   const long long sh = w.weight_rows - (long long)c.E * c.I;
   if (!run_shared) {
     if (c.E <= kFewExperts) return false;
-    if (!gate_up) return short_rows && c.T * c.k_big >= (many ? 130 : 65);
+    if (!gate_up) return short_rows && c.T * c.k_big >= (few_columns ? 300 : many ? 130 : 100);
     if (long_groups) return c.T >= 8;
-    return many ? c.T >= 16 && c.T <= 64 && c.I >= 768 : c.T >= 12 && c.T < 128;
+    if (c.T < (short_rows ? 8 : 12) || (long long)c.T * c.k_big * c.I < 66000) return false;
+    return !many ? c.T < 128 : short_rows ? c.T >= 16 && c.T <= 64 && c.I >= 768 : c.T >= 48;
   }
   if (c.E <= kFewExperts) return c.T > 64 && (sh > 0 || w.expert_rows >= 20);
   if (many && c.T < 8) return false;
-  const long long pairs = (long long)c.T * (c.k_big + c.k_little) / 2;
-  if (!gate_up) return c.T > 64 || ((pairs < c.E ? pairs : c.E) + sh / c.I) * c.H >= 13000;
+  const long long pairs = (long long)c.T * (c.k_big + c.k_little) / 2, hit = (pairs < c.E ? pairs : c.E) + sh / c.I;
+  if (!gate_up) return !few_columns && (c.T > 64 || hit * c.H >= 20000);
+  if (hit * c.I < (short_rows ? 8192 : 12288)) return false;
   // token tiles of 16 rows that the weight rows meet, in sixteenths
   const long long tiles = c.E * (long long)c.I * (w.expert_rows > 16 ? w.expert_rows : 16) + 16 * sh * ceil_div(c.T, 16);
   if (100 * tiles >= 16 * w.weight_rows * (many ? 115 : 110)) return true;
-  if (many) return false;
-  if (c.T == 1) return sh > 0 && short_rows;
+  if (many) return long_groups;
   return (short_rows && (sh > 0 || w.expert_rows >= 12)) || long_groups || 4 * pairs <= 3 * c.E;
 }
 bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool gate_up) {
   if (!run_routed) return false;       // the shared experts alone: few rows per wave
-  return c.dtype == MOE_BF16 ? bf16_panels(c, run_shared, gate_up) : narrow_panels(c, run_shared);
+  return c.dtype == MOE_BF16 ? bf16_panels(c, run_shared, gate_up) : narrow_panels(c, run_shared, gate_up);
 }
 
 // The same kernel for prefill of few rows per expert, where the tiled kernels' blocks of 128 token rows are mostly
@@ -204,14 +218,18 @@ bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool g
 // that layers of any size gain), bf16 weights of up to kFewExperts experts.  Above, a panel's passes of 64 token rows over its
 // weights are more and the tiled kernels' 128 are full.  Each launch by itself: the down projection, with half the columns and
 // thus fewer tiles for the CUs, gains longer than gate/up.  Rates: the tiled kernel's time / the panels' (two tiles per wave where
-// the next rule wants them), gate/up, down, geometric mean of four selections; token rows per weight row in brackets:
+// the next rule wants them), gate/up, down, geometric mean of four selections; token rows per weight row in brackets.  Held against
+// other layers, drawn at random: narrow formats, 1434 calls, 1.15 in the mean, of the 1344 over 18 us 5 below 0.97, 0.82 at worst; bf16, 716 calls,
+// 1.01, 3 of 699, 0.96.
 //   * few experts, alike: 8 of 14336, 8-bit, 256 tokens (48) 1.19, 1.61, 340 tokens (64) 1.11, 1.35, 420 tokens (79) 0.90, 0.87; MXFP4, 256
 //     tokens 1.28, 1.68, 380 tokens (71) 1.12, 1.94, 500 tokens (94) 0.96, 1.39; 8 of 512, hidden 512, 256 tokens, 8-bit 1.67, 2.1, MXFP4
 //     1.34, 1.42.  Where the panels fill one round of the CUs, but not two, a second block of 64 rows is another round, which the faster
 //     MXFP4 tiles do not lose: 16 of 1408, 560 tokens (52) 1.12, 1.10, 620 tokens (58) 0.82, 1.10, 8-bit 1.12, 1.59, 740 tokens (69) 1.12, 1.39.
 //   * many: 60 of 1408 + 5632, 8-bit, 256 tokens (28) 1.05, 1.46, 740 tokens (81) 1.01, 1.09, 900 tokens (99) 0.99, 1.16; MXFP4 1.33, 1.59, 1.07,
 //     0.95, 1.01, 0.93; 64 of 1408 + 2 shared, 8-bit, 800 tokens (79) 1.24, 1.32, MXFP4 1.07, 0.98; 20 of 4096, 8-bit, 900 tokens (68) 1.24, 1.25,
-//     MXFP4 1.12, 0.97.
+//     MXFP4 1.12, 0.97.  With fewer of
+//     them the rows are more alike: 24 of 4096 + 2 shared, hidden 1792, 8-bit, 582 tokens (78) 0.97, 0.70, 32 of 3456, hidden 7168, 873 tokens (82) 0.83, 0.98, 17
+//     of 8192 + 16384, 299 tokens (79) 0.92, 0.84; MXFP4, 40 of 2048 + 2 shared, hidden 2816, 380 tokens (72) 0.77, 1.31, 440 tokens (84) 0.80, 1.13.
 //   * many of up to 1024, with a selection skewed as by gate biases of a standard deviation of 0 / 1 / 2: 64 of 1024, 8-bit, gate/up, 300
 //     tokens (28) 1.28 / 0.98 / 0.96, 380 tokens (36) 1.26 / 0.99 / 0.93, 460 tokens (43) 1.34 / 0.82 / 1.03, 620 tokens (58) 1.11 / 0.90 / 0.78, 680
 //     tokens (64) 1.05 / 0.98 / 0.80, 740 tokens (69) 0.98 / 1.11 / 0.86, down 1.0 .. 1.5 throughout; MXFP4, gate/up, 500 tokens (47) 0.96 / 1.08 / 1.10, 620
@@ -225,7 +243,8 @@ bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool g
 //   * bf16, where the tiles leave part of the CUs idle in their rounds: 8 of 14336, 256 .. 319 tokens (48 .. 60), gate/up (896 tiles, 3.5 rounds) 1.03, down
 //     (128 tiles) 1.38, 380 tokens (71) 0.97, 0.88; 16 of 1024, hidden 4096, 256 tokens, gate/up (128) 1.24, down (256) 1.02, 560 tokens (52)
 //     1.11, 0.95; 16 of 4096, hidden 4096, gate/up (512) 0.95, down (256) 0.94 .. 0.98; but 20 of 4096, 420 tokens (32) 0.97, 60 of 1408
-//     + 5632, 256 tokens (28) 0.86, 8 of 4096 + 4096, hidden 4096, 300 tokens 0.90, 0.84.
+//     + 5632, 256 tokens (28) 0.86, and beside shared experts, whose groups are full: 8 of 4096 + 4096, hidden 4096, 300 tokens 0.90, 0.84, 16
+//     of 5152 + 5152, hidden 4680, 468 tokens 0.82, 0.90.
 //   * fallback passes (20 % of the tokens) gain more: 60 of 1408, 8-bit 1.31 .. 1.45, 1.33 .. 1.41, MXFP4 1.8 .. 2.0, 1.55 .. 1.60; 64 of 1024, 8-bit 1.22 .. 1.49,
 //     1.40 .. 1.62, MXFP4 1.30 .. 1.87, 1.31 .. 1.69; bf16, 8 of 14336 1.03, 1.27, 16 of 4096 1.00 .. 1.04, 1.04 .. 1.10.  The lines by rows are
 //     those of the whole step all the same, for a part may have all of its rows; second blocks are rare in it.
@@ -237,10 +256,11 @@ bool prefill_panels(const moe_config& c, bool run_routed, bool run_shared, bool 
   if (c.dtype == MOE_BF16) {
     if (!few || layer_bytes(c) < kMediumLayer || !fewer_rows(60)) return false;
     const long long tiles = gate_up ? gate_up_tiles(c, kTiledRows) : down_tiles(c);
-    return !run_shared || 8 * tiles <= 7 * cus * ceil_div(tiles, cus);
+    return !run_shared || (c.n_shared == 0 && 8 * tiles <= 7 * cus * ceil_div(tiles, cus));
   }
   if (!w8 && c.dtype != MOE_BF16_MXFP4) return false;
-  const int most = few ? (w8 ? 70 : 76) : c.I > 1024 ? 84 : large ? 76 : 36;
+  int most = few ? (w8 ? 70 : 76) : c.I > 1024 ? (c.E < 48 ? 76 : 84) : large ? 76 : 36;
+  if (!w8 && !few && c.I > 1024 && c.E < 48 && gate_up && run_shared) most = 70;
   if (!fewer_rows(most)) return false;
   if (!gate_up || !run_shared) return true;
   constexpr int kColumns = 64, kPanelRows = 64;      // of a panel of one tile per wave
@@ -289,17 +309,19 @@ bool weights_once(const moe_config& c) {
 }
 
 // Gate/up of a whole step of 129 .. 255 tokens on the tiled kernel, past the caches, whose blocks of 128 token rows pass half as
-// often over the weights of the large groups.  At 128 tokens and less the shared experts' blocks are as many as the panels', and
-// with many experts so is everything that counts.  stream_lds' time / panels' / tiles', geometric mean of five selections:
+// often over the weights of the large groups: of the shared experts and of few experts.  At 128 tokens and less the shared experts'
+// blocks are as many as the panels', and with many experts so is everything that counts.  stream_lds' time / panels' / tiles', geometric mean of five selections:
 // 60 of 1408 + 5632, 128 tokens 1.15 / 1.03, 129 tokens 1.02 / 1.18, 255 tokens 1.11 / 1.36; 64 of 1408 + 2 shared 1.04 / 1.00, 1.03 / 1.10, 1.08 /
-// 1.22; 48 of 1408 + 2816 1.03 / 0.97, 1.04 / 1.05, 1.20 / 1.23; 64 of 1408 alone 0.96 / 1.03 at all three; 64 of 1024 1.08 / 1.10, 1.08 / 1.10,
-// 1.19 / 1.29; 20 of 4096 1.08 / 1.14, 1.08 / 1.14, 1.10 / 1.20; 8 of 14336 1.06 / 1.13, 1.06 / 1.14, 1.33 / 1.42; 8 of 8192 + 8192 1.16 / 1.12, 1.22 /
-// 1.41, 1.43 / 1.90; hidden 4096, 64 of 1536 + 3072 1.04 / 0.97, 1.06 / 1.07, 1.10 / 1.17, 32 of 2048 + 4096 1.05 / 0.96, 1.11 / 1.14, 1.16 / 1.30, 24 of 4096
-// 0.97 / 1.02, 255 tokens 1.13 / 1.20.  Many: 160 of 1408 + 2 shared, 129 tokens 0.99 / 0.99, 255 tokens 1.03 / 1.03; 128 of 768 + 768 0.92 / 0.99,
+// 1.22; 48 of 1408 + 2816 1.03 / 0.97, 1.04 / 1.05, 1.20 / 1.23; 8 of 14336 1.06 / 1.13, 1.06 / 1.14, 1.33 / 1.42; 8 of 8192 + 8192 1.16 / 1.12, 1.22 /
+// 1.41, 1.43 / 1.90; hidden 4096, 64 of 1536 + 3072 1.04 / 0.97, 1.06 / 1.07, 1.10 / 1.17, 32 of 2048 + 4096 1.05 / 0.96, 1.11 / 1.14, 1.16 / 1.30.
+// Alone, either may win: 64 of 1408 0.96 / 1.03 at all three, 64 of 1024 1.08 / 1.10, 1.08 / 1.10, 1.19 / 1.29, 20 of 4096 1.08 / 1.14, 1.08 / 1.14, 1.10 / 1.20, 40 of 1280,
+// hidden 4096, 186 tokens 1.00 / 0.88, 12 of 2880, hidden 7168, 150 tokens (19 rows each) 1.10 / 0.92, 64 of 2880, hidden 3312, 157 tokens 1.05 / 0.88, 60 of 4096, hidden 1024, 150 tokens 1.12 / 1.06, 28 random ones 1.08 / 1.02.
+// Many: 160 of 1408 + 2 shared, 129 tokens 0.99 / 0.99, 255 tokens 1.03 / 1.03; 128 of 768 + 768 0.92 / 0.99,
 // 0.96 / 0.97; 256 of 512 + 512 0.96 / 0.93, 0.96 / 0.97.  The down projection has half as many columns and more of K: on the tiles
 // of 256 rows, which have one sum, it gained only in 8 of 8192 + 8192 and 32 of 2048 + 4096 (255 tokens 132 / 115 us).
 bool tiled_gate_up(const moe_config& c) {
-  return c.T > kTiledRows && c.E <= kScanExperts && layer_bytes(c) >= kLargeLayer && weights_once(c);
+  const bool large_groups = c.n_shared > 0 ? c.E <= kScanExperts : c.E <= kFewExperts && layer_work(c).expert_rows >= 20;
+  return c.T > kTiledRows && large_groups && layer_bytes(c) >= kLargeLayer && weights_once(c);
 }
 
 }  // namespace
