@@ -252,6 +252,29 @@ def test_streamed_by_waves(counts, H, I, shared, dtype):
             assert torch.isfinite(y1).all() and torch.equal(y1, y4) and (out1 is None or torch.equal(out1, out4))
 
 
+@pytest.mark.parametrize("dtype,counts,H,I,shared", [
+    ("bf16", [5, 0, 20, 17, 1], 200, 264, ()),                     # K ends inside a unit of 256 bytes; quads that the waves do not divide
+    ("bf16", [30, 2, 64, 65], 1032, 72, (520,)),                   # gate rows that end inside a tile; K in parts of a unit
+    ("bf16", [1, 3], 136, 1480, (8,)),
+    ("bf16w8", [5, 0, 20, 17, 1], 208, 272, ()),
+    ("bf16w8", [30, 2, 64, 65], 1040, 80, (528, 48)),
+    ("bf16w8", [1, 3], 144, 1488, (16,)),
+    ("bf16w8", [43, 44, 0, 130, 66], 272, 336, (208,)),            # 256 tokens and more
+    ("bf16w8", [260, 1, 3], 1040, 48, ()),
+    ("bf16", [60, 66, 0, 130, 9], 200, 264, (1032,)),
+    ("bf16", [300, 2], 72, 520, ()),
+])
+def test_streamed_by_waves_ragged(dtype, counts, H, I, shared):
+    """Rows and columns of any size that the layer may have: the bits of the kernel that such a step has otherwise."""
+    cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
+    b = _assigned_step(cfg, x, table, sh, of)
+    ref, ref_out = _run_on(*((STREAM, 1) if cfg.T < 256 else (TILED, 0)), b, x, table, sh)
+    assert torch.isfinite(ref).all()
+    for variant in (4,) if dtype == "bf16" else (4, 5):
+        y, out = _run_on(STREAM, variant, b, x, table, sh)
+        assert torch.equal(y, ref) and (not shared or torch.equal(out, ref_out)), variant
+
+
 @pytest.mark.parametrize("counts,H,I,shared", [
     ([0, 1, 32, 33, 64, 65, 50], 200, 264, ()),
     ([1, 127, 0, 1, 126], 1032, 72, (520,)),                       # 255 tokens: a shared expert of two row blocks
