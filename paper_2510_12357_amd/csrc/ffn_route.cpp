@@ -88,19 +88,18 @@ bool wide_by_rows(const moe_config& c) {
   return c.n_shared == 0 || (long long)c.T * (c.k_big + c.k_little) < 2 * kContiguousMinRows * c.E;
 }
 
-// Order of the 128 x 256 tiles.  By rows pays for narrow weights in steps of few rows and few tiles per
-// workgroup where tiles differ: beside shared experts, whose groups are full, and where the selection is skewed.
-// Contiguous order's rate of the order by rows', gate/up, down, geometric mean of four selections, at sizes that do not run in panels: 60 of
-// 1408 + 5632 shared, 8-bit, 770 tokens 0.90, 0.90, 810 tokens (88 rows) 0.93, 0.92, 1000 tokens 275 / 277 us, MXFP4 0.94, 0.96 and
-// 0.96, 0.98; 64 of 1408 + 2 shared, 8-bit, 870 tokens 0.98, 0.99, 900 tokens 257 / 263 us, MXFP4 0.97, 1.03; 32 of 1024 + 2048, 8-bit, 256 tokens 0.97, 0.98, 400 tokens 0.84,
-// 0.85, 580 tokens 0.91, 0.95, MXFP4 0.97, 1.02, 0.88, 0.91, 0.93, 0.95; 32 of 2048 + 4096, hidden 4096, 8-bit, 580 tokens 0.93, 0.92; 60 of 1024 + 1024, skewed, 8-bit, 700
-// tokens 0.91, 0.89.  Alone, 64 of 1024, 8-bit, skewed, 420 .. 1000 tokens (gate/up) 0.90 .. 0.93, 2000 tokens 0.95, 0.94, unskewed 1.02 .. 1.06.  Alike tiles
-// of MXFP4, which are the shortest, lose more, gate+up + down, us, contiguous / by rows: 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096,
-// 800 tokens 90 / 99.  So do small layers: 32 of 512, hidden 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122.
-// With bf16 weights, twice the bytes per tile, mixing the two kinds of tiles over the XCDs is worth more (60 experts,
-// 1000 tokens 286 / 312), and with more panels than three per CU the balance is there already.
-// In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is: fallback passes, 64 of 1024,
-// 8-bit, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of 14336 416 / 415.
+// Order of the 128 x 256 tiles.  By rows pays for narrow weights in steps of few rows and few tiles per workgroup where tiles differ: beside shared
+// experts, whose groups are full, and where the selection is skewed. Contiguous order's rate of the order by rows', gate/up, down, geometric mean of
+// four selections, at sizes that do not run in panels: 60 of 1408 + 5632 shared, 8-bit, 770 tokens 0.90, 0.90, 810 tokens (88 rows) 0.93, 0.92, 1000
+// tokens 275 / 277 us, MXFP4 0.94, 0.96 and 0.96, 0.98; 64 of 1408 + 2 shared, 8-bit, 870 tokens 0.98, 0.99, 900 tokens 257 / 263 us, MXFP4 0.97,
+// 1.03; 32 of 1024 + 2048, 8-bit, 256 tokens 0.97, 0.98, 400 tokens 0.84, 0.85, 580 tokens 0.91, 0.95, MXFP4 0.97, 1.02, 0.88, 0.91, 0.93, 0.95; 32
+// of 2048 + 4096, hidden 4096, 8-bit, 580 tokens 0.93, 0.92; 60 of 1024 + 1024, skewed, 8-bit, 700 tokens 0.91, 0.89.  Alone, 64 of 1024, 8-bit,
+// skewed, 420 .. 1000 tokens (gate/up) 0.90 .. 0.93, 2000 tokens 0.95, 0.94, unskewed 1.02 .. 1.06.  Alike tiles of MXFP4, which are the shortest,
+// lose more, gate+up + down, us, contiguous / by rows: 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096, 800 tokens 90 / 99.  So do small
+// layers: 32 of 512, hidden 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122. With bf16 weights, twice the bytes per tile,
+// mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more panels than three per CU the balance
+// is there already. In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is: fallback passes, 64 of
+// 1024, 8-bit, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of 14336 416 / 415.
 bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
   const bool alone = c.n_shared == 0;
@@ -176,15 +175,15 @@ bool narrow_panels(const moe_config& c, bool run_shared, bool gate_up) {
 //   * bf16, few experts: long groups stream as well through stream_lds.hip, whose loads are 512 bytes of a row, while they have few
 //     rows: 8 of 14336, gate/up, down, 65 tokens 0.98, 0.94, 96 tokens (18 rows) 1.01, 0.97, 128 tokens (24) 1.06, 1.02, 255 tokens 1.33,
 //     1.26; 8 of 8192 + 8192, 65 tokens 1.27, 1.14.
-//   * bf16, fallback passes (20 % of the tokens), whose rows the host does not know.  gate/up (k_big x tokens x I in thousands): 60 of 1408, 8
-//     tokens (45) 0.99, 12 tokens (68) 1.08, 12 .. 64 tokens 1.01 .. 1.15, 128 tokens 0.97; 64 of 1024, 8 tokens (66) 0.97, 12 .. 96 tokens 1.03 .. 1.14, 160
-//     tokens 0.98; 64 of 1408, 8 tokens (68) 1.04, 12 tokens 1.15, 24 .. 96 tokens 0.97 .. 1.02; 32 of 2048, hidden 4096, 8 tokens (66) 0.89, 16 tokens 1.04; 48 of 2048, hidden 4096, 9
-//     tokens (147) 0.84; 60 of
-//     512, hidden 6144, 16 tokens (16) 0.90; more than 64 experts with rows of more than 2048 0.93 .. 0.98 below 48 tokens, 1.02 .. 1.05 above; 20 and 32 of 4096, 8 .. 255 tokens 1.00 .. 1.21; 128 of 768, 16 tokens 1.11, 64 tokens 1.00, 96 tokens 0.97; 256 of
-//     512 0.92 .. 0.99; 8 of 14336 0.97; 8 of 8192 0.95.  down: 60 of 1408, 16 tokens (k_big x tokens = 64) 0.97, 24 tokens 1.07; 20 of 4096, 24 tokens
-//     (48) 0.97, 64 tokens 1.14; 64 of 1024, 8 tokens (64) 0.93, 16 tokens 1.05; 256 of 512, 16 tokens (128) 0.95, 32 tokens 1.01; random layers 65 .. 130 0.99,
-//     hidden below 1300 65 .. 300 0.95, above 1.03; hidden 4096, 32 of
-//     2048 0.91 .. 0.96, 64 of 1536 0.97 .. 1.00; 8 of 14336 0.95 .. 0.98.
+//   * bf16, fallback passes (20 % of the tokens), whose rows the host does not know.  gate/up (k_big x tokens x I in thousands): 60 of 1408, 8 tokens
+//     (45) 0.99, 12 tokens (68) 1.08, 12 .. 64 tokens 1.01 .. 1.15, 128 tokens 0.97; 64 of 1024, 8 tokens (66) 0.97, 12 .. 96 tokens 1.03 .. 1.14,
+//     160 tokens 0.98; 64 of 1408, 8 tokens (68) 1.04, 12 tokens 1.15, 24 .. 96 tokens 0.97 .. 1.02; 32 of 2048, hidden 4096, 8 tokens (66) 0.89, 16
+//     tokens 1.04; 48 of 2048, hidden 4096, 9 tokens (147) 0.84; 60 of 512, hidden 6144, 16 tokens (16) 0.90; more than 64 experts with rows of more
+//     than 2048 0.93 .. 0.98 below 48 tokens, 1.02 .. 1.05 above; 20 and 32 of 4096, 8 .. 255 tokens 1.00 .. 1.21; 128 of 768, 16 tokens 1.11, 64
+//     tokens 1.00, 96 tokens 0.97; 256 of 512 0.92 .. 0.99; 8 of 14336 0.97; 8 of 8192 0.95.  down: 60 of 1408, 16 tokens (k_big x tokens = 64) 0.97,
+//     24 tokens 1.07; 20 of 4096, 24 tokens (48) 0.97, 64 tokens 1.14; 64 of 1024, 8 tokens (64) 0.93, 16 tokens 1.05; 256 of 512, 16 tokens (128)
+//     0.95, 32 tokens 1.01; random layers 65 .. 130 0.99, hidden below 1300 65 .. 300 0.95, above 1.03; hidden 4096, 32 of 2048 0.91 .. 0.96, 64 of
+//     1536 0.97 .. 1.00; 8 of 14336 0.95 .. 0.98.
 bool bf16_panels(const moe_config& c, bool run_shared, bool gate_up) {
   if (layer_bytes(c) < kLargeLayer) return false;
   const bool many = c.E > kScanExperts, short_rows = c.H <= 2048, long_groups = c.I >= 2 * c.H, few_columns = c.H < 1280;
@@ -308,17 +307,18 @@ bool weights_once(const moe_config& c) {
   return c.dtype == MOE_BF16 && lines && layer_bytes(c) >= kMediumLayer;
 }
 
-// Gate/up of a whole step of 129 .. 255 tokens on the tiled kernel, past the caches, whose blocks of 128 token rows pass half as
-// often over the weights of the large groups: of the shared experts and of few experts.  At 128 tokens and less the shared experts'
-// blocks are as many as the panels', and with many experts so is everything that counts.  stream_lds' time / panels' / tiles', geometric mean of five selections:
-// 60 of 1408 + 5632, 128 tokens 1.15 / 1.03, 129 tokens 1.02 / 1.18, 255 tokens 1.11 / 1.36; 64 of 1408 + 2 shared 1.04 / 1.00, 1.03 / 1.10, 1.08 /
-// 1.22; 48 of 1408 + 2816 1.03 / 0.97, 1.04 / 1.05, 1.20 / 1.23; 8 of 14336 1.06 / 1.13, 1.06 / 1.14, 1.33 / 1.42; 8 of 8192 + 8192 1.16 / 1.12, 1.22 /
-// 1.41, 1.43 / 1.90; hidden 4096, 64 of 1536 + 3072 1.04 / 0.97, 1.06 / 1.07, 1.10 / 1.17, 32 of 2048 + 4096 1.05 / 0.96, 1.11 / 1.14, 1.16 / 1.30.
-// Alone, either may win: 64 of 1408 0.96 / 1.03 at all three, 64 of 1024 1.08 / 1.10, 1.08 / 1.10, 1.19 / 1.29, 20 of 4096 1.08 / 1.14, 1.08 / 1.14, 1.10 / 1.20, 40 of 1280,
-// hidden 4096, 186 tokens 1.00 / 0.88, 12 of 2880, hidden 7168, 150 tokens (19 rows each) 1.10 / 0.92, 64 of 2880, hidden 3312, 157 tokens 1.05 / 0.88, 60 of 4096, hidden 1024, 150 tokens 1.12 / 1.06, 28 random ones 1.08 / 1.02.
-// Many: 160 of 1408 + 2 shared, 129 tokens 0.99 / 0.99, 255 tokens 1.03 / 1.03; 128 of 768 + 768 0.92 / 0.99,
-// 0.96 / 0.97; 256 of 512 + 512 0.96 / 0.93, 0.96 / 0.97.  The down projection has half as many columns and more of K: on the tiles
-// of 256 rows, which have one sum, it gained only in 8 of 8192 + 8192 and 32 of 2048 + 4096 (255 tokens 132 / 115 us).
+// Gate/up of a whole step of 129 .. 255 tokens on the tiled kernel, past the caches, whose blocks of 128 token rows pass half as often over the
+// weights of the large groups: of the shared experts and of few experts.  At 128 tokens and less the shared experts' blocks are as many as the
+// panels', and with many experts so is everything that counts.  stream_lds' time / panels' / tiles', geometric mean of five selections: 60 of 1408 +
+// 5632, 128 tokens 1.15 / 1.03, 129 tokens 1.02 / 1.18, 255 tokens 1.11 / 1.36; 64 of 1408 + 2 shared 1.04 / 1.00, 1.03 / 1.10, 1.08 / 1.22; 48 of
+// 1408 + 2816 1.03 / 0.97, 1.04 / 1.05, 1.20 / 1.23; 8 of 14336 1.06 / 1.13, 1.06 / 1.14, 1.33 / 1.42; 8 of 8192 + 8192 1.16 / 1.12, 1.22 / 1.41,
+// 1.43 / 1.90; hidden 4096, 64 of 1536 + 3072 1.04 / 0.97, 1.06 / 1.07, 1.10 / 1.17, 32 of 2048 + 4096 1.05 / 0.96, 1.11 / 1.14, 1.16 / 1.30. Alone,
+// either may win: 64 of 1408 0.96 / 1.03 at all three, 64 of 1024 1.08 / 1.10, 1.08 / 1.10, 1.19 / 1.29, 20 of 4096 1.08 / 1.14, 1.08 / 1.14, 1.10 /
+// 1.20, 40 of 1280, hidden 4096, 186 tokens 1.00 / 0.88, 12 of 2880, hidden 7168, 150 tokens (19 rows each) 1.10 / 0.92, 64 of 2880, hidden 3312, 157
+// tokens 1.05 / 0.88, 60 of 4096, hidden 1024, 150 tokens 1.12 / 1.06, 28 random ones 1.08 / 1.02. Many: 160 of 1408 + 2 shared, 129 tokens 0.99 /
+// 0.99, 255 tokens 1.03 / 1.03; 128 of 768 + 768 0.92 / 0.99, 0.96 / 0.97; 256 of 512 + 512 0.96 / 0.93, 0.96 / 0.97.  The down projection has half
+// as many columns and more of K: on the tiles of 256 rows, which have one sum, it gained only in 8 of 8192 + 8192 and 32 of 2048 + 4096 (255 tokens
+// 132 / 115 us).
 bool tiled_gate_up(const moe_config& c) {
   const bool large_groups = c.n_shared > 0 ? c.E <= kScanExperts : c.E <= kFewExperts && layer_work(c).expert_rows >= 20;
   return c.T > kTiledRows && large_groups && layer_bytes(c) >= kLargeLayer && weights_once(c);

@@ -1,5 +1,5 @@
-// Grouped expert GEMM for the prefill regime (many tokens per expert) and for bf16 gate/up of steps whose shared experts have more
-// than 128 token rows: LDS-tiled bf16 MFMA.
+// Grouped expert GEMM for the prefill regime (many tokens per expert) and for bf16 gate/up of large layers whose shared or few experts
+// have 129 to 255 tokens: LDS-tiled bf16 MFMA.
 //
 //   kGateUp  h[r][i] = silu(sum_k x[tok(r)][k] Wgate[i][k]) * (sum_k x[tok(r)][k] Wup[i][k])
 //   kDown    y[r][c] = sum_i h[r][i] Wdown[c][i]
@@ -28,7 +28,7 @@
 //     the XCDs by panels (two orders, below); either way
 //     the token tiles that share a weight panel are adjacent in the list, so a panel is fetched
 //     from HBM once and re-read from that XCD's L2.
-//   * Steps of fewer than 256 tokens (a.two_sums: bf16 gate/up beside shared experts of more than 128 rows) keep the streaming
+//   * Steps of fewer than 256 tokens (a.two_sums: bf16 gate/up of 129 and more, tiled_gate_up in ffn_route.cpp) keep the streaming
 //     kernels' bits, which have two sums per output, of the even and of the odd blocks of 32 k: two accumulators each, hence
 //     tiles of half as many weight rows (128 tokens x 128, four stages of 32 KB).  A product of 16 k adds up as half of one of
 //     32 k, so nothing else differs.  gate/up, us, panels / these tiles / one sum and 256 rows: 60 experts of 1408 + 5632, 160 tokens
