@@ -166,8 +166,11 @@ bool narrow_panels(const moe_config& c, bool run_shared, bool gate_up) {
 //     512 0.94 .. 0.99, 160 of 1408 + 2 shared, 32 tokens 0.95, 128 tokens 0.99, but 128 of 4096 + 8192, hidden 640, 123 tokens 1.40, 128
 //     of 2048 + 2048, hidden 512, 8 tokens 1.15.
 //   * bf16, whole steps, down.  Few rows of weights hit (mean selection x hidden + shared; 128 make a panel): 64 of 1024, 1 token (6 x 2048) 0.90;
-//     20 of 4096, 4 tokens (6 x 2048) 0.85, 6 tokens (9 x 2048) 1.01; 24 of 4096, hidden 4096, 1 token (3 x 4096) 0.88; 60 of 1408 + 5632, 1
-//     token (7 x 2048) 1.01, 2 tokens (10 x 2048) 1.07; 64 of 1408, 1 token 0.91; random layers 13000 .. 20000 0.97, 20000 .. 30000 1.04.  Few columns:
+//     20 of 4096, 4 tokens (6 x 2048) 0.85, 6 tokens (9 x 2048) 1.01; 24 of 4096, hidden 4096, 1 token (3 x 4096) 0.88; 64 of 1408, 1
+//     token (4 x 2048) 0.90, 2 tokens (9 x 2048) 1.00; random layers 13000 .. 20000 0.97, 20000 .. 30000 1.04.  Beside shared experts, little ranks and all:
+//     48 of 1408 + 2816, 1 token (5 x 2048) 0.88, 1.00, 2 tokens (8 x 2048) 1.00, 1.13; hidden 2560, 40 of 1792 + 1792, 1 token (4 x 2560) 0.84, 0.97, 2
+//     tokens (7 x 2560) 0.97, 1.07; 64 of 1408 + 2 shared, 1 token (6 x 2048) 1.04, 1.03; 60 of 1408 + 5632, 1 token (7 x 2048) 0.98, 1.00, 2 tokens 1.01,
+//     1.06; 64 of 1024 + 1024, 1 token (7 x 2048) 0.99, 1.13; hidden 3072, 32 of 1536 + 2 shared, 1 token (5 x 3072) 0.97, 1.12.  Few columns:
 //     64 of 14336, hidden 512, 31 .. 55 tokens 0.46 .. 0.65; 96 of 2048, hidden 768, 55 tokens 0.84; 256 of 920, hidden 1024, 133 tokens 0.87; random
 //     layers, hidden 900 .. 1200 0.96, 1200 .. 1600 1.02.  Above: 60 of 1408 + 5632 1.02 .. 1.15; 64 of 1408 + 2 shared 1.00
 //     .. 1.13; 64 of 1024 0.97 .. 1.06; 24 of 4096, hidden 4096 1.12 .. 1.24; 256 of 512 + 512 1.06 .. 1.12.  32 of 2048 + 4096, hidden 4096, loses
@@ -199,7 +202,7 @@ bool bf16_panels(const moe_config& c, bool run_shared, bool gate_up) {
   if (c.E <= kFewExperts) return c.T > 64 && (sh > 0 || w.expert_rows >= 20);
   if (many && c.T < 8) return false;
   const long long pairs = (long long)c.T * (c.k_big + c.k_little) / 2, hit = (pairs < c.E ? pairs : c.E) + sh / c.I;
-  if (!gate_up) return !few_columns && (c.T > 64 || hit * c.H >= 20000);
+  if (!gate_up) return !few_columns && (c.T > 64 || hit * c.H >= (sh > 0 ? 12000 : 20000));
   if (hit * c.I < (short_rows ? 8192 : 12288)) return false;
   // token tiles of 16 rows that the weight rows meet, in sixteenths
   const long long tiles = c.E * (long long)c.I * (w.expert_rows > 16 ? w.expert_rows : 16) + 16 * sh * ceil_div(c.T, 16);

@@ -23,7 +23,7 @@ def test_large_layers_stream_in_panels(panels):
     """Large layers, narrow formats medium ones too; never the shared experts alone, nor many experts that few tokens hit."""
     few, many = wl.CONFIGS["coarse8"], wl.CONFIGS["fine60_decode"]
     for T in (1, 2, 64, 65, 128):
-        assert panels(many.with_(T=T)) == ("PP" if T > 1 else "PS") and panels(few.with_(T=T)) == ("PP" if T > 106 else "SS")
+        assert panels(many.with_(T=T)) == "PP" and panels(few.with_(T=T)) == ("PP" if T > 106 else "SS")
         assert panels(many.with_(T=T), False, True) == panels(many.with_(T=T, dtype="fp32")) == "SS"
         for dtype in ("bf16w8", "bf16mx4"):
             assert panels(few.with_(T=T, dtype=dtype))[:2] == panels(many.with_(T=T, dtype=dtype), True, False) == "PP"
@@ -49,7 +49,8 @@ def test_bf16_launches_choose_by_themselves(panels):
     fine64, wide_rows = _layer(2048, 64, 1024, 8, 1), _layer(4096, 64, 1536, 6, 1, (3072,))
     for layer, expect in ((fine64, {1: "SS", 2: "PP", 8: "PP", 9: "SP", 117: "SP", 118: "PP", 128: "PP"}),
                           (wide_rows, {1: "SP", 2: "PP", 10: "PP", 11: "SP", 64: "SP", 65: "PP", 128: "PP"}),
-                          (wl.CONFIGS["shared2_offload"], {1: "PS", 2: "PP", 128: "PP"}),
+                          (wl.CONFIGS["shared2_offload"], {1: "PP", 2: "PP", 128: "PP"}),
+                          (_layer(2048, 48, 1408, 4, 1, (2816,)), {1: "SS", 2: "PP"}), (_layer(2048, 64, 1408, 6, 1), {1: "SS", 2: "PS", 3: "PP"}),
                           (_layer(2048, 20, 4096, 2, 1), {1: "SS", 2: "PS", 6: "PS", 7: "PP", 255: "PP"}),
                           (_layer(2048, 128, 768, 8, 1, (768,)), {7: "SS", 8: "SP", 128: "SP"}),
                           (_layer(640, 128, 4096, 4, 1, (8192,)), {7: "SS", 8: "PS", 128: "PS"}),
