@@ -209,6 +209,8 @@ int moe_dispatch(const moe_config* cfg, const int32_t* topk_idx, const int32_t* 
  *            step of a layer without shared experts pass run_shared = 1 too: nothing more is run.
  * ws         device scratch holding the SwiGLU activations
  * The number of pairs per expert is read on the device; the host never waits for it.
+ * The order in which the products of an output are added up depends on cfg->dtype and on whether T reaches 256, not on the
+ * parts that a call runs or the kernels that it takes: a step has the same bits whole and in parts.
  */
 size_t moe_expert_ffn_workspace_bytes(const moe_config* cfg);
 /* Bytes of one expert blob with intermediate size I (cfg->I for a routed expert, cfg->shared_I[s]

@@ -278,12 +278,14 @@ bool prefill_panels(const moe_config& c, bool run_routed, bool run_shared, bool 
 // is computed from LDS slower than it comes from HBM once it meets several tiles of token rows, and half of the reads are
 // the token rows'.  With fewer rows the larger panels leave more of the last round empty.  gate+up + down, us, one / two:
 //   * MXFP4, 60 of 1408 + 5632, 200 tokens (22 rows per weight row) 105 / 107, 255 tokens (28) 121 / 114; 64 of 1408 + 2 shared,
-//     255 tokens (25) 108 / 114, 420 tokens (41) 160 / 138; 8 of 14336, 128 tokens (24) 197 / 206, 200 tokens (38) 268 / 246.
-//   * 8-bit: 60 of 1408 + 5632, 256 tokens (28) 149 / 152, 420 tokens (46) 181 / 171; 64 of 1024, 540 tokens (51) 130 / 144, 680
-//     tokens (64) 156 / 143; 64 of 1408 + 2 shared, 420 tokens (41) 158 / 160, 540 tokens (53) 188 / 174; 8 of 14336, 256 tokens
-//     (48) 325 / 326, 330 tokens (62) 433 / 381.  bf16 weights: 8 of 14336, 256 tokens 484 / 494.
-//   * Parts of a step have fewer rows than that: 60 of 1408, fallback pass, 420 tokens, 8-bit 1.41 / 1.33 times the tiled
-//     kernel's rate.  There they pay where they make one round over the CUs of two: 64 of 272, hidden 528, 256 tokens 29.2 / 25.4.
+//     255 tokens (25) 108 / 114; 8 of 14336, 128 tokens (24) 197 / 206, 200 tokens (38) 268 / 246.
+//     Above 255 tokens, 20 % of the tokens with all ranks: 60 of 1408 + 5632, 256 tokens (28) 121 / 120, 420 tokens (46) 149 / 153; 64 of 1408 + 2
+//     shared, 420 tokens (41) 142 / 132; 64 of 1024, 300 tokens (28) 75 / 74; 8 of 14336, 256 tokens (48) 327 / 306, 400 tokens (75) 417 / 376.
+//   * 8-bit, likewise: 60 of 1408 + 5632, 256 tokens (28) 155 / 155, 420 tokens (46) 185 / 171; 64 of 1408 + 2 shared, 420 tokens (41) 162 / 163, 540
+//     tokens (53) 191 / 172; 64 of 1024, 540 tokens (51) 113 / 108, with half of the tokens 128 / 117, with all 177 / 180; 8 of 14336, 256 tokens (48)
+//     298 / 311, 278 tokens (52) 332 / 340, 339 / 349, 528 / 476, 370 tokens (69) 450 / 400, 511 / 463, 600 / 518.
+//   * Parts of a step have fewer rows than that: 60 of 1408, fallback pass, 420 tokens, 8-bit 95 / 99, MXFP4 63 / 68.  There they pay where they make one
+//     round over the CUs of two: 64 of 272, hidden 528, 256 tokens 30.7 / 27.8.  bf16 weights: 8 of 14336, 256 tokens 484 / 494.
 bool wide_panels(const moe_config& c, bool run_shared, int cus) {
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
   if (!run_shared) {

@@ -1,5 +1,5 @@
-// Skinny grouped GEMM for the decode regime (layers too small for stream_panels.hip) with the weights streamed from HBM directly into
-// LDS (bf16 activations; bf16 weights, or 8-bit E4M3 weights with fp32 row scales; same
+// Skinny grouped GEMM for the decode regime (launches that ffn_route does not give to stream_panels.hip, small layers above all)
+// with the weights streamed from HBM directly into LDS (bf16 activations; bf16 weights, or 8-bit E4M3 weights with fp32 row scales; same
 // operation, groups and work items as stream_gemm.hip).
 //
 //   kGateUp  h = silu(W_gate x) * (W_up x)     (execution stage of Sec. II-A, SwiGLU)

@@ -25,8 +25,8 @@
 //     median, now 7).
 //   * With many token rows it is the reads from LDS that bound the narrow formats: 16 KB of a panel's token rows for every 4 KB of
 //     weights.  RT = 2 makes a wave's share two tiles of up to four quads, whose products share the fragments of the token rows:
-//     8 experts of 14336, MXFP4, 256 tokens, gate/up + down 336 / 280, 8-bit 330 tokens 433 / 381, 60 of 1408 + 5632, MXFP4 420 tokens
-//     155 / 152, 8-bit 181 / 171.  The 16 quads' accumulators still fit 256 registers at 64 rows.
+//     8 experts of 14336, MXFP4, 256 tokens, gate/up + down 327 / 306, 8-bit 370 tokens 450 / 400, 64 of 1408 + 2 shared, MXFP4 420 tokens
+//     142 / 132, 60 of 1408 + 5632, 8-bit 420 tokens 185 / 171.  The 16 quads' accumulators still fit 256 registers at 64 rows.
 //   * Steps of 256 tokens and more (MANY) have token numbers of two bytes, too many for LDS at once: the workgroup
 //     looks them up for 32 of its panels at a time.  Their weights pass the caches as well: loaded through them the steps
 //     were slower.
