@@ -333,6 +333,23 @@ def test_parts_through_the_rules_have_the_bits_of_the_whole(counts, H, I, shared
     assert torch.isfinite(y).all() and torch.equal(run(True, False)[0], y) and torch.equal(run(False, True)[1], out)
 
 
+@pytest.mark.parametrize("counts,H,I,shared,dtype", [
+    ([3] * 40 + [4] * 20, 2048, 1408, (5632,), "bf16"),            # 200 tokens: whole with gate/up on tiles
+    ([15] * 20, 512, 512, (512, 256), "bf16w8"),                   # 300 tokens: whole on panels
+])
+def test_side_stream_step_has_the_bits_of_the_whole(counts, H, I, shared, dtype):
+    """The shared experts on a stream of their own, through layer_step."""
+    cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
+    whole = _assigned_step(cfg, x, table, sh, of)
+    b, side = mm.StepBuffers(cfg), torch.cuda.Stream()
+    b.logits.copy_(whole.logits)
+    torch.cuda.synchronize()
+    for _ in range(2):
+        mm.layer_step(b, x, None, None, None, table, sh, logits_given=True, side_stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(b.out.view(torch.int16), whole.out.view(torch.int16))
+
+
 @pytest.mark.parametrize("counts,H,I", [
     ([0, 5, 128, 129, 1, 40, 64, 33], 256, 384),                   # few rows per expert
     ([300, 0, 290, 400], 128, 256),                                # many rows per expert
