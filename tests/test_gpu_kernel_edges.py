@@ -408,3 +408,27 @@ def test_dispatch_masks(T, E, K, j_lo):
     assert np.array_equal(b.expert_offsets.cpu().numpy(), off)
     assert np.array_equal(b.sorted_token.cpu().numpy(), tok) and np.array_equal(b.sorted_rank.cpu().numpy(), rank)
     assert np.array_equal(b.inv_pos.cpu().numpy(), inv)
+
+
+# ------------------------------------------------------------------ router
+@pytest.mark.parametrize("E", [1, 63, 64, 65, 128, 129, 256])
+def test_selection_with_ties_in_every_set_of_64_experts(E):
+    """A round takes the first set bit of a ballot per 64 experts: equal logits within a set, across sets and in
+    all of a row, and rows that run out of numbers."""
+    K, T = min(E, 16), 9
+    g = np.random.default_rng(E)
+    z = np.round(g.standard_normal((T, E)) * 2).astype(np.float32)      # few distinct values: ties everywhere
+    z[1] = 0.25
+    z[2] = -np.inf
+    z[3] = np.nan
+    z[4, :] = -np.inf
+    z[4, E - 1] = 1.0
+    z[5, E // 2:] = np.nan
+    cfg = wl.LayerConfig("r", T=T, H=8, E=E, I=8, k_big=K, k_little=1)
+    b = mm.StepBuffers(cfg)
+    b.logits.copy_(torch.from_numpy(z))
+    mm.moe_route(b.c, None, None, None, None, b.logits, True, b.topk_idx, b.topk_w, b.important, b.k_t)
+    torch.cuda.synchronize()
+    idx, w, _, _ = oracle.route(z, None, cfg.gamma, K, 1, False)
+    assert np.array_equal(b.topk_idx.cpu().numpy(), idx)
+    assert np.abs(b.topk_w.cpu().numpy() - w).max() <= 2e-6
