@@ -212,14 +212,8 @@ extern "C" int moe_route(const moe_config* cfg, const void* x, const void* Wg, c
   }
   if (!logits_given) {
     ProfScope ps(kProfRouterGemm, s);
-    if (router == kRouterGemv) {
-      rc = launch_gate_gemv(*cfg, x, Wg, gate_bias, logits, s);
-    } else {
-      StreamArgs a = {};
-      a.T = cfg->T; a.H = cfg->H; a.E = cfg->E; a.I = cfg->I;
-      a.x = x; a.Wg = Wg; a.bias = gate_bias; a.logits = logits;
-      rc = launch_stream(kRouter, cfg->dtype, a, s);
-    }
+    rc = router == kRouterGemv ? launch_gate_gemv(*cfg, x, Wg, gate_bias, logits, s)
+                               : launch_gate_mfma(*cfg, x, Wg, gate_bias, logits, s);
     if (rc) return rc;
   }
   ProfScope ps(kProfRouteTopk, s);

@@ -94,7 +94,6 @@ template <int MODE>
 __device__ __forceinline__ GroupSrc load_group_src(const StreamArgs& a, int g) {
   GroupSrc s;
   s.row0 = 0;
-  if (MODE == kRouter) { s.m = a.T; s.blob = a.Wg; return s; }
   const int n_sh_groups = (MODE == kDown) ? a.n_slabs : a.n_shared;
   if (g < n_sh_groups) {
     s.m = a.T;
@@ -125,12 +124,6 @@ __device__ __forceinline__ Group make_group(const StreamArgs& a, int g, const Gr
   Group G;
   G.gather = 0; G.row0 = src.row0; G.m = src.m; G.scale = nullptr;
   const char* blob = static_cast<const char*>(src.blob);
-  if (MODE == kRouter) {
-    G.N = a.E; G.K = a.H; G.ldw = a.H;
-    G.w0 = a.Wg; G.b = a.x; G.out = a.logits;
-    G.wbytes = (unsigned)a.E * a.H * esz; G.bbytes = (unsigned)a.T * a.H * esz;
-    return G;
-  }
   const int n_sh_groups = (MODE == kDown) ? a.n_slabs : a.n_shared;
   if (g < n_sh_groups) {
     int s = g, chunk = 0;
@@ -183,7 +176,6 @@ __device__ __forceinline__ Group resolve_group(const StreamArgs& a, int g) {
 inline long item_upper_bound(StreamMode mode, const StreamArgs& a, int tok) {
   auto row_items = [](int n, int per) { return (long)((n + per - 1) / per); };
   const long tg_all = (a.T + tok - 1) / tok;
-  if (mode == kRouter) return row_items(a.E, 32) * ((a.T + 15) / 16);
   const int per = (mode == kGateUp) ? 16 : 32;
   long items = 0;
   // a routed expert holds at most T pairs, and all experts together at most T*k_big

@@ -47,8 +47,8 @@ inline size_t expert_blob_bytes(int dtype, int H, int I) {
 }
 
 // ---- skinny grouped GEMM  D[r][n] = sum_k W[n][k] * B[r][k]  (weights streamed once) --------
-// Three uses: router logits, gate/up projection with fused SwiGLU, down projection.
-enum StreamMode { kRouter = 0, kGateUp = 1, kDown = 2 };
+// Two uses: gate/up projection with fused SwiGLU, down projection.
+enum StreamMode { kGateUp = 1, kDown = 2 };
 
 // The down projection of a wide shared expert is cut along its contraction into chunks that
 // are computed as independent groups and written to separate [T,H] slabs of shared_out.
@@ -86,9 +86,6 @@ struct StreamArgs {
   void* h_shared[MOE_MAX_SHARED];     // [T, I_s]
   float* y;                           // [T*k_big, H]
   float* shared_out;                  // [n_slabs, T, H]
-  const void* Wg;                     // router: [E,H]
-  const float* bias;                  // router: [E] or null
-  float* logits;                      // router: [T,E]
 };
 
 int launch_stream(StreamMode mode, int dtype, const StreamArgs& a, hipStream_t s);
@@ -132,6 +129,7 @@ int launch_gate_gemv(const moe_config& c, const void* x, const void* Wg, const f
                      hipStream_t s);
 int launch_gate_route(const moe_config& c, const void* x, const void* Wg, const float* bias, const float* conf,
                       float* logits, int32_t* idx, float* w, uint8_t* important, int32_t* k_t, hipStream_t s);
+int launch_gate_mfma(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits, hipStream_t s);
 int launch_confidence(const float* z, int T, int V, float* conf, hipStream_t s);
 int dispatch_chunks(int T);          // workgroups (token chunks) of the large-T dispatch
 // pairs (t, j) with j_lo <= j < k_t[t]

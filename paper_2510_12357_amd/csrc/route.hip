@@ -10,8 +10,10 @@
 //   gate_route_kernel router logits and selection of one token per workgroup (small steps)
 //   gate_gemv_kernel  router logits alone (65 to 256 tokens that the former is not for): plain fp32
 //                     FMAs, one wave per block of 2 experts x 4 tokens
-//   route_kernel      softmax / importance / top-k on given logits
+//   gate_mfma_kernel  router logits alone (more than 256 tokens): MFMA
+//   route_kernel      softmax / importance / top-k on given logits, and the number of pairs of each expert for the dispatch
 #include "internal.h"
+#include "groups.h"
 #include "route_device.h"
 
 namespace mm {
@@ -131,6 +133,130 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gate_route_kernel(const S* _
     raw[c] = (e < E) ? s_logit[e] : 0.f;
   }
   select_token(P, t, lane, raw);
+}
+
+// Router logits of more than 256 tokens: MT x 16 tokens and NT x 16 experts per workgroup of 16 waves, which split the
+// contraction.  What bounds it is what one CU fetches of rows that the weight stream has pushed out of the caches: about 50
+// bytes per ns, whatever is in flight.  So the tile is the smallest whose workgroups still fit the CUs at once (128 KB for one
+// tile of either at a hidden size of 2048), a wave issues the loads of whole cache lines of all its rows before the
+// first product, and the partial sums meet in LDS.  us, a register-ring GEMM with items of 16 tokens x 32 experts on four waves /
+// here: 64 experts of 2048, 300 tokens 10.7 / 6.0, 700 tokens 10.6 / 6.1, 2000 tokens 11.2 / 8.1, 4000 tokens 18.0 / 11.0; 8 experts of
+// 4096, 300 tokens 11.3 / 8.0, 4000 tokens 15.1 / 13.4.  Measured and not kept: all experts and the selection in the same workgroup (300 tokens, 64
+// experts of 2048: 14.2, against 6.8 and a selection of 4.6: 320 KB through one CU).
+constexpr int kMfmaWaves = 16;
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// 8 consecutive k of one row: the operand of one 16x16x32 product, or of eight 16x16x4 ones, whose i-th takes
+// the i-th element of every lane's eight
+template <typename S> struct Frag8;
+template <> struct Frag8<uint16_t> {
+  bf16x8 v;
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, unsigned off, int soff) {
+    v = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, soff, 0));
+  }
+  static __device__ __forceinline__ f32x4 mma(const Frag8& a, const Frag8& b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+  }
+};
+template <> struct Frag8<float> {
+  f32x4 lo, hi;
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, unsigned off, int soff) {
+    lo = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, soff, 0));
+    hi = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16u), soff, 0));   // kOob + 16 is out of range too
+  }
+  static __device__ __forceinline__ f32x4 mma(const Frag8& a, const Frag8& b, f32x4 c) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.lo[i], b.lo[i], c, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.hi[i], b.hi[i], c, 0, 0, 0);
+    return c;
+  }
+};
+
+template <typename S, int MT, int NT>
+__global__ __launch_bounds__(kMfmaWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void gate_mfma_kernel(
+    const S* __restrict__ x, const S* __restrict__ Wg, const float* __restrict__ bias, int T, int H, int E, float* __restrict__ logits) {
+  constexpr int U = sizeof(S) == 2 ? 4 : 2;              // k-steps of 32 per trip: 256 bytes of a row
+  constexpr int kRow = 20;                               // floats of a tile's row: the lanes of a store meet a bank twice at most
+  constexpr unsigned esz = sizeof(S);
+  __shared__ float s_part[kMfmaWaves][MT * NT][16][kRow];
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int q = lane >> 4, c16 = lane & 15;
+  const int t0 = blockIdx.x * MT * 16, e0 = blockIdx.y * NT * 16;
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (unsigned)T * (unsigned)H * esz), rw = make_rsrc(Wg, (unsigned)E * (unsigned)H * esz);
+  const unsigned row = (unsigned)H * esz;
+  unsigned xo[MT], wo[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xo[i] = t0 + 16 * i + c16 < T ? (unsigned)(t0 + 16 * i + c16) * row + (unsigned)q * 8u * esz : kOob;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) wo[j] = e0 + 16 * j + c16 < E ? (unsigned)(e0 + 16 * j + c16) * row + (unsigned)q * 8u * esz : kOob;
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // groups of U k-steps, dealt to the waves; then the k-steps left over, one by one
+  const int groups = H / (32 * U), steps = (H + 31) >> 5;
+  for (int g = wave; g < groups; g += kMfmaWaves) {
+    const int k = uniform(g * U * 32);
+    Frag8<S> fx[U][MT], fw[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) fx[u][i].load(rx, xo[i], (k + 32 * u) * (int)esz);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) fw[u][j].load(rw, wo[j], (k + 32 * u) * (int)esz);
+    }
+    __builtin_amdgcn_sched_barrier(0);                   // all loads before the first product
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = Frag8<S>::mma(fx[u][i], fw[u][j], acc[i][j]);
+  }
+  for (int st = groups * U + wave; st < steps; st += kMfmaWaves) {
+    const unsigned none = st * 32 + q * 8 < H ? 0u : kOob;   // beyond the row: zeros
+    Frag8<S> fx[MT], fw[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) fx[i].load(rx, (xo[i] + (unsigned)(st * 32) * esz) | none, 0);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) fw[j].load(rw, (wo[j] + (unsigned)(st * 32) * esz) | none, 0);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = Frag8<S>::mma(fx[i], fw[j], acc[i][j]);
+  }
+  // accumulator v of a lane: token 4 q + v, expert c16 of the tile
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s_part[wave][i * NT + j][4 * q + v][c16] = acc[i][j][v];
+  __syncthreads();
+  if (tid < MT * NT * 256) {
+    const int r = tid / (16 * NT), c = tid % (16 * NT), t = t0 + r, e = e0 + c;
+    float z = 0.f;
+#pragma unroll
+    for (int w = 0; w < kMfmaWaves; ++w) z += s_part[w][(r >> 4) * NT + (c >> 4)][r & 15][c & 15];
+    if (t < T && e < E) logits[(size_t)t * E + e] = z + (bias ? bias[e] : 0.f);
+  }
+}
+
+template <typename S, int MT, int NT>
+void launch_gate_mfma_tile(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits, hipStream_t s) {
+  const dim3 grid((unsigned)((c.T + 16 * MT - 1) / (16 * MT)), (unsigned)((c.E + 16 * NT - 1) / (16 * NT)));
+  hipLaunchKernelGGL((gate_mfma_kernel<S, MT, NT>), grid, dim3(kMfmaWaves * 64), 0, s, static_cast<const S*>(x),
+                     static_cast<const S*>(Wg), bias, c.T, c.H, c.E, logits);
+}
+template <typename S>
+void launch_gate_mfma_typed(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits, hipStream_t s) {
+  const int tt = (c.T + 15) / 16, et = (c.E + 15) / 16, cus = device_cu_count();
+  if (tt * et <= cus) launch_gate_mfma_tile<S, 1, 1>(c, x, Wg, bias, logits, s);
+  else if (tt * ((et + 1) / 2) <= cus) launch_gate_mfma_tile<S, 1, 2>(c, x, Wg, bias, logits, s);
+  else launch_gate_mfma_tile<S, 2, 2>(c, x, Wg, bias, logits, s);
 }
 
 // conf[t] = 1 / sum_v exp(z_tv - max_v z_tv): one workgroup per token, one sweep over the row.
@@ -256,6 +382,13 @@ int launch_gate_route(const moe_config& c, const void* x, const void* Wg, const 
     hipLaunchKernelGGL(gate_route_kernel<float>, dim3((unsigned)c.T), dim3(kFusedWaves * 64), 0, s,
                        static_cast<const float*>(x), static_cast<const float*>(Wg), bias, c.H, logits, P);
   return hip_fail(hipGetLastError(), "gate_route_kernel launch");
+}
+
+int launch_gate_mfma(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits, hipStream_t s) {
+  if (c.T == 0) return MOE_OK;
+  if (c.dtype != MOE_FP32) launch_gate_mfma_typed<uint16_t>(c, x, Wg, bias, logits, s);
+  else launch_gate_mfma_typed<float>(c, x, Wg, bias, logits, s);
+  return hip_fail(hipGetLastError(), "gate_mfma_kernel launch");
 }
 
 int launch_gate_gemv(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits,

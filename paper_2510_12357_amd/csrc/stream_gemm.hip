@@ -1,8 +1,7 @@
 // Skinny grouped GEMM for the decode regime: D[r][n] = sum_k W[n][k] * B[r][k] with few rows r
 // (tokens) per group and weights W that are read exactly once from HBM.
 //
-// Used three times per step (execution stage of Sec. II-A, router of the selection stage):
-//   kRouter  logits = x Wg^T + bias
+// The execution stage of fp32 layers (Sec. II-A):
 //   kGateUp  h = silu(W_gate x) * (W_up x)     (SwiGLU activation, stored in the storage dtype)
 //   kDown    y = W_down h                       (fp32)
 //
@@ -36,7 +35,6 @@
 namespace mm {
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
@@ -45,34 +43,8 @@ constexpr int kRT = 2;             // row tiles (16 rows each) per work item
 #define MOE_STREAM_NT 4
 #endif
 constexpr int kNT = MOE_STREAM_NT; // token tiles (16 tokens each) per work item, at most
-#ifndef MOE_STREAM_D1
-#define MOE_STREAM_D1 4
-#endif
-#ifndef MOE_STREAM_D4
-#define MOE_STREAM_D4 2
-#endif
 
 // ---- element-type specifics -----------------------------------------------------------------
-struct BF16 {
-  typedef uint16_t storage;
-  typedef bf16x8 frag;                       // 8 consecutive k
-  static constexpr int kWavesPerSimd = 3;        // register budget: three workgroups per CU
-  static constexpr int kDepth1 = MOE_STREAM_D1;  // k-steps in flight with 1 token tile
-  static constexpr int kDepth4 = MOE_STREAM_D4;  // ... with up to 4 token tiles
-  static __device__ __forceinline__ frag load(__amdgpu_buffer_rsrc_t r, unsigned off) {
-    const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
-    return __builtin_bit_cast(frag, v);
-  }
-  static __device__ __forceinline__ f32x4 mma(const frag& a, const frag& b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ void store4(storage* p, float v0, float v1, float v2, float v3) {
-    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-    bf16x4 o = {(__bf16)v0, (__bf16)v1, (__bf16)v2, (__bf16)v3};
-    *reinterpret_cast<bf16x4*>(p) = o;
-  }
-};
-
 struct FP32 {
   typedef float storage;
   struct frag { f32x4 lo, hi; };             // 8 consecutive k
@@ -101,11 +73,8 @@ struct FP32 {
 
 template <int MODE>
 __device__ __forceinline__ int rows_per_item() { return MODE == kGateUp ? 16 : 16 * kRT; }
-// tokens per work item: the router uses single token tiles (its weight matrix is tiny and stays
-// in L2, so more and smaller items only add parallelism); the expert GEMMs reuse the streamed
-// weights for up to kNT tiles
-template <int MODE>
-__device__ __forceinline__ int tokens_per_item() { return MODE == kRouter ? 16 : 16 * kNT; }
+// tokens per work item: the streamed weights are reused for up to kNT tiles
+constexpr int kItemTokens = 16 * kNT;
 
 // What a wave needs of a work item to run its K loop.
 struct Operands {
@@ -204,13 +173,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int q = lane >> 4, c16 = lane & 15;
-  const int n_groups = (MODE == kRouter) ? 1 : a.n_routed + (MODE == kDown ? a.n_slabs : a.n_shared);
+  const int n_groups = a.n_routed + (MODE == kDown ? a.n_slabs : a.n_shared);
 
   // ---- group table and item list: tiles per group, exclusive prefix (wave 0) ----
   for (int g = tid; g < n_groups; g += kThreads) {
     const Group G = resolve_group<typename ET::storage, MODE>(a, g);
     const int rows = (G.N + rows_per_item<MODE>() - 1) / rows_per_item<MODE>();
-    const int tgs = (G.m + tokens_per_item<MODE>() - 1) / tokens_per_item<MODE>();
+    const int tgs = (G.m + kItemTokens - 1) / kItemTokens;
     s_group[g] = G;
     s_cnt[g] = rows * tgs;
   }
@@ -272,11 +241,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
     G.gather = uniform(G.gather); G.wbytes = uniform(G.wbytes); G.bbytes = uniform(G.bbytes);
     G.w0 = uniform(G.w0); G.b = uniform(G.b);
     const int local = item - uniform(s_prefix[it.g]);
-    const int tgs = max(1, (G.m + tokens_per_item<MODE>() - 1) / tokens_per_item<MODE>());
+    const int tgs = max(1, (G.m + kItemTokens - 1) / kItemTokens);
     const int row_item = local / tgs;
-    it.r0 = (local - row_item * tgs) * tokens_per_item<MODE>();
+    it.r0 = (local - row_item * tgs) * kItemTokens;
     it.n0 = row_item * rows_per_item<MODE>();
-    it.ntn = (MODE == kRouter) ? 1 : clampi((G.m - it.r0 + 15) >> 4, 1, kNT);   // token tiles in use (wave-uniform)
+    it.ntn = clampi((G.m - it.r0 + 15) >> 4, 1, kNT);   // token tiles in use (wave-uniform)
     // an item past the end of the list keeps valid pointers and empty buffers
     it.w = it.valid ? G.w0 : a.x; it.b = it.valid ? G.b : a.x;
     it.wbytes = it.valid ? G.wbytes : 0u; it.bbytes = it.valid ? G.bbytes : 0u;
@@ -362,7 +331,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
             }
             ET::store4(static_cast<S*>(G.out) + (size_t)r * G.N + i, hv[0], hv[1], hv[2], hv[3]);
           }
-        } else if (MODE == kDown) {
+        } else {
 #pragma unroll
           for (int rt = 0; rt < kRT; ++rt) {
             const int c = n0 + rt * 16 + 4 * q;
@@ -370,14 +339,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
               *reinterpret_cast<f32x4*>(static_cast<float*>(G.out) + (size_t)r * a.H + c) =
                   f32x4{val[rt][0], val[rt][1], val[rt][2], val[rt][3]};
           }
-        } else {  // kRouter
-#pragma unroll
-          for (int rt = 0; rt < kRT; ++rt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int n = n0 + rt * 16 + 4 * q + v;
-              if (n < G.N) a.logits[(size_t)r * a.E + n] = val[rt][v] + (a.bias ? a.bias[n] : 0.f);
-            }
         }
       }
     }
@@ -389,7 +350,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
 template <typename ET, int MODE, int NW>
 int launch_typed(const StreamArgs& a, hipStream_t s) {
   constexpr int kThreads = NW * 64;
-  const long items = item_upper_bound((StreamMode)MODE, a, MODE == kRouter ? 16 : 16 * kNT);
+  const long items = item_upper_bound((StreamMode)MODE, a, kItemTokens);
   if (items <= 0) return MOE_OK;
   // persistent workgroups: exactly as many as are resident at once, so that the static striding
   // over the item list never leaves a second, partially filled round of workgroups
@@ -410,24 +371,9 @@ int launch_typed(const StreamArgs& a, hipStream_t s) {
 }  // namespace
 
 int launch_stream(StreamMode mode, int dtype, const StreamArgs& a, hipStream_t s) {
-  if (dtype == MOE_BF16_W8 || dtype == MOE_BF16_MXFP4) {
-    // the router matrix of such a layer is bf16; its expert weights exist for the LDS kernel only
-    if (mode == kRouter) return launch_typed<BF16, kRouter, 4>(a, s);
-    return launch_stream_lds(mode, dtype == MOE_BF16_W8 ? 1 : 0, a, s);
-  }
-  if (dtype == MOE_BF16) {
-    // the bf16 expert GEMMs stream through LDS (stream_lds.hip); this file's kernel serves the
-    // router GEMM and the fp32 layers
-    if (mode != kRouter) return launch_stream_lds(mode, 2, a, s);
-    return launch_typed<BF16, kRouter, 4>(a, s);
-  } else {
-    switch (mode) {
-      case kRouter: return launch_typed<FP32, kRouter, 4>(a, s);
-      case kGateUp: return launch_typed<FP32, kGateUp, 4>(a, s);
-      case kDown: return launch_typed<FP32, kDown, 4>(a, s);
-    }
-  }
-  return fail(MOE_E_BADARG, "bad stream mode/dtype");
+  // bf16 activations stream through LDS (stream_lds.hip); this file's kernel serves the fp32 layers
+  if (dtype != MOE_FP32) return launch_stream_lds(mode, dtype == MOE_BF16 ? 2 : (dtype == MOE_BF16_W8 ? 1 : 0), a, s);
+  return mode == kGateUp ? launch_typed<FP32, kGateUp, 4>(a, s) : launch_typed<FP32, kDown, 4>(a, s);
 }
 
 }  // namespace mm

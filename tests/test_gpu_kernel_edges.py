@@ -432,3 +432,21 @@ def test_selection_with_ties_in_every_set_of_64_experts(E):
     idx, w, _, _ = oracle.route(z, None, cfg.gamma, K, 1, False)
     assert np.array_equal(b.topk_idx.cpu().numpy(), idx)
     assert np.abs(b.topk_w.cpu().numpy() - w).max() <= 2e-6
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,E,H", [(257, 1, 8), (257, 10, 40), (300, 16, 264), (1030, 17, 128), (272, 64, 136), (1100, 64, 2048), (4097, 33, 72),
+                                   (258, 256, 520), (600, 133, 4104)])
+def test_router_logits_of_many_tokens(dtype, T, E, H):
+    """Tiles of 16 or 32 tokens and experts, k-steps left over, and a last one that is not full.  Products of bf16 are exact
+    in fp32 and a sum of H terms in any order is off by at most H 2^-24 times the sum of their magnitudes (fp32: one rounding more)."""
+    cfg = wl.LayerConfig("g", T=T, H=H, E=E, I=8, k_big=1, k_little=1, dtype=dtype, gate_std=0.1, gate_bias_std=1.0)
+    layer = wl.make_layer(cfg, seed=T + E, experts=False)
+    x, Wg = mm.to_device(layer.x, cfg), mm.to_device(layer.Wg, cfg)
+    b = mm.StepBuffers(cfg)
+    mm.moe_route(b.c, x, Wg, torch.from_numpy(layer.gate_bias).cuda(), None, b.logits, False, b.topk_idx, b.topk_w, b.important, b.k_t)
+    x, Wg, bias = x.double().cpu(), Wg.double().cpu(), torch.from_numpy(layer.gate_bias).double()
+    bound = (H + 2) * 2.0 ** -24 * (x.abs() @ Wg.abs().t() + bias.abs())
+    assert bool(((b.logits.double().cpu() - (x @ Wg.t() + bias)).abs() <= bound).all())
+    idx, _, _, _ = oracle.route(b.logits.cpu().numpy(), None, cfg.gamma, 1, 1, False)
+    assert np.array_equal(b.topk_idx.cpu().numpy(), idx)
