@@ -307,6 +307,29 @@ int moe_combine_add(const moe_config* cfg, const float* y, const float* topk_w, 
                     const int32_t* k_t, int32_t j_lo, void* out, void* stream);
 
 /* ------------------------------------------------------------------------------------------
+ * A whole step, and the second pass of Alg. 1, in one call each: the calls above in their order on one
+ * stream, with their checks, outputs and errors (a call that is refused has enqueued what came in front of the
+ * refused part).  What is saved is the host's time for four calls and, above 256 tokens, a launch: the selection
+ * counts the pairs of each expert for the dispatch, in the activations' workspace, which is free at that point.
+ *   moe_layer_step      moe_route, moe_dispatch, moe_expert_ffn (routed and shared), moe_combine
+ *   moe_layer_fallback  moe_route(logits_given), moe_dispatch_from(j_lo = k_little), moe_expert_ffn(routed only),
+ *                       moe_combine_add(j_lo = k_little)
+ * The buffers are those of the separate calls; the struct itself is read during the call only.
+ */
+typedef struct {
+  float* logits; int32_t* topk_idx; float* topk_w; uint8_t* important; int32_t* k_t;
+  int32_t* expert_offsets; int32_t* sorted_token; int32_t* sorted_rank; int32_t* inv_pos;
+  float* y; float* shared_out; void* out;
+  void* dispatch_ws; size_t dispatch_ws_bytes;
+  void* ffn_ws; size_t ffn_ws_bytes;
+} moe_step_buffers;
+int moe_layer_step(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias,
+                   const float* conf, const void* const* expert_w, const void* const* shared_w,
+                   int logits_given, const moe_step_buffers* buffers, void* stream);
+int moe_layer_fallback(const moe_config* cfg, const void* x, const float* conf,
+                       const void* const* expert_w, const moe_step_buffers* buffers, void* stream);
+
+/* ------------------------------------------------------------------------------------------
  * Fallback fetch and prefetch of expert weights (Sec. II-B: experts stay in host DRAM and are
  * loaded when the router asks for them; Sec. III-B: for a token that falls back, the router
  * outputs of its discarded little pass name the experts of the big pass ahead of time, for

@@ -29,7 +29,7 @@ EXPORTS = ("moe_last_error", "moe_device_info", "moe_profile_enable", "moe_profi
            "moe_token_confidence", "moe_dispatch_workspace_bytes", "moe_dispatch", "moe_dispatch_from", "moe_combine_add",
            "moe_expert_ffn_workspace_bytes", "moe_expert_blob_bytes",
            "moe_shared_out_slabs", "moe_layer_decode_workspace_bytes", "moe_layer_decode_init",
-           "moe_layer_decode_status", "moe_layer_decode", "moe_expert_ffn", "moe_expert_ffn_static", "moe_expert_ffn_static_max_bytes",
+           "moe_layer_decode_status", "moe_layer_decode", "moe_layer_step", "moe_layer_fallback", "moe_expert_ffn", "moe_expert_ffn_static", "moe_expert_ffn_static_max_bytes",
            "moe_combine", "moe_cache_create", "moe_cache_destroy",
            "moe_cache_expert_table", "expert_cache_fetch", "moe_expert_ffn_cached", "moe_cache_snapshot", "moe_cache_sync",
            "moe_cache_set_prefetch_limit", "moe_cache_emulate_link", "moe_prefetcher_create", "moe_prefetcher_destroy",
@@ -48,6 +48,13 @@ class moe_config(ctypes.Structure):
                 ("I", ctypes.c_int32), ("k_big", ctypes.c_int32), ("k_little", ctypes.c_int32),
                 ("n_shared", ctypes.c_int32), ("shared_I", ctypes.c_int32 * MOE_MAX_SHARED),
                 ("dtype", ctypes.c_int32), ("renorm", ctypes.c_int32), ("gamma", ctypes.c_float)]
+
+
+class moe_step_buffers(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("logits", "topk_idx", "topk_w", "important", "k_t", "expert_offsets", "sorted_token",
+                                               "sorted_rank", "inv_pos", "y", "shared_out", "out")] + [
+        ("dispatch_ws", ctypes.c_void_p), ("dispatch_ws_bytes", ctypes.c_size_t),
+        ("ffn_ws", ctypes.c_void_p), ("ffn_ws_bytes", ctypes.c_size_t)]
 
 
 class moe_fetch_stats(ctypes.Structure):
@@ -105,6 +112,10 @@ def load_library() -> ctypes.CDLL:
     lib.moe_layer_decode.argtypes = [cfgp, vp, vp, vp, vp, vp, ctypes.POINTER(vp), vp, ctypes.c_int] + [vp] * 11 + [
         vp, sz, vp]
     lib.moe_layer_decode.restype = ctypes.c_int
+    lib.moe_layer_step.argtypes = [cfgp, vp, vp, vp, vp, vp, ctypes.POINTER(vp), ctypes.c_int, ctypes.POINTER(moe_step_buffers), vp]
+    lib.moe_layer_step.restype = ctypes.c_int
+    lib.moe_layer_fallback.argtypes = [cfgp, vp, vp, vp, ctypes.POINTER(moe_step_buffers), vp]
+    lib.moe_layer_fallback.restype = ctypes.c_int
     lib.moe_expert_ffn_static.argtypes = [cfgp, vp, vp, vp, vp, ctypes.POINTER(vp), ctypes.c_int,
                                           ctypes.c_int, vp, vp, vp]
     lib.moe_expert_ffn_static.restype = ctypes.c_int
@@ -170,6 +181,13 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     assert t.is_contiguous(), "tensors passed to the C ABI must be dense"
     return ctypes.c_void_p(t.data_ptr())
+
+
+def _addr(t: Optional[torch.Tensor]):
+    if t is None:
+        return None
+    assert t.is_contiguous(), "tensors passed to the C ABI must be dense"
+    return t.data_ptr()
 
 
 def _stream(stream) -> ctypes.c_void_p:
@@ -334,6 +352,19 @@ def moe_combine(cfg: moe_config, y, topk_w, inv_pos, k_t, shared_out, out, strea
                                       _ptr(k_t), _ptr(shared_out), _ptr(out), _stream(stream)))
 
 
+def moe_layer_step(cfg: moe_config, x, Wg, gate_bias, conf, expert_w, shared_w: Sequence, logits_given, buffers: moe_step_buffers,
+                   stream=None) -> None:
+    sw = (ctypes.c_void_p * max(1, len(shared_w)))(*[t.data_ptr() for t in shared_w])
+    ew = ctypes.c_void_p(expert_w) if isinstance(expert_w, int) else _ptr(expert_w)
+    _check(load_library().moe_layer_step(ctypes.byref(cfg), _ptr(x), _ptr(Wg), _ptr(gate_bias), _ptr(conf), ew, sw,
+                                         int(bool(logits_given)), ctypes.byref(buffers), _stream(stream)))
+
+
+def moe_layer_fallback(cfg: moe_config, x, conf, expert_w, buffers: moe_step_buffers, stream=None) -> None:
+    ew = ctypes.c_void_p(expert_w) if isinstance(expert_w, int) else _ptr(expert_w)
+    _check(load_library().moe_layer_fallback(ctypes.byref(cfg), _ptr(x), _ptr(conf), ew, ctypes.byref(buffers), _stream(stream)))
+
+
 def moe_cache_create(E: int, blob_bytes: int, n_slots: int, host_blobs: torch.Tensor,
                      device_slots: torch.Tensor) -> int:
     assert host_blobs.is_pinned(), "host arena must be pinned memory"
@@ -490,29 +521,37 @@ class StepBuffers:
             moe_layer_decode_init(self.lws, self.lws_bytes)
 
 
+    def as_struct(self) -> moe_step_buffers:
+        """The buffers as the one-call entry points take them, with the addresses of this moment."""
+        return moe_step_buffers(_addr(self.logits), _addr(self.topk_idx), _addr(self.topk_w), _addr(self.important), _addr(self.k_t),
+                                _addr(self.expert_offsets), _addr(self.sorted_token), _addr(self.sorted_rank), _addr(self.inv_pos),
+                                _addr(self.y), _addr(self.shared_out), _addr(self.out), _addr(self.dws), self.dws_bytes,
+                                _addr(self.fws), self.fws_bytes)
+
+
 def layer_step(b: StepBuffers, x, Wg, gate_bias, conf, expert_table, shared_w, logits_given=False,
                stream=None, side_stream=None) -> torch.Tensor:
-    """One step of the layer with all experts resident: the C calls back to back on `stream`.
+    """One step of the layer with all experts resident: one C call on `stream`.
 
-    With `side_stream` (a second torch stream of default priority) the shared experts, which do not
+    With `side_stream` (a second torch stream of default priority) the separate calls: the shared experts, which do not
     depend on the router, are enqueued there first and run under the router, selection and dispatch
-    kernels; the combine waits for them.  Only stream plumbing is added; the calls are the same."""
-    overlap = side_stream is not None and b.shared_out is not None
-    if overlap:
-        main = stream if stream is not None else torch.cuda.current_stream()
-        b.ev_in.record(main)                     # x is ready; the previous combine has read shared_out
-        side_stream.wait_event(b.ev_in)
-        moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, None, shared_w, False, True, b.y,
-                       b.shared_out, b.fws, b.fws_bytes, side_stream)
-        b.ev_shared.record(side_stream)
+    kernels; the combine waits for them.  Only stream plumbing is added; the results are the same."""
+    if side_stream is None or b.shared_out is None:
+        moe_layer_step(b.c, x, Wg, gate_bias, conf, expert_table, shared_w, logits_given, b.as_struct(), stream)
+        return b.out
+    main = stream if stream is not None else torch.cuda.current_stream()
+    b.ev_in.record(main)                         # x is ready; the previous combine has read shared_out
+    side_stream.wait_event(b.ev_in)
+    moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, None, shared_w, False, True, b.y,
+                   b.shared_out, b.fws, b.fws_bytes, side_stream)
+    b.ev_shared.record(side_stream)
     moe_route(b.c, x, Wg, gate_bias, conf, b.logits, logits_given, b.topk_idx, b.topk_w, b.important,
               b.k_t, stream)
     moe_dispatch(b.c, b.topk_idx, b.k_t, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos,
                  b.dws, b.dws_bytes, stream)
-    moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, expert_table, shared_w, True, not overlap, b.y,
+    moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, expert_table, shared_w, True, False, b.y,
                    b.shared_out, b.fws, b.fws_bytes, stream)
-    if overlap:
-        main.wait_event(b.ev_shared)
+    main.wait_event(b.ev_shared)
     moe_combine(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, b.shared_out, b.out, stream)
     return b.out
 
@@ -529,14 +568,8 @@ def layer_decode_step(b: StepBuffers, x, Wg, gate_bias, conf, expert_table, shar
 def fallback_step(b: StepBuffers, x, conf, expert_table, stream=None) -> torch.Tensor:
     """Second pass of Alg. 1 on the buffers of a little pass (layer_step with a confidence above gamma
     for every token, which leaves the router logits in b.logits and the little output in b.out): the
-    tokens rejected by `conf` get the experts of ranks k_little .. k_big-1 added.  Four C calls."""
-    kl = int(b.c.k_little)
-    moe_route(b.c, x, None, None, conf, b.logits, True, b.topk_idx, b.topk_w, b.important, b.k_t, stream)
-    moe_dispatch_from(b.c, b.topk_idx, b.k_t, kl, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos,
-                      b.dws, b.dws_bytes, stream)
-    moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, expert_table, (), True, False, b.y,
-                   b.shared_out, b.fws, b.fws_bytes, stream)
-    moe_combine_add(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, kl, b.out, stream)
+    tokens rejected by `conf` get the experts of ranks k_little .. k_big-1 added.  One C call."""
+    moe_layer_fallback(b.c, x, conf, expert_table, b.as_struct(), stream)
     return b.out
 
 

@@ -195,9 +195,10 @@ extern "C" int moe_device_info(int32_t* n_cu, int32_t* is_gfx950) {
   return MOE_OK;
 }
 
-extern "C" int moe_route(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias,
-                         const float* conf, float* logits, int logits_given, int32_t* topk_idx,
-                         float* topk_w, uint8_t* important, int32_t* k_t, void* stream) {
+namespace {
+// counts: as launch_route; only asked for where router_kernel says kRouterGemm
+int route_step(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias, const float* conf, float* logits,
+               int logits_given, int32_t* topk_idx, float* topk_w, uint8_t* important, int32_t* k_t, int32_t* counts, void* stream) {
   int rc = validate_config(cfg);
   if (rc) return rc;
   if (cfg->T == 0) return MOE_OK;
@@ -217,7 +218,14 @@ extern "C" int moe_route(const moe_config* cfg, const void* x, const void* Wg, c
     if (rc) return rc;
   }
   ProfScope ps(kProfRouteTopk, s);
-  return launch_route(*cfg, conf, logits, topk_idx, topk_w, important, k_t, s);
+  return launch_route(*cfg, conf, logits, topk_idx, topk_w, important, k_t, counts, s);
+}
+}  // namespace
+
+extern "C" int moe_route(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias,
+                         const float* conf, float* logits, int logits_given, int32_t* topk_idx,
+                         float* topk_w, uint8_t* important, int32_t* k_t, void* stream) {
+  return route_step(cfg, x, Wg, gate_bias, conf, logits, logits_given, topk_idx, topk_w, important, k_t, nullptr, stream);
 }
 
 extern "C" int moe_token_confidence(const float* lm_logits, int32_t T, int32_t V, float* conf, void* stream) {
@@ -232,17 +240,11 @@ extern "C" size_t moe_dispatch_workspace_bytes(const moe_config* cfg) {
   return align256(sizeof(int32_t) * (size_t)cfg->E * (size_t)(dispatch_chunks(cfg->T) + 1));
 }
 
-extern "C" int moe_dispatch(const moe_config* cfg, const int32_t* topk_idx, const int32_t* k_t,
-                            int32_t* expert_offsets, int32_t* sorted_token, int32_t* sorted_rank,
-                            int32_t* inv_pos, void* ws, size_t ws_bytes, void* stream) {
-  return moe_dispatch_from(cfg, topk_idx, k_t, 0, expert_offsets, sorted_token, sorted_rank, inv_pos, ws, ws_bytes,
-                           stream);
-}
-
-extern "C" int moe_dispatch_from(const moe_config* cfg, const int32_t* topk_idx, const int32_t* k_t,
-                                 int32_t j_lo, int32_t* expert_offsets, int32_t* sorted_token,
-                                 int32_t* sorted_rank, int32_t* inv_pos, void* ws, size_t ws_bytes,
-                                 void* stream) {
+namespace {
+// counted: the table that launch_route has filled, or null
+int dispatch_step(const moe_config* cfg, const int32_t* topk_idx, const int32_t* k_t, int32_t j_lo, int32_t* expert_offsets,
+                  int32_t* sorted_token, int32_t* sorted_rank, int32_t* inv_pos, void* ws, size_t ws_bytes, int32_t* counted,
+                  void* stream) {
   int rc = validate_config(cfg);
   if (rc) return rc;
   if (j_lo < 0 || j_lo > cfg->k_big) return fail(MOE_E_BADARG, "moe_dispatch_from: j_lo=%d outside [0, k_big=%d]", j_lo, cfg->k_big);
@@ -254,7 +256,22 @@ extern "C" int moe_dispatch_from(const moe_config* cfg, const int32_t* topk_idx,
                 ws_bytes, moe_dispatch_workspace_bytes(cfg));
   ProfScope ps(kProfDispatch, static_cast<hipStream_t>(stream));
   return launch_dispatch(*cfg, topk_idx, k_t, j_lo, expert_offsets, sorted_token, sorted_rank, inv_pos,
-                         static_cast<int32_t*>(ws), static_cast<hipStream_t>(stream));
+                         counted ? counted : static_cast<int32_t*>(ws), counted != nullptr, static_cast<hipStream_t>(stream));
+}
+}  // namespace
+
+extern "C" int moe_dispatch(const moe_config* cfg, const int32_t* topk_idx, const int32_t* k_t,
+                            int32_t* expert_offsets, int32_t* sorted_token, int32_t* sorted_rank,
+                            int32_t* inv_pos, void* ws, size_t ws_bytes, void* stream) {
+  return moe_dispatch_from(cfg, topk_idx, k_t, 0, expert_offsets, sorted_token, sorted_rank, inv_pos, ws, ws_bytes,
+                           stream);
+}
+
+extern "C" int moe_dispatch_from(const moe_config* cfg, const int32_t* topk_idx, const int32_t* k_t,
+                                 int32_t j_lo, int32_t* expert_offsets, int32_t* sorted_token,
+                                 int32_t* sorted_rank, int32_t* inv_pos, void* ws, size_t ws_bytes,
+                                 void* stream) {
+  return dispatch_step(cfg, topk_idx, k_t, j_lo, expert_offsets, sorted_token, sorted_rank, inv_pos, ws, ws_bytes, nullptr, stream);
 }
 
 extern "C" int32_t moe_shared_out_slabs(const moe_config* cfg) {
@@ -410,6 +427,45 @@ extern "C" int moe_combine_add(const moe_config* cfg, const float* y, const floa
   if (!y || !topk_w || !inv_pos || !k_t || !out) return fail(MOE_E_BADARG, "moe_combine_add: null tensor");
   ProfScope ps(kProfCombine, static_cast<hipStream_t>(stream));
   return launch_combine_add(*cfg, y, topk_w, inv_pos, k_t, j_lo, out, static_cast<hipStream_t>(stream));
+}
+
+// ---- a step in one call ----------------------------------------------------------------------------
+extern "C" int moe_layer_step(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias, const float* conf,
+                              const void* const* expert_w, const void* const* shared_w, int logits_given,
+                              const moe_step_buffers* b, void* stream) {
+  int rc = validate_config(cfg);
+  if (rc) return rc;
+  if (!b) return fail(MOE_E_BADARG, "moe_layer_step: buffers are NULL");
+  // the activations' workspace is free until gate/up: the selection's counts go there (never written by a call that is refused)
+  const bool fits = b->ffn_ws && !((uintptr_t)b->ffn_ws & 255) && b->ffn_ws_bytes >= ffn_layout(*cfg).total &&
+                    sizeof(int32_t) * (size_t)cfg->E * (size_t)route_count_rows(cfg->T) <= b->ffn_ws_bytes;
+  int32_t* counted = fits && dispatch_counts(cfg->T) ? static_cast<int32_t*>(b->ffn_ws) : nullptr;
+  rc = route_step(cfg, x, Wg, gate_bias, conf, b->logits, logits_given, b->topk_idx, b->topk_w, b->important, b->k_t, counted, stream);
+  if (rc) return rc;
+  rc = dispatch_step(cfg, b->topk_idx, b->k_t, 0, b->expert_offsets, b->sorted_token, b->sorted_rank, b->inv_pos, b->dispatch_ws,
+                     b->dispatch_ws_bytes, counted, stream);
+  if (rc) return rc;
+  rc = moe_expert_ffn(cfg, x, b->expert_offsets, b->sorted_token, expert_w, shared_w, 1, 1, b->y, b->shared_out, b->ffn_ws,
+                      b->ffn_ws_bytes, stream);
+  if (rc) return rc;
+  return moe_combine(cfg, b->y, b->topk_w, b->inv_pos, b->k_t, b->shared_out, b->out, stream);
+}
+
+extern "C" int moe_layer_fallback(const moe_config* cfg, const void* x, const float* conf, const void* const* expert_w,
+                                  const moe_step_buffers* b, void* stream) {
+  int rc = validate_config(cfg);
+  if (rc) return rc;
+  if (!b) return fail(MOE_E_BADARG, "moe_layer_fallback: buffers are NULL");
+  const int kl = cfg->k_little;
+  rc = moe_route(cfg, x, nullptr, nullptr, conf, b->logits, 1, b->topk_idx, b->topk_w, b->important, b->k_t, stream);
+  if (rc) return rc;
+  rc = moe_dispatch_from(cfg, b->topk_idx, b->k_t, kl, b->expert_offsets, b->sorted_token, b->sorted_rank, b->inv_pos, b->dispatch_ws,
+                         b->dispatch_ws_bytes, stream);
+  if (rc) return rc;
+  rc = moe_expert_ffn(cfg, x, b->expert_offsets, b->sorted_token, expert_w, nullptr, 1, 0, b->y, b->shared_out, b->ffn_ws,
+                      b->ffn_ws_bytes, stream);
+  if (rc) return rc;
+  return moe_combine_add(cfg, b->y, b->topk_w, b->inv_pos, b->k_t, kl, b->out, stream);
 }
 
 // ---- one decode step in one launch --------------------------------------------------------------

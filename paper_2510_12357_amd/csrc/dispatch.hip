@@ -12,7 +12,8 @@
 // as the selection stage produces them.  Two shapes:
 //   * T <= kSmallT: one workgroup, one launch.
 //   * larger T: one workgroup per chunk of 128 tokens; a count kernel, then a scatter kernel
-//     that rebuilds the prefixes of the counts itself.
+//     that rebuilds the prefixes of the counts itself.  In a step of one call the selection kernel has counted already,
+//     per 16 tokens, and the count kernel is not launched (4.6 us as part of a step, whatever it has to do).
 #include "internal.h"
 
 namespace mm {
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
 // which keeps tokens ascending inside a segment.
 constexpr int kChunk = 128;
 static_assert(kChunk == 128, "two mask words per chunk");
-constexpr int kCountSlab = 32 * MOE_MAX_EXPERTS;        // ints of the count table held in LDS at a time
+static_assert(MOE_MAX_EXPERTS <= kBigThreads, "one thread per expert");
 
 __global__ __launch_bounds__(kBigThreads) void dispatch_count_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t, int j_lo, int T, int E, int K,
@@ -123,12 +124,13 @@ __global__ __launch_bounds__(kBigThreads) void dispatch_count_kernel(
 
 __global__ __launch_bounds__(kBigThreads) void dispatch_scatter_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t, int j_lo, int T, int E, int K,
-    const int32_t* __restrict__ counts, int n_chunks, int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ counts, int n_chunks, int per_chunk, int32_t* __restrict__ offsets,
     int32_t* __restrict__ sorted_token, int32_t* __restrict__ sorted_rank,
     int32_t* __restrict__ inv_pos) {
   constexpr int kWords = kChunk / 64, kPerThread = kChunk * MOE_MAX_TOPK / kBigThreads;
   __shared__ unsigned long long s_mask[MOE_MAX_EXPERTS][kWords];
   __shared__ int s_base[MOE_MAX_EXPERTS];       // first position of this chunk inside expert e's segment
+  __shared__ int s_before[MOE_MAX_EXPERTS], s_tot[MOE_MAX_EXPERTS];
   __shared__ int s_wsum[kBigThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int chunk = blockIdx.x, t0 = chunk * kChunk, np = min(kChunk, T - t0) * K;
@@ -146,23 +148,27 @@ __global__ __launch_bounds__(kBigThreads) void dispatch_scatter_kernel(
     if (pe[c] >= 0) atomicOr(&s_mask[pe[c]][tl >> 6], 1ull << (tl & 63));
   }
   // per expert (one thread each, E <= 256 = kBigThreads): pairs in earlier chunks, pairs in all
-  // chunks.  The count table goes through LDS in slabs with coalesced, independent loads (a
-  // per-thread loop over global memory would pay one memory latency per chunk).
-  __shared__ int s_cnt[kCountSlab];
-  int before = 0, tot = 0;
-  const int slab_chunks = kCountSlab / E;                  // >= 32 chunks per slab
-  for (int c0 = 0; c0 < n_chunks; c0 += slab_chunks) {
-    const int nc = min(slab_chunks, n_chunks - c0);
-    __syncthreads();
-    for (int i = tid; i < nc * E; i += kBigThreads) s_cnt[i] = counts[(size_t)c0 * E + i];
-    __syncthreads();
-    if (tid < E)
-      for (int c = 0; c < nc; ++c) {
-        const int v = s_cnt[c * E + tid];
-        if (c0 + c < chunk) before += v;
-        tot += v;
-      }
+  // chunks.  The count table (per_chunk rows for a chunk) is read with coalesced loads by all threads, each of which adds up
+  // every 256/E-th row of an expert; the parts meet in LDS (a per-thread loop over global memory would pay one
+  // memory latency per row).
+  const int first_row = chunk * per_chunk, n_rows = n_chunks * per_chunk, parts = kBigThreads / E;
+  if (tid < E) s_before[tid] = s_tot[tid] = 0;
+  __syncthreads();
+  if (tid < parts * E) {
+    const int e = tid % E;
+    int bf = 0, all = 0;
+    for (int r0 = tid / E; r0 < n_rows; r0 += 8 * parts) {
+      int v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { const int r = r0 + u * parts; v[u] = r < n_rows ? counts[(size_t)r * E + e] : 0; }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { all += v[u]; if (r0 + u * parts < first_row) bf += v[u]; }
+    }
+    atomicAdd(&s_before[e], bf);
+    atomicAdd(&s_tot[e], all);
   }
+  __syncthreads();
+  const int before = tid < E ? s_before[tid] : 0, tot = tid < E ? s_tot[tid] : 0;
   // exclusive prefix of tot over the experts -> expert_offsets
   int incl = tot;
 #pragma unroll
@@ -206,10 +212,12 @@ __global__ void dispatch_empty_kernel(int E, int32_t* offsets) {
 }  // namespace
 
 int dispatch_chunks(int T) { return (T + kChunk - 1) / kChunk; }
+int route_count_rows(int T) { return dispatch_chunks(T) * (kChunk / kRouteTokens); }
+bool dispatch_counts(int T) { return T > kSmallT; }
 
 int launch_dispatch(const moe_config& c, const int32_t* idx, const int32_t* k_t, int j_lo, int32_t* offsets,
                     int32_t* sorted_token, int32_t* sorted_rank, int32_t* inv_pos, int32_t* counts,
-                    hipStream_t s) {
+                    bool counted, hipStream_t s) {
   if (c.T == 0) {
     hipLaunchKernelGGL(dispatch_empty_kernel, dim3(1), dim3(256), 0, s, c.E, offsets);
   } else if (c.T <= kSmallT) {
@@ -217,10 +225,13 @@ int launch_dispatch(const moe_config& c, const int32_t* idx, const int32_t* k_t,
                        c.k_big, offsets, sorted_token, sorted_rank, inv_pos);
   } else {
     const int n_chunks = dispatch_chunks(c.T);
-    hipLaunchKernelGGL(dispatch_count_kernel, dim3((unsigned)n_chunks), dim3(kBigThreads), 0, s, idx, k_t,
-                       j_lo, c.T, c.E, c.k_big, counts);
+    if (!counted)
+      hipLaunchKernelGGL(dispatch_count_kernel, dim3((unsigned)n_chunks), dim3(kBigThreads), 0, s, idx, k_t,
+                         j_lo, c.T, c.E, c.k_big, counts);
+    // rows behind the last 16 tokens do not exist: the selection kernel writes zeros there
     hipLaunchKernelGGL(dispatch_scatter_kernel, dim3((unsigned)n_chunks), dim3(kBigThreads), 0, s, idx, k_t,
-                       j_lo, c.T, c.E, c.k_big, counts, n_chunks, offsets, sorted_token, sorted_rank, inv_pos);
+                       j_lo, c.T, c.E, c.k_big, counts, n_chunks, counted ? kChunk / kRouteTokens : 1, offsets,
+                       sorted_token, sorted_rank, inv_pos);
   }
   return hip_fail(hipGetLastError(), "dispatch launch");
 }

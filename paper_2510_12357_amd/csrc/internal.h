@@ -123,8 +123,10 @@ int launch_decode_sync_clear(void* sync, hipStream_t s);
 int launch_decode_step(const moe_config& c, const DecodeLaunch& L, hipStream_t s);
 
 // ---- selection, dispatch, combine -----------------------------------------------------------
+// counts: null, or the pairs of each expert per kRouteTokens tokens, route_count_rows(T) rows of E
+constexpr int kRouteTokens = 16;
 int launch_route(const moe_config& c, const float* conf, const float* logits, int32_t* idx,
-                 float* w, uint8_t* important, int32_t* k_t, hipStream_t s);
+                 float* w, uint8_t* important, int32_t* k_t, int32_t* counts, hipStream_t s);
 int launch_gate_gemv(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits,
                      hipStream_t s);
 int launch_gate_route(const moe_config& c, const void* x, const void* Wg, const float* bias, const float* conf,
@@ -132,10 +134,12 @@ int launch_gate_route(const moe_config& c, const void* x, const void* Wg, const 
 int launch_gate_mfma(const moe_config& c, const void* x, const void* Wg, const float* bias, float* logits, hipStream_t s);
 int launch_confidence(const float* z, int T, int V, float* conf, hipStream_t s);
 int dispatch_chunks(int T);          // workgroups (token chunks) of the large-T dispatch
-// pairs (t, j) with j_lo <= j < k_t[t]
+int route_count_rows(int T);         // rows of the count table that launch_route fills: whole chunks
+bool dispatch_counts(int T);         // more tokens than one workgroup places
+// pairs (t, j) with j_lo <= j < k_t[t]; counted (j_lo = 0): launch_route has filled `counts`
 int launch_dispatch(const moe_config& c, const int32_t* idx, const int32_t* k_t, int j_lo, int32_t* offsets,
                     int32_t* sorted_token, int32_t* sorted_rank, int32_t* inv_pos, int32_t* counts,
-                    hipStream_t s);
+                    bool counted, hipStream_t s);
 int launch_combine(const moe_config& c, const float* y, const float* w, const int32_t* inv_pos,
                    const int32_t* k_t, const float* shared_out, void* out, hipStream_t s);
 // out[t] += sum over the ranks j_lo <= j < k_t[t]; tokens without such ranks are not written

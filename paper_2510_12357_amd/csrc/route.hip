@@ -19,18 +19,31 @@
 namespace mm {
 namespace {
 
-__global__ __launch_bounds__(kWavesPerBlock * 64) void route_kernel(const float* __restrict__ logits,
-                                                                     const RouteParams P) {
+// COUNT: kRouteTokens tokens per workgroup, and a row of `counts` with the pairs of each expert among them.  Rows
+// behind the last token are zeros.
+template <int WAVES, bool COUNT>
+__global__ __launch_bounds__(WAVES * 64) void route_kernel(const float* __restrict__ logits, int32_t* __restrict__ counts,
+                                                            const RouteParams P) {
+  __shared__ int s_hist[COUNT ? MOE_MAX_EXPERTS : 1];
   const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  if (t >= P.T) return;                                // whole wave leaves together
-  float raw[kPerLane];
-#pragma unroll
-  for (int c = 0; c < kPerLane; ++c) {
-    const int e = lane + 64 * c;
-    raw[c] = (e < P.E) ? logits[(size_t)t * P.E + e] : 0.f;
+  const int t = blockIdx.x * WAVES + (threadIdx.x >> 6);
+  if (COUNT) {
+    for (int e = threadIdx.x; e < P.E; e += WAVES * 64) s_hist[e] = 0;
+    __syncthreads();
   }
-  select_token(P, t, lane, raw);
+  if (t < P.T) {
+    float raw[kPerLane];
+#pragma unroll
+    for (int c = 0; c < kPerLane; ++c) {
+      const int e = lane + 64 * c;
+      raw[c] = (e < P.E) ? logits[(size_t)t * P.E + e] : 0.f;
+    }
+    const Selection sel = select_token(P, t, lane, raw);
+    if (COUNT && lane < sel.k) atomicAdd(&s_hist[sel.expert], 1);
+  }
+  if (!COUNT) return;
+  __syncthreads();
+  for (int e = threadIdx.x; e < P.E; e += WAVES * 64) counts[(size_t)blockIdx.x * P.E + e] = s_hist[e];
 }
 
 // One wave per block of TE experts x TT tokens: the lanes split the hidden dimension, every
@@ -362,11 +375,14 @@ RouteParams make_params(const moe_config& c, const float* conf, int32_t* idx, fl
 }  // namespace
 
 int launch_route(const moe_config& c, const float* conf, const float* logits, int32_t* idx, float* w,
-                 uint8_t* important, int32_t* k_t, hipStream_t s) {
+                 uint8_t* important, int32_t* k_t, int32_t* counts, hipStream_t s) {
   if (c.T == 0) return MOE_OK;
-  const unsigned grid = (unsigned)((c.T + kWavesPerBlock - 1) / kWavesPerBlock);
-  hipLaunchKernelGGL(route_kernel, dim3(grid), dim3(kWavesPerBlock * 64), 0, s, logits,
-                     make_params(c, conf, idx, w, important, k_t));
+  const RouteParams P = make_params(c, conf, idx, w, important, k_t);
+  if (counts)
+    hipLaunchKernelGGL((route_kernel<kRouteTokens, true>), dim3((unsigned)route_count_rows(c.T)), dim3(kRouteTokens * 64), 0, s, logits, counts, P);
+  else
+    hipLaunchKernelGGL((route_kernel<kWavesPerBlock, false>), dim3((unsigned)((c.T + kWavesPerBlock - 1) / kWavesPerBlock)),
+                       dim3(kWavesPerBlock * 64), 0, s, logits, counts, P);
   return hip_fail(hipGetLastError(), "route_kernel launch");
 }
 

@@ -450,3 +450,40 @@ def test_router_logits_of_many_tokens(dtype, T, E, H):
     assert bool(((b.logits.double().cpu() - (x @ Wg.t() + bias)).abs() <= bound).all())
     idx, _, _, _ = oracle.route(b.logits.cpu().numpy(), None, cfg.gamma, 1, 1, False)
     assert np.array_equal(b.topk_idx.cpu().numpy(), idx)
+
+
+# ------------------------------------------------------------------ a step in one call
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("T,E,K,kl,I,shared", [(1, 8, 2, 1, 64, ()), (256, 60, 4, 2, 64, (72,)), (257, 1, 1, 1, 8, ()), (300, 64, 8, 4, 72, (64, 40)),
+                                               (300, 256, 1, 1, 8, ()), (1111, 200, 3, 2, 40, ()), (2049, 7, 7, 3, 16, ())])
+def test_step_in_one_call_equals_the_separate_calls(T, E, K, kl, I, shared, given):
+    """Above 256 tokens the selection counts for the dispatch, where the table fits the activations' workspace
+    (300 tokens, 256 experts of 8: it does not).  Every output array is the same."""
+    cfg = wl.LayerConfig("one", T=T, H=64, E=E, I=I, k_big=K, k_little=kl, shared_I=shared, gate_std=0.3, gate_bias_std=1.0,
+                         w_std=0.1, fallback_ratio=0.4)
+    layer = wl.make_layer(cfg, seed=T + E)
+    x, Wg = mm.to_device(layer.x, cfg), mm.to_device(layer.Wg, cfg)
+    bias, conf = torch.from_numpy(layer.gate_bias).cuda(), torch.from_numpy(layer.conf).cuda()
+    experts = torch.stack([mm.to_device(e, cfg) for e in layer.expert_w])
+    table = torch.tensor([e.data_ptr() for e in experts], dtype=torch.int64, device="cuda")
+    sh = [mm.to_device(s, cfg) for s in layer.shared_w]
+    b1, b2 = mm.StepBuffers(cfg), mm.StepBuffers(cfg)
+    for b in (b1, b2):
+        b.fws.fill_(0x5A)                                          # whatever the last step left there
+        if given:
+            b.logits.copy_(torch.from_numpy(oracle.gate_logits(layer.x, layer.Wg, layer.gate_bias)))
+    arrays = ("logits", "topk_idx", "topk_w", "important", "k_t", "expert_offsets", "sorted_token", "sorted_rank", "inv_pos", "out")
+    b = b2
+    mm.layer_step(b1, x, Wg, bias, conf, table, sh, logits_given=given)
+    mm.moe_route(b.c, x, Wg, bias, conf, b.logits, given, b.topk_idx, b.topk_w, b.important, b.k_t)
+    mm.moe_dispatch(b.c, b.topk_idx, b.k_t, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos, b.dws, b.dws_bytes)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, sh, True, True, b.y, b.shared_out, b.fws, b.fws_bytes)
+    mm.moe_combine(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, b.shared_out, b.out)
+    assert [n for n in arrays if not torch.equal(getattr(b1, n), getattr(b2, n))] == []
+    # the second pass, here on top of a mixed step: the same calls on both sides
+    mm.fallback_step(b1, x, conf, table)
+    mm.moe_route(b.c, x, None, None, conf, b.logits, True, b.topk_idx, b.topk_w, b.important, b.k_t)
+    mm.moe_dispatch_from(b.c, b.topk_idx, b.k_t, kl, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos, b.dws, b.dws_bytes)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
+    mm.moe_combine_add(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, kl, b.out)
+    assert [n for n in arrays if not torch.equal(getattr(b1, n), getattr(b2, n))] == []
