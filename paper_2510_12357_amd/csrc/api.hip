@@ -290,6 +290,53 @@ extern "C" size_t moe_expert_ffn_workspace_bytes(const moe_config* cfg) {
 }
 
 namespace {
+int weight_format(int dtype) { return dtype == MOE_BF16_W8 ? 1 : (dtype == MOE_BF16_MXFP4 ? 0 : 2); }
+
+// Arguments of the gate/up and down launches; `ws` holds the activations
+StreamArgs ffn_args(const moe_config& c, bool routed, bool shared, const void* x, const int32_t* expert_offsets,
+                    const int32_t* sorted_token, const void* const* expert_w, const void* const* shared_w, float* y,
+                    float* shared_out, void* ws) {
+  const FfnLayout L = ffn_layout(c);
+  StreamArgs a = {};
+  a.T = c.T; a.H = c.H; a.E = c.E; a.I = c.I;
+  a.n_routed = routed ? c.E : 0;
+  a.n_shared = shared ? c.n_shared : 0;
+  a.expert_w = expert_w; a.offsets = expert_offsets; a.sorted_token = sorted_token;
+  a.max_pairs = c.T * c.k_big;
+  a.x = x; a.y = y; a.shared_out = shared_out;
+  char* wsb = static_cast<char*>(ws);
+  a.h_routed = wsb + L.h_routed;
+  const SlabPlan plan = slab_plan(c);
+  for (int s = 0; s < a.n_shared; ++s) {
+    a.shared_I[s] = c.shared_I[s];
+    a.shared_kchunk[s] = plan.kchunk[s];
+    a.shared_w[s] = shared_w[s];
+    a.h_shared[s] = wsb + L.h_shared[s];
+  }
+  a.n_slabs = shared ? plan.n_slabs : 0;
+  for (int i = 0; i < a.n_slabs; ++i) { a.slab_shared[i] = plan.slab_shared[i]; a.slab_chunk[i] = plan.slab_chunk[i]; }
+  return a;
+}
+
+void take_route(StreamArgs& a, const FfnRoute& r, const moe_config& c) {
+  a.two_tiles = r.two_tiles;
+  a.wide_panels = r.wide_panels;
+  a.weights_once = r.weights_once;
+  a.two_sums = r.gate_up == kFfnTiled && c.T < kTiledMinT;
+}
+
+int launch_ffn(StreamMode mode, const FfnRoute& r, const moe_config& c, StreamArgs& a, hipStream_t s) {
+  const int wfmt = weight_format(c.dtype);
+  ProfScope ps(mode == kGateUp ? kProfFfnGateUp : kProfFfnDown, s);
+  a.by_rows = mode == kGateUp ? r.by_rows_gate_up : r.by_rows_down;
+  switch (mode == kGateUp ? r.gate_up : r.down) {
+    case kFfnPanels: return launch_stream_panels(mode, wfmt, a, s);
+    case kFfnWide: return launch_wide(mode, a, s);
+    case kFfnTiled: return launch_tiled(mode, wfmt, a, s);
+    default: return launch_stream(mode, c.dtype, a, s);
+  }
+}
+
 int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, const int32_t* expert_offsets,
                const int32_t* sorted_token, const void* const* expert_w, const void* const* shared_w,
                int run_routed, int run_shared, float* y, float* shared_out, void* ws, size_t ws_bytes, void* stream) {
@@ -316,49 +363,13 @@ int expert_ffn(const moe_config* cfg, const FfnRoute* given, const void* x, cons
     return fail(MOE_E_WORKSPACE, "moe_expert_ffn: workspace %p of %zu bytes (need %zu, 256-byte aligned)", ws,
                 ws_bytes, L.total);
 
-  StreamArgs a = {};
-  a.T = cfg->T; a.H = cfg->H; a.E = cfg->E; a.I = cfg->I;
-  a.n_routed = routed ? cfg->E : 0;
-  a.n_shared = shared ? cfg->n_shared : 0;
-  a.expert_w = expert_w; a.offsets = expert_offsets; a.sorted_token = sorted_token;
-  a.max_pairs = cfg->T * cfg->k_big;
-  a.x = x; a.y = y; a.shared_out = shared_out;
-  char* wsb = static_cast<char*>(ws);
-  a.h_routed = wsb + L.h_routed;
-  const SlabPlan plan = slab_plan(*cfg);
-  for (int s = 0; s < a.n_shared; ++s) {
-    a.shared_I[s] = cfg->shared_I[s];
-    a.shared_kchunk[s] = plan.kchunk[s];
-    a.shared_w[s] = shared_w[s];
-    a.h_shared[s] = wsb + L.h_shared[s];
-  }
-  a.n_slabs = shared ? plan.n_slabs : 0;
-  for (int i = 0; i < a.n_slabs; ++i) { a.slab_shared[i] = plan.slab_shared[i]; a.slab_chunk[i] = plan.slab_chunk[i]; }
+  StreamArgs a = ffn_args(*cfg, routed, shared, x, expert_offsets, sorted_token, expert_w, shared_w, y, shared_out, ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int wfmt = cfg->dtype == MOE_BF16_W8 ? 1 : (cfg->dtype == MOE_BF16_MXFP4 ? 0 : 2);
   const int cus = cfg->T >= kTiledMinT ? device_cu_count() : 0;   // a runtime call, which small steps feel
   const FfnRoute r = given ? *given : ffn_route(*cfg, routed, run_shared != 0, cus);
-  a.two_tiles = r.two_tiles;
-  a.wide_panels = r.wide_panels;
-  a.weights_once = r.weights_once;
-  a.two_sums = r.gate_up == kFfnTiled && cfg->T < kTiledMinT;
-  auto launch = [&](StreamMode mode) {
-    switch (mode == kGateUp ? r.gate_up : r.down) {
-      case kFfnPanels: return launch_stream_panels(mode, wfmt, a, s);
-      case kFfnWide: return launch_wide(mode, a, s);
-      case kFfnTiled: return launch_tiled(mode, wfmt, a, s);
-      default: return launch_stream(mode, cfg->dtype, a, s);
-    }
-  };
-  {
-    ProfScope ps(kProfFfnGateUp, s);
-    a.by_rows = r.by_rows_gate_up;
-    rc = launch(kGateUp);
-    if (rc) return rc;
-  }
-  ProfScope ps(kProfFfnDown, s);
-  a.by_rows = r.by_rows_down;
-  return launch(kDown);
+  take_route(a, r, *cfg);
+  rc = launch_ffn(kGateUp, r, *cfg, a, s);
+  return rc ? rc : launch_ffn(kDown, r, *cfg, a, s);
 }
 }  // namespace
 
@@ -430,15 +441,60 @@ extern "C" int moe_combine_add(const moe_config* cfg, const float* y, const floa
 }
 
 // ---- a step in one call ----------------------------------------------------------------------------
+namespace {
+bool complete(const moe_config& c, const moe_step_buffers& b) {
+  return b.logits && b.topk_idx && b.topk_w && b.important && b.k_t && b.expert_offsets && b.sorted_token && b.sorted_rank && b.inv_pos &&
+         b.y && b.out && b.ffn_ws && !((uintptr_t)b.ffn_ws & 255) && b.ffn_ws_bytes >= ffn_layout(c).total;
+}
+bool dispatch_ws_complete(const moe_config& c, const moe_step_buffers& b) {
+  return b.dispatch_ws && !((uintptr_t)b.dispatch_ws & 255) && b.dispatch_ws_bytes >= moe_dispatch_workspace_bytes(&c);
+}
+bool shared_complete(const moe_config& c, const void* const* shared_w, const moe_step_buffers& b) {
+  if (c.n_shared == 0) return true;
+  if (!shared_w || !b.shared_out) return false;
+  for (int s = 0; s < c.n_shared; ++s)
+    if (!shared_w[s] || ((uintptr_t)shared_w[s] & 15)) return false;
+  return true;
+}
+StepDispatch step_dispatch(const moe_config& c, const moe_step_buffers& b, int j_lo) {
+  return {1, j_lo, c.k_big, b.topk_idx, b.k_t, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos};
+}
+
+// The dispatch and the execution stage of a step of fewer than 256 tokens whose gate/up runs in panels, with all arguments there: the
+// gate/up launch builds the dispatch for itself.  The outputs are those of the separate calls, bit for bit.
+int panel_step(const moe_config& c, const FfnRoute& r, const void* x, const void* const* expert_w, const void* const* shared_w,
+               bool shared, int j_lo, const moe_step_buffers& b, hipStream_t s) {
+  StreamArgs a = ffn_args(c, true, shared, x, b.expert_offsets, b.sorted_token, expert_w, shared_w, b.y, b.shared_out, b.ffn_ws);
+  take_route(a, r, c);
+  {
+    ProfScope ps(kProfFfnGateUp, s);
+    const int rc = launch_dispatch_gate_up(weight_format(c.dtype), a, step_dispatch(c, b, j_lo), s);
+    if (rc) return rc;
+  }
+  return launch_ffn(kDown, r, c, a, s);
+}
+bool panels_below_tiles(const moe_config& c, const FfnRoute& r) { return c.T > 0 && c.T < kTiledMinT && r.gate_up == kFfnPanels; }
+}  // namespace
+
 extern "C" int moe_layer_step(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias, const float* conf,
                               const void* const* expert_w, const void* const* shared_w, int logits_given,
                               const moe_step_buffers* b, void* stream) {
   int rc = validate_config(cfg);
   if (rc) return rc;
   if (!b) return fail(MOE_E_BADARG, "moe_layer_step: buffers are NULL");
-  // the activations' workspace is free until gate/up: the selection's counts go there (never written by a call that is refused)
-  const bool fits = b->ffn_ws && !((uintptr_t)b->ffn_ws & 255) && b->ffn_ws_bytes >= ffn_layout(*cfg).total &&
-                    sizeof(int32_t) * (size_t)cfg->E * (size_t)route_count_rows(cfg->T) <= b->ffn_ws_bytes;
+  const bool whole = complete(*cfg, *b);
+  if (whole && x && expert_w && (Wg || logits_given) && shared_complete(*cfg, shared_w, *b) && dispatch_ws_complete(*cfg, *b)) {
+    const FfnRoute r = cfg->T < kTiledMinT ? ffn_route(*cfg, true, true, 0) : FfnRoute{};   // 0: CUs count from 256 tokens on
+    if (panels_below_tiles(*cfg, r)) {
+      rc = route_step(cfg, x, Wg, gate_bias, conf, b->logits, logits_given, b->topk_idx, b->topk_w, b->important, b->k_t, nullptr, stream);
+      if (rc) return rc;
+      rc = panel_step(*cfg, r, x, expert_w, shared_w, cfg->n_shared > 0, 0, *b, static_cast<hipStream_t>(stream));
+      if (rc) return rc;
+      return moe_combine(cfg, b->y, b->topk_w, b->inv_pos, b->k_t, b->shared_out, b->out, stream);
+    }
+  }
+  // the activations' workspace is free until gate/up: the selection's counts go there
+  const bool fits = whole && sizeof(int32_t) * (size_t)cfg->E * (size_t)route_count_rows(cfg->T) <= b->ffn_ws_bytes;
   int32_t* counted = fits && dispatch_counts(cfg->T) ? static_cast<int32_t*>(b->ffn_ws) : nullptr;
   rc = route_step(cfg, x, Wg, gate_bias, conf, b->logits, logits_given, b->topk_idx, b->topk_w, b->important, b->k_t, counted, stream);
   if (rc) return rc;
@@ -459,6 +515,14 @@ extern "C" int moe_layer_fallback(const moe_config* cfg, const void* x, const fl
   const int kl = cfg->k_little;
   rc = moe_route(cfg, x, nullptr, nullptr, conf, b->logits, 1, b->topk_idx, b->topk_w, b->important, b->k_t, stream);
   if (rc) return rc;
+  if (complete(*cfg, *b) && x && expert_w && !cfg->renorm && dispatch_ws_complete(*cfg, *b)) {
+    const FfnRoute r = cfg->T < kTiledMinT ? ffn_route(*cfg, true, false, 0) : FfnRoute{};
+    if (panels_below_tiles(*cfg, r)) {
+      rc = panel_step(*cfg, r, x, expert_w, nullptr, false, kl, *b, static_cast<hipStream_t>(stream));
+      if (rc) return rc;
+      return moe_combine_add(cfg, b->y, b->topk_w, b->inv_pos, b->k_t, kl, b->out, stream);
+    }
+  }
   rc = moe_dispatch_from(cfg, b->topk_idx, b->k_t, kl, b->expert_offsets, b->sorted_token, b->sorted_rank, b->inv_pos, b->dispatch_ws,
                          b->dispatch_ws_bytes, stream);
   if (rc) return rc;

@@ -15,6 +15,7 @@
 //     that rebuilds the prefixes of the counts itself.  In a step of one call the selection kernel has counted already,
 //     per 16 tokens, and the count kernel is not launched (4.6 us as part of a step, whatever it has to do).
 #include "internal.h"
+#include "dispatch_device.h"
 
 namespace mm {
 namespace {
@@ -22,19 +23,6 @@ namespace {
 constexpr int kSmallT = 256;
 constexpr int kSmallThreads = 1024;
 constexpr int kBigThreads = 256;
-
-__device__ __forceinline__ unsigned long long lanemask_lt(int lane) {
-  return lane == 0 ? 0ull : (~0ull >> (64 - lane));
-}
-
-// expert of rank j of token t, at idx[at]; -1 if that is no pair
-__device__ __forceinline__ int pair_expert(const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t,
-                                           int j_lo, int t, int j, size_t at, int E, int K) {
-  int kt = k_t[t];
-  kt = kt < 0 ? 0 : (kt > K ? K : kt);
-  const int e = idx[at];
-  return j >= j_lo && j < kt && (unsigned)e < (unsigned)E ? e : -1;
-}
 
 __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t, int j_lo, int T, int E, int K,

@@ -95,6 +95,14 @@ int launch_stream(StreamMode mode, int dtype, const StreamArgs& a, hipStream_t s
 int launch_stream_lds(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
 // the same for large layers and for prefill of few rows per expert: every wave streams rows of its own (stream_panels.hip)
 int launch_stream_panels(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s);
+// The dispatch of a step of fewer than 256 tokens, built by the gate/up launch itself from the selections (offsets and sorted_token of
+// StreamArgs are not read there): every workgroup for itself, and one writes the arrays for the launches behind it.
+struct StepDispatch {
+  int on, j_lo, k_big;                                 // pairs with a rank of j_lo and more
+  const int32_t* topk_idx; const int32_t* k_t;
+  int32_t* offsets; int32_t* sorted_token; int32_t* sorted_rank; int32_t* inv_pos;
+};
+int launch_dispatch_gate_up(int weight_format, const StreamArgs& a, const StepDispatch& d, hipStream_t s);
 
 // ---- large-m grouped GEMM on LDS-tiled MFMA (prefill regime; bf16 activations) ---------------
 // weight_format: 2 = bf16, 1 = 8-bit codes with row scales, 0 = MXFP4

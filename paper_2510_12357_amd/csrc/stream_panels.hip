@@ -30,6 +30,10 @@
 //   * Steps of 256 tokens and more (MANY) have token numbers of two bytes, too many for LDS at once: the workgroup
 //     looks them up for 32 of its panels at a time.  Their weights pass the caches as well: loaded through them the steps
 //     were slower.
+//   * In a step of one call below 256 tokens the gate/up launch builds the dispatch for itself: 0.8 us more, where a launch of
+//     its own takes 3.5 to 4.8 (60 experts, 8 tokens bf16, whole step 78.7 -> 75.2, 64 tokens MXFP4 93.0 -> 88.8).  Measured and not kept: the
+//     shared experts' gate/up as a launch of its own in which other workgroups select (1 token 5.7 + 20.8 -> 15.6 + 16.1: the
+//     selection's loads wait behind the weight stream, and two launches fill the pipeline twice).
 //   * Groups of more token rows are several blocks of even length, whose panels over the same weights are eight places
 //     apart, i.e. on one XCD at one time.
 //   * The two sums per output (even and odd groups of four 16-byte columns) are those of the two k parts in stream_lds.hip.
@@ -50,6 +54,7 @@
 
 #include "internal.h"
 #include "groups.h"
+#include "dispatch_device.h"
 
 namespace mm {
 namespace {
@@ -172,9 +177,84 @@ struct __attribute__((aligned(1024))) SmemP {
   };
 };
 
+// The dispatch of a step of fewer than 256 tokens, built by a whole workgroup for itself: as dispatch.hip has it (token masks by
+// LDS atomic OR, positions by bit counts), with the token of each position in sm.index and the experts' rows in the lanes of every wave.
+// `scratch` holds the masks and the offsets until the token rows come.  `write`: this workgroup fills the arrays of the C ABI.
+struct DispatchScratch {
+  unsigned long long mask[MOE_MAX_EXPERTS][kTiledMinT / 64];
+  int off[MOE_MAX_EXPERTS + 1];
+};
+// PER: pairs of a thread
+template <int NE, int PER>
+__device__ __forceinline__ void build_dispatch(const StreamArgs& a, const StepDispatch& d, DispatchScratch& sc, unsigned char* index, int tid,
+                                               bool write, int (&v_m)[NE], int (&v_row0)[NE]) {
+  constexpr int kWords = kTiledMinT / 64;
+  const int lane = tid & 63, wave = tid >> 6, E = a.E, K = d.k_big, n = a.T * K;
+  const float inv_k = 1.f / (float)K;
+  int pe[PER], pt[PER];                                  // this thread's pairs tid, tid + kThreadsP, ..: expert (-1: none) and token
+  {
+    int kt[PER];
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {                      // all loads before the first use
+      const int i = min(tid + c * kThreadsP, n - 1);
+      pt[c] = (int)(((float)i + 0.5f) * inv_k);          // i / K: i < 2^12, K <= 16
+      pe[c] = d.topk_idx[i];
+      kt[c] = d.k_t[pt[c]];
+    }
+    for (int i = tid; i < E * kWords; i += kThreadsP) (&sc.mask[0][0])[i] = 0;
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      const int i = tid + c * kThreadsP, j = i - pt[c] * K;
+      if (!(i < n && j >= d.j_lo && j < min(kt[c], K) && (unsigned)pe[c] < (unsigned)E)) pe[c] = -1;
+    }
+  }
+  lds_barrier();
+#pragma unroll
+  for (int c = 0; c < PER; ++c)
+    if (pe[c] >= 0) atomicOr(&sc.mask[pe[c]][pt[c] >> 6], 1ull << (pt[c] & 63));
+  lds_barrier();
+  int base = 0;
+#pragma unroll
+  for (int j = 0; j < NE; ++j) {
+    v_m[j] = v_row0[j] = 0;
+    if (64 * j < E) {
+      const int e = 64 * j + lane;
+      int m = 0;
+      if (e < E)
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) m += __popcll(sc.mask[e][w]);
+      int incl = m;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) { const int v = __shfl_up(incl, s); if (lane >= s) incl += v; }
+      v_m[j] = m; v_row0[j] = base + incl - m;
+      if (wave == 0 && e < E) { sc.off[e] = base + incl - m; if (e == E - 1) sc.off[E] = base + incl; }
+      base += __builtin_amdgcn_readlane(incl, 63);
+    }
+  }
+  lds_barrier();
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int i = tid + c * kThreadsP, t = pt[c];
+    int p = -1;
+    if (pe[c] >= 0) {
+      p = sc.off[pe[c]] + __popcll(sc.mask[pe[c]][t >> 6] & lanemask_lt(t & 63));
+#pragma unroll
+      for (int w = 0; w < kWords - 1; ++w) if (w < t >> 6) p += __popcll(sc.mask[pe[c]][w]);
+      index[p] = (unsigned char)t;
+      if (write) { d.sorted_token[p] = t; d.sorted_rank[p] = i - t * K; }
+    }
+    if (write && i < n) d.inv_pos[i] = p;
+  }
+  if (write) {
+    for (int e = tid; e <= E; e += kThreadsP) d.offsets[e] = sc.off[e];
+    for (int i = base + tid; i < n; i += kThreadsP) { d.sorted_token[i] = -1; d.sorted_rank[i] = -1; }
+  }
+}
+
 // MANY: 256 tokens and more; RT: tiles of four quads of a wave in a panel, at most
 template <int MODE, int WB, bool MANY, int RT>
-__global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2))) void stream_panel_kernel(const StreamArgs a) {
+__global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2))) void stream_panel_kernel(const StreamArgs a, const StepDispatch d) {
+  constexpr bool DISPATCH = MODE == kGateUp && !MANY;
   typedef Unit<WB> U;
   constexpr int OQ = MODE == kGateUp ? 2 : 4;            // output columns per quad
   constexpr int kPanelQuads = 4 * RT * kWaves;           // quads of a panel, at most
@@ -188,17 +268,35 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
   constexpr int NE = MOE_MAX_EXPERTS / 64;
   int v_end[NE], v_m[NE], v_row0[NE], v_lo[NE], v_hi[NE];   // token blocks up to and with the expert; rows, first dispatch position; weights
   int routed_blocks = 0;
+  const bool dispatch = DISPATCH && d.on != 0;
 #pragma unroll
   for (int j = 0; j < NE; ++j) {
     v_end[j] = v_m[j] = v_row0[j] = v_lo[j] = v_hi[j] = 0;
+    if (64 * j + lane < a.n_routed) {
+      GroupSrc src = {};
+      if (dispatch) src.blob = a.expert_w[64 * j + lane];
+      else src = load_group_src<MODE>(a, n_sh + 64 * j + lane);
+      v_m[j] = src.m; v_row0[j] = src.row0;
+      v_lo[j] = (int)(uint64_t)src.blob; v_hi[j] = (int)((uint64_t)src.blob >> 32);
+    }
+  }
+  if constexpr (DISPATCH) {
+    static_assert(sizeof(DispatchScratch) <= sizeof(sm.tok), "the token rows' place");
+    if (dispatch) {
+      DispatchScratch& sc = *reinterpret_cast<DispatchScratch*>(sm.tok[0]);
+      const bool write = blockIdx.x == gridDim.x - 1;
+      if (a.max_pairs <= kThreadsP) build_dispatch<NE, 1>(a, d, sc, sm.index, tid, write, v_m, v_row0);
+      else if (a.max_pairs <= 2 * kThreadsP) build_dispatch<NE, 2>(a, d, sc, sm.index, tid, write, v_m, v_row0);
+      else build_dispatch<NE, (kIndexMax + kThreadsP - 1) / kThreadsP>(a, d, sc, sm.index, tid, write, v_m, v_row0);
+#pragma unroll
+      for (int j = 0; j < NE; ++j)
+        if ((v_lo[j] | v_hi[j]) == 0) v_m[j] = 0;              // an expert without weights
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NE; ++j) {
     if (64 * j < a.n_routed) {
-      int nb = 0;
-      if (64 * j + lane < a.n_routed) {
-        const GroupSrc src = load_group_src<MODE>(a, n_sh + 64 * j + lane);
-        v_m[j] = src.m; v_row0[j] = src.row0;
-        v_lo[j] = (int)(uint64_t)src.blob; v_hi[j] = (int)((uint64_t)src.blob >> 32);
-        nb = token_blocks<WB>(src.m);
-      }
+      int nb = token_blocks<WB>(v_m[j]);
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
         const int v = __shfl_up(nb, d);
@@ -208,7 +306,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
       routed_blocks = __builtin_amdgcn_readlane(v_end[j], 63);
     }
   }
-  if (!MANY && MODE == kGateUp && a.n_routed)
+  if (DISPATCH && a.n_routed && !dispatch)
     for (int i = tid; i < a.max_pairs; i += kThreadsP) sm.index[i] = (unsigned char)clampi(a.sorted_token[i], 0, a.T - 1);
 
   // ---- panels: every group's quads in panels of at most `per`, the smallest size that needs no more rounds of workgroups ----
@@ -619,34 +717,40 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
 }
 
 template <int MODE, int WB, bool MANY, int RT>
-int launch_panels_typed(const StreamArgs& a, hipStream_t s) {
+int launch_panels_typed(const StreamArgs& a, const StepDispatch& d, hipStream_t s) {
   if (a.T > kPanelsMaxT) return fail(MOE_E_UNSUPPORTED, "stream_panel_kernel: T=%d", a.T);
   const long items = item_upper_bound((StreamMode)MODE, a, 32);
   if (items <= 0) return MOE_OK;
   long grid = device_cu_count();                          // 158 KB of LDS: one workgroup per CU
   if (grid > items) grid = items;
-  hipLaunchKernelGGL((stream_panel_kernel<MODE, WB, MANY, RT>), dim3((unsigned)grid), dim3(kThreadsP), 0, s, a);
+  hipLaunchKernelGGL((stream_panel_kernel<MODE, WB, MANY, RT>), dim3((unsigned)grid), dim3(kThreadsP), 0, s, a, d);
   return hip_fail(hipGetLastError(), "stream_panel_kernel launch");
 }
 template <int MODE, int WB>
-int launch_panels(const StreamArgs& a, hipStream_t s) {
+int launch_panels(const StreamArgs& a, const StepDispatch& d, hipStream_t s) {
   const bool many = a.T >= kTiledMinT;
   if constexpr (WB != 2)                       // bf16 weights: never faster (ffn_route)
-    if (a.wide_panels) return many ? launch_panels_typed<MODE, WB, true, 2>(a, s) : launch_panels_typed<MODE, WB, false, 2>(a, s);
-  return many ? launch_panels_typed<MODE, WB, true, 1>(a, s) : launch_panels_typed<MODE, WB, false, 1>(a, s);
+    if (a.wide_panels) return many ? launch_panels_typed<MODE, WB, true, 2>(a, d, s) : launch_panels_typed<MODE, WB, false, 2>(a, d, s);
+  return many ? launch_panels_typed<MODE, WB, true, 1>(a, d, s) : launch_panels_typed<MODE, WB, false, 1>(a, d, s);
+}
+template <int MODE>
+int launch_panels_of(int weight_format, const StreamArgs& a, const StepDispatch& d, hipStream_t s) {
+  if (weight_format == 2) return launch_panels<MODE, 2>(a, d, s);
+  if (weight_format == 1) return launch_panels<MODE, 1>(a, d, s);
+  return launch_panels<MODE, 0>(a, d, s);
 }
 
 }  // namespace
 
 int launch_stream_panels(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
-  if (mode == kGateUp) {
-    if (weight_format == 2) return launch_panels<kGateUp, 2>(a, s);
-    if (weight_format == 1) return launch_panels<kGateUp, 1>(a, s);
-    return launch_panels<kGateUp, 0>(a, s);
-  }
-  if (weight_format == 2) return launch_panels<kDown, 2>(a, s);
-  if (weight_format == 1) return launch_panels<kDown, 1>(a, s);
-  return launch_panels<kDown, 0>(a, s);
+  const StepDispatch none = {};
+  return mode == kGateUp ? launch_panels_of<kGateUp>(weight_format, a, none, s) : launch_panels_of<kDown>(weight_format, a, none, s);
+}
+
+int launch_dispatch_gate_up(int weight_format, const StreamArgs& a, const StepDispatch& d, hipStream_t s) {
+  if (a.T <= 0 || a.T >= kTiledMinT || !d.on || a.n_routed != a.E || a.max_pairs != a.T * d.k_big || d.k_big > MOE_MAX_TOPK)
+    return fail(MOE_E_UNSUPPORTED, "dispatch beside gate/up: T=%d", a.T);
+  return launch_panels_of<kGateUp>(weight_format, a, d, s);
 }
 
 }  // namespace mm

@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_kernel_edges as edges
 import test_gpu_parity as parity
 from paper_2510_12357_amd import workloads as wl
 
@@ -176,6 +177,14 @@ def test_router_tests_reach_both_kernels(route):
     gemv = [c for c in _cases(parity.test_gate_logits)
             if route.router(wl.LayerConfig("r", T=c[1], H=c[2], E=c[3], I=8, k_big=1, k_little=1, dtype=c[0])) == GEMV]
     assert {c[0] for c in gemv} == {"bf16", "fp32"} and any(c[1] % 4 for c in gemv)
+
+
+def test_dispatch_beside_gate_up_is_tested_where_the_rules_take_it(route):
+    """Its cases run in panels, as whole steps and (most of them) as fallback passes."""
+    cases = _cases(edges.test_dispatch_built_by_the_gate_up_launch)
+    layers = [wl.LayerConfig("f", T=T, H=H, E=E, I=I, k_big=K, k_little=kl, shared_I=sh, dtype=d) for d, T, E, K, kl, H, I, sh in cases]
+    assert all(route.raw(c, True, True)[0] == PANELS for c in layers)
+    assert sum(route.raw(c, True, False)[0] == PANELS for c in layers) >= 5
 
 
 def _cases(test):

@@ -487,3 +487,53 @@ def test_step_in_one_call_equals_the_separate_calls(T, E, K, kl, I, shared, give
     mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
     mm.moe_combine_add(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, kl, b.out)
     assert [n for n in arrays if not torch.equal(getattr(b1, n), getattr(b2, n))] == []
+
+
+@pytest.mark.parametrize("dtype,T,E,K,kl,H,I,shared", [
+    ("bf16mx4", 8, 200, 16, 8, 1024, 384, (128,)), ("bf16mx4", 63, 256, 3, 1, 512, 640, ()), ("bf16mx4", 64, 200, 8, 4, 1024, 384, ()),
+    ("bf16mx4", 65, 200, 16, 8, 1024, 384, (128, 256)), ("bf16mx4", 255, 200, 16, 8, 1024, 384, (128,)),
+    ("bf16w8", 1, 40, 4, 2, 1024, 2064, (48,)), ("bf16w8", 130, 65, 8, 4, 1040, 1040, ()), ("bf16w8", 255, 40, 2, 1, 1024, 2064, (48,))])
+def test_dispatch_built_by_the_gate_up_launch(dtype, T, E, K, kl, H, I, shared):
+    """Steps in panels below 256 tokens: one, two and eight pairs per thread, one to four words of a token mask, all sets of 64
+    experts, an expert without weights; the pass and its fallback pass have every array and every bit of the separate calls."""
+    cfg = wl.LayerConfig("fold", T=T, H=H, E=E, I=I, k_big=K, k_little=kl, shared_I=shared, dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    c = mm.make_config(cfg)
+
+    def blob(i):
+        n = mm.moe_expert_blob_bytes(c, i)
+        b = torch.randint(0, 256, (n,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
+        w = 3 * H * i
+        if dtype == "bf16mx4":
+            b[w // 2:] = torch.randint(118, 122, (n - w // 2,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
+        else:
+            b[:w] = (torch.randn((w,), generator=g, device="cuda") * 50).to(torch.float8_e4m3fn).view(torch.uint8)
+            b[w:] = torch.full(((n - w) // 4,), 4e-4, device="cuda").view(torch.uint8)
+        return b
+    one = [blob(I) for _ in range(3)]                               # three different experts, over and over
+    table = torch.tensor([one[e % 3].data_ptr() for e in range(E)], dtype=torch.int64, device="cuda")
+    table[E // 2] = 0
+    sh = [blob(i) for i in shared]
+    x = torch.randn((T, H), generator=g, device="cuda").bfloat16()
+    Wg = (torch.randn((E, H), generator=g, device="cuda") * 0.05).bfloat16()
+    conf = torch.rand((T,), generator=g, device="cuda")
+    b1, b = mm.StepBuffers(cfg), mm.StepBuffers(cfg)
+    arrays = ("logits", "topk_idx", "topk_w", "important", "k_t", "expert_offsets", "sorted_token", "sorted_rank", "inv_pos", "out")
+
+    def same():
+        P = int(b.expert_offsets[-1])
+        return [n for n in arrays if not torch.equal(getattr(b1, n), getattr(b, n))] == [] and torch.equal(b1.y[:P], b.y[:P])
+    mm.layer_step(b1, x, Wg, None, conf, table, sh)
+    mm.moe_route(b.c, x, Wg, None, conf, b.logits, False, b.topk_idx, b.topk_w, b.important, b.k_t)
+    mm.moe_dispatch(b.c, b.topk_idx, b.k_t, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos, b.dws, b.dws_bytes)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, sh, True, True, b.y, b.shared_out, b.fws, b.fws_bytes)
+    mm.moe_combine(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, b.shared_out, b.out)
+    assert same() and bool(b.out.isfinite().all()) and b.out.float().abs().max() > 0
+    for a in (b1, b):
+        a.fws.fill_(0x5A)
+    mm.fallback_step(b1, x, conf, table)
+    mm.moe_route(b.c, x, None, None, conf, b.logits, True, b.topk_idx, b.topk_w, b.important, b.k_t)
+    mm.moe_dispatch_from(b.c, b.topk_idx, b.k_t, kl, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos, b.dws, b.dws_bytes)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, (), True, False, b.y, b.shared_out, b.fws, b.fws_bytes)
+    mm.moe_combine_add(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, kl, b.out)
+    assert same()
