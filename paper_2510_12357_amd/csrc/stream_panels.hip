@@ -34,6 +34,9 @@
 //     its own takes 3.5 to 4.8 (60 experts, 8 tokens bf16, whole step 78.7 -> 75.2, 64 tokens MXFP4 93.0 -> 88.8).  Measured and not kept: the
 //     shared experts' gate/up as a launch of its own in which other workgroups select (1 token 5.7 + 20.8 -> 15.6 + 16.1: the
 //     selection's loads wait behind the weight stream, and two launches fill the pipeline twice).
+//   * What stands in front of the first load counts twice in a step.  From a workgroup's first instruction to its first loads of weights,
+//     us: gate/up 4.7 -> 4.1 (1.9 of them for the dispatch), down 3.8 -> 3.3; the first data come 2 us later.  Measured and not kept:
+//     the first loads before the table of panels, and token rows before weights (first product as late as before).
 //   * Groups of more token rows are several blocks of even length, whose panels over the same weights are eight places
 //     apart, i.e. on one XCD at one time.
 //   * The two sums per output (even and odd groups of four 16-byte columns) are those of the two k parts in stream_lds.hip.
@@ -165,6 +168,15 @@ __device__ __forceinline__ int token_key(int row) {
   return WB == 0 && MANY ? (row & 9) | (row & 2) << 1 | (row & 4) >> 1 : row;
 }
 
+// a / b, a >= 0, b >= 1, by the hardware's reciprocal (off by at most 2^-23 of it): the product is off by less than one while the quotient
+// stays below 2^21, and panels, blocks and quads of a step do.
+// Every workgroup's first loads wait for a dozen of these; the compiler's integer division takes 35 instructions, one after the other.
+__device__ __forceinline__ int quotient(int a, int b) {
+  int n = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const int rest = a - n * b;
+  return n + (rest >= b ? 1 : 0) - (rest < 0 ? 1 : 0);
+}
+
 template <int WB> __device__ __forceinline__ int token_blocks(int m) { return (m + Unit<WB>::kBlock - 1) / Unit<WB>::kBlock; }
 
 template <int WB>
@@ -223,9 +235,7 @@ __device__ __forceinline__ void build_dispatch(const StreamArgs& a, const StepDi
       if (e < E)
 #pragma unroll
         for (int w = 0; w < kWords; ++w) m += __popcll(sc.mask[e][w]);
-      int incl = m;
-#pragma unroll
-      for (int s = 1; s < 64; s <<= 1) { const int v = __shfl_up(incl, s); if (lane >= s) incl += v; }
+      const int incl = wave_scan(m);
       v_m[j] = m; v_row0[j] = base + incl - m;
       if (wave == 0 && e < E) { sc.off[e] = base + incl - m; if (e == E - 1) sc.off[E] = base + incl; }
       base += __builtin_amdgcn_readlane(incl, 63);
@@ -259,6 +269,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
   constexpr int OQ = MODE == kGateUp ? 2 : 4;            // output columns per quad
   constexpr int kPanelQuads = 4 * RT * kWaves;           // quads of a panel, at most
   __shared__ SmemP<WB> sm;
+  fetch_arguments<sizeof(StreamArgs) + (DISPATCH ? sizeof(StepDispatch) : 0)>();
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int q = lane >> 4, c16 = lane & 15;
   const int n_sh = MODE == kDown ? a.n_slabs : a.n_shared;
@@ -297,11 +308,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
   for (int j = 0; j < NE; ++j) {
     if (64 * j < a.n_routed) {
       int nb = token_blocks<WB>(v_m[j]);
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int v = __shfl_up(nb, d);
-        if (lane >= d) nb += v;
-      }
+      nb = wave_scan(nb);
       v_end[j] = routed_blocks + nb;
       routed_blocks = __builtin_amdgcn_readlane(v_end[j], 63);
     }
@@ -314,17 +321,17 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int Qr = (MODE == kGateUp ? a.I : a.H) / OQ;
   auto shared_quads = [&](int g) -> int { return (MODE == kGateUp ? a.shared_I[g] : a.H) / OQ; };
   auto panels_with = [&](int per) -> int {
-    int n = routed_blocks * ((Qr + per - 1) / per);
-    for (int g = 0; g < n_sh; ++g) n += sh_blocks * ((shared_quads(g) + per - 1) / per);
+    int n = routed_blocks * quotient(Qr + per - 1, per);
+    for (int g = 0; g < n_sh; ++g) n += sh_blocks * quotient(shared_quads(g) + per - 1, per);
     return n;
   };
   int per;
   {
-    const int rounds = (panels_with(kPanelQuads) + grid - 1) / grid;
+    const int rounds = quotient(panels_with(kPanelQuads) + grid - 1, grid);
     const uint64_t fits = __ballot(panels_with(min(lane + 1, kPanelQuads)) <= rounds * grid);
     per = uniform((int)__builtin_ctzll(fits | 1ull << (kPanelQuads - 1)) + 1);
   }
-  const int npr = (Qr + per - 1) / per;
+  const int npr = quotient(Qr + per - 1, per);
   const int total = panels_with(per), total_sh = total - routed_blocks * npr;
 
   // this lane's 16 bytes of the four column groups of a unit of weights, and of four k-steps of a token row; column c of row r
@@ -342,23 +349,22 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
 #pragma unroll 1
   for (int first = blockIdx.x; first < total; first += kLook * grid) {
     // ---- panels first, first + grid, ..: one per lane ----
-    const int np = min(kLook, (total - first + grid - 1) / grid);
+    const int np = min(kLook, quotient(total - first + grid - 1, grid));
     int p_g = 0, p_qa = 0, p_n = 0, p_r0 = 0, p_rows = 0, p_m = a.T, p_row0 = 0, p_lo = 0, p_hi = 0;
     {
       int item = first + min(lane, np - 1) * grid, nb = sh_blocks, panels = npr, Q = Qr;
       const bool sh = item < total_sh;
-      if (sh) {
-        for (;; ++p_g) {
-          Q = shared_quads(p_g); panels = (Q + per - 1) / per;
-          if (item < nb * panels || p_g == n_sh - 1) break;
-          item -= nb * panels;
-        }
-        const uint64_t blob = (uint64_t)a.shared_w[MODE == kDown ? a.slab_shared[p_g] : p_g];
-        p_lo = (int)blob; p_hi = (int)(blob >> 32);
-      } else {
-        item -= total_sh;
+      int rest = sh ? item : 0x7fffffff;                 // counts down to this lane's group: an index of its own would be a load from memory per lane
+      for (int g = 0; g < n_sh; ++g) {
+        const int Qg = shared_quads(g), pg = quotient(Qg + per - 1, per), n = sh_blocks * pg;
+        const uint64_t blob = (uint64_t)a.shared_w[MODE == kDown ? a.slab_shared[g] : g];
+        const bool here = rest >= 0 && rest < n;
+        p_g = here ? g : p_g; Q = here ? Qg : Q; panels = here ? pg : panels; item = here ? rest : item;
+        p_lo = here ? (int)blob : p_lo; p_hi = here ? (int)(blob >> 32) : p_hi;
+        rest -= n;
       }
-      const int blk = sh ? 0 : item / npr;               // the expert that holds this block: the first whose blocks end behind it
+      if (!sh) item -= total_sh;
+      const int blk = sh ? 0 : quotient(item, npr);               // the expert that holds this block: the first whose blocks end behind it
       int e = 0, m = a.T, row0 = 0, lo = 0, hi = 0, end = 0;
 #pragma unroll
       for (int j = 0; j < NE; ++j) {
@@ -382,10 +388,10 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
       m = p_m;
       int tb = 0, panel = item;
       if (nb > 1) {
-        const int b8 = item / (8 * nb), rem = item - b8 * 8 * nb, w8 = min(8, panels - 8 * b8);
-        tb = rem / w8; panel = 8 * b8 + (rem - tb * w8);
+        const int b8 = quotient(item, 8 * nb), rem = item - b8 * 8 * nb, w8 = min(8, panels - 8 * b8);
+        tb = quotient(rem, w8); panel = 8 * b8 + (rem - tb * w8);
       }
-      const int block = nb > 1 ? (m + nb - 1) / nb : m, base = Q / panels, more = Q - base * panels;
+      const int block = nb > 1 ? quotient(m + nb - 1, nb) : m, base = quotient(Q, panels), more = Q - base * panels;
       p_qa = panel * base + min(panel, more);
       p_n = base + (panel < more ? 1 : 0);
       p_r0 = tb * block; p_rows = min(block, m - p_r0);
@@ -420,7 +426,7 @@ __global__ __launch_bounds__(kThreadsP) __attribute__((amdgpu_waves_per_eu(2, 2)
     auto tile_start = [](int wn, int r) -> int { return r == 0 ? 0 : (RT > 1 && wn > 4 && r == 1 ? (wn + 1) / 2 : wn); };
     auto slice_rows = [](const Panel& p) -> int { return (p.rows + U::kRowsPerLoad - 1) & ~(U::kRowsPerLoad - 1); };
     // units per slice of token rows
-    auto slice_units = [&](const Panel& p, int nu) -> int { return min(nu, (U::kBuffer >> U::kRowShift) / slice_rows(p)); };
+    auto slice_units = [&](const Panel& p, int nu) -> int { return min(nu, quotient(U::kBuffer >> U::kRowShift, slice_rows(p))); };
 
     // ---- weight cursor ----
     int w_p = -1, w_u = 0, w_nu = 0, w_left = 0, w_n = 0, w_tile = 0, w_tiles = 1, slot = 0;
