@@ -184,19 +184,15 @@ def side_stream(torch):
 SEPARATE_CALLS = False
 
 
-def one_launch(cfg) -> bool:
-    """Which decode steps run as one launch (moe_layer_decode): at most 32 tokens, bf16 weights, and
-    shared experts to stream while the selection is computed - where it was measured to be the faster
-    of the two ways through the C ABI (60-expert layer, one launch against separate calls, us per
-    step: b = 1 43 / 51, b = 8 79 / 88, b = 16 119 / 122, b = 24 147 / 148, b = 32 166 / 168,
-    b = 48 196 / 192, b = 64 211 / 205; without shared experts nothing hides the selection, and the
-    8-bit instance of the kernel is short of registers; those steps take the separate calls)."""
+def decode_call(cfg) -> bool:
+    """Which steps go through moe_layer_decode: at most 32 tokens, bf16 weights, shared experts.  In large layers the
+    library runs them, like moe_layer_step, as a few launches, in the others as one."""
     return not SEPARATE_CALLS and 0 < cfg.T <= 32 and cfg.dtype == "bf16" and len(cfg.shared_I) > 0
 
 
 def run_steps(mm, torch, layers: DeviceLayers, bufs, n: int, first: int = 0):
     L = layers.L
-    if one_launch(layers.cfg):
+    if decode_call(layers.cfg):
         for i in range(first, first + n):
             l = i % L
             mm.layer_decode_step(bufs, layers.x[l], layers.Wg[l], layers.bias[l], layers.conf[l], layers.table[l],
@@ -937,7 +933,7 @@ def main():
     main_res = time_workload(mm, torch, cfg, args.steps, args.warmup, args.layers)
     work = algorithmic_work(cfg, main_res["P_mean"], main_res["D_mean"])
     kern = main_res["kernels"]
-    fused = one_launch(cfg)
+    fused = "decode_step" in kern
     gu = kern["decode_step"] if fused else kern["ffn_gate_up"]
     if fused:       # the one kernel of the step moves all of the step's bytes
         work["gate_up_bytes"], work["gate_up_flops"] = work["step_bytes"], work["step_flops"]

@@ -247,16 +247,17 @@ int moe_combine(const moe_config* cfg, const float* y, const float* topk_w,
                 void* stream);
 
 /* ------------------------------------------------------------------------------------------
- * One decode step of the layer in ONE kernel launch: moe_route + moe_dispatch + moe_expert_ffn +
+ * One decode step of the layer: moe_route + moe_dispatch + moe_expert_ffn +
  * moe_combine (selection and execution stage of Sec. II-A with the per-token expert count of
  * Sec. III-A / Alg. 1) for steps of at most 64 tokens, dtype MOE_BF16 or MOE_BF16_W8.  Same
  * arithmetic and the same outputs as the four calls: logits, topk_idx, topk_w, important, k_t,
  * expert_offsets, sorted_token, sorted_rank, inv_pos, y, shared_out and out are all written and
  * have the layouts documented above.  A decode step only streams 0.1 .. 1 GB of weights, so the
- * launch gaps and pipeline ramps of five dependent kernels are a large part of it; here the
+ * launch gaps and pipeline ramps of five dependent kernels are a large part of it.  Large layers run the
+ * launches of moe_layer_step (below); the others ONE persistent kernel in which the
  * shared experts (which need nothing from the router) stream while the selection is computed,
- * and the down projections, the final sum and the next weights overlap inside one persistent
- * kernel whose workgroups hand results over through device memory.
+ * and the down projections, the final sum and the next weights overlap; its workgroups hand results
+ * over through device memory.
  *
  * expert_w  DEVICE array of E device pointers; every expert the step selects must be non-NULL
  *           (an expert with a NULL entry is skipped and its rows of y keep their old contents)

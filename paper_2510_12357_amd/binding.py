@@ -558,7 +558,7 @@ def layer_step(b: StepBuffers, x, Wg, gate_bias, conf, expert_table, shared_w, l
 
 def layer_decode_step(b: StepBuffers, x, Wg, gate_bias, conf, expert_table, shared_w, logits_given=False,
                       stream=None) -> torch.Tensor:
-    """One decode step (at most 64 tokens) of the layer in one launch: a single C call."""
+    """One decode step (at most 64 tokens) of the layer: a single C call."""
     moe_layer_decode(b.c, x, Wg, gate_bias, conf, expert_table, shared_w, b.logits, logits_given, b.topk_idx,
                      b.topk_w, b.important, b.k_t, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos, b.y,
                      b.shared_out, b.out, b.lws, b.lws_bytes, stream)

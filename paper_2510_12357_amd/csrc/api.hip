@@ -585,9 +585,26 @@ extern "C" int moe_layer_decode(const moe_config* cfg, const void* x, const void
   if (!ws || ((uintptr_t)ws & 255) || ws_bytes < sync_bytes + L.total)
     return fail(MOE_E_WORKSPACE, "moe_layer_decode: workspace %p of %zu bytes (need %zu, 256-byte aligned)", ws, ws_bytes,
                 sync_bytes + L.total);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  char* wsb = static_cast<char*>(ws) + sync_bytes;
+  // Large layers take the launches of moe_layer_step, whose weight stream no wave with other work stands in.  us per step, one launch /
+  // these: 60 experts of 1408 + 5632, 1 token 42.9 / 40.5, 4 tokens 59.5 / 54.4, 8 tokens 78.7 / 74.6, 16 tokens 109.3 / 103.0, 32 tokens
+  // 158.6 / 152.6, 64 tokens 202.7 / 190.6; 64 of 1408 + 2 shared, 1 token 45.0 / 40.8, 8 tokens 95.6 / 95.3, 32 tokens 189.6 / 179.4.
+  const FfnRoute r = ffn_route(*cfg, true, true, 0);
+  if (panels_below_tiles(*cfg, r)) {
+    moe_step_buffers b = {};
+    b.logits = logits; b.topk_idx = topk_idx; b.topk_w = topk_w; b.important = important; b.k_t = k_t;
+    b.expert_offsets = expert_offsets; b.sorted_token = sorted_token; b.sorted_rank = sorted_rank; b.inv_pos = inv_pos;
+    b.y = y; b.shared_out = shared_out; b.out = out;
+    b.ffn_ws = wsb; b.ffn_ws_bytes = ws_bytes - sync_bytes;
+    rc = route_step(cfg, x, Wg, gate_bias, conf, logits, logits_given, topk_idx, topk_w, important, k_t, nullptr, stream);
+    if (rc) return rc;
+    rc = panel_step(*cfg, r, x, expert_w, shared_w, cfg->n_shared > 0, 0, b, s);
+    if (rc) return rc;
+    return moe_combine(cfg, y, topk_w, inv_pos, k_t, shared_out, out, stream);
+  }
   DecodeLaunch D = {};
   D.x = x; D.Wg = Wg; D.gate_bias = gate_bias; D.conf = conf; D.expert_w = expert_w;
-  char* wsb = static_cast<char*>(ws) + sync_bytes;
   for (int s = 0; s < cfg->n_shared; ++s) { D.shared_w[s] = shared_w[s]; D.h_shared[s] = wsb + L.h_shared[s]; }
   D.logits_given = logits_given != 0;
   D.logits = logits; D.topk_idx = topk_idx; D.topk_w = topk_w; D.important = important; D.k_t = k_t;
@@ -595,8 +612,8 @@ extern "C" int moe_layer_decode(const moe_config* cfg, const void* x, const void
   D.h_routed = wsb + L.h_routed; D.y = y; D.shared_out = shared_out; D.out = out;
   D.sync = ws;
   D.spin_limit = 1 << 18;                 // a good tenth of a second of polling: far beyond any wait of a healthy step
-  ProfScope ps(kProfDecodeStep, static_cast<hipStream_t>(stream));
-  return launch_decode_step(*cfg, D, static_cast<hipStream_t>(stream));
+  ProfScope ps(kProfDecodeStep, s);
+  return launch_decode_step(*cfg, D, s);
 }
 
 // ---- the execution stage without any allocation ------------------------------------------------

@@ -492,7 +492,8 @@ def test_step_in_one_call_equals_the_separate_calls(T, E, K, kl, I, shared, give
 @pytest.mark.parametrize("dtype,T,E,K,kl,H,I,shared", [
     ("bf16mx4", 8, 200, 16, 8, 1024, 384, (128,)), ("bf16mx4", 63, 256, 3, 1, 512, 640, ()), ("bf16mx4", 64, 200, 8, 4, 1024, 384, ()),
     ("bf16mx4", 65, 200, 16, 8, 1024, 384, (128, 256)), ("bf16mx4", 255, 200, 16, 8, 1024, 384, (128,)),
-    ("bf16w8", 1, 40, 4, 2, 1024, 2064, (48,)), ("bf16w8", 130, 65, 8, 4, 1040, 1040, ()), ("bf16w8", 255, 40, 2, 1, 1024, 2064, (48,))])
+    ("bf16", 1, 60, 4, 2, 2048, 1408, (5632,)), ("bf16", 33, 60, 4, 2, 2048, 1408, (5632,)), ("bf16", 64, 60, 4, 2, 2048, 1408, (5632,)),
+    ("bf16w8", 1, 40, 4, 2, 1024, 2064, (48,)), ("bf16w8", 64, 40, 8, 3, 1024, 2064, (48,)), ("bf16w8", 130, 65, 8, 4, 1040, 1040, ()), ("bf16w8", 255, 40, 2, 1, 1024, 2064, (48,))])
 def test_dispatch_built_by_the_gate_up_launch(dtype, T, E, K, kl, H, I, shared):
     """Steps in panels below 256 tokens: one, two and eight pairs per thread, one to four words of a token mask, all sets of 64
     experts, an expert without weights; the pass and its fallback pass have every array and every bit of the separate calls."""
@@ -504,6 +505,8 @@ def test_dispatch_built_by_the_gate_up_launch(dtype, T, E, K, kl, H, I, shared):
         n = mm.moe_expert_blob_bytes(c, i)
         b = torch.randint(0, 256, (n,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
         w = 3 * H * i
+        if dtype == "bf16":
+            return (torch.randn((w,), generator=g, device="cuda") * 0.02).bfloat16()
         if dtype == "bf16mx4":
             b[w // 2:] = torch.randint(118, 122, (n - w // 2,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
         else:
@@ -529,6 +532,11 @@ def test_dispatch_built_by_the_gate_up_launch(dtype, T, E, K, kl, H, I, shared):
     mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, sh, True, True, b.y, b.shared_out, b.fws, b.fws_bytes)
     mm.moe_combine(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, b.shared_out, b.out)
     assert same() and bool(b.out.isfinite().all()) and b.out.float().abs().max() > 0
+    if b1.lws is not None:                                          # the decode call takes the same launches
+        for n in arrays + ("y",):
+            getattr(b1, n).zero_()
+        mm.layer_decode_step(b1, x, Wg, None, conf, table, sh)
+        assert same() and mm.moe_layer_decode_status(b1.lws) == 0
     for a in (b1, b):
         a.fws.fill_(0x5A)
     mm.fallback_step(b1, x, conf, table)
