@@ -58,9 +58,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
         for (int w = 0; w < kWords; ++w) loc[c] += __popcll(s_mask[e][w]);
       sum += loc[c];
     }
-    int incl = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(incl, d); if (lane >= d) incl += v; }
+    const int incl = wave_scan(sum);
     int run = incl - sum;
 #pragma unroll
     for (int c = 0; c < C; ++c) { const int e = lane * C + c; if (e < E) s_off[e] = run; run += loc[c]; }
@@ -158,9 +156,7 @@ __global__ __launch_bounds__(kBigThreads) void dispatch_scatter_kernel(
   __syncthreads();
   const int before = tid < E ? s_before[tid] : 0, tot = tid < E ? s_tot[tid] : 0;
   // exclusive prefix of tot over the experts -> expert_offsets
-  int incl = tot;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(incl, d); if (lane >= d) incl += v; }
+  const int incl = wave_scan(tot);
   if (lane == 63) s_wsum[wave] = incl;
   __syncthreads();
   int wbase = 0, P = 0;

@@ -53,6 +53,7 @@
 
 #include "internal.h"
 #include "groups.h"
+#include "dispatch_device.h"
 
 namespace mm {
 namespace {
@@ -158,6 +159,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   __shared__ short s_group[kMaxGroups];                            // list entry -> group
   extern __shared__ __attribute__((aligned(1024))) char s_tiles[];   // kStages x (A rows | B rows)
 
+  fetch_arguments<sizeof(StreamArgs)>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool loader = wave >= SH::kWaves;                          // waves kWaves.. only move data
@@ -212,12 +214,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
     const int base = lane * C;
     int sum = 0;
     for (int c = 0; c < C; ++c) if (base + c < n_groups) sum += s_cnt[base + c];
-    int incl = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int v = __shfl_up(incl, d);
-      if (lane >= d) incl += v;
-    }
+    const int incl = wave_scan(sum);
     int run = incl - sum;
     for (int c = 0; c < C; ++c) if (base + c < n_groups) { s_prefix[base + c] = run; run += s_cnt[base + c]; }
     if (lane == 63) s_prefix[n_groups] = incl;

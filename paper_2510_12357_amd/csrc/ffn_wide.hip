@@ -35,6 +35,7 @@
 
 #include "internal.h"
 #include "groups.h"
+#include "dispatch_device.h"
 #include "wide_layout.h"
 
 namespace mm {
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
   const StreamArgs& a = *(const StreamArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   extern __shared__ __attribute__((aligned(1024))) char s_ring[];
   constexpr int kOut = kOutCols(MODE);
+  fetch_arguments<sizeof(StreamArgs)>();
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const unsigned lds0 = (unsigned)(size_t)s_ring;
   const int n_sh = MODE == kDown ? a.n_slabs : a.n_shared;
@@ -283,10 +285,7 @@ __global__ __launch_bounds__(kThreadsW) __attribute__((amdgpu_waves_per_eu(1, 1)
     for (int k = 0; k < kBuckets; ++k) {
       pref[k][c] = 0x7fffffff;
       if (c * 64 < n_groups) {
-        int w = m > 0 && bk == k ? v : 0;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) { const int o = __shfl_up(w, d); if (lane >= d) w += o; }
-        pref[k][c] = w + tot[k];
+        pref[k][c] = wave_scan(m > 0 && bk == k ? v : 0) + tot[k];
         tot[k] = uniform(__shfl(pref[k][c], 63));
       }
     }

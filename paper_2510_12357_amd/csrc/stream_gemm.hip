@@ -31,6 +31,7 @@
 
 #include "internal.h"
 #include "groups.h"
+#include "dispatch_device.h"
 
 namespace mm {
 namespace {
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
   __shared__ Group s_group[kMaxGroups];
   __shared__ float s_red[NW][kRT * kNT][4][64];
 
+  fetch_arguments<sizeof(StreamArgs)>();
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int q = lane >> 4, c16 = lane & 15;
   const int n_groups = a.n_routed + (MODE == kDown ? a.n_slabs : a.n_shared);
@@ -189,12 +191,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ET::kWa
     const int base = lane * C;
     int sum = 0;
     for (int c = 0; c < C; ++c) if (base + c < n_groups) sum += s_cnt[base + c];
-    int incl = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int v = __shfl_up(incl, d);
-      if (lane >= d) incl += v;
-    }
+    const int incl = wave_scan(sum);
     int run = incl - sum;
     for (int c = 0; c < C; ++c) if (base + c < n_groups) { s_prefix[base + c] = run; run += s_cnt[base + c]; }
     if (lane == 63) s_prefix[n_groups] = incl;

@@ -54,6 +54,7 @@
 
 #include "internal.h"
 #include "groups.h"
+#include "dispatch_device.h"
 
 namespace mm {
 namespace {
@@ -243,6 +244,7 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
   GroupSrc* const s_src = sm.src;
   int* const s_prefix = sm.prefix;
 
+  fetch_arguments<sizeof(StreamArgs)>();
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int q = lane >> 4, c16 = lane & 15;
   const int n_groups = a.n_routed + (MODE == kDown ? a.n_slabs : a.n_shared);
@@ -264,12 +266,7 @@ __global__ __launch_bounds__(kThreadsL) __attribute__((amdgpu_waves_per_eu(4, 4)
     const int base = lane * C;
     int sum = 0;
     for (int c = 0; c < C; ++c) if (base + c < n_groups) sum += s_cnt[base + c];
-    int incl = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int v = __shfl_up(incl, d);
-      if (lane >= d) incl += v;
-    }
+    const int incl = wave_scan(sum);
     int run = incl - sum;
     if (lane == 0) s_prefix[0] = 0;
     for (int c = 0; c < C; ++c) if (base + c < n_groups) { run += s_cnt[base + c]; s_prefix[base + c + 1] = run; }
