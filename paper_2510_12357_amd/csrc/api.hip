@@ -329,6 +329,7 @@ int launch_ffn(StreamMode mode, const FfnRoute& r, const moe_config& c, StreamAr
   const int wfmt = weight_format(c.dtype);
   ProfScope ps(mode == kGateUp ? kProfFfnGateUp : kProfFfnDown, s);
   a.by_rows = mode == kGateUp ? r.by_rows_gate_up : r.by_rows_down;
+  a.even_tiles = mode == kGateUp ? r.even_gate_up : r.even_down;
   switch (mode == kGateUp ? r.gate_up : r.down) {
     case kFfnPanels: return launch_stream_panels(mode, wfmt, a, s);
     case kFfnWide: return launch_wide(mode, a, s);
@@ -408,7 +409,7 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   if (panels && variant == 6) r.gate_up = kFfnTiled;
   r.two_tiles = kernel == kFfnStream && variant == 2;
   r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
-  r.weights_once = r.gate_up == kFfnTiled && variant >= 2;
+  r.weights_once = r.even_gate_up = r.even_down = r.gate_up == kFfnTiled && variant >= 2;
   return expert_ffn(cfg, &r, x, expert_offsets, sorted_token, expert_w, shared_w, run_routed, run_shared, y, shared_out,
                     ws, ws_bytes, stream);
 }

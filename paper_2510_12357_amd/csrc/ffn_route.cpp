@@ -329,6 +329,15 @@ bool tiled_gate_up(const moe_config& c) {
   return c.T > kTiledRows && large_groups && layer_bytes(c) >= kLargeLayer && weights_once(c);
 }
 
+// bf16 tiles of a width that fills their last round over the CUs, which the kernel chooses where that round has room (ffn_tiled.hip, with
+// figures).  With so many rows that the matrix cores set the pace of gate/up (rows per weight row: 8 of 14336, 131, 350 / 360 us, 225, 521 / 538) or
+// have no room left in the down projection (20 of 4096, 150, 87 / 88; but 8 of 14336, 131, 252 / 218) it only costs, and a small layer
+// has no rounds to speak of (8 of 512, hidden 512, 1000 tokens 18.0 + 16.6 / 18.7 + 17.1; 8 of 1408 + 1408, hidden 1024 (78 MB), 700 tokens 30.2 / 26.2).
+bool even_tiles(const moe_config& c, bool gate_up) {
+  const Work w = layer_work(c);
+  return c.dtype == MOE_BF16 && layer_bytes(c) >= 64ll << 20 && w.rows < (gate_up ? 96 : 150) * w.weight_rows;
+}
+
 }  // namespace
 
 // A call that runs the routed part alone is taken for a part of a step: a fallback pass (some ranks of the
@@ -354,6 +363,8 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
     const bool by_rows = tiled_by_rows(c, run_routed, run_shared, cus);
     r.by_rows_down = r.down == kFfnTiled && by_rows;
     r.by_rows_gate_up = r.gate_up == kFfnTiled && by_rows;
+    r.even_gate_up = r.gate_up == kFfnTiled && even_tiles(c, true);
+    r.even_down = r.down == kFfnTiled && even_tiles(c, false);
   }
   auto any = [&](FfnKernel k) { return r.gate_up == k || r.down == k; };
   r.two_tiles = any(kFfnStream) && whole && two_tiles(c);

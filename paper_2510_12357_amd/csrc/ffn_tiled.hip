@@ -143,7 +143,8 @@ struct Shape {
   static_assert((TM == 2 || TM == 4) && (TN == 2 || TN == 4), "the fragment reads are written for 2 or 4 MFMA tiles per wave and side");
 };
 
-template <int MODE, typename SH, int WB>
+// EVEN: tiles of a width that fills the rounds, below
+template <int MODE, typename SH, int WB, bool EVEN>
 __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(const StreamArgs a) {
   typedef WFmt<WB> WF;
   constexpr int BM = SH::BM, BNR = SH::BNR, TM = SH::TM, TN = SH::TN, kStages = SH::kStages, SUMS = SH::SUMS;
@@ -181,15 +182,43 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   const bool by_rows = a.by_rows != 0, weights_once = a.weights_once != 0;
   constexpr int kPerThread = (kMaxGroups + kThreads - 1) / kThreads;
   int my_tiles[kPerThread], my_rank[kPerThread];
-  if (by_rows) {
+  const int n_sh = MODE == kDown ? a.n_slabs : a.n_shared;
+  if (EVEN || by_rows) {
     for (int g = tid; g < n_groups; g += kThreads) s_cnt[g] = load_group_src<MODE>(a, g).m;
     __syncthreads();
+  }
+  // EVEN: output columns per tile.  Where the tiles leave a good part of their last round over the CUs empty, they are made as narrow as that
+  // round allows: tiles that wait for their weights are shorter then.  us, gate/up + down, full width / so (tiles of full width in rounds): 60
+  // experts of 1408 + 5632, 300 tokens (3.1, 2.25) 147 + 85 / 131 + 83, 400 tokens (3.3, 2.4) 149 + 85 / 138 + 82; 64 of 1408 + 2 shared, 256 tokens
+  // (2.9, 2.1) down 85 / 75, 350 tokens (3.0, 2.25) 152 + 86 / 133 + 79, 800 tokens (3.4, 2.5) 165 + 97 / 158 + 95; 64 of 1024, skewed, 800
+  // tokens 124 + 74 / 117 + 68; 8 of 14336, down (0.5), 300 tokens 219 / 186, 640 tokens 247 / 203.  Not where the round is nearly full, and less
+  // so where tiles are: the matrix cores set their pace, and multiply the columns left out as well.  8 of 14336, gate/up, 640 tokens (3.5) 344 /
+  // 357, 1500 tokens 502 / 515, 20 of 4096, 1500 tokens 181 / 190; 60 experts, 256 tokens, gate/up (2.92) 123 / 125.  Narrow weights, half the bytes per tile, lose: 8 bits, 64 of 1408 + 2 shared, 350 tokens 117 + 92 / 135 + 90.
+  constexpr int kFull = 86, kFullBusy = 65, kBusyRows = 80;        // per cent of the rounds' tiles; rows of a tile on average
+  int oc = kOutCols;
+  if constexpr (EVEN) {
+    int mr = 0, rows = 0;
+    for (int g = n_sh + lane; g < n_groups; g += 64) { mr += (s_cnt[g] + BM - 1) / BM; rows += s_cnt[g]; }
+    mr = __builtin_amdgcn_readlane(wave_scan(mr), 63);
+    rows = __builtin_amdgcn_readlane(wave_scan(rows), 63);
+    const int ms = (a.T + BM - 1) / BM, grid = (int)gridDim.x;
+    // routed, shared: tiles, or token rows, of a panel of all routed and of one shared group
+    auto across = [&](int cols, int routed, int shared) -> int {
+      int n = routed * quotient((MODE == kDown ? a.H : a.I) + cols - 1, cols);
+      for (int s = 0; s < n_sh; ++s) n += shared * quotient((MODE == kDown ? a.H : a.shared_I[s]) + cols - 1, cols);
+      return n;
+    };
+    auto tiles_with = [&](int cols) -> int { return across(cols, mr, ms); };
+    const int tiles = tiles_with(kOutCols), rounds = quotient(tiles + grid - 1, grid), cols = kOutCols / 2 + 8 * min(lane, kOutCols / 16);
+    const uint64_t fits = __ballot(tiles_with(cols) <= rounds * grid);
+    const bool busy = across(kOutCols, rows, a.T) > (long)kBusyRows * tiles;
+    if (100l * tiles < (long)(busy ? kFullBusy : kFull) * rounds * grid) oc = uniform(kOutCols / 2 + 8 * (int)__builtin_ctzll(fits | 1ull << (kOutCols / 16)));
   }
 #pragma unroll
   for (int k = 0; k < kPerThread; ++k) {
     const int g = tid + k * kThreads;
     if (g < n_groups) {
-      const int N = MODE == kDown ? a.H : (g < a.n_shared ? a.shared_I[g] : a.I), nt = (N + kOutCols - 1) / kOutCols;
+      const int N = MODE == kDown ? a.H : (g < a.n_shared ? a.shared_I[g] : a.I), nt = EVEN ? quotient(N + oc - 1, oc) : (N + kOutCols - 1) / kOutCols;
       if (by_rows) {
         const int m = s_cnt[g], first = (xcd - g) & 7;
         int rank = 0;
@@ -198,7 +227,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         my_tiles[k] = (nt > first ? (nt - first + 7) >> 3 : 0) * ((m + BM - 1) / BM);
       } else {
         my_rank[k] = g;
-        my_tiles[k] = nt * ((load_group_src<MODE>(a, g).m + BM - 1) / BM);
+        my_tiles[k] = nt * (((EVEN ? s_cnt[g] : load_group_src<MODE>(a, g).m) + BM - 1) / BM);
       }
     }
   }
@@ -258,7 +287,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
     const int mt = (G.m + BM - 1) / BM;
     const int panel = local / mt;
     const int m0 = (local - panel * mt) * BM;
-    const int n0 = (by_rows ? ((xcd - g) & 7) + 8 * panel : panel) * kOutCols;
+    const int n0 = (by_rows ? ((xcd - g) & 7) + 8 * panel : panel) * (EVEN ? oc : kOutCols), n_end = EVEN ? min(G.N, n0 + oc) : G.N;
     const int K = G.K;
 
     const int nk = (K + BK - 1) / BK;
@@ -294,7 +323,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
           n = n0 + br;
         }
         bcol[p] = (ld_pcw ^ WF::key(br)) * WF::kPerCol;
-        boff[p] = (n < G.N ? (unsigned)n * WF::bytes((unsigned)G.ldw) + extra : kOob) + WF::bytes((unsigned)bcol[p]);
+        boff[p] = (n < n_end ? (unsigned)n * WF::bytes((unsigned)G.ldw) + extra : kOob) + WF::bytes((unsigned)bcol[p]);
       }
       // The weights of a panel with one token tile are read once in the launch (a.weights_once).  One branch for
       // a chunk's loads: one for each of them costs small launches up to a quarter (8 experts of 392, hidden 3008, a
@@ -539,7 +568,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
 #pragma unroll
           for (int j = 0; j < TN / 2; ++j) {
             const int col = n0 + wn * (TN / 2) * 32 + j * 32 + (lane & 31);
-            if (col < G.N) {
+            if (col < n_end) {
               const float gte = WB == 1 ? acc[0][i][j][v] * wsc[j] : acc[0][i][j][v];
               const float upv = WB == 1 ? acc[0][i][j + TN / 2][v] * wsc[j + TN / 2] : acc[0][i][j + TN / 2][v];
               const float hv = gte / (1.f + __expf(-gte)) * upv;
@@ -551,31 +580,31 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             const int col = n0 + wn * TN * 32 + j * 32 + (lane & 31);
-            if (col < G.N) static_cast<float*>(G.out)[(size_t)r * a.H + col] = WB == 1 ? acc[0][i][j][v] * wsc[j] : acc[0][i][j][v];
+            if (col < n_end) static_cast<float*>(G.out)[(size_t)r * a.H + col] = WB == 1 ? acc[0][i][j][v] * wsc[j] : acc[0][i][j][v];
           }
         }
       }
   }
 }
 
-template <int MODE, typename SH, int WB>
+template <int MODE, typename SH, int WB, bool EVEN = false>
 int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
   constexpr size_t kLds = (size_t)SH::kStages * SH::template stage_bytes<WB>();
   static std::atomic<int> cached{0};
   int per_cu = cached.load(std::memory_order_relaxed);
   if (per_cu == 0) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tiled_kernel<MODE, SH, WB>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tiled_kernel<MODE, SH, WB, EVEN>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds) != hipSuccess)
       return hip_fail(hipGetLastError(), "tiled_kernel: LDS size attribute");
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled_kernel<MODE, SH, WB>, SH::kThreads, kLds) != hipSuccess || n < 1) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled_kernel<MODE, SH, WB, EVEN>, SH::kThreads, kLds) != hipSuccess || n < 1) n = 1;
     per_cu = n;
     cached.store(n, std::memory_order_relaxed);
   }
   int grid = device_cu_count() * per_cu;
   grid = grid / 8 * 8;                                      // the XCD walk wants a multiple of 8
   if (grid < 8) grid = 8;
-  hipLaunchKernelGGL((tiled_kernel<MODE, SH, WB>), dim3((unsigned)grid), dim3(SH::kThreads), kLds, s, a);
+  hipLaunchKernelGGL((tiled_kernel<MODE, SH, WB, EVEN>), dim3((unsigned)grid), dim3(SH::kThreads), kLds, s, a);
   return hip_fail(hipGetLastError(), "tiled_kernel launch");
 }
 
@@ -591,8 +620,8 @@ static_assert(DefaultShape::BNR / 2 == kTiledPanel && DefaultShape::BM == kTiled
 int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStream_t s) {
   if (weight_format == 2) {
     if (mode == kGateUp && a.two_sums) return launch_tiled_shape<kGateUp, TwoSumShape, 2>(a, s);
-    if (mode == kGateUp) return launch_tiled_shape<kGateUp, DefaultShape, 2>(a, s);
-    if (mode == kDown) return launch_tiled_shape<kDown, DefaultShape, 2>(a, s);
+    if (mode == kGateUp) return a.even_tiles ? launch_tiled_shape<kGateUp, DefaultShape, 2, true>(a, s) : launch_tiled_shape<kGateUp, DefaultShape, 2>(a, s);
+    if (mode == kDown) return a.even_tiles ? launch_tiled_shape<kDown, DefaultShape, 2, true>(a, s) : launch_tiled_shape<kDown, DefaultShape, 2>(a, s);
   }
 #if MOE_TILED_BK == 64   // the narrow formats are written for 64-k chunks
   else if (weight_format == 1) {

@@ -52,6 +52,15 @@ __device__ __forceinline__ P* uniform(P* p) {
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
+// a / b, a >= 0, b >= 1, by the hardware's reciprocal (off by at most 2^-23 of it): the product is off by less than one while the quotient
+// stays below 2^21, and panels, blocks, quads and tiles of a step do.
+// A workgroup's first loads wait for up to a dozen of these; the compiler's integer division takes 35 instructions, one after the other.
+__device__ __forceinline__ int quotient(int a, int b) {
+  int n = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const int rest = a - n * b;
+  return n + (rest >= b ? 1 : 0) - (rest < 0 ? 1 : 0);
+}
+
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 // 8 E4M3 codes (two dwords, k ascending with the byte address) -> 8 bf16, exactly.
 __device__ __forceinline__ bf16x8 widen_e4m3(int lo, int hi) {

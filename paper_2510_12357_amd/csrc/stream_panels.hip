@@ -168,15 +168,6 @@ __device__ __forceinline__ int token_key(int row) {
   return WB == 0 && MANY ? (row & 9) | (row & 2) << 1 | (row & 4) >> 1 : row;
 }
 
-// a / b, a >= 0, b >= 1, by the hardware's reciprocal (off by at most 2^-23 of it): the product is off by less than one while the quotient
-// stays below 2^21, and panels, blocks and quads of a step do.
-// Every workgroup's first loads wait for a dozen of these; the compiler's integer division takes 35 instructions, one after the other.
-__device__ __forceinline__ int quotient(int a, int b) {
-  int n = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
-  const int rest = a - n * b;
-  return n + (rest >= b ? 1 : 0) - (rest < 0 ? 1 : 0);
-}
-
 template <int WB> __device__ __forceinline__ int token_blocks(int m) { return (m + Unit<WB>::kBlock - 1) / Unit<WB>::kBlock; }
 
 template <int WB>

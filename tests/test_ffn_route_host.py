@@ -35,7 +35,9 @@ def route(tmp_path_factory):
         v = [DTYPES[cfg.dtype], cfg.T, cfg.H, cfg.E, cfg.I, cfg.k_big, cfg.k_little, len(cfg.shared_I), *cfg.shared_I,
              int(routed), int(shared), CUS]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True, env=env)
-        return tuple(map(int, r.stdout.split()))
+        v = tuple(map(int, r.stdout.split()))
+        run.even = v[8:]
+        return v[:8]
 
     def ask(cfg, routed=True, shared=True):
         """Kernel of both launches with what it is told: token tiles two (STREAM), order of tiles (TILED, WIDE), row tiles
@@ -48,6 +50,7 @@ def route(tmp_path_factory):
             return gate_up, (g[1] if g[1] == d[1] else (g[1], d[1]))
         return g, d
     ask.raw = run
+    ask.even = lambda cfg, shared=True: (run(cfg, True, shared), run.even)[1]
     ask.router = lambda cfg: run(cfg, True, True)[7]
     ask.weights_once = lambda cfg, routed=True: run(cfg, routed, True)[6]
     return ask
@@ -177,6 +180,17 @@ def test_router_tests_reach_both_kernels(route):
     gemv = [c for c in _cases(parity.test_gate_logits)
             if route.router(wl.LayerConfig("r", T=c[1], H=c[2], E=c[3], I=8, k_big=1, k_little=1, dtype=c[0])) == GEMV]
     assert {c[0] for c in gemv} == {"bf16", "fp32"} and any(c[1] % 4 for c in gemv)
+
+
+def test_tiles_that_fill_their_rounds(route):
+    """bf16 tiles while the weights set the pace, each launch by its rows; narrow weights, wide tiles, panels and small layers never."""
+    c = wl.CONFIGS
+    assert [route.even(c["fine60_decode"].with_(T=T)) for T in (255, 300, 800, 1200, 2000)] == [(0, 0), (1, 1), (1, 1), (0, 1), (0, 0)]
+    assert [route.even(c["coarse8"].with_(T=T)) for T in (300, 400, 700, 1000)] == [(0, 0), (1, 1), (0, 1), (0, 0)]
+    assert route.even(c["fine60_decode"].with_(T=300), shared=False) == (1, 1)
+    for dtype in ("bf16w8", "bf16mx4"):
+        assert route.even(c["fine60_decode"].with_(T=1000, dtype=dtype)) == (0, 0)
+    assert route.even(wl.LayerConfig("small", T=300, H=512, E=8, I=512, k_big=2, k_little=1)) == (0, 0)
 
 
 def test_dispatch_beside_gate_up_is_tested_where_the_rules_take_it(route):

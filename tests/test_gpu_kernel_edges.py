@@ -189,6 +189,25 @@ def test_tiled_bf16_weights_read_once(counts, H, I, shared):
 
 
 @pytest.mark.parametrize("counts,H,I,shared", [
+    ([0, 1, 40, 127, 128, 129, 1], 200, 264, ()),                  # less than a round: half the width, with remainders
+    ([20] * 40, 520, 1032, ()),                                    # 360 tiles of gate/up: two rounds of 256 CUs, narrower by a quarter
+    ([9] * 30 + [0, 130], 264, 1160, (2056, 72)),                  # shared experts of several token tiles
+    ([300, 1, 2], 72, 136, (264,)),
+])
+def test_tiles_that_fill_their_rounds(counts, H, I, shared):
+    """Tiles narrower than the kernel's (variants 2 and 3): every column once, and the bits of full ones."""
+    _check_assigned(counts, H, I, shared, TILED, (2, 3))
+    cfg, x, experts, sh, table, b = _assigned_layer(counts, H, I, shared, seed=5)
+    mm.layer_step(b, x, None, None, None, table, sh, logits_given=True)
+    y0, out0 = _run_on(TILED, 0, b, x, table, sh)
+    for variant in (2, 3):
+        y, out = _run_on(TILED, variant, b, x, table, sh)
+        assert torch.equal(y, y0) and (out is None or torch.equal(out, out0)), variant
+        y, out = _run_on(TILED, variant, b, x, table, (), shared=False)
+        assert torch.equal(y, y0) and (out is None or bool((out == 7.0).all())), variant
+
+
+@pytest.mark.parametrize("counts,H,I,shared", [
     ([0, 1, 32, 33, 64, 65, 50], 200, 264, ()),                    # items of 64 token rows, their remainders
     ([16, 17, 48, 49], 1032, 72, (520,)),                          # several chunks of K; a shared expert of 130 rows
     ([65], 64, 40, ()),
