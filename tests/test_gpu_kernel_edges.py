@@ -271,6 +271,25 @@ def test_streamed_by_waves(counts, H, I, shared, dtype):
             assert torch.isfinite(y1).all() and torch.equal(y1, y4) and (out1 is None or torch.equal(out1, out4))
 
 
+@pytest.mark.parametrize("T,kernel,variants", [(16, STREAM, (1, 4, 5)), (256, STREAM, (4, 5)), (256, TILED, (0, 1))])
+def test_every_code_of_8_bits(T, kernel, variants):
+    """Widening is exact: one activation h0 other than zero meets each code once, so a column is h0 times its value in one fp32 product (or NaN)."""
+    H, I = 256, 16
+    cfg = wl.LayerConfig("codes", T=T, H=H, E=1, I=I, k_big=1, k_little=1, dtype="bf16w8")
+    codes = torch.arange(256, dtype=torch.int32, device="cuda").to(torch.uint8)
+    gate, down = torch.zeros(I, H, dtype=torch.uint8, device="cuda"), torch.zeros(H, I, dtype=torch.uint8, device="cuda")
+    gate[0], down[:, 0] = 0x38, codes                              # 1.0
+    scale = torch.cat([torch.full((2 * I,), 2.0 ** -7, device="cuda"), torch.ones(H, device="cuda")])
+    blob = torch.cat([gate.flatten(), gate.flatten(), down.flatten(), scale.view(torch.uint8)])
+    table = torch.tensor([blob.data_ptr()], dtype=torch.int64, device="cuda")
+    x = torch.ones(T, H, dtype=torch.bfloat16, device="cuda")
+    b = _assigned_step(cfg, x, table, [], torch.zeros(T, dtype=torch.int64, device="cuda"))
+    value = codes.view(torch.float8_e4m3fn).float()
+    for variant in variants:
+        y, _ = _run_on(kernel, variant, b, x, table, [])
+        assert torch.equal(torch.nan_to_num(y, 1e9), torch.nan_to_num(y[:, 0x38:0x39] * value, 1e9)) and y[0, 0x38] > 3, variant
+
+
 @pytest.mark.parametrize("dtype,counts,H,I,shared", [
     ("bf16", [5, 0, 20, 17, 1], 200, 264, ()),                     # K ends inside a unit of 256 bytes; quads that the waves do not divide
     ("bf16", [30, 2, 64, 65], 1032, 72, (520,)),                   # gate rows that end inside a tile; K in parts of a unit
