@@ -8,12 +8,19 @@
 // A operand and weight rows the B operand, each read from LDS as 16-byte K chunks.
 //
 // Tiling for gfx950 (64-wide waves, v_mfma_f32_32x32x16_bf16):
-//   * workgroup tile (Shape<WM,WN,TM,TN>): default 128 tokens x 256 weight rows, K chunk 64,
+//   * workgroup tile (Shape<WM,WN,TM,TN>): 128 tokens x 256 weight rows, K chunk 64,
 //     one workgroup per CU.  Waves 0..3 compute, in a 2x2 grid, each 64 x 128 outputs = 2x4 MFMA
 //     tiles (128 accumulator registers, 6 fragment reads per 8 MFMAs); waves 4..7 only load, so a
 //     full vector-memory queue never stops the MFMA issue.  For gate/up the weight rows of a
 //     tile are half rows of W_gate plus the same rows of W_up, arranged so that a wave holds
 //     gate and up of the same outputs and applies SwiGLU in registers.
+//   * narrow weights: the four waves side by side, each all 128 tokens x 64 weight rows = 4x2 MFMA tiles (as many accumulators and reads), so
+//     that a code is widened in one wave of the workgroup and not in two: the conversions, not the matrix cores, set the pace of those
+//     tiles.  Blocks of 32 tokens without rows shorten a tile by a quarter each, not in pairs.  us, gate/up + down, 2x2 / so: MXFP4, 64
+//     experts of 1024, 600 tokens 85.8 + 49.5 / 76.4 + 46.2, 4000 tokens 219 + 132 / 203 + 127; 8 of 14336, 600 tokens 292 + 259 /
+//     248 + 213, 2000 tokens 702 + 495 / 596 + 388; 60 of 1408 + 5632, 1400 tokens 178 + 108 / 161 + 100.  8 bits, 64 of 1024, 256 tokens
+//     74.8 + 58.9 / 71.5 + 52.8, 2000 tokens 147 + 116 / 148 + 114; 8 of 14336, 2000 tokens 626 + 352 / 600 + 355.  bf16 gains in
+//     gate/up what it loses in the down projection (2000 tokens 147 + 92 / 145 + 93, 256 tokens 77.6 + 46.6 / 78.5 + 47.2).  A fourth stage: nothing.
 //   * global -> LDS without registers: buffer loads with the LDS destination move 8 tile rows x
 //     128 bytes per instruction (token gather and all ragged edges are offsets beyond the
 //     buffer: zero fill, no branches).  A ring of stages; a loader issues the chunk that is
@@ -40,7 +47,7 @@
 //     inside a chunk is permuted: k-step 2p + e takes, for the lanes of half h, the 8 k behind
 //     32 p + 16 h + 8 e, and the token fragments are read with the same permutation.  A computing
 //     wave widens the codes of the next k-step to bf16 (exact) between the MFMAs of the current one,
-//     and the row scale multiplies the fp32 sum in the epilogue.  Tokens, tile shape, pipeline and
+//     and the row scale multiplies the fp32 sum in the epilogue.  Tokens, tile size, pipeline and
 //     tile order are those of the bf16 kernel.
 //   * MXFP4 weights (WB = 0: 4-bit E2M1 codes, one E8M0 scale per 32 k): a weight tile row is 32
 //     bytes (32 rows per load instruction, key (row >> 3) & 1).  The 16 bytes a lane reads per
@@ -608,12 +615,10 @@ int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
   return hip_fail(hipGetLastError(), "tiled_kernel launch");
 }
 
-#ifndef MOE_TILED_SHAPE
-#define MOE_TILED_SHAPE 2, 2, 2, 4
-#endif
-typedef Shape<MOE_TILED_SHAPE> DefaultShape;
+typedef Shape<2, 2, 2, 4> DefaultShape;
+typedef Shape<1, 4, 4, 2> NarrowShape;
 typedef Shape<2, 2, 2, 2, 4, 2> TwoSumShape;
-static_assert(DefaultShape::BNR / 2 == kTiledPanel && DefaultShape::BM == kTiledRows, "tiles of the dispatch rules");
+static_assert(DefaultShape::BNR / 2 == kTiledPanel && DefaultShape::BM == kTiledRows && NarrowShape::BNR == DefaultShape::BNR && NarrowShape::BM == DefaultShape::BM, "tiles of the dispatch rules");
 
 }  // namespace
 
@@ -625,11 +630,11 @@ int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStr
   }
 #if MOE_TILED_BK == 64   // the narrow formats are written for 64-k chunks
   else if (weight_format == 1) {
-    if (mode == kGateUp) return launch_tiled_shape<kGateUp, DefaultShape, 1>(a, s);
-    if (mode == kDown) return launch_tiled_shape<kDown, DefaultShape, 1>(a, s);
+    if (mode == kGateUp) return launch_tiled_shape<kGateUp, NarrowShape, 1>(a, s);
+    if (mode == kDown) return launch_tiled_shape<kDown, NarrowShape, 1>(a, s);
   } else if (weight_format == 0) {
-    if (mode == kGateUp) return launch_tiled_shape<kGateUp, DefaultShape, 0>(a, s);
-    if (mode == kDown) return launch_tiled_shape<kDown, DefaultShape, 0>(a, s);
+    if (mode == kGateUp) return launch_tiled_shape<kGateUp, NarrowShape, 0>(a, s);
+    if (mode == kDown) return launch_tiled_shape<kDown, NarrowShape, 0>(a, s);
   }
 #endif
   return fail(MOE_E_BADARG, "tiled kernel: bad mode or weight format");
