@@ -126,7 +126,8 @@ int moe_profile_plain_read(const void* buf, size_t bytes, int32_t* sink, void* s
  *             tokens unless MOE_FP32; 4 or 5: every wave streams rows of its own, tiles of 16 rows per wave one
  *             or two (5: not MOE_BF16), up to 65535 tokens, not MOE_FP32; 6 (MOE_BF16): 4 with gate/up on tiles
  *   kernel 1  tiles of 128 x 256, kernel 2 of 256 x 256 (MOE_BF16 only); 256 tokens and more, not
- *             MOE_FP32; variant 0: tiles in contiguous ranges, 1: by rows; 2, 3 (kernel 1, MOE_BF16): the same
+ *             MOE_FP32; variant 0: tiles in contiguous ranges, 1: by rows (and narrow
+ *             weights in whole lines); 2, 3 (kernel 1, MOE_BF16): the same
  *             with the weights of panels of one token tile loaded past the caches and tiles of a width that
  *             fills their rounds over the CUs
  * Anything else is MOE_E_UNSUPPORTED.  moe_profile_expert_ffn_kernel returns the kernel (0, 1 or 2) that

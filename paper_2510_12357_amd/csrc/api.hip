@@ -322,6 +322,7 @@ void take_route(StreamArgs& a, const FfnRoute& r, const moe_config& c) {
   a.two_tiles = r.two_tiles;
   a.wide_panels = r.wide_panels;
   a.weights_once = r.weights_once;
+  a.lines = r.lines;
   a.two_sums = r.gate_up == kFfnTiled && c.T < kTiledMinT;
 }
 
@@ -409,6 +410,7 @@ extern "C" int moe_profile_expert_ffn(const moe_config* cfg, int kernel, int var
   if (panels && variant == 6) r.gate_up = kFfnTiled;
   r.two_tiles = kernel == kFfnStream && variant == 2;
   r.by_rows_gate_up = r.by_rows_down = kernel != kFfnStream && (variant & 1);
+  r.lines = r.gate_up == kFfnTiled && !bf16 && variant == 1;
   r.weights_once = r.even_gate_up = r.even_down = r.gate_up == kFfnTiled && variant >= 2;
   return expert_ffn(cfg, &r, x, expert_offsets, sorted_token, expert_w, shared_w, run_routed, run_shared, y, shared_out,
                     ws, ws_bytes, stream);

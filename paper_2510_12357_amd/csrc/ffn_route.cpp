@@ -329,6 +329,16 @@ bool tiled_gate_up(const moe_config& c) {
   return c.T > kTiledRows && large_groups && layer_bytes(c) >= kLargeLayer && weights_once(c);
 }
 
+// Narrow weights in whole lines (ffn_tiled.hip, with figures of the layers that gain): a tile waits for a line before its first chunk, which
+// layers of little time per tile feel (us, MXFP4, chunks / lines: 64 experts of 256, hidden 512, 900 tokens 17.0 + 13.5 / 18.5 + 14.5; 32
+// of 1024, hidden 1024 (201 MB in bf16) 24.8 + 22.9 / 27.1 + 23.1; 16 of 1024, hidden 4096 (403 MB) 67.5 + 26.5 / 62.0 + 24.1), and 8-bit
+// ones whose matrix cores set the pace (8 bits, 64 of 1024, 2500 tokens 173 + 130 / 175 + 131; 8 of 14336, 1400 tokens 474 + 210 / 477 + 209,
+// 900 tokens 422 + 203 / 418 + 186).
+bool whole_lines(const moe_config& c) {
+  const Work w = layer_work(c);
+  return c.dtype != MOE_BF16 && layer_bytes(c) >= 384ll << 20 && (c.dtype != MOE_BF16_W8 || w.rows < 200 * w.weight_rows);
+}
+
 // bf16 tiles of a width that fills their last round over the CUs, which the kernel chooses where that round has room (ffn_tiled.hip, with
 // figures).  With so many rows that the matrix cores set the pace of gate/up (rows per weight row: 8 of 14336, 131, 350 / 360 us, 225, 521 / 538) or
 // have no room left in the down projection (20 of 4096, 150, 87 / 88; but 8 of 14336, 131, 252 / 218) it only costs, and a small layer
@@ -370,6 +380,7 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
   r.two_tiles = any(kFfnStream) && whole && two_tiles(c);
   r.wide_panels = any(kFfnPanels) && wide_panels(c, run_shared, cus);
   r.weights_once = any(kFfnTiled) && weights_once(c);
+  r.lines = any(kFfnTiled) && whole_lines(c);
   return r;
 }
 

@@ -24,6 +24,7 @@ struct FfnRoute {
   bool wide_panels;                  // StreamArgs::wide_panels (stream_panels.hip)
   bool two_tiles;                    // StreamArgs::two_tiles (stream_lds.hip)
   bool weights_once;                 // StreamArgs::weights_once (ffn_tiled.hip)
+  bool lines;                        // StreamArgs::lines (ffn_tiled.hip)
   bool even_gate_up, even_down;      // StreamArgs::even_tiles of the two launches (ffn_tiled.hip)
   bool by_rows_gate_up, by_rows_down;   // StreamArgs::by_rows of the two launches (ffn_tiled.hip, ffn_wide.hip)
 };

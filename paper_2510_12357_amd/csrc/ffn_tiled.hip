@@ -49,6 +49,12 @@
 //     wave widens the codes of the next k-step to bf16 (exact) between the MFMAs of the current one,
 //     and the row scale multiplies the fp32 sum in the epilogue.  Tokens, tile size, pipeline and
 //     tile order are those of the bf16 kernel.
+//   * Such a chunk is half or a quarter of a line of weights, and by its next part a line has often left the CU's cache.  LINES: the
+//     weight rows of a tile are whole lines in LDS, two or four chunks, a ring of three lines beside the ring of token chunks.  A line's
+//     parts are loaded with the chunks of the line before it, as many instructions with each, so the counted waits stay as they are.
+//     Panels of one token tile go past the caches as in bf16.  us, gate/up + down, chunks / lines: MXFP4, 64 experts of 1024, 512 tokens
+//     69.1 + 43.1 / 59.6 + 38.7, 2500 tokens 168 + 103 / 151 + 96; 8 of 14336, 900 tokens 404 + 223 / 368 + 215; 60 of 1408 + 5632, 1400
+//     tokens 159 + 103 / 147 + 98.  8 bits, 60 of 1408 + 5632, 900 tokens 156 + 89 / 151 + 85; 16 of 1024, hidden 4096, 65 + 34 / 57 + 33.
 //   * MXFP4 weights (WB = 0: 4-bit E2M1 codes, one E8M0 scale per 32 k): a weight tile row is 32
 //     bytes (32 rows per load instruction, key (row >> 3) & 1).  The 16 bytes a lane reads per
 //     column tile and chunk are the 32 codes of ONE scale block, i.e. of all four k-steps of the
@@ -86,11 +92,14 @@ static_assert(BK == 32 || BK == 64, "K chunk of 32 or 64");
 // swizzle key of a tile row: rows that share 256 bytes of LDS get the same key, the next ones the next
 __device__ __forceinline__ constexpr int row_key(int row) { return (row >> kKeyShift) & (kCols - 1); }
 
-// Weight rows of a tile in LDS, by weight format (WB bytes per weight).
-template <int WB>
+// Weight rows of a tile in LDS, by weight format (WB bytes per weight).  LINES: whole lines of 128 bytes, the weights of kChunks chunks,
+// loaded in as many parts.
+template <int WB, bool LINES>
 struct WFmt {
   static_assert(WB == 0 || WB == 1 || WB == 2, "bf16, 8-bit or MXFP4 weights");
-  static constexpr int kRowB = WB ? BK * WB : BK / 2;   // bytes of a weight tile row
+  static_assert(!LINES || (BK == 64 && WB != 2), "a line is 2 or 4 chunks; a chunk of bf16 is one");
+  static constexpr int kChunks = LINES ? (WB ? 2 : 4) : 1;
+  static constexpr int kRowB = kChunks * (WB ? BK * WB : BK / 2);   // bytes of a weight tile row
   static constexpr int kCols = kRowB / 16;           // its 16-byte columns
   static constexpr int kRowsPerIns = 1024 / kRowB;   // tile rows that one load instruction fills
   static constexpr int kPerCol = WB ? 16 / WB : 32;  // weights per 16-byte column
@@ -99,7 +108,7 @@ struct WFmt {
   // 64-byte rows: four rows share 256 bytes of LDS, and 16 consecutive rows get every key once per
   // residue of the row number mod 4; 32-byte rows: eight rows share 256 bytes
   static __device__ __forceinline__ constexpr int key(int row) {
-    return WB == 2 ? row_key(row) : (WB == 1 ? (row >> 2) & 3 : (row >> 3) & 1);
+    return WB == 2 || LINES ? row_key(row) : (WB == 1 ? (row >> 2) & 3 : (row >> 3) & 1);
   }
   static __device__ __forceinline__ constexpr unsigned bytes(unsigned n) { return WB ? n * (unsigned)WB : n / 2u; }
 };
@@ -144,22 +153,23 @@ struct Shape {
   static constexpr int BM = WM * TM * 32;            // tokens per tile
   static constexpr int BNR = WN * TN * 32;           // weight rows per tile (gate/up: half + half)
   static constexpr int kInsA = BM / kRowsPerIns / kWaves;      // token-row load instructions per wave and chunk
-  template <int WB> static constexpr int ins_b() { return BNR / WFmt<WB>::kRowsPerIns / kWaves; }   // weight-row ones
-  template <int WB> static constexpr int stage_bytes() { return BM * kRowB + BNR * WFmt<WB>::kRowB; }
+  template <typename WF> static constexpr int ins_b() { return BNR / WF::kRowsPerIns / kWaves; }   // weight-row ones, per chunk or line
+  template <typename WF> static constexpr int stage_bytes() { return BM * kRowB + BNR * WF::kRowB; }
   static_assert(BM % (kRowsPerIns * kWaves) == 0 && BNR % (32 * kWaves) == 0, "tile rows must divide evenly");
   static_assert((TM == 2 || TM == 4) && (TN == 2 || TN == 4), "the fragment reads are written for 2 or 4 MFMA tiles per wave and side");
 };
 
 // EVEN: tiles of a width that fills the rounds, below
-template <int MODE, typename SH, int WB, bool EVEN>
+// LINES: narrow weights in whole lines
+template <int MODE, typename SH, int WB, bool EVEN, bool LINES>
 __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(const StreamArgs a) {
-  typedef WFmt<WB> WF;
+  typedef WFmt<WB, LINES> WF;
   constexpr int BM = SH::BM, BNR = SH::BNR, TM = SH::TM, TN = SH::TN, kStages = SH::kStages, SUMS = SH::SUMS;
   static_assert(SUMS == 1 || WB == 2, "two sums are those of the streaming kernels for bf16 weights");
-  constexpr int kThreads = SH::kThreads, kInsA = SH::kInsA, kInsB = SH::template ins_b<WB>();
-  constexpr int kStageBytes = SH::template stage_bytes<WB>();
+  constexpr int kThreads = SH::kThreads, kInsA = SH::kInsA, kInsB = SH::template ins_b<WF>();
+  constexpr int kStageBytes = SH::template stage_bytes<WF>(), kChunks = WF::kChunks;
   constexpr int kRowBW = WF::kRowB;                                // bytes of a weight tile row
-  constexpr int kPerChunk = kInsA + kInsB;                         // loads of one wave per chunk
+  constexpr int kPerChunk = kInsA + kInsB / kChunks;                       // loads of one wave per chunk
   constexpr int kOutCols = (MODE == kGateUp) ? BNR / 2 : BNR;     // output columns per tile
 
   __shared__ int s_cnt[kMaxGroups];                                // rows per group, then tiles per list entry
@@ -173,6 +183,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   const bool loader = wave >= SH::kWaves;                          // waves kWaves.. only move data
   const int lw = wave - SH::kWaves;                                // index among the loaders
   const int wm = (wave % SH::kWaves) / SH::WN, wn = wave % SH::WN;
+  static_assert(kChunks == 1 || kStages == 3, "three lines of weights");
   constexpr int kAhead = kStages - 1;                              // chunks in flight ahead of the one consumed
   const int n_groups = a.n_routed + (MODE == kDown ? a.n_slabs : a.n_shared);
 
@@ -276,7 +287,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
                         (unsigned)(((MODE == kGateUp ? wn * (TN / 2) * 32 : wn * TN * 32) + (lane & 31)) * kRowBW);
   // byte distance between the fragment rows of consecutive token blocks i / column tiles j
   constexpr int kJ = 32 * kRowB;                                   // next 32 token rows
-  constexpr int kJw = 32 * kRowBW;                                 // next 32 weight rows
+  constexpr int kJw = 32 * kRowBW;                                // next 32 weight rows
   constexpr int kUp = (MODE == kGateUp) ? (BNR / 2) * kRowBW : (TN / 2) * kJw;   // j >= TN/2: the up rows / the next blocks
 
   for (int i_tile = 0; i_tile < mine; ++i_tile) {
@@ -332,14 +343,42 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         bcol[p] = (ld_pcw ^ WF::key(br)) * WF::kPerCol;
         boff[p] = (n < n_end ? (unsigned)n * WF::bytes((unsigned)G.ldw) + extra : kOob) + WF::bytes((unsigned)bcol[p]);
       }
-      // The weights of a panel with one token tile are read once in the launch (a.weights_once).  One branch for
+      // The weights of a panel with one token tile are read once in the launch (a.weights_once; LINES).  One branch for
       // a chunk's loads: one for each of them costs small launches up to a quarter (8 experts of 392, hidden 3008, a
       // fallback pass of 444 tokens, gate+up 37 us, 31 so).
-      const bool once = WB == 2 && mt == 1 && weights_once;
-      // chunk `kt` into stage `st`, then step the offsets to the next chunk
+      const bool once = mt == 1 && (LINES || (WB == 2 && weights_once));
+      // part `part` of line `line` of the weights into stage `st`, then step its offsets to the next line
+      auto load_weights = [&](int st, int line, auto part) {
+        constexpr int kIns = kInsB / kChunks, kFirst = decltype(part)::value * kIns;
+        char* const sb = s_tiles + st * kStageBytes + BM * kRowB + (lw * kInsB + kFirst) * 1024;
+        const int k0 = line * (kChunks * BK);
+        const bool full = k0 + kChunks * BK <= K;
+        unsigned off[kIns];
+#pragma unroll
+        for (int p = 0; p < kIns; ++p) {
+          off[p] = full ? boff[kFirst + p] : ((k0 + bcol[kFirst + p] < K) ? boff[kFirst + p] : kOob);
+          boff[kFirst + p] += kRowBW;
+        }
+        if (once) {
+#pragma unroll
+          for (int p = 0; p < kIns; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off[p], 0, 0, kStreamOnce);
+        } else {
+#pragma unroll
+          for (int p = 0; p < kIns; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off[p], 0, 0, 0);
+        }
+      };
+      auto each_part = [&](auto f) {
+        f(std::integral_constant<int, 0>{});
+        if constexpr (kChunks > 1) f(std::integral_constant<int, 1>{});
+        if constexpr (kChunks > 2) { f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{}); }
+      };
+      // chunk `kt` of the tokens into stage `st`, then step the offsets to the next chunk; and of the weights the same chunk, or a part of
+      // the line behind the chunk's.  That line L takes the stage of line L - 3, read to its end at chunk (L - 2) kChunks - 1; chunk kt
+      // is at least (L - 1) kChunks, and issued when chunk kt - 3 has been read.
       auto issue = [&](int st, int kt) {
         char* const sa = s_tiles + st * kStageBytes + (lw * kInsA) * 1024;
-        char* const sb = s_tiles + st * kStageBytes + BM * kRowB + (lw * kInsB) * 1024;
         const bool full = (kt + 1) * BK <= K;
 #pragma unroll
         for (int p = 0; p < kInsA; ++p) {
@@ -347,20 +386,11 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
           __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(sa + p * 1024), 16, (int)off, 0, 0, 0);
           aoff[p] += kRowB;
         }
-        unsigned off[kInsB];
-#pragma unroll
-        for (int p = 0; p < kInsB; ++p) {
-          off[p] = full ? boff[p] : ((kt * BK + bcol[p] < K) ? boff[p] : kOob);
-          boff[p] += kRowBW;
-        }
-        if (once) {
-#pragma unroll
-          for (int p = 0; p < kInsB; ++p)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off[p], 0, 0, kStreamOnce);
+        if constexpr (kChunks == 1) {
+          load_weights(st, kt, std::integral_constant<int, 0>{});
         } else {
-#pragma unroll
-          for (int p = 0; p < kInsB; ++p)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sb + p * 1024), 16, (int)off[p], 0, 0, 0);
+          const int line = kt / kChunks + 1;
+          each_part([&](auto part) { if (kt % kChunks == decltype(part)::value) load_weights(line % 3, line, part); });
         }
       };
       // wait until at most `pending` whole chunks of this wave's loads are still in flight
@@ -371,6 +401,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         else MM_WAIT_VMCNT(2 * kPerChunk);
       };
       int issued = 0, st_is = 0;                             // chunks issued; stage of the next one
+      if constexpr (kChunks > 1) each_part([&](auto part) { load_weights(0, 0, part); });
       for (; issued < kAhead && issued < nk; ++issued) { issue(st_is, issued); st_is = st_is + 1 == kStages ? 0 : st_is + 1; }
       wait_chunks(issued - 1);                               // chunk 0 has landed
       lds_barrier();                                         // barrier 0
@@ -422,6 +453,23 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
         sc_row[j] = n < G.N ? (unsigned)((MODE == kGateUp && j >= TN / 2 ? G.N : 0) + n) * blocks : kOob;
       }
     }
+    // 8-bit weights: the scale of the weight row behind column tile j (gate/up: of the gate row and
+    // of the up row behind output column j)
+    float wsc[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      wsc[j] = 1.f;
+      if (WB == 1) {
+        const float* sc = static_cast<const float*>(G.scale);
+        if (MODE == kGateUp) {
+          const int col = n0 + wn * (TN / 2) * 32 + (j % (TN / 2)) * 32 + (lane & 31);
+          if (col < G.N) wsc[j] = sc[(j >= TN / 2 ? G.N : 0) + col];
+        } else {
+          const int col = n0 + wn * TN * 32 + j * 32 + (lane & 31);
+          if (col < G.N) wsc[j] = sc[col];
+        }
+      }
+    }
     auto main_loop = [&](auto nb_tag) {
       constexpr int NB = decltype(nb_tag)::value;          // token blocks in use: 1 .. TM
       // token fragments of k-step kk of the chunk in stage st (8-bit weights: k-step 2p + e reads
@@ -437,9 +485,10 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
       };
       // weight fragments, 16 bytes per lane and column tile: bf16, the 8 k of k-step c; 8-bit, the
       // 2 x 8 codes of the k-steps 2c and 2c + 1; MXFP4 (c = 0), the 4 x 8 codes of the chunk
-      auto read_b = [&](int st, int c, bf16x8 (&fb)[TN]) {
-        const unsigned lc = (unsigned)(c * 2 + (lane >> 5));
-        const unsigned col = (lc ^ (WB == 2 ? fkey : fkeyw)) * 16u + (unsigned)(st * kStageBytes);
+      // (q: chunk of the line in stage st)
+      auto read_b = [&](int st, int q, int c, bf16x8 (&fb)[TN]) {
+        const unsigned lc = (unsigned)(q * (WF::kCols / kChunks) + c * 2 + (lane >> 5));
+        const unsigned col = (lc ^ fkeyw) * 16u + (unsigned)(st * kStageBytes);
         if constexpr (TN == 2) {
           frag_read2<0, kUp>(fb[0], fb[1], b_rd + col);
         } else {
@@ -474,26 +523,27 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
       if constexpr (WB == 0) { load_mx_scales(0); }
       lds_barrier();                                       // barrier 0
       read_a(0, 0, fa[0]);
-      if constexpr (WB == 2) { read_b(0, 0, fb[0]); frag_wait(fa[0]); frag_wait(fb[0]); }
+      if constexpr (WB == 2) { read_b(0, 0, 0, fb[0]); frag_wait(fa[0]); frag_wait(fb[0]); }
       else {
-        read_b(0, 0, fr); frag_wait(fa[0]); frag_wait(fr);
+        read_b(0, 0, 0, fr); frag_wait(fa[0]); frag_wait(fr);
         if constexpr (WB == 0) { take_mx_scales(); load_mx_scales(1); }
         widen(fb[0], 0);
       }
-      int st = 0;                                          // stage of chunk kt
+      int st = 0, stw = 0, q = 0;                          // stages of chunk kt and of its weights' line; its number in that line
       for (int kt = 0; kt < nk; ++kt) {
         const int st_nx = st + 1 == kStages ? 0 : st + 1;  // stage of chunk kt+1
+        const int q_nx = kChunks == 1 || q + 1 == kChunks ? 0 : q + 1, stw_nx = kChunks == 1 ? st_nx : (q_nx ? stw : (stw + 1 == kStages ? 0 : stw + 1));
 #pragma unroll
         for (int kk = 0; kk < kParts; ++kk) {
           const int cur = kk & 1, nxt = (kk + 1) & 1, u = SUMS == 1 ? 0 : kk >> 1;   // kParts is even: set 0 again holds k-step 0 of the next chunk
-          int st_rd = st, kk_rd = kk + 1;
+          int st_rd = st, stw_rd = stw, q_rd = q, kk_rd = kk + 1;
           if (kk + 1 == kParts) {
             lds_barrier();                                 // barrier kt+1
-            st_rd = st_nx; kk_rd = 0;                      // stale data behind the last chunk; never used
+            st_rd = st_nx; stw_rd = stw_nx; q_rd = q_nx; kk_rd = 0;                 // stale data behind the last chunk; never used
           }
           read_a(st_rd, kk_rd, fa[nxt]);
           if constexpr (WB == 2) {
-            read_b(st_rd, kk_rd, fb[nxt]);
+            read_b(stw_rd, q_rd, kk_rd, fb[nxt]);
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -506,7 +556,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
             // They are widened behind the first token block's MFMAs, so that the conversions run while
             // the matrix unit works.
             const bool kRead = (kk % kPer) == kPer - 1;     // known after unrolling
-            if (kRead) read_b(st_rd, kk_rd / kPer, fr);
+            if (kRead) read_b(stw_rd, q_rd, kk_rd / kPer, fr);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
               acc[u][0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][j], acc[u][0][j], 0, 0, 0);
@@ -524,7 +574,7 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
           }
           __builtin_amdgcn_sched_barrier(0);               // keep the steps apart; free order inside a step
         }
-        st = st_nx;
+        st = st_nx; stw = stw_nx; q = q_nx;
       }
     };
     if (n_blk == TM) {
@@ -542,23 +592,6 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
     }
 
     // ---- epilogue: accumulator v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32 ----
-    // 8-bit weights: the scale of the weight row behind column tile j (gate/up: of the gate row and
-    // of the up row behind output column j)
-    float wsc[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      wsc[j] = 1.f;
-      if (WB == 1) {
-        const float* sc = static_cast<const float*>(G.scale);
-        if (MODE == kGateUp) {
-          const int col = n0 + wn * (TN / 2) * 32 + (j % (TN / 2)) * 32 + (lane & 31);
-          if (col < G.N) wsc[j] = sc[(j >= TN / 2 ? G.N : 0) + col];
-        } else {
-          const int col = n0 + wn * TN * 32 + j * 32 + (lane & 31);
-          if (col < G.N) wsc[j] = sc[col];
-        }
-      }
-    }
     if constexpr (SUMS == 2) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -594,24 +627,24 @@ __global__ __launch_bounds__(SH::kThreads) MOE_TILED_ATTR void tiled_kernel(cons
   }
 }
 
-template <int MODE, typename SH, int WB, bool EVEN = false>
+template <int MODE, typename SH, int WB, bool EVEN = false, bool LINES = false>
 int launch_tiled_shape(const StreamArgs& a, hipStream_t s) {
-  constexpr size_t kLds = (size_t)SH::kStages * SH::template stage_bytes<WB>();
+  constexpr size_t kLds = (size_t)SH::kStages * SH::template stage_bytes<WFmt<WB, LINES>>();
   static std::atomic<int> cached{0};
   int per_cu = cached.load(std::memory_order_relaxed);
   if (per_cu == 0) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tiled_kernel<MODE, SH, WB, EVEN>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tiled_kernel<MODE, SH, WB, EVEN, LINES>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds) != hipSuccess)
       return hip_fail(hipGetLastError(), "tiled_kernel: LDS size attribute");
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled_kernel<MODE, SH, WB, EVEN>, SH::kThreads, kLds) != hipSuccess || n < 1) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled_kernel<MODE, SH, WB, EVEN, LINES>, SH::kThreads, kLds) != hipSuccess || n < 1) n = 1;
     per_cu = n;
     cached.store(n, std::memory_order_relaxed);
   }
   int grid = device_cu_count() * per_cu;
   grid = grid / 8 * 8;                                      // the XCD walk wants a multiple of 8
   if (grid < 8) grid = 8;
-  hipLaunchKernelGGL((tiled_kernel<MODE, SH, WB, EVEN>), dim3((unsigned)grid), dim3(SH::kThreads), kLds, s, a);
+  hipLaunchKernelGGL((tiled_kernel<MODE, SH, WB, EVEN, LINES>), dim3((unsigned)grid), dim3(SH::kThreads), kLds, s, a);
   return hip_fail(hipGetLastError(), "tiled_kernel launch");
 }
 
@@ -630,11 +663,11 @@ int launch_tiled(StreamMode mode, int weight_format, const StreamArgs& a, hipStr
   }
 #if MOE_TILED_BK == 64   // the narrow formats are written for 64-k chunks
   else if (weight_format == 1) {
-    if (mode == kGateUp) return launch_tiled_shape<kGateUp, NarrowShape, 1>(a, s);
-    if (mode == kDown) return launch_tiled_shape<kDown, NarrowShape, 1>(a, s);
+    if (mode == kGateUp) return a.lines ? launch_tiled_shape<kGateUp, NarrowShape, 1, false, true>(a, s) : launch_tiled_shape<kGateUp, NarrowShape, 1>(a, s);
+    if (mode == kDown) return a.lines ? launch_tiled_shape<kDown, NarrowShape, 1, false, true>(a, s) : launch_tiled_shape<kDown, NarrowShape, 1>(a, s);
   } else if (weight_format == 0) {
-    if (mode == kGateUp) return launch_tiled_shape<kGateUp, NarrowShape, 0>(a, s);
-    if (mode == kDown) return launch_tiled_shape<kDown, NarrowShape, 0>(a, s);
+    if (mode == kGateUp) return a.lines ? launch_tiled_shape<kGateUp, NarrowShape, 0, false, true>(a, s) : launch_tiled_shape<kGateUp, NarrowShape, 0>(a, s);
+    if (mode == kDown) return a.lines ? launch_tiled_shape<kDown, NarrowShape, 0, false, true>(a, s) : launch_tiled_shape<kDown, NarrowShape, 0>(a, s);
   }
 #endif
   return fail(MOE_E_BADARG, "tiled kernel: bad mode or weight format");

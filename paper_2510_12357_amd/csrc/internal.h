@@ -81,6 +81,7 @@ struct StreamArgs {
   int by_rows;                        // tiled and wide kernels: order of their tiles (ffn_route)
   int two_sums;                       // tiled kernel, bf16 gate/up: the two sums per output of the streaming kernels
   int even_tiles;                     // tiled kernel, bf16: tiles of a width that fills the rounds over the CUs (ffn_route)
+  int lines;                          // tiled kernel, narrow weights: loaded in whole lines (ffn_route)
   int weights_once;                   // tiled kernel, bf16: weights read once go past the caches (ffn_route)
   const void* x;                      // [T,H]
   void* h_routed;                     // [T*k_big, I]   SwiGLU activations (storage dtype)

@@ -14,7 +14,7 @@ int main() {
       if (s >= MOE_MAX_SHARED || scanf("%d", &c.shared_I[s]) != 1) return 2;
     if (scanf("%d %d %d", &routed, &shared, &cus) != 3) return 2;
     const mm::FfnRoute r = mm::ffn_route(c, routed != 0, shared != 0, cus);
-    printf("%d %d %d %d %d %d %d %d %d %d\n", (int)r.gate_up, (int)r.down, (int)r.by_rows_gate_up, (int)r.by_rows_down, (int)r.two_tiles,
-           (int)r.wide_panels, (int)r.weights_once, (int)mm::router_kernel(c), (int)r.even_gate_up, (int)r.even_down);
+    printf("%d %d %d %d %d %d %d %d %d %d %d\n", (int)r.gate_up, (int)r.down, (int)r.by_rows_gate_up, (int)r.by_rows_down, (int)r.two_tiles,
+           (int)r.wide_panels, (int)r.weights_once, (int)mm::router_kernel(c), (int)r.even_gate_up, (int)r.even_down, (int)r.lines);
   }
 }

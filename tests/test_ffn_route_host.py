@@ -36,7 +36,7 @@ def route(tmp_path_factory):
              int(routed), int(shared), CUS]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True, env=env)
         v = tuple(map(int, r.stdout.split()))
-        run.even = v[8:]
+        run.even, run.lines = v[8:10], v[10]
         return v[:8]
 
     def ask(cfg, routed=True, shared=True):
@@ -50,6 +50,7 @@ def route(tmp_path_factory):
             return gate_up, (g[1] if g[1] == d[1] else (g[1], d[1]))
         return g, d
     ask.raw = run
+    ask.lines = lambda cfg: (run(cfg, True, True), run.lines)[1]
     ask.even = lambda cfg, shared=True: (run(cfg, True, shared), run.even)[1]
     ask.router = lambda cfg: run(cfg, True, True)[7]
     ask.weights_once = lambda cfg, routed=True: run(cfg, routed, True)[6]
@@ -191,6 +192,16 @@ def test_tiles_that_fill_their_rounds(route):
     for dtype in ("bf16w8", "bf16mx4"):
         assert route.even(c["fine60_decode"].with_(T=1000, dtype=dtype)) == (0, 0)
     assert route.even(wl.LayerConfig("small", T=300, H=512, E=8, I=512, k_big=2, k_little=1)) == (0, 0)
+
+
+def test_narrow_weights_in_whole_lines(route):
+    """MXFP4 tiles of large layers, 8-bit ones while their experts have fewer than 200 rows on average; bf16, panels and smaller layers never."""
+    c = wl.CONFIGS["fine64_prefill"]
+    assert [route.lines(c.with_(T=T, dtype="bf16mx4")) for T in (255, 1500, 4096)] == [0, 1, 1]
+    assert [route.lines(c.with_(T=T, dtype="bf16w8")) for T in (255, 1500, 4096)] == [0, 1, 0]
+    assert route.lines(c.with_(T=1500)) == 0
+    for H, line in ((1024, 0), (4096, 1)):
+        assert route.lines(wl.LayerConfig("l", T=2000, H=H, E=16, I=1024, k_big=2, k_little=1, dtype="bf16mx4")) == line
 
 
 def test_dispatch_beside_gate_up_is_tested_where_the_rules_take_it(route):

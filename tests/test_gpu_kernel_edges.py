@@ -290,6 +290,26 @@ def test_every_code_of_8_bits(T, kernel, variants):
         assert torch.equal(torch.nan_to_num(y, 1e9), torch.nan_to_num(y[:, 0x38:0x39] * value, 1e9)) and y[0, 0x38] > 3, variant
 
 
+@pytest.mark.parametrize("dtype", ["bf16w8", "bf16mx4"])
+@pytest.mark.parametrize("counts,H,I,shared", [
+    ([200, 0, 1, 55], 32, 96, ()),                                 # K within a line, a line ends in its middle
+    ([31, 32, 33, 64, 96, 127], 128, 256, (288,)),                 # whole lines, one of them; every number of token blocks
+    ([129, 257, 2], 160, 544, (64, 1056)),                         # several token tiles; last line of one chunk or less
+    ([300], 640, 352, (32,)),
+    ([9] * 30, 1056, 736, ()),                                     # several tiles per workgroup
+])
+def test_narrow_weights_in_whole_lines(dtype, counts, H, I, shared):
+    """Variant 1 loads whole lines: every bit is that of chunk after chunk, which the fp32 oracle checks."""
+    if dtype == "bf16mx4":                                         # multiples of 128: lines of two chunks and four
+        H, I, shared = -(-H // 128) * 128, -(-I // 128) * 128, [-(-i // 128) * 128 for i in shared]
+    cfg, experts, sh, table, x, of = _coded_layer(counts, H, I, shared, dtype)
+    b = _assigned_step(cfg, x, table, sh, of)
+    ref, ref_out = _run_on(TILED, 0, b, x, table, sh)
+    assert torch.isfinite(ref).all()
+    y, out = _run_on(TILED, 1, b, x, table, sh)
+    assert torch.equal(y, ref) and (not shared or torch.equal(out, ref_out))
+
+
 @pytest.mark.parametrize("dtype,counts,H,I,shared", [
     ("bf16", [5, 0, 20, 17, 1], 200, 264, ()),                     # K ends inside a unit of 256 bytes; quads that the waves do not divide
     ("bf16", [30, 2, 64, 65], 1032, 72, (520,)),                   # gate rows that end inside a tile; K in parts of a unit
