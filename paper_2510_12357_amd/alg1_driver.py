@@ -195,7 +195,7 @@ class Alg1Batch:
             if dev.block_work is not None:
                 dev.block_work()
             if self.caches is None:
-                # resident experts: a batch of at most 64 slots is one launch per layer
+                # resident experts: a batch of at most 64 slots is one call per layer
                 step = mm.layer_decode_step if b.lws is not None else mm.layer_step
                 x = step(b, x, ly["Wg"], ly["gate_bias"], self.conf_dev, ly["table"], ly["shared"])
             else:

@@ -34,7 +34,7 @@ struct FfnRoute {
 FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cus);
 
 // Router logits of a step.  kRouterOneLaunch: logits and selection of a token in one workgroup; kRouterGemv:
-// plain-FMA GEMV over many waves, then the selection; kRouterGemm: MFMA GEMM, then the selection.
+// plain-FMA GEMV over many waves, then the selection; kRouterGemm: MFMA tiles (gate_mfma_kernel), then the selection.
 enum RouterKernel { kRouterOneLaunch = 0, kRouterGemv = 1, kRouterGemm = 2 };
 RouterKernel router_kernel(const moe_config& c);
 
