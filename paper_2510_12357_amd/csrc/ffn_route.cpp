@@ -304,7 +304,7 @@ bool wide_panels(const moe_config& c, bool run_shared, int cus) {
 // 2048 + 2048 (226 MB), 256 tokens 66 / 81, 84 / 75, 16 of 1408 (277 MB), 600 tokens 87 / 94, 93 / 91.  A chunk has to be a
 // cache line: of rows that are not whole lines its pieces share lines with the next chunk's, which then come twice (64 of
 // 1968 + 2064, hidden 3256, 3424 tokens 894 / 1064, 64 of 1864, hidden 3104, fallback pass of 273 tokens 436 / 502), and
-// narrow weights have half a line and less (MXFP4, 60 experts, 600 tokens, gate+up 123 / 147).
+// a chunk of narrow weights is half a line and less (MXFP4, 60 experts, 600 tokens, gate+up 123 / 147; whole_lines has its own).
 constexpr int kLineWeights = 64;                     // bf16 weights in a cache line of 128 bytes
 bool weights_once(const moe_config& c) {
   bool lines = c.H % kLineWeights == 0 && c.I % kLineWeights == 0;
