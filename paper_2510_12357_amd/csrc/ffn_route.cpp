@@ -333,10 +333,15 @@ bool tiled_gate_up(const moe_config& c) {
 // layers of little time per tile feel (us, MXFP4, chunks / lines: 64 experts of 256, hidden 512, 900 tokens 17.0 + 13.5 / 18.5 + 14.5; 32
 // of 1024, hidden 1024 (201 MB in bf16) 24.8 + 22.9 / 27.1 + 23.1; 16 of 1024, hidden 4096 (403 MB) 67.5 + 26.5 / 62.0 + 24.1), and 8-bit
 // ones whose matrix cores set the pace (8 bits, 64 of 1024, 2500 tokens 173 + 130 / 175 + 131; 8 of 14336, 1400 tokens 474 + 210 / 477 + 209,
-// 900 tokens 422 + 203 / 418 + 186).
+// 900 tokens 422 + 203 / 418 + 186) or whose rows are not whole lines (64 of 1968 + 2064, hidden 3264, 600 tokens 243 + 160 / 247 + 176;
+// 24 of 1872, hidden 3120, 121 + 83 / 117 + 80).  MXFP4 gains there too (64 of 1920, hidden 3200, 600 tokens 184 + 110 / 175 + 106).
 bool whole_lines(const moe_config& c) {
   const Work w = layer_work(c);
-  return c.dtype != MOE_BF16 && layer_bytes(c) >= 384ll << 20 && (c.dtype != MOE_BF16_W8 || w.rows < 200 * w.weight_rows);
+  if (c.dtype == MOE_BF16 || layer_bytes(c) < 384ll << 20) return false;
+  if (c.dtype != MOE_BF16_W8) return true;
+  bool lines = c.H % 128 == 0 && c.I % 128 == 0;
+  for (int s = 0; s < c.n_shared; ++s) lines = lines && c.shared_I[s] % 128 == 0;
+  return lines && w.rows < 200 * w.weight_rows;
 }
 
 // bf16 tiles of a width that fills their last round over the CUs, which the kernel chooses where that round has room (ffn_tiled.hip, with

@@ -195,11 +195,13 @@ def test_tiles_that_fill_their_rounds(route):
 
 
 def test_narrow_weights_in_whole_lines(route):
-    """MXFP4 tiles of large layers, 8-bit ones while their experts have fewer than 200 rows on average; bf16, panels and smaller layers never."""
+    """MXFP4 tiles of large layers, 8-bit ones of whole lines per row while their experts have fewer than 200 rows on average; bf16, panels and smaller layers never."""
     c = wl.CONFIGS["fine64_prefill"]
     assert [route.lines(c.with_(T=T, dtype="bf16mx4")) for T in (255, 1500, 4096)] == [0, 1, 1]
     assert [route.lines(c.with_(T=T, dtype="bf16w8")) for T in (255, 1500, 4096)] == [0, 1, 0]
     assert route.lines(c.with_(T=1500)) == 0
+    for odd in (dict(I=1040), dict(H=2064), dict(shared_I=(1040,))):
+        assert route.lines(c.with_(T=1500, dtype="bf16w8", **odd)) == 0
     for H, line in ((1024, 0), (4096, 1)):
         assert route.lines(wl.LayerConfig("l", T=2000, H=H, E=16, I=1024, k_big=2, k_little=1, dtype="bf16mx4")) == line
 
