@@ -61,22 +61,13 @@ struct Selection {
   bool imp;
 };
 
-// Lowest expert id, not taken, whose value is `best`: one ballot per set of 64 experts.  Some lane holds it.
-template <int PL>
-__device__ __forceinline__ int first_expert_with(const float (&v)[PL], unsigned open, float best) {
-  int sel = 0;
-#pragma unroll
-  for (int c = PL - 1; c >= 0; --c) {
-    const unsigned long long at = __ballot(((open >> c) & 1u) && v[c] == best);
-    if (at) sel = 64 * c + (int)__builtin_ctzll(at);
-  }
-  return sel;
-}
-
 // One wave selects for token t.  raw[c] = logit of expert lane + 64*c (anything for e >= E); E <= 64 PL.
 // A round costs one reduction: the best value's expert is the first bit of a ballot and its probability one lane's.  With
 // a second reduction for the lowest id and a third for the probability, and four experts per lane whatever E, route_kernel took, us, now /
 // then: 8 / 4 of 64 experts, 300 tokens 4.8 / 5.5, 2000 tokens 4.9 / 6.3, 4000 tokens 5.2 / 8.3 (4.6 is what any launch takes there).
+// Lanes of several experts keep their best one beside them, so that a ballot for each set of 64 is only taken where lanes tie.  us in a
+// graph, moe_route on given logits, three reductions / a ballot per set in every round / so: 16 of 65 experts, 64 tokens 7.3 / 8.4 / 6.7, 8 of 128, 64
+// tokens 4.8 / 5.3 / 4.5, 2048 tokens 6.0 / 6.1 / 5.1.
 template <int PL>
 __device__ __forceinline__ Selection select_values(const RouteParams& P, int t, int lane, const float* raw) {
   const float NINF = -INFINITY;
@@ -107,28 +98,44 @@ __device__ __forceinline__ Selection select_values(const RouteParams& P, int t, 
 
   // Alg. 1: the little result is kept only if the confidence is strictly above gamma
   const bool imp = P.conf ? !(P.conf[t] > P.gamma) : true;
-  const int k = imp ? P.k_big : P.k_little;
+  const int k = __builtin_amdgcn_readfirstlane(imp ? P.k_big : P.k_little);   // one token: the same in all lanes
 
   // k rounds of "best expert not taken yet"
   float my_w = 0.f;                                    // lane j keeps the j-th weight
   int my_e = -1;
   float wsum = 0.f;
   float best = m;                                      // of the experts not taken
-  for (int j = 0; j < k; ++j) {
-    const int sel = first_expert_with<PL>(v, open, best);
-    float psel = 0.f;
+  // PL > 1: this lane's best expert not taken, the lowest of equal ones: value, probability, set (PL: none left)
+  float mine = NINF, p_mine = p[0];
+  int c_mine = 0;
+  auto best_of_lane = [&] {
+    mine = NINF; c_mine = PL;
 #pragma unroll
-    for (int c = 0; c < PL; ++c) {
-      if (sel >> 6 == c) psel = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, p[c]), sel & 63));
-      if (lane + 64 * c == sel) open &= ~(1u << c);
+    for (int c = PL - 1; c >= 0; --c)
+      if (((open >> c) & 1u) && v[c] >= mine) { mine = v[c]; p_mine = p[c]; c_mine = c; }
+  };
+  if (PL > 1) best_of_lane();
+  for (int j = 0; j < k; ++j) {
+    const unsigned long long at = __ballot(PL > 1 ? c_mine < PL && mine == best : (open & 1u) && v[0] == best);   // some lane holds it
+    int l = (int)__builtin_ctzll(at), set = 0;
+    if (PL > 1) {
+      if (at & (at - 1)) {                             // several: the lowest set goes first
+#pragma unroll
+        for (int c = PL - 1; c >= 0; --c) {
+          const unsigned long long in_set = __ballot(c_mine == c && mine == best);
+          if (in_set) l = (int)__builtin_ctzll(in_set);
+        }
+      }
+      set = __builtin_amdgcn_readlane(c_mine, l);
     }
-    psel *= inv_s;
+    const int sel = 64 * set + l;
+    const float psel = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, p_mine), l)) * inv_s;
+    if (lane == l) open &= ~(1u << set);
     wsum += psel;
     if (lane == j) { my_w = psel; my_e = sel; }
     if (j + 1 < k) {
-      float mine = NINF;
-#pragma unroll
-      for (int c = 0; c < PL; ++c) mine = (open >> c) & 1u ? fmaxf(mine, v[c]) : mine;
+      if (PL > 1) best_of_lane();
+      else mine = open & 1u ? v[0] : NINF;
       best = wave_max(mine);
     }
   }
