@@ -312,8 +312,9 @@ int moe_combine_add(const moe_config* cfg, const float* y, const float* topk_w, 
 /* ------------------------------------------------------------------------------------------
  * A whole step, and the second pass of Alg. 1, in one call each: the calls above in their order on one
  * stream, with their checks, outputs and errors (a call that is refused has enqueued what came in front of the
- * refused part).  What is saved is the host's time for four calls and, above 256 tokens, a launch: the selection
- * counts the pairs of each expert for the dispatch, in the activations' workspace, which is free at that point.
+ * refused part).  What is saved is the host's time for four calls and, above 256 tokens while tokens and experts are
+ * not too many, a launch: the selection counts the pairs of each expert for the dispatch, in the activations' workspace, which
+ * is free at that point.
  *   moe_layer_step      moe_route, moe_dispatch, moe_expert_ffn (routed and shared), moe_combine
  *   moe_layer_fallback  moe_route(logits_given), moe_dispatch_from(j_lo = k_little), moe_expert_ffn(routed only),
  *                       moe_combine_add(j_lo = k_little)

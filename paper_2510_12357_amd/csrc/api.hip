@@ -196,7 +196,7 @@ extern "C" int moe_device_info(int32_t* n_cu, int32_t* is_gfx950) {
 }
 
 namespace {
-// counts: as launch_route; only asked for where router_kernel says kRouterGemm
+// counts: as launch_route; only asked for where selection_counts says so
 int route_step(const moe_config* cfg, const void* x, const void* Wg, const float* gate_bias, const float* conf, float* logits,
                int logits_given, int32_t* topk_idx, float* topk_w, uint8_t* important, int32_t* k_t, int32_t* counts, void* stream) {
   int rc = validate_config(cfg);
@@ -498,7 +498,7 @@ extern "C" int moe_layer_step(const moe_config* cfg, const void* x, const void* 
   }
   // the activations' workspace is free until gate/up: the selection's counts go there
   const bool fits = whole && sizeof(int32_t) * (size_t)cfg->E * (size_t)route_count_rows(cfg->T) <= b->ffn_ws_bytes;
-  int32_t* counted = fits && dispatch_counts(cfg->T) ? static_cast<int32_t*>(b->ffn_ws) : nullptr;
+  int32_t* counted = fits && selection_counts(*cfg) ? static_cast<int32_t*>(b->ffn_ws) : nullptr;
   rc = route_step(cfg, x, Wg, gate_bias, conf, b->logits, logits_given, b->topk_idx, b->topk_w, b->important, b->k_t, counted, stream);
   if (rc) return rc;
   rc = dispatch_step(cfg, b->topk_idx, b->k_t, 0, b->expert_offsets, b->sorted_token, b->sorted_rank, b->inv_pos, b->dispatch_ws,

@@ -10,17 +10,16 @@
 // the tokens for each: 200 tokens 12.4 -> 4.8 us, 64 tokens 5.5 -> 4.6; the scatter kernel at 2048 tokens, 8 of 64
 // experts, 11.3 -> 7.2).  The experts of one token must be distinct,
 // as the selection stage produces them.  Two shapes:
-//   * T <= kSmallT: one workgroup, one launch.
+//   * T <= kSmallDispatchT: one workgroup, one launch.
 //   * larger T: one workgroup per chunk of 128 tokens; a count kernel, then a scatter kernel
-//     that rebuilds the prefixes of the counts itself.  In a step of one call the selection kernel has counted already,
-//     per 16 tokens, and the count kernel is not launched (4.6 us as part of a step, whatever it has to do).
+//     that rebuilds the prefixes of the counts itself.  In a step of one call the selection kernel may have counted
+//     already, per 16 tokens, and the count kernel is not launched (selection_counts has the rule).
 #include "internal.h"
 #include "dispatch_device.h"
 
 namespace mm {
 namespace {
 
-constexpr int kSmallT = 256;
 constexpr int kSmallThreads = 1024;
 constexpr int kBigThreads = 256;
 
@@ -28,7 +27,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ k_t, int j_lo, int T, int E, int K,
     int32_t* __restrict__ offsets, int32_t* __restrict__ sorted_token,
     int32_t* __restrict__ sorted_rank, int32_t* __restrict__ inv_pos) {
-  constexpr int kWords = kSmallT / 64, kPerThread = kSmallT * MOE_MAX_TOPK / kSmallThreads;
+  constexpr int kWords = kSmallDispatchT / 64, kPerThread = kSmallDispatchT * MOE_MAX_TOPK / kSmallThreads;
   __shared__ unsigned long long s_mask[MOE_MAX_EXPERTS][kWords];
   __shared__ int s_off[MOE_MAX_EXPERTS + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = T * K;
@@ -197,14 +196,13 @@ __global__ void dispatch_empty_kernel(int E, int32_t* offsets) {
 
 int dispatch_chunks(int T) { return (T + kChunk - 1) / kChunk; }
 int route_count_rows(int T) { return dispatch_chunks(T) * (kChunk / kRouteTokens); }
-bool dispatch_counts(int T) { return T > kSmallT; }
 
 int launch_dispatch(const moe_config& c, const int32_t* idx, const int32_t* k_t, int j_lo, int32_t* offsets,
                     int32_t* sorted_token, int32_t* sorted_rank, int32_t* inv_pos, int32_t* counts,
                     bool counted, hipStream_t s) {
   if (c.T == 0) {
     hipLaunchKernelGGL(dispatch_empty_kernel, dim3(1), dim3(256), 0, s, c.E, offsets);
-  } else if (c.T <= kSmallT) {
+  } else if (c.T <= kSmallDispatchT) {
     hipLaunchKernelGGL(dispatch_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, idx, k_t, j_lo, c.T, c.E,
                        c.k_big, offsets, sorted_token, sorted_rank, inv_pos);
   } else {

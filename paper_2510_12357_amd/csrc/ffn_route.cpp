@@ -407,4 +407,14 @@ RouterKernel router_kernel(const moe_config& c) {
   return c.E <= kOneLaunchExperts && reads <= limit ? kRouterOneLaunch : kRouterGemv;
 }
 
+// Counting in the selection saves a launch, and every workgroup of the dispatch then adds up a row per 16 tokens instead of one per 128, eight times
+// the table, which grows with T^2 E.  us per step, counted by the selection / by a launch of its own, hidden 2048: 8 experts of 2048, 8192 tokens 325 /
+// 328, 16384 tokens 629 / 629; 16 of 1024, 8192 tokens 219 / 221, 12000 tokens 295 / 294; 32 of 512, 4096 tokens 157 / 158, 8192 tokens 254 / 252; 64
+// of 256, 300 tokens 70 / 73, 2048 tokens 123 / 124, 4096 tokens 200 / 200, 8192 tokens 345 / 341, 16384 tokens 684 / 671; 128 of 128, 1024 tokens
+// 96 / 97, 2048 tokens 124 / 123, 16384 tokens 627 / 599; 256 of 128, 512 tokens 125 / 126, 1024 tokens 137 / 136, 16384 tokens 759 / 703.
+bool selection_counts(const moe_config& c) {
+  constexpr int kMaxT = 8192, kMaxTable = 128 << 10;
+  return c.T > kSmallDispatchT && c.T <= kMaxT && c.T * c.E <= kMaxTable && router_kernel(c) == kRouterGemm;
+}
+
 }  // namespace mm

@@ -1,4 +1,4 @@
-// Which kernel a call of moe_route or moe_expert_ffn runs on, and in which order its tiles: plain host C++ (no
+// Which kernel a call of moe_route, moe_expert_ffn or moe_layer_step runs on, and in which order its tiles: plain host C++ (no
 // HIP), from sizes alone, so that the rules can be checked without a GPU.
 #pragma once
 
@@ -37,5 +37,9 @@ FfnRoute ffn_route(const moe_config& c, bool run_routed, bool run_shared, int cu
 // plain-FMA GEMV over many waves, then the selection; kRouterGemm: MFMA tiles (gate_mfma_kernel), then the selection.
 enum RouterKernel { kRouterOneLaunch = 0, kRouterGemv = 1, kRouterGemm = 2 };
 RouterKernel router_kernel(const moe_config& c);
+
+constexpr int kSmallDispatchT = 256; // tokens that one workgroup of the dispatch places without counting
+// A step of one call: the selection counts the pairs of each expert for the dispatch, per 16 tokens.
+bool selection_counts(const moe_config& c);
 
 }  // namespace mm

@@ -145,7 +145,6 @@ int launch_gate_mfma(const moe_config& c, const void* x, const void* Wg, const f
 int launch_confidence(const float* z, int T, int V, float* conf, hipStream_t s);
 int dispatch_chunks(int T);          // workgroups (token chunks) of the large-T dispatch
 int route_count_rows(int T);         // rows of the count table that launch_route fills: whole chunks
-bool dispatch_counts(int T);         // more tokens than one workgroup places
 // pairs (t, j) with j_lo <= j < k_t[t]; counted (j_lo = 0): launch_route has filled `counts`
 int launch_dispatch(const moe_config& c, const int32_t* idx, const int32_t* k_t, int j_lo, int32_t* offsets,
                     int32_t* sorted_token, int32_t* sorted_rank, int32_t* inv_pos, int32_t* counts,

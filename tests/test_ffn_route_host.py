@@ -36,7 +36,7 @@ def route(tmp_path_factory):
              int(routed), int(shared), CUS]
         r = subprocess.run([out], input=" ".join(map(str, v)) + "\n", capture_output=True, text=True, check=True, env=env)
         v = tuple(map(int, r.stdout.split()))
-        run.even, run.lines = v[8:10], v[10]
+        run.even, run.lines, run.counts = v[8:10], v[10], v[11]
         return v[:8]
 
     def ask(cfg, routed=True, shared=True):
@@ -52,6 +52,7 @@ def route(tmp_path_factory):
     ask.raw = run
     ask.lines = lambda cfg: (run(cfg, True, True), run.lines)[1]
     ask.even = lambda cfg, shared=True: (run(cfg, True, shared), run.even)[1]
+    ask.counts = lambda cfg: (run(cfg, True, True), run.counts)[1]
     ask.router = lambda cfg: run(cfg, True, True)[7]
     ask.weights_once = lambda cfg, routed=True: run(cfg, routed, True)[6]
     return ask
@@ -212,6 +213,16 @@ def test_dispatch_beside_gate_up_is_tested_where_the_rules_take_it(route):
     layers = [wl.LayerConfig("f", T=T, H=H, E=E, I=I, k_big=K, k_little=kl, shared_I=sh, dtype=d) for d, T, E, K, kl, H, I, sh in cases]
     assert all(route.raw(c, True, True)[0] == PANELS for c in layers)
     assert sum(route.raw(c, True, False)[0] == PANELS for c in layers) >= 5
+
+
+def test_selection_counts_while_its_table_is_small(route):
+    """The dispatch reads a table of a row per 16 tokens in every workgroup: with many tokens or experts a count launch is faster."""
+    layer = lambda T, E, dtype="bf16": wl.LayerConfig("c", T=T, H=64, E=E, I=8, k_big=1, k_little=1, dtype=dtype)  # noqa: E731
+    for E, last in ((1, 8192), (16, 8192), (60, 2184), (64, 2048), (128, 1024), (200, 655), (256, 512)):
+        for dtype in ("bf16", "fp32", "bf16w8"):
+            assert [route.counts(layer(T, E, dtype)) for T in (256, 257, last, last + 1, 65535, 1 << 20)] == [0, 1, 1, 0, 0, 0]
+    edge = {c[:2] for c in _cases(edges.test_step_in_one_call_with_many_tokens_or_experts)}
+    assert {route.counts(layer(*c)) for c in edge} == {0, 1}
 
 
 def _cases(test):

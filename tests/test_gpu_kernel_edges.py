@@ -547,6 +547,12 @@ def test_step_in_one_call_equals_the_separate_calls(T, E, K, kl, I, shared, give
     assert [n for n in arrays if not torch.equal(getattr(b1, n), getattr(b2, n))] == []
 
 
+@pytest.mark.parametrize("T,E", [(512, 256), (513, 256), (1024, 128), (655, 200), (8192, 16), (8193, 16)])
+def test_step_in_one_call_with_many_tokens_or_experts(T, E):
+    """The largest steps whose selection counts, and steps just above them: every output array of the separate calls."""
+    test_step_in_one_call_equals_the_separate_calls(T, E, 8, 4, 16, (), False)
+
+
 @pytest.mark.parametrize("dtype,T,E,K,kl,H,I,shared", [
     ("bf16mx4", 8, 200, 16, 8, 1024, 384, (128,)), ("bf16mx4", 63, 256, 3, 1, 512, 640, ()), ("bf16mx4", 64, 200, 8, 4, 1024, 384, ()),
     ("bf16mx4", 65, 200, 16, 8, 1024, 384, (128, 256)), ("bf16mx4", 255, 200, 16, 8, 1024, 384, (128,)),
