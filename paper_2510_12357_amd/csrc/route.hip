@@ -154,7 +154,9 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gate_route_kernel(const S* _
 // tile of either at a hidden size of 2048), a wave issues the loads of whole cache lines of all its rows before the
 // first product, and the partial sums meet in LDS.  us, a register-ring GEMM with items of 16 tokens x 32 experts on four waves /
 // here: 64 experts of 2048, 300 tokens 10.7 / 6.0, 700 tokens 10.6 / 6.1, 2000 tokens 11.2 / 8.1, 4000 tokens 18.0 / 11.0; 8 experts of
-// 4096, 300 tokens 11.3 / 8.0, 4000 tokens 15.1 / 13.4.  Measured and not kept: all experts and the selection in the same workgroup (300 tokens, 64
+// 4096, 300 tokens 11.3 / 8.0, 4000 tokens 15.1 / 13.4.  Steps that do not fit take 32 tokens x 32 experts, with up to 16 experts x 16: half of the
+// larger tile would not exist (in a graph, 32 x 32 / 32 x 16: 8 of 4096, 4500 tokens 16.1 / 15.0, 32768 tokens 58.9 / 55.3; 16 of 2048, 16384 tokens
+// 21.5 / 20.2; rows from memory the same; 16 x 16, two workgroups per CU 31.1 / 28.0 from memory there but 37 / 30 at 16 of 7168, 4112 tokens).  Measured and not kept: all experts and the selection in the same workgroup (300 tokens, 64
 // experts of 2048: 14.2, against 6.8 and a selection of 4.6: 320 KB through one CU).
 constexpr int kMfmaWaves = 16;
 
@@ -269,6 +271,7 @@ void launch_gate_mfma_typed(const moe_config& c, const void* x, const void* Wg, 
   const int tt = (c.T + 15) / 16, et = (c.E + 15) / 16, cus = device_cu_count();
   if (tt * et <= cus) launch_gate_mfma_tile<S, 1, 1>(c, x, Wg, bias, logits, s);
   else if (tt * ((et + 1) / 2) <= cus) launch_gate_mfma_tile<S, 1, 2>(c, x, Wg, bias, logits, s);
+  else if (et == 1) launch_gate_mfma_tile<S, 2, 1>(c, x, Wg, bias, logits, s);
   else launch_gate_mfma_tile<S, 2, 2>(c, x, Wg, bias, logits, s);
 }
 

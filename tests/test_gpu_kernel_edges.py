@@ -510,6 +510,13 @@ def test_router_logits_of_many_tokens(dtype, T, E, H):
     assert np.array_equal(b.topk_idx.cpu().numpy(), idx)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,E,H", [(4097, 1, 8), (4112, 16, 264), (4129, 9, 2048)])
+def test_router_logits_of_many_tokens_and_few_experts(dtype, T, E, H):
+    """Tiles of 32 tokens x 16 experts: more than 4096 tokens on 256 CUs, a last tile of 1 or 16 tokens."""
+    test_router_logits_of_many_tokens(dtype, T, E, H)
+
+
 # ------------------------------------------------------------------ a step in one call
 @pytest.mark.parametrize("given", [False, True])
 @pytest.mark.parametrize("T,E,K,kl,I,shared", [(1, 8, 2, 1, 64, ()), (256, 60, 4, 2, 64, (72,)), (257, 1, 1, 1, 8, ()), (300, 64, 8, 4, 72, (64, 40)),
