@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_decode_step as decode
 import test_gpu_kernel_edges as edges
 import test_gpu_parity as parity
 from paper_2510_12357_amd import workloads as wl
@@ -215,6 +216,14 @@ def test_dispatch_beside_gate_up_is_tested_where_the_rules_take_it(route):
     assert sum(route.raw(c, True, False)[0] == PANELS for c in layers) >= 5
 
 
+def test_full_size_decode_tests_reach_the_one_launch_kernel(route):
+    """moe_layer_decode leaves it where gate/up runs in panels."""
+    layer = lambda d, T, H, E, I, K, kl, sh: wl.LayerConfig("d", T=T, H=H, E=E, I=I, k_big=K, k_little=kl, shared_I=sh, dtype=d)  # noqa: E731
+    cases = [layer(*c) for c in _cases(decode.test_one_launch_full_size)]
+    assert all(route.raw(c, True, True)[0] != PANELS for c in cases) and {c.dtype for c in cases} == {"bf16", "bf16w8"}
+    assert all(route.raw(wl.CONFIGS["fine60_decode"].with_(T=T), True, True)[0] == PANELS for T, in _cases_of_one(decode.test_fine60_decode_full_size))
+
+
 def test_selection_counts_while_its_table_is_small(route):
     """The dispatch reads a table of a row per 16 tokens in every workgroup: with many tokens or experts a count launch is faster."""
     layer = lambda T, E, dtype="bf16": wl.LayerConfig("c", T=T, H=64, E=E, I=8, k_big=1, k_little=1, dtype=dtype)  # noqa: E731
@@ -223,6 +232,10 @@ def test_selection_counts_while_its_table_is_small(route):
             assert [route.counts(layer(T, E, dtype)) for T in (256, 257, last, last + 1, 65535, 1 << 20)] == [0, 1, 1, 0, 0, 0]
     edge = {c[:2] for c in _cases(edges.test_step_in_one_call_with_many_tokens_or_experts)}
     assert {route.counts(layer(*c)) for c in edge} == {0, 1}
+
+
+def _cases_of_one(test):
+    return [(a,) for m in test.pytestmark if m.name == "parametrize" for a in m.args[1]]
 
 
 def _cases(test):

@@ -1,8 +1,9 @@
-"""moe_layer_decode (one decode step of the layer in one kernel launch) against the oracle and
+"""moe_layer_decode (one decode step of the layer in one call: one kernel launch, or, where gate/up streams in
+panels, the launches of moe_layer_step) against the oracle and
 against the four separate calls: selection, importance flags and every dispatch array bit-exact
 given the same gate logits, the layer output within the output tolerance, y / shared_out / out
 identical to the separate calls (same arithmetic in the same order), and no wait inside the
-kernel ever giving up."""
+one-launch kernel ever giving up."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +18,13 @@ pytestmark = pytest.mark.gpu
 
 def i32(t):
     return t.cpu().numpy().astype(np.int32)
+
+
+def separate_calls(b, x, Wg, gate_bias, conf, table, shared, logits_given):
+    mm.moe_route(b.c, x, Wg, gate_bias, conf, b.logits, logits_given, b.topk_idx, b.topk_w, b.important, b.k_t)
+    mm.moe_dispatch(b.c, b.topk_idx, b.k_t, b.expert_offsets, b.sorted_token, b.sorted_rank, b.inv_pos, b.dws, b.dws_bytes)
+    mm.moe_expert_ffn(b.c, x, b.expert_offsets, b.sorted_token, table, shared, True, True, b.y, b.shared_out, b.fws, b.fws_bytes)
+    mm.moe_combine(b.c, b.y, b.topk_w, b.inv_pos, b.k_t, b.shared_out, b.out)
 
 
 def check_step(cfg, seed, logits_given=True, conf="layer", steps=1, check_separate=True):
@@ -53,7 +61,7 @@ def check_step(cfg, seed, logits_given=True, conf="layer", steps=1, check_separa
         b2 = mm.StepBuffers(cfg)
         if logits_given:
             b2.logits.copy_(torch.from_numpy(logits))
-        mm.layer_step(b2, dl.x, dl.Wg, dl.gate_bias, c, dl.table, dl.shared, logits_given=logits_given)
+        separate_calls(b2, dl.x, dl.Wg, dl.gate_bias, c, dl.table, dl.shared, logits_given)
         torch.cuda.synchronize()
         P = int(b2.expert_offsets[-1])
         assert torch.equal(b.logits, b2.logits)
@@ -97,6 +105,7 @@ def test_all_tokens_important_without_confidences():
 
 @pytest.mark.parametrize("T", [1, 8, 32, 64])
 def test_fine60_decode_full_size(T):
+    """Panels: the launches of moe_layer_step."""
     cfg = wl.CONFIGS["fine60_decode"].with_(T=T)
     check_step(cfg, seed=0, logits_given=False, steps=2)
 
@@ -104,6 +113,54 @@ def test_fine60_decode_full_size(T):
 def test_8_bit_expert_weights():
     check_step(cfg_small(T=19, H=272, I=144, shared_I=(80,), dtype="bf16w8"), seed=5, steps=2)
     check_step(wl.CONFIGS["fine60_decode"].with_(T=8, dtype="bf16w8"), seed=1, logits_given=False)
+
+
+def _full_blob(dtype, H, I, g):
+    n = 3 * H * I
+    w = torch.randn((n,), generator=g, device="cuda")
+    if dtype == "bf16":
+        return (w * 0.02).bfloat16()
+    return torch.cat([(w * 50).to(torch.float8_e4m3fn).view(torch.uint8), torch.full((2 * I + H,), 4e-4, device="cuda").view(torch.uint8)])
+
+
+def _full_ffn(dtype, blob, H, I, x):
+    n = H * I
+    w = (blob if dtype == "bf16" else blob[:3 * n].view(torch.float8_e4m3fn)).float() * (1.0 if dtype == "bf16" else 4e-4)
+    a = x.float() @ w[:n].view(I, H).t()
+    return (a * torch.sigmoid(a) * (x.float() @ w[n:2 * n].view(I, H).t())) @ w[2 * n:].view(H, I).t()
+
+
+@pytest.mark.parametrize("dtype,T,H,E,I,K,kl,shared", [
+    ("bf16", 1, 4096, 8, 14336, 2, 1, ()), ("bf16", 64, 4096, 8, 14336, 2, 1, ()), ("bf16", 7, 2048, 128, 1408, 8, 4, (5632,)),
+    ("bf16", 33, 2048, 16, 2048, 2, 1, (2048,)), ("bf16", 64, 2048, 64, 1024, 8, 4, ()),
+    ("bf16w8", 7, 2048, 128, 1408, 8, 4, (5632,)), ("bf16w8", 64, 2048, 64, 1024, 8, 4, ())])
+def test_one_launch_full_size(dtype, T, H, E, I, K, kl, shared):
+    """Full-size layers that stay on the one-launch kernel: thousands of items on every workgroup's walk, hand-overs across
+    all of them, two steps on one workspace.  Every array and bit of the separate calls, and two tokens against fp32 products."""
+    cfg = wl.LayerConfig("full", T=T, H=H, E=E, I=I, k_big=K, k_little=kl, shared_I=shared, dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    blobs = [_full_blob(dtype, H, I, g) for _ in range(3)]         # three different experts, over and over
+    table = torch.tensor([blobs[e % 3].data_ptr() for e in range(E)], dtype=torch.int64, device="cuda")
+    sh = [_full_blob(dtype, H, i, g) for i in shared]
+    x = torch.randn((T, H), generator=g, device="cuda").bfloat16()
+    Wg = (torch.randn((E, H), generator=g, device="cuda") * 0.05).bfloat16()
+    conf = torch.rand((T,), generator=g, device="cuda")
+    b, b2 = mm.StepBuffers(cfg), mm.StepBuffers(cfg)
+    separate_calls(b2, x, Wg, None, conf, table, sh, False)
+    P = int(b2.expert_offsets[-1])
+    for _ in range(2):
+        b.y.fill_(float("nan"))
+        b.out.fill_(float("nan"))
+        mm.layer_decode_step(b, x, Wg, None, conf, table, sh)
+        assert mm.moe_layer_decode_status(b.lws) == 0, "a wait inside the kernel gave up"
+        for n in ("logits", "topk_idx", "topk_w", "important", "k_t", "expert_offsets", "sorted_token", "sorted_rank", "inv_pos", "out"):
+            assert torch.equal(getattr(b, n), getattr(b2, n)), n
+        assert torch.equal(b.y[:P], b2.y[:P]) and (b.shared_out is None or torch.equal(b.shared_out, b2.shared_out))
+    for t in {0, T - 1}:
+        ref = sum((_full_ffn(dtype, w, H, i, x[t:t + 1]) for w, i in zip(sh, shared)), torch.zeros((1, H), device="cuda"))
+        for j in range(int(b.k_t[t])):
+            ref += b.topk_w[t, j] * _full_ffn(dtype, blobs[int(b.topk_idx[t, j]) % 3], H, I, x[t:t + 1])
+        assert ((b.out[t] - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= TOL_OUT
 
 
 def test_limits():
