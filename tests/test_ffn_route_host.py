@@ -208,6 +208,17 @@ def test_narrow_weights_in_whole_lines(route):
         assert route.lines(wl.LayerConfig("l", T=2000, H=H, E=16, I=1024, k_big=2, k_little=1, dtype="bf16mx4")) == line
 
 
+def test_narrow_tiles_are_tested_in_every_pair_of_choices(route):
+    """By rows or contiguous, lines or chunks: what variants 0 and 1 do not have is tested through the public call."""
+    seen = set()
+    for d, T, E, I, sh in _cases(edges.test_narrow_tiles_as_the_rules_take_them):
+        c = wl.LayerConfig("n", T=T, H=2048, E=E, I=I, k_big=8, k_little=4, shared_I=sh, dtype=d)
+        gate_up, down, rows_gate_up, rows_down = route.raw(c, True, True)[:4]
+        assert gate_up == down == TILED and rows_gate_up == rows_down
+        seen.add((d, rows_down, route.lines(c)))
+    assert {("bf16mx4", 0, 1), ("bf16w8", 1, 0), ("bf16w8", 1, 1), ("bf16mx4", 1, 1)} <= seen
+
+
 def test_dispatch_beside_gate_up_is_tested_where_the_rules_take_it(route):
     """Its cases run in panels, as whole steps and (most of them) as fallback passes."""
     cases = _cases(edges.test_dispatch_built_by_the_gate_up_launch)

@@ -310,6 +310,42 @@ def test_narrow_weights_in_whole_lines(dtype, counts, H, I, shared):
     assert torch.equal(y, ref) and (not shared or torch.equal(out, ref_out))
 
 
+@pytest.mark.parametrize("dtype,T,E,I,shared", [
+    ("bf16mx4", 900, 64, 1024, ()),                                # lines, tiles in contiguous ranges
+    ("bf16w8", 800, 64, 1040, (1040,)),                            # chunks, tiles by rows
+    ("bf16w8", 1500, 64, 1024, ()), ("bf16mx4", 550, 60, 1408, (5632,)),   # lines, by rows
+])
+def test_narrow_tiles_as_the_rules_take_them(dtype, T, E, I, shared):
+    """Order of the tiles and pieces of the weights are chosen each by itself, which variants 0 and 1 are not: the public call
+    has every bit of variant 0 (contiguous, chunk after chunk)."""
+    H = 2048
+    cfg = wl.LayerConfig("rules", T=T, H=H, E=E, I=I, k_big=8, k_little=4, shared_I=shared, dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    c = mm.make_config(cfg)
+
+    def blob(i):
+        b = torch.randint(0, 256, (mm.moe_expert_blob_bytes(c, i),), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
+        n = 3 * H * i
+        if dtype == "bf16mx4":
+            b[n // 2:] = torch.randint(118, 122, (n // 32,), generator=g, device="cuda", dtype=torch.int32).to(torch.uint8)
+        else:
+            b[:n] &= 0xF7                                          # no NaN
+            b[n:] = torch.full((2 * i + H,), 2e-4, device="cuda").view(torch.uint8)
+        return b
+    experts = [blob(I) for _ in range(3)]                           # three different experts, over and over
+    table = torch.tensor([experts[e % 3].data_ptr() for e in range(E)], dtype=torch.int64, device="cuda")
+    sh = [blob(i) for i in shared]
+    x = torch.randn((T, H), generator=g, device="cuda").bfloat16()
+    conf = torch.rand((T,), generator=g, device="cuda")
+    b = mm.StepBuffers(cfg)
+    b.logits.copy_(torch.randn((T, E), generator=g, device="cuda") * 1.5)
+    mm.layer_step(b, x, None, None, conf, table, sh, logits_given=True)
+    P = int(b.expert_offsets[-1])
+    y, out = b.y[:P].clone(), None if b.shared_out is None else b.shared_out.clone()
+    y0, out0 = _run_on(TILED, 0, b, x, table, sh)
+    assert torch.isfinite(y).all() and torch.equal(y, y0[:P]) and (out is None or torch.equal(out, out0))
+
+
 @pytest.mark.parametrize("dtype,counts,H,I,shared", [
     ("bf16", [5, 0, 20, 17, 1], 200, 264, ()),                     # K ends inside a unit of 256 bytes; quads that the waves do not divide
     ("bf16", [30, 2, 64, 65], 1032, 72, (520,)),                   # gate rows that end inside a tile; K in parts of a unit
