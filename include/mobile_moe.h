@@ -255,8 +255,10 @@ int moe_combine(const moe_config* cfg, const float* y, const float* topk_w,
  * arithmetic and the same outputs as the four calls: logits, topk_idx, topk_w, important, k_t,
  * expert_offsets, sorted_token, sorted_rank, inv_pos, y, shared_out and out are all written and
  * have the layouts documented above.  A decode step only streams 0.1 .. 1 GB of weights, so the
- * launch gaps and pipeline ramps of five dependent kernels are a large part of it.  Large layers run the
- * launches of moe_layer_step (below); the others ONE persistent kernel in which the
+ * launch gaps and pipeline ramps of five dependent kernels are a large part of it.  Layers whose gate/up launch
+ * streams in panels run the launches of moe_layer_step (below): 8-bit ones of 403 MB and more (counted as bf16), bf16 ones of
+ * 805 MB and more and of more than 16 experts, but for few tokens of many experts and, in either, a few shapes
+ * between (narrow_panels and bf16_panels in csrc/ffn_route.cpp).  The others run ONE persistent kernel in which the
  * shared experts (which need nothing from the router) stream while the selection is computed,
  * and the down projections, the final sum and the next weights overlap; its workgroups hand results
  * over through device memory.

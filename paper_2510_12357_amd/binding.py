@@ -290,7 +290,7 @@ def moe_expert_ffn(cfg: moe_config, x, expert_offsets, sorted_token, expert_w, s
 def moe_profile_expert_ffn(cfg: moe_config, kernel: int, variant: int, x, expert_offsets, sorted_token, expert_w,
                            shared_w: Sequence, run_routed, run_shared, y, shared_out, ws, ws_bytes: int, stream=None) -> None:
     """moe_expert_ffn on a given kernel: 0 streamed (variant: token tiles per wave; 4, 5: rows of its own per wave, one or two tiles of them), 1 tiles of 128 x 256, 2 of
-    256 x 256 (variant 1: by rows)."""
+    256 x 256 (variant 1: by rows; on 1, narrow weights then in whole lines, and 2, 3: the same with bf16 weights past the caches and tiles that fill their rounds)."""
     sw = (ctypes.c_void_p * max(1, len(shared_w)))(*[t.data_ptr() for t in shared_w])
     ew = ctypes.c_void_p(expert_w) if isinstance(expert_w, int) else _ptr(expert_w)
     _check(load_library().moe_profile_expert_ffn(ctypes.byref(cfg), kernel, variant, _ptr(x), _ptr(expert_offsets),

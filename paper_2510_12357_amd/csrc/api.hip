@@ -535,7 +535,7 @@ extern "C" int moe_layer_fallback(const moe_config* cfg, const void* x, const fl
   return moe_combine_add(cfg, b->y, b->topk_w, b->inv_pos, b->k_t, kl, b->out, stream);
 }
 
-// ---- one decode step in one launch --------------------------------------------------------------
+// ---- one decode step in one call ----------------------------------------------------------------
 namespace {
 int validate_decode(const moe_config* cfg) {
   int rc = validate_config(cfg);
@@ -590,9 +590,13 @@ extern "C" int moe_layer_decode(const moe_config* cfg, const void* x, const void
                 sync_bytes + L.total);
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws) + sync_bytes;
-  // Large layers take the launches of moe_layer_step, whose weight stream no wave with other work stands in.  us per step, one launch /
-  // these: 60 experts of 1408 + 5632, 1 token 42.9 / 40.5, 4 tokens 59.5 / 54.4, 8 tokens 78.7 / 74.6, 16 tokens 109.3 / 103.0, 32 tokens
-  // 158.6 / 152.6, 64 tokens 202.7 / 190.6; 64 of 1408 + 2 shared, 1 token 45.0 / 40.8, 8 tokens 95.6 / 95.3, 32 tokens 189.6 / 179.4.
+  // Where gate/up streams in panels, the launches of moe_layer_step, whose weight stream no wave with other work stands in.  us per step, two sets of
+  // weights, one launch / these: bf16, 60 experts of 1408 + 5632, 1 token 43.1 / 39.8, 4 tokens 67 / 61, 8 tokens 83 / 81 (the place of the weights in
+  // memory moves these by up to 7 %: 0.98 .. 1.08 in other processes), 64 tokens 206 / 189; 64 of 1408 + 2 shared, 1 token 46.2 / 40.5, 64 tokens 219 / 197; 24
+  // of 4096, 8 tokens 94 / 79.  8 bits, 60 of 1408 + 5632, 1 token 42.8 / 33.8, 64 tokens 203 / 114; 8 of 14336, 1 token 130 / 81, 64 tokens 394 / 252; 16 of
+  // 2048 + 2048, 8 tokens 59 / 38; 256 of 512 + 512, 8 tokens 87 / 64.  The other layers stay on the one launch, which is not to say that it is the faster there: one
+  // launch / moe_layer_step (other kernels of the same bits), bf16, 8 of 14336, 1 token 138 / 115, 64 tokens 453 / 444; 64 of 1024, 16 tokens 127 / 120; 16 of 2048 +
+  // 2048, 1 token 34.6 / 31.9, 8 tokens 62.8 / 61.5; 256 of 512 + 512, 2 tokens 50.5 / 51.2, 32 tokens 200 / 156; 8 bits, 64 of 1024, 64 tokens 158 / 92.
   const FfnRoute r = ffn_route(*cfg, true, true, 0);
   if (panels_below_tiles(*cfg, r)) {
     moe_step_buffers b = {};

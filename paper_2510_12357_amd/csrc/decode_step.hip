@@ -1,7 +1,7 @@
 // One decode step of the layer (at most 64 tokens) in ONE kernel launch: selection stage, dispatch,
 // grouped SwiGLU feed-forward and the final weighted sum (Sec. II-A), with the per-token number of
 // experts of the big-little rule (Sec. III-A, Alg. 1).
-// Large layers run elsewhere (moe_layer_decode in api.hip has the rule).
+// Layers whose gate/up streams in panels run elsewhere (moe_layer_decode in api.hip).
 //
 // Why one kernel: a decode step moves 0.1 .. 1 GB of expert weights, i.e. 15 .. 130 us of HBM
 // time, and five dependent launches (router, dispatch, gate/up, down, combine) each pay a launch

@@ -89,17 +89,18 @@ bool wide_by_rows(const moe_config& c) {
 }
 
 // Order of the 128 x 256 tiles.  By rows pays for narrow weights in steps of few rows and few tiles per workgroup where tiles differ: beside shared
-// experts, whose groups are full, and where the selection is skewed. Contiguous order's rate of the order by rows', gate/up, down, geometric mean of
-// four selections, at sizes that do not run in panels: 60 of 1408 + 5632 shared, 8-bit, 770 tokens 0.90, 0.90, 810 tokens (88 rows) 0.93, 0.92, 1000
-// tokens 275 / 277 us, MXFP4 0.94, 0.96 and 0.96, 0.98; 64 of 1408 + 2 shared, 8-bit, 870 tokens 0.98, 0.99, 900 tokens 257 / 263 us, MXFP4 0.97,
-// 1.03; 32 of 1024 + 2048, 8-bit, 256 tokens 0.97, 0.98, 400 tokens 0.84, 0.85, 580 tokens 0.91, 0.95, MXFP4 0.97, 1.02, 0.88, 0.91, 0.93, 0.95; 32
-// of 2048 + 4096, hidden 4096, 8-bit, 580 tokens 0.93, 0.92; 60 of 1024 + 1024, skewed, 8-bit, 700 tokens 0.91, 0.89.  Alone, 64 of 1024, 8-bit,
-// skewed, 420 .. 1000 tokens (gate/up) 0.90 .. 0.93, 2000 tokens 0.95, 0.94, unskewed 1.02 .. 1.06.  Alike tiles of MXFP4, which are the shortest,
-// lose more, gate+up + down, us, contiguous / by rows: 32 of 2048, 256 tokens 159 / 171, 16 of 1024, hidden 4096, 800 tokens 90 / 99.  So do small
-// layers: 32 of 512, hidden 1024, 400 tokens, 8-bit 50 / 53, 24 of 2048, 800 tokens, 8-bit 119 / 122. With bf16 weights, twice the bytes per tile,
+// experts, whose groups are full, and where the selection is skewed.  Contiguous order's time / the time by rows, gate/up, down, geometric mean of
+// four selections, at sizes that do not run in panels: 60 of 1408 + 5632 shared, 8-bit, 770 tokens 1.17, 1.25, 810 tokens (88 rows) 1.18, 1.25, 1000
+// tokens 264 / 239 us, MXFP4 1.12, 1.09, 1.13, 1.09, 203 / 202 us; 64 of 1408 + 2 shared, 8-bit, 870 tokens 1.15, 1.18, 900 tokens 246 / 217 us, MXFP4
+// 1.08, 1.01, 183 / 178 us; 32 of 1024 + 2048, 8-bit, 256 tokens 1.04, 1.04, 400 tokens 1.17, 1.22, 580 tokens 1.14, 1.14, MXFP4 1.04, 1.04, 1.07, 1.07,
+// 1.08, 1.04; 32 of 2048 + 4096, hidden 4096, 8-bit, 580 tokens 1.14, 1.19; 60 of 1024 + 1024, skewed, 8-bit, 700 tokens 1.12, 1.22.  Alone, 64 of 1024,
+// 8-bit, skewed, 420 .. 1000 tokens 1.08 .. 1.12, 1.10 .. 1.17, 2000 tokens 1.04, 1.06, unskewed 0.95 .. 0.99, 0.94 .. 0.97.  Alike tiles of MXFP4, which
+// are the shortest, lose, gate+up + down, us: 32 of 2048, 256 tokens 85 / 89, 16 of 1024, hidden 4096, 800 tokens 80 / 85.  So do small
+// layers: 32 of 512, hidden 1024, 400 tokens, 8-bit 37 / 39, 24 of 2048, 800 tokens, 8-bit 117 / 121.  With bf16 weights, twice the bytes per tile,
 // mixing the two kinds of tiles over the XCDs is worth more (60 experts, 1000 tokens 286 / 312), and with more panels than three per CU the balance
-// is there already. In a part of a step the tiles are alike, and the order only pays where 8-bit experts are all there is: fallback passes, 64 of
-// 1024, 8-bit, 1200 tokens 125 / 120, 2048 tokens 137 / 128, 8 of 14336 416 / 415.
+// is there already.  In a part of a step the tiles are alike.  8-bit experts alone take the order there too, for which the reason has gone: with 2 x 2
+// waves and chunks of weights the fallback passes of 64 of 1024 took 125 / 120 at 1200 tokens and 137 / 128 at 2048, now 92 / 101 and 101 / 109, 8 of
+// 14336 384 / 391.
 bool tiled_by_rows(const moe_config& c, bool run_routed, bool run_shared, int cus) {
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
   const bool alone = c.n_shared == 0;
@@ -221,34 +222,36 @@ bool stream_panels(const moe_config& c, bool run_routed, bool run_shared, bool g
 // weights are more and the tiled kernels' 128 are full.  Each launch by itself: the down projection, with half the columns and
 // thus fewer tiles for the CUs, gains longer than gate/up.  Rates: the tiled kernel's time / the panels' (two tiles per wave where
 // the next rule wants them), gate/up, down, geometric mean of four selections; token rows per weight row in brackets.  Held against
-// other layers, drawn at random: narrow formats, 1434 calls, 1.15 in the mean, of the 1344 over 18 us 5 below 0.97, 0.82 at worst; bf16, 716 calls,
-// 1.01, 3 of 699, 0.96.
-//   * few experts, alike: 8 of 14336, 8-bit, 256 tokens (48) 1.19, 1.61, 340 tokens (64) 1.11, 1.35, 420 tokens (79) 0.90, 0.87; MXFP4, 256
-//     tokens 1.28, 1.68, 380 tokens (71) 1.12, 1.94, 500 tokens (94) 0.96, 1.39; 8 of 512, hidden 512, 256 tokens, 8-bit 1.67, 2.1, MXFP4
-//     1.34, 1.42.  Where the panels fill one round of the CUs, but not two, a second block of 64 rows is another round, which the faster
-//     MXFP4 tiles do not lose: 16 of 1408, 560 tokens (52) 1.12, 1.10, 620 tokens (58) 0.82, 1.10, 8-bit 1.12, 1.59, 740 tokens (69) 1.12, 1.39.
-//   * many: 60 of 1408 + 5632, 8-bit, 256 tokens (28) 1.05, 1.46, 740 tokens (81) 1.01, 1.09, 900 tokens (99) 0.99, 1.16; MXFP4 1.33, 1.59, 1.07,
-//     0.95, 1.01, 0.93; 64 of 1408 + 2 shared, 8-bit, 800 tokens (79) 1.24, 1.32, MXFP4 1.07, 0.98; 20 of 4096, 8-bit, 900 tokens (68) 1.24, 1.25,
-//     MXFP4 1.12, 0.97.  With fewer of
-//     them the rows are more alike: 24 of 4096 + 2 shared, hidden 1792, 8-bit, 582 tokens (78) 0.97, 0.70, 32 of 3456, hidden 7168, 873 tokens (82) 0.83, 0.98, 17
-//     of 8192 + 16384, 299 tokens (79) 0.92, 0.84; MXFP4, 40 of 2048 + 2 shared, hidden 2816, 380 tokens (72) 0.77, 1.31, 440 tokens (84) 0.80, 1.13.
+// other layers, drawn at random, with the tiles of then: narrow formats, 1434 calls, 1.15 in the mean, of the 1344 over 18 us 5 below 0.97, 0.82 at
+// worst; bf16, 716 calls, 1.01, 3 of 699, 0.96.
+// The lines were drawn while the tiles of narrow weights took up to 25 % (MXFP4) and 10 % (8-bit) longer, the figures are from the present ones: below 1
+// on the panels' side of a line is what the line gives away since, in MXFP4 from about 50 rows on and in gate/up of skewed 8-bit experts.
+//   * few experts, alike: 8 of 14336, 8-bit, 256 tokens (48) 1.00, 1.38, 340 tokens (64) 0.94, 1.23, 420 tokens (79) 0.77, 0.73; MXFP4, 256
+//     tokens 1.23, 1.40, 380 tokens (71) 0.89, 1.38, 500 tokens (94) 0.69, 0.92; 8 of 512, hidden 512, 256 tokens, 8-bit 1.36, 1.50, MXFP4
+//     1.10, 1.11.  Where the panels fill one round of the CUs, but not two, a second block of 64 rows is another round, which the faster
+//     MXFP4 tiles do not lose: 16 of 1408, 560 tokens (52) 0.90, 0.91, 620 tokens (58) 0.75, 0.91, 8-bit 1.00, 1.32, 740 tokens (69) 1.01, 1.13.
+//   * many: 60 of 1408 + 5632, 8-bit, 256 tokens (28) 1.00, 1.32, 740 tokens (81) 0.97, 0.96, 900 tokens (98) 0.93, 1.07; MXFP4 1.13, 1.35, 0.90,
+//     0.81, 0.83, 0.83; 64 of 1408 + 2 shared, 8-bit, 800 tokens (79) 1.11, 1.13, MXFP4 0.89, 0.87; 20 of 4096, 400 tokens (30), 8-bit 1.27, 1.12, MXFP4
+//     1.28, 1.29, 900 tokens (68) 1.10, 1.06, 0.89, 0.80.  With fewer of
+//     them the rows are more alike: 24 of 4096 + 2 shared, hidden 1792, 8-bit, 582 tokens (78) 1.15, 0.84, 32 of 3456, hidden 7168, 873 tokens (82) 0.70, 0.80, 17
+//     of 8192 + 16384, 299 tokens (79) 0.92, 0.89; MXFP4, 40 of 2048 + 2 shared, hidden 2816, 380 tokens (72) 0.65, 1.07, 440 tokens (84) 0.58, 0.93.
 //   * many of up to 1024, with a selection skewed as by gate biases of a standard deviation of 0 / 1 / 2: 64 of 1024, 8-bit, gate/up, 300
-//     tokens (28) 1.28 / 0.98 / 0.96, 380 tokens (36) 1.26 / 0.99 / 0.93, 460 tokens (43) 1.34 / 0.82 / 1.03, 620 tokens (58) 1.11 / 0.90 / 0.78, 680
-//     tokens (64) 1.05 / 0.98 / 0.80, 740 tokens (69) 0.98 / 1.11 / 0.86, down 1.0 .. 1.5 throughout; MXFP4, gate/up, 500 tokens (47) 0.96 / 1.08 / 1.10, 620
-//     tokens 0.82 / 0.92 / 1.12, 740 tokens 0.87 / 1.14 / 0.86, down 1.04 / 1.11 / 1.14, 0.90 / 0.99 / 1.12, 0.94 / 1.18 / 0.90.  What gate/up
+//     tokens (28) 1.15 / 1.09 / 1.08, 380 tokens (36) 1.15 / 0.92 / 1.00, 460 tokens (43) 1.11 / 0.82 / 0.93, 620 tokens (58) 1.14 / 0.82 / 0.82, 680
+//     tokens (64) 1.00 / 0.95 / 0.83, 740 tokens (69) 0.85 / 1.07 / 0.84, down 1.0 .. 1.35 throughout; MXFP4, gate/up, 300 tokens 1.25 / 0.93 / 1.10, 500
+//     tokens (47) 0.89 / 0.95 / 0.94, 620 tokens 0.76 / 0.75 / 0.96, 740 tokens 0.78 / 1.02 / 0.75, down 1.17 / 1.02 / 1.14, 0.92 / 1.04 / 1.04, 0.80 / 0.86 /
+//     1.02, 0.82 / 1.12 / 0.84.  What gate/up
 //     loses at 36 .. 61 rows (8-bit) and from 56 on (MXFP4) it loses by its rounds: 1024 panels are four of 256 CUs exactly, so that
 //     every expert with a second block makes a fifth.  Where the last round has room it gains as before: 8-bit, 96 of 768 (4.5
-//     rounds), 800 tokens (37) 1.38, 128 of 768 + 768 (6.5), 740 tokens (40) 1.34, 64 of 1024 + 1024, hidden 4096 (4.4), 340 tokens (37) 1.28,
-//     560 tokens (60) 1.17, MXFP4 1.24, 680 tokens (73) 1.10.
-//     Smaller layers of them: 32 of 1024, 8-bit, 340 tokens (32) 1.07, 1.19, 740 tokens (69) 0.78, 1.00; MXFP4, 380 tokens (36) 1.12, 1.06, 460 tokens
-//     (43) 0.91, 0.96; 64 of 512, hidden 1024, MXFP4, 380 tokens (36) 1.10, 1.06, 460 tokens (43) 0.87, 0.95.
-//   * bf16, where the tiles leave part of the CUs idle in their rounds: 8 of 14336, 256 .. 319 tokens (48 .. 60), gate/up (896 tiles, 3.5 rounds) 1.03, down
-//     (128 tiles) 1.38, 380 tokens (71) 0.97, 0.88; 16 of 1024, hidden 4096, 256 tokens, gate/up (128) 1.24, down (256) 1.02, 560 tokens (52)
-//     1.11, 0.95; 16 of 4096, hidden 4096, gate/up (512) 0.95, down (256) 0.94 .. 0.98; but 20 of 4096, 420 tokens (32) 0.97, 60 of 1408
-//     + 5632, 256 tokens (28) 0.86, and beside shared experts, whose groups are full: 8 of 4096 + 4096, hidden 4096, 300 tokens 0.90, 0.84, 16
-//     of 5152 + 5152, hidden 4680, 468 tokens 0.82, 0.90.
-//   * fallback passes (20 % of the tokens) gain more: 60 of 1408, 8-bit 1.31 .. 1.45, 1.33 .. 1.41, MXFP4 1.8 .. 2.0, 1.55 .. 1.60; 64 of 1024, 8-bit 1.22 .. 1.49,
-//     1.40 .. 1.62, MXFP4 1.30 .. 1.87, 1.31 .. 1.69; bf16, 8 of 14336 1.03, 1.27, 16 of 4096 1.00 .. 1.04, 1.04 .. 1.10.  The lines by rows are
+//     rounds), 800 tokens (38) 1.27, 128 of 768 + 768 (6.5), 740 tokens (40) 1.27, 64 of 1024 + 1024, hidden 4096 (4.4), 340 tokens (37) 1.19,
+//     560 tokens (60) 1.05, MXFP4 0.99, 680 tokens (73) 0.87.
+//     Smaller layers of them: 32 of 1024, 8-bit, 340 tokens (32) 1.02, 1.06, 740 tokens (69) 0.67, 0.85; MXFP4, 380 tokens (36) 1.14, 1.01, 460 tokens
+//     (43) 0.85, 0.89; 64 of 512, hidden 1024, MXFP4, 380 tokens (36) 0.90, 0.92, 460 tokens (43) 0.78, 0.87.
+//   * bf16, where the tiles leave part of the CUs idle in their rounds: 8 of 14336, 256 tokens (48), gate/up (896 tiles, 3.5 rounds) 1.05, down
+//     (128 tiles) 1.12, 319 tokens (60) 1.04, 1.09, 380 tokens (71) 0.96, 0.80; 16 of 1024, hidden 4096, 256 tokens, gate/up (128) 1.11, down (256) 1.05, 560
+//     tokens (52) 1.03, 0.96; beside shared experts, whose groups are full, and with many it loses: 60 of 1408 + 5632, 256 tokens (28) 0.96, 0.89, 8 of
+//     4096 + 4096, hidden 4096, 300 tokens 0.81, 0.77.  16 of 4096, hidden 4096, 300 tokens 1.03, 1.08 and 20 of 4096, 420 tokens (32) 1.12, 1.06 stay on tiles.
+//   * fallback passes (20 % of the tokens) gain more: 60 of 1408, 8-bit 1.14 .. 1.36, 1.09 .. 1.23, MXFP4 1.7 .. 2.1, 1.46 .. 1.63; 64 of 1024, 8-bit 1.10 .. 1.12,
+//     1.18 .. 1.21, MXFP4 1.55 .. 1.66, 1.39 .. 1.47; bf16, 8 of 14336 1.06, 1.14, 16 of 4096 1.10, 1.16.  The lines by rows are
 //     those of the whole step all the same, for a part may have all of its rows; second blocks are rare in it.
 bool prefill_panels(const moe_config& c, bool run_routed, bool run_shared, bool gate_up, int cus) {
   if (!run_routed || c.T > kPanelsMaxT) return false;
@@ -277,15 +280,15 @@ bool prefill_panels(const moe_config& c, bool run_routed, bool run_shared, bool 
 // Two tiles of weight rows per wave, which share the token rows' fragments, instead of one.  A tile of narrow weights
 // is computed from LDS slower than it comes from HBM once it meets several tiles of token rows, and half of the reads are
 // the token rows'.  With fewer rows the larger panels leave more of the last round empty.  gate+up + down, us, one / two:
-//   * MXFP4, 60 of 1408 + 5632, 200 tokens (22 rows per weight row) 105 / 107, 255 tokens (28) 121 / 114; 64 of 1408 + 2 shared,
-//     255 tokens (25) 108 / 114; 8 of 14336, 128 tokens (24) 197 / 206, 200 tokens (38) 268 / 246.
-//     Above 255 tokens, 20 % of the tokens with all ranks: 60 of 1408 + 5632, 256 tokens (28) 121 / 120, 420 tokens (46) 149 / 153; 64 of 1408 + 2
-//     shared, 420 tokens (41) 142 / 132; 64 of 1024, 300 tokens (28) 75 / 74; 8 of 14336, 256 tokens (48) 327 / 306, 400 tokens (75) 417 / 376.
-//   * 8-bit, likewise: 60 of 1408 + 5632, 256 tokens (28) 155 / 155, 420 tokens (46) 185 / 171; 64 of 1408 + 2 shared, 420 tokens (41) 162 / 163, 540
-//     tokens (53) 191 / 172; 64 of 1024, 540 tokens (51) 113 / 108, with half of the tokens 128 / 117, with all 177 / 180; 8 of 14336, 256 tokens (48)
-//     298 / 311, 278 tokens (52) 332 / 340, 339 / 349, 528 / 476, 370 tokens (69) 450 / 400, 511 / 463, 600 / 518.
-//   * Parts of a step have fewer rows than that: 60 of 1408, fallback pass, 420 tokens, 8-bit 95 / 99, MXFP4 63 / 68.  There they pay where they make one
-//     round over the CUs of two: 64 of 272, hidden 528, 256 tokens 30.7 / 27.8.  bf16 weights: 8 of 14336, 256 tokens 484 / 494.
+//   * MXFP4, 60 of 1408 + 5632, 200 tokens (22 rows per weight row) 103 / 105, 255 tokens (28) 119 / 112; 64 of 1408 + 2 shared,
+//     255 tokens (25) 108 / 112; 8 of 14336, 128 tokens (24) 191 / 198, 200 tokens (38) 235 / 232.
+//     Above 255 tokens, 20 % of the tokens with all ranks: 60 of 1408 + 5632, 256 tokens (28) 116 / 115, 420 tokens (46) 146 / 151; 64 of 1408 + 2
+//     shared, 420 tokens (41) 136 / 129; 64 of 1024, 300 tokens (28) 74 / 72; 8 of 14336, 256 tokens (48) 316 / 284, 400 tokens (75) 407 / 372.
+//   * 8-bit, likewise: 60 of 1408 + 5632, 256 tokens (28) 144 / 145, 420 tokens (46) 174 / 161; 64 of 1408 + 2 shared, 420 tokens (41) 152 / 153, 540
+//     tokens (53) 178 / 163; 64 of 1024, 540 tokens (51) 106 / 102, with half of the tokens 132 / 126, with all 167 / 169; 8 of 14336, 256 tokens (48)
+//     298 / 312, 278 tokens (52) 307 / 318, 360 / 353, 508 / 457, 370 tokens (69) 389 / 362, 502 / 447, 576 / 493.
+//   * Parts of a step have fewer rows than that: 60 of 1408, fallback pass, 420 tokens, 8-bit 91 / 95, MXFP4 63 / 68.  There they pay where they make one
+//     round over the CUs of two: 64 of 272, hidden 528, 256 tokens 27.1 / 25.0.  bf16 weights: 8 of 14336, 256 tokens 484 / 494.
 bool wide_panels(const moe_config& c, bool run_shared, int cus) {
   if (c.dtype != MOE_BF16_W8 && c.dtype != MOE_BF16_MXFP4) return false;
   if (!run_shared) {
@@ -346,7 +349,9 @@ bool whole_lines(const moe_config& c) {
 
 // bf16 tiles of a width that fills their last round over the CUs, which the kernel chooses where that round has room (ffn_tiled.hip, with
 // figures).  With so many rows that the matrix cores set the pace of gate/up (rows per weight row: 8 of 14336, 131, 350 / 360 us, 225, 521 / 538) or
-// have no room left in the down projection (20 of 4096, 150, 87 / 88; but 8 of 14336, 131, 252 / 218) it only costs, and a small layer
+// have no room left in the down projection (20 of 4096, 150, 87 / 88; but 8 of 14336, 131, 252 / 218) it only costs.  Below, launches whose rounds have no
+// room lose at most a microsecond or two where others gain 5 to 25 % (8 of 14336, 450 tokens, gate/up (84) 350 / 350, down 232 / 185; 64 of 1024, 450
+// tokens, gate/up 99.7 / 95.0, down 56.9 / 57.8; 40 of 1280, hidden 4096, 500 tokens, gate/up 142.7 / 145.3, down 92.3 / 88.4).  A small layer
 // has no rounds to speak of (8 of 512, hidden 512, 1000 tokens 18.0 + 16.6 / 18.7 + 17.1; 8 of 1408 + 1408, hidden 1024 (78 MB), 700 tokens 30.2 / 26.2).
 bool even_tiles(const moe_config& c, bool gate_up) {
   const Work w = layer_work(c);
