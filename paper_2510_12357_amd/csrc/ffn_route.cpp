@@ -338,6 +338,9 @@ bool tiled_gate_up(const moe_config& c) {
 // ones whose matrix cores set the pace (8 bits, 64 of 1024, 2500 tokens 173 + 130 / 175 + 131; 8 of 14336, 1400 tokens 474 + 210 / 477 + 209,
 // 900 tokens 422 + 203 / 418 + 186) or whose rows are not whole lines (64 of 1968 + 2064, hidden 3264, 600 tokens 243 + 160 / 247 + 176;
 // 24 of 1872, hidden 3120, 121 + 83 / 117 + 80).  MXFP4 gains there too (64 of 1920, hidden 3200, 600 tokens 184 + 110 / 175 + 106).
+// A line of a panel of one token tile goes past the caches, which MXFP4 layers of up to twice the 384 MB feel in fallback passes where they would
+// stay in the 256 MB behind the L2s, i.e. where no other layer runs in between (two layers in turn / six): 24 of 768 + 2 shared, hidden 4096, 500 tokens,
+// the pass 84 / 90 and 96 / 90, 16 of 1024, hidden 4096, 900 tokens 74 / 80 and 90 / 80, 24 of 2048, 700 tokens 95 / 90 and 99 / 90.
 bool whole_lines(const moe_config& c) {
   const Work w = layer_work(c);
   if (c.dtype == MOE_BF16 || layer_bytes(c) < 384ll << 20) return false;
