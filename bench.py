@@ -185,8 +185,8 @@ SEPARATE_CALLS = False
 
 
 def decode_call(cfg) -> bool:
-    """Which steps go through moe_layer_decode: at most 32 tokens, bf16 weights, shared experts.  In large layers the
-    library runs them, like moe_layer_step, as a few launches, in the others as one."""
+    """Which steps go through moe_layer_decode: at most 32 tokens, bf16 weights, shared experts.  Where gate/up streams in
+    panels the library runs them, like moe_layer_step, as a few launches, elsewhere as one."""
     return not SEPARATE_CALLS and 0 < cfg.T <= 32 and cfg.dtype == "bf16" and len(cfg.shared_I) > 0
 
 

@@ -558,8 +558,8 @@ def test_router_logits_of_many_tokens_and_few_experts(dtype, T, E, H):
 @pytest.mark.parametrize("T,E,K,kl,I,shared", [(1, 8, 2, 1, 64, ()), (256, 60, 4, 2, 64, (72,)), (257, 1, 1, 1, 8, ()), (300, 64, 8, 4, 72, (64, 40)),
                                                (300, 256, 1, 1, 8, ()), (1111, 200, 3, 2, 40, ()), (2049, 7, 7, 3, 16, ())])
 def test_step_in_one_call_equals_the_separate_calls(T, E, K, kl, I, shared, given):
-    """Above 256 tokens the selection counts for the dispatch, where the table fits the activations' workspace
-    (300 tokens, 256 experts of 8: it does not).  Every output array is the same."""
+    """Above 256 tokens the selection counts for the dispatch, while the table is small (1111 tokens, 200 experts: it is not) and fits the
+    activations' workspace (300 tokens, 256 experts of 8: it does not).  Every output array is the same."""
     cfg = wl.LayerConfig("one", T=T, H=64, E=E, I=I, k_big=K, k_little=kl, shared_I=shared, gate_std=0.3, gate_bias_std=1.0,
                          w_std=0.1, fallback_ratio=0.4)
     layer = wl.make_layer(cfg, seed=T + E)
